@@ -134,10 +134,42 @@ struct WsLayout {
   // 2: as two (pooling; everything else).  In both the batch-reducing rest (gamma_n's gradient,
   // batch-mean loss) rides on the reduction launch.  0: pooling, linear layer + loss, backward.
   int head_fused;
+  // > 0: that contraction runs as wino_fwd (fp32 mode) with this many reduction splits; the
+  // transformed filter, then the partial sums of the splits, alias `part`
+  int wino_layer, wino_aux, wino_dgrad;
   // head_fused == 2 only: F_n is formed from column sums left by the aux convolution's epilogue
   // (region ppart), no pooling launch
   int pool_fused;
 };
+
+// data gradient of beta_n: the forward-type contraction of dU with the re-laid filter (pointers left null)
+FwdProblem dgrad_problem(const nf_aux_desc *a, const AuxDims &ad, int B) {
+  FwdProblem f;
+  std::memset((void *)&f, 0, sizeof(f));
+  f.H = ad.Hu, f.W = ad.Wu, f.C = a->A, f.N = a->C_in, f.R = a->R, f.S = a->S, f.stride = 1,
+  f.pad = a->R - 1 - a->pad, f.Ho = a->H_in, f.Wo = a->W_in;
+  f.M = B * a->H_in * a->W_in, f.RSC = a->R * a->S * a->A, f.Kg = f.RSC;
+  f.div_howo = FastDiv(a->H_in * a->W_in), f.div_wo = FastDiv(a->W_in);
+  return f;
+}
+
+// theta_n of Eq. 1 as a forward-type contraction (pointers left null)
+FwdProblem layer_fwd_problem(const nf_layer_desc *d, const LayerDims &ld, int B) {
+  FwdProblem f;
+  std::memset((void *)&f, 0, sizeof(f));
+  f.H = d->H_in, f.W = d->W_in, f.C = d->C_in, f.N = d->C_out, f.R = d->R, f.S = d->S, f.stride = d->stride,
+  f.pad = d->pad, f.Ho = ld.Ho, f.Wo = ld.Wo;
+  if (d->skip_kind == 2) f.Cs = d->skip_C, f.Hs = d->skip_H, f.Ws = d->skip_W, f.ss = d->skip_stride;
+  f.relu = 1;
+  f.M = B * ld.Ho * ld.Wo, f.RSC = d->R * d->S * d->C_in, f.Kg = f.RSC + f.Cs;
+  f.div_howo = FastDiv(ld.Ho * ld.Wo), f.div_wo = FastDiv(ld.Wo);
+  return f;
+}
+
+// scratch of a forward-type contraction that runs as wino_fwd (out: elements of its result)
+size_t wino_scratch_floats(int splits, int N, int C, size_t out) {
+  return splits ? wino_fwd_filter_floats(N, C) + (splits > 1 ? splits * out : 0) : 0;
+}
 
 WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B) {
   WsLayout w;
@@ -157,6 +189,8 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
   const int Kl = d->R * d->S * d->C_in + (d->skip_kind == 2 ? d->skip_C : 0);
   w.ksplits_layer = igemm_fwd_pick_ksplits(B * ld.Ho * ld.Wo, d->C_out, Kl, d->C_in, d->R * d->S);
   size_t pmax = w.ksplits_layer > 1 ? (size_t)w.ksplits_layer * conv_out : 0;
+  w.wino_layer = wino_fwd_pick_splits(layer_fwd_problem(d, ld, B));
+  size_t pwino = wino_scratch_floats(w.wino_layer, d->C_out, d->C_in, conv_out);
   w.ksplits_aux = w.ksplits_dgrad = 1;
   if (a) {
     const size_t u = (size_t)B * ad.Hu * ad.Wu * a->A;
@@ -185,6 +219,10 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     if (w.ksplits_aux > 1 && (size_t)w.ksplits_aux * u > pmax) pmax = (size_t)w.ksplits_aux * u;
     w.ksplits_dgrad = igemm_fwd_pick_ksplits(B * a->H_in * a->W_in, a->C_in, a->R * a->S * a->A, a->A, a->R * a->S);
     if (w.ksplits_dgrad > 1 && (size_t)w.ksplits_dgrad * emitted > pmax) pmax = (size_t)w.ksplits_dgrad * emitted;
+    w.wino_aux = wino_fwd_pick_splits(aux_fwd_problem(a, ad, B));
+    w.wino_dgrad = wino_fwd_pick_splits(dgrad_problem(a, ad, B));
+    pwino = std::max(pwino, wino_scratch_floats(w.wino_aux, a->A, a->C_in, u));
+    pwino = std::max(pwino, wino_scratch_floats(w.wino_dgrad, a->C_in, a->A, emitted));
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;
     if (w.head_fused == 2 && head_pool_partials_applicable(head_shape(a, ad, B))) {
       // (a reduction split in two gives way: the pooling launch it would need costs more than it gains)
@@ -197,6 +235,12 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     w.part_b = take((size_t)w.splits_layer * d->C_out * f);
     w.part_aux = take(pa * f);
     w.part_b_aux = take((size_t)w.splits_aux * a->A * f);
+  }
+  if (pwino > pmax) {
+    // this scratch must not push a step that the static array holds out of it
+    const size_t lim = (size_t)NF_STATIC_SCRATCH_BYTES;
+    if (off + up(pmax * f) <= lim && off + up(pwino * f) > lim) w.wino_layer = w.wino_aux = w.wino_dgrad = 0;
+    else pmax = pwino;
   }
   w.part = take(pmax * f);
   w.total = off ? off : ALIGN;
@@ -295,6 +339,28 @@ int32_t enqueue_fwd_split(FwdProblem f, float *out, int ksplits, float *part, hi
   return enqueue_fwd(f, st);
 }
 
+// the same contraction through wino_fwd (flops of the dense formula; scratch: the transformed filter,
+// then the partial sums of the splits)
+int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, hipStream_t st) {
+  const double B = (double)f.M / ((double)f.Ho * f.Wo), mn = (double)f.M * f.N;
+  double elems = B * f.H * f.W * f.C + (double)f.N * f.Kg + mn;
+  const float *bias = f.bias, *addsrc = f.addsrc, *mask = f.mask;
+  if (splits <= 1 && (addsrc || mask)) elems += mn;
+  float *part = scratch + wino_fwd_filter_floats(f.N, f.C);
+  f.ksplits = splits, f.out = splits > 1 ? part : out;
+  NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, 4.0 * elems, launch_wino_fwd(f, scratch, st));
+  if (splits > 1)
+    NF_RUN(st, "fwd_finish", 0.0, 4.0 * mn * (splits + 1.0 + (addsrc ? 1.0 : 0.0) + (mask ? 1.0 : 0.0)),
+           launch_fwd_finish(part, splits, f.M, f.N, bias, addsrc, mask, f.relu, out, st));
+  return NF_OK;
+}
+
+// by the layout's plan: wino_fwd, or the direct kernels (the split-operand modes always use those)
+int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, float *part, hipStream_t st) {
+  if (wino && contraction_mode() == NF_CONTRACT_F32) return enqueue_wino(f, out, wino, part, st);
+  return enqueue_fwd_split(f, out, ksplits, part, st);
+}
+
 int32_t enqueue_wgrad(const WgradProblem &g, hipStream_t st) {
   const double B = (double)g.M / ((double)g.Ho * g.Wo);
   const double flops = 2.0 * g.M * g.P * g.Q;
@@ -318,18 +384,12 @@ WgradReduce reduce_job(const WgradProblem &g, float *out0, float *out1, float *o
 int32_t run_layer_fwd(const nf_layer_desc *d, const LayerDims &ld, int B, const float *x, const float *xs,
                       const nf_layer_params *p, float *y, void *ws, const WsLayout &w, hipStream_t st) {
   const bool pooled = d->pool_kind != 0;
-  FwdProblem f;
-  std::memset((void *)&f, 0, sizeof(f));
+  FwdProblem f = layer_fwd_problem(d, ld, B);
   f.x = x, f.w = p->W, f.bias = p->b;
-  f.H = d->H_in, f.W = d->W_in, f.C = d->C_in, f.N = d->C_out, f.R = d->R, f.S = d->S, f.stride = d->stride,
-  f.pad = d->pad, f.Ho = ld.Ho, f.Wo = ld.Wo;
   if (d->skip_kind == 1) f.addsrc = xs;
-  if (d->skip_kind == 2) f.xs = xs, f.wp = p->Wp, f.Cs = d->skip_C, f.Hs = d->skip_H, f.Ws = d->skip_W, f.ss = d->skip_stride;
-  f.relu = 1;
-  f.M = B * ld.Ho * ld.Wo, f.RSC = d->R * d->S * d->C_in, f.Kg = f.RSC + f.Cs;
-  f.div_howo = FastDiv(ld.Ho * ld.Wo), f.div_wo = FastDiv(ld.Wo);
+  if (d->skip_kind == 2) f.xs = xs, f.wp = p->Wp;
   float *conv_out = pooled ? wsf(ws, w.T_dZ) : y;
-  int32_t rc = enqueue_fwd_split(f, conv_out, w.ksplits_layer, wsf(ws, w.part), st);
+  int32_t rc = enqueue_conv(f, conv_out, w.wino_layer, w.ksplits_layer, wsf(ws, w.part), st);
   if (rc) return rc;
   if (pooled) {
     const double pre = (double)B * ld.Ho * ld.Wo * d->C_out, post = (double)B * ld.Hp * ld.Wp * d->C_out;
@@ -340,27 +400,41 @@ int32_t run_layer_fwd(const nf_layer_desc *d, const LayerDims &ld, int B, const 
   return NF_OK;
 }
 
+// beta_n of Eq. 2: U (with bias and ReLU), or with *ks > 0 the raw partial sums *parts [*ks][B*Hu*Wu*A]
+// of a split reduction, which the consumer adds.  pool_partials: the epilogue also leaves the column sums
+// per 16 pixels that F_n is formed from, so that there is no pooling launch.
+int32_t run_aux_conv(const nf_aux_desc *a, const AuxDims &ad, int B, const float *y, const nf_aux_params *ap, void *ws,
+                     const WsLayout &w, hipStream_t st, bool pool_partials, int *ks, const float **parts) {
+  FwdProblem f = aux_fwd_problem(a, ad, B);
+  f.x = y, f.w = ap->Wa, f.bias = ap->ba;
+  const bool wino = w.wino_aux && contraction_mode() == NF_CONTRACT_F32;
+  const int splits = wino ? w.wino_aux : igemm_fwd_fast_applicable(f) ? w.ksplits_aux : 1;
+  *ks = splits > 1 ? splits : 0;
+  float *const part = wsf(ws, w.part) + (wino ? wino_fwd_filter_floats(f.N, f.C) : 0);
+  *parts = part;
+  f.ksplits = *ks;
+  f.out = *ks ? part : wsf(ws, w.U);
+  if (pool_partials) f.pool_part = wsf(ws, w.ppart), f.pool_split = ad.Wu == 16 ? 1 : 0;
+  if (!wino) return enqueue_fwd(f, st);
+  const double mn = (double)f.M * f.N, byts = 4.0 * ((double)B * f.H * f.W * f.C + (double)f.N * f.Kg + mn);
+  NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, byts, launch_wino_fwd(f, wsf(ws, w.part), st));
+  return NF_OK;
+}
+
 // beta_n and F_n of Eq. 2: the head's convolution (+ bias, ReLU) and its pooling; leaves U and Pq
 // (and the max-pooling selection) in the workspace
 int32_t run_aux_features(const nf_aux_desc *a, const AuxDims &ad, int B, const float *y, const nf_aux_params *ap,
                          void *ws, const WsLayout &w, hipStream_t st, bool partials_only = false) {
-  FwdProblem f = aux_fwd_problem(a, ad, B);
-  f.x = y, f.w = ap->Wa, f.bias = ap->ba;
-  // skinny head, long reduction: split it; the pooling kernel adds the parts, bias and ReLU
-  const int ks = (w.ksplits_aux > 1 && igemm_fwd_fast_applicable(f)) ? w.ksplits_aux : 0;
-  f.ksplits = ks;
-  f.out = ks ? wsf(ws, w.part) : wsf(ws, w.U);
-  // partials_only (the caller's next launch forms F_n itself): the convolution's epilogue leaves
-  // the column sums per 16 pixels, and there is no pooling launch
   const bool fused = partials_only && w.pool_fused;
-  if (fused) f.pool_part = wsf(ws, w.ppart), f.pool_split = ad.Wu == 16 ? 1 : 0;
-  int32_t rc = enqueue_fwd(f, st);
+  int ks;
+  const float *parts;
+  const int32_t rc = run_aux_conv(a, ad, B, y, ap, ws, w, st, fused, &ks, &parts);
   if (rc) return rc;
   if (fused) return NF_OK;
   const HeadShape hs = head_shape(a, ad, B);
   const double u = (double)B * ad.Hu * ad.Wu * a->A;
   NF_RUN(st, "head_pool", 0.0, 4.0 * (u * (ks ? ks + 1.0 : 1.0) + (double)B * ad.F),
-         launch_head_pool(hs, wsf(ws, w.U), wsf(ws, w.part), ks, ap->ba, wsf(ws, w.Pq),
+         launch_head_pool(hs, wsf(ws, w.U), parts, ks, ap->ba, wsf(ws, w.Pq),
                           reinterpret_cast<int32_t *>(wsf(ws, w.parg)), st));
   return NF_OK;
 }
@@ -372,25 +446,16 @@ int32_t run_aux_fwd(const nf_aux_desc *a, const AuxDims &ad, int B, const float 
   if (w.head_fused == 1) {
     // small activation map: the convolution, then ONE launch for the head's whole per-sample chain
     // (F_n, gamma_n, loss, dL/dz, dPq, dU) and the re-laid filter the data gradient will read
-    FwdProblem f;
-    std::memset((void *)&f, 0, sizeof(f));
-    f.x = y, f.w = ap->Wa, f.bias = ap->ba;
-    f.H = a->H_in, f.W = a->W_in, f.C = a->C_in, f.N = a->A, f.R = a->R, f.S = a->S, f.stride = 1, f.pad = a->pad,
-    f.Ho = ad.Hu, f.Wo = ad.Wu;
-    f.relu = a->relu ? 1 : 0;
-    f.M = B * ad.Hu * ad.Wu, f.RSC = a->R * a->S * a->C_in, f.Kg = f.RSC;
-    f.div_howo = FastDiv(ad.Hu * ad.Wu), f.div_wo = FastDiv(ad.Wu);
-    // skinny head, long reduction: split it; the per-sample launch adds the parts, bias and ReLU
-    const int ks = (w.ksplits_aux > 1 && igemm_fwd_fast_applicable(f)) ? w.ksplits_aux : 0;
-    f.ksplits = ks;
-    f.out = ks ? wsf(ws, w.part) : wsf(ws, w.U);
-    int32_t rc = enqueue_fwd(f, st);
+    // the per-sample launch adds the parts of a split reduction, bias and ReLU
+    int ks;
+    const float *parts;
+    const int32_t rc = run_aux_conv(a, ad, B, y, ap, ws, w, st, false, &ks, &parts);
     if (rc) return rc;
     const double u = (double)B * ad.Hu * ad.Wu * a->A, fc = (double)a->n_classes * ad.F;
     const double wa = (double)a->A * a->R * a->S * a->C_in;
     NF_RUN(st, "head_sample", 4.0 * B * fc,
            4.0 * ((3.0 + ks) * u + 2.0 * B * fc + (double)B * (ad.F + a->n_classes + 1.0)) + 8.0 * wa,
-           launch_head_sample(hs, wsf(ws, w.U), wsf(ws, w.part), ks, ap->ba, labels, ap->Wf, ap->bf, wsf(ws, w.Pq),
+           launch_head_sample(hs, wsf(ws, w.U), parts, ks, ap->ba, labels, ap->Wf, ap->bf, wsf(ws, w.Pq),
                               reinterpret_cast<int32_t *>(wsf(ws, w.parg)), wsf(ws, w.dz), wsf(ws, w.loss_n),
                               wsf(ws, w.dU), ap->Wa, wsf(ws, w.WaT), a->R, a->S, a->C_in, st));
     if (loss_out) NF_RUN(st, "loss_mean", 0.0, 4.0 * B, launch_loss_mean(wsf(ws, w.loss_n), B, loss_out, st));
@@ -449,15 +514,10 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
   }
   // beta_n: data gradient w.r.t. the emitted activation, layer ReLU mask fused when un-pooled
   {
-    FwdProblem f;
-    std::memset((void *)&f, 0, sizeof(f));
+    FwdProblem f = dgrad_problem(a, ad, B);
     f.x = dU, f.w = wsf(ws, w.WaT);
-    f.H = ad.Hu, f.W = ad.Wu, f.C = a->A, f.N = a->C_in, f.R = a->R, f.S = a->S, f.stride = 1,
-    f.pad = a->R - 1 - a->pad, f.Ho = a->H_in, f.Wo = a->W_in;
-    f.M = B * a->H_in * a->W_in, f.RSC = a->R * a->S * a->A, f.Kg = f.RSC;
-    f.div_howo = FastDiv(a->H_in * a->W_in), f.div_wo = FastDiv(a->W_in);
     f.mask = pooled ? nullptr : y;
-    const int32_t rc = enqueue_fwd_split(f, pooled ? wsf(ws, w.dY) : dZ, w.ksplits_dgrad, wsf(ws, w.part), st);
+    const int32_t rc = enqueue_conv(f, pooled ? wsf(ws, w.dY) : dZ, w.wino_dgrad, w.ksplits_dgrad, wsf(ws, w.part), st);
     if (rc) return rc;
     if (pooled) {
       const double pre = (double)B * ld.Ho * ld.Wo * d->C_out, post = (double)B * ld.Hp * ld.Wp * d->C_out;

@@ -70,6 +70,13 @@ bool prof_active();
 bool igemm_fwd_split_applicable(const FwdProblem &p);
 hipError_t launch_igemm_fwd_split(const FwdProblem &p, bool nine, hipStream_t st, const char **kernel);
 
+// 3x3 / stride 1 / pad 1 through F(2x2, 3x3) in fp32 (wino_fwd.hip).  `U` is scratch for the transformed
+// filter (wino_fwd_filter_floats floats, 16-byte aligned); two launches.
+size_t wino_fwd_filter_floats(int N, int C);
+// 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none)
+int wino_fwd_pick_splits(const FwdProblem &p);
+hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st);
+
 // first-layer shapes (stem.hip): the whole reduction R*S*C <= 32 in one staging step, channel counts
 // that are not multiples of 4; launch_igemm_fwd / launch_igemm_wgrad pick them when applicable
 bool stem_fwd_applicable(const FwdProblem &p);

@@ -1,0 +1,418 @@
+// 3x3 / stride 1 / pad 1 convolution (Eq. 1, NeuroFlux, arXiv 2402.14139) through the minimal
+// filtering algorithm F(2x2, 3x3) (S. Winograd, "Arithmetic Complexity of Computations", 1980;
+// A. Lavin, S. Gray, arXiv 1509.09308), entirely in fp32: a 2x2 output tile is
+//     Y = A^T [ (G g G^T) . (B^T d B) ] A
+// with d the 4x4 input patch and g the 3x3 filter: 16 multiplications per channel where the direct
+// sum takes 36.  The 16 positions of the transformed domain are 16 independent contractions over
+// the channels, run on the fp32 matrix cores.
+//
+// What bounds it: the fp32 MFMA rate (16/36 of the direct kernel's MFMAs).  Layout of the work:
+//   - a workgroup owns 32 output tiles (128 pixels) x 64 filters x all 16 positions, so the patches
+//     are transformed on their way into the MFMA and the results on their way out: nothing of the
+//     transformed domain but the filters (wino_filter_kernel) ever reaches memory;
+//   - 4 waves = the 4 rows of the transformed domain.  A wave's row needs two rows of the patch (B^T
+//     has two non-zeros per row), which it reads from LDS and combines in registers (32 additions
+//     per 32 MFMAs); its filters come straight from memory in fragment order (no other wave of the
+//     workgroup uses them, so LDS would only add a copy);
+//   - 8 channels per step, one barrier per step; patches are loaded three steps ahead, written to
+//     LDS two steps ahead, read and row-combined one step ahead; a filter fragment is re-loaded
+//     for the next step right after its last MFMA;
+//   - 128 accumulators per lane, two workgroups per CU: one's transforms, LDS traffic, loads and
+//     stores fill in under the other's MFMAs (one workgroup of 64 tiles per CU: 101 us where this
+//     takes 84, 64 channels on 56x56 maps, batch 64; equal where both fill the chip once).
+// The reduction has C terms per position instead of 9 C: the rounding error against 64 bits is
+// smaller than that of the direct sum (emitted activation, relative: 64 channels 1.7e-7 against 2.2e-7, four
+// layers of 256 channels in a row 5.9e-7 against 7.1e-7).
+//
+// Measured (us, the direct kernel / this with its filter launch of 5-8 us): 64 -> 64 channels, 65 536 pixels
+// 43 / 35; 128 -> 128, 32 768 pixels 80 / 48; 256 -> 256, 16 384 pixels 155 / 83; 512 -> 512, 8192 pixels 312 / 150
+// (a step of 8 channels takes 2.1 us on a CU with two workgroups, 0.87 of it MFMAs).
+//
+// A value that is not finite anywhere in a tile makes neighbours of the transformed domain NaN that
+// the direct sum would leave finite (or infinite): a thread that finds one among its results
+// forms those results again by the direct sum.
+#include "nf_internal.h"
+
+namespace nf {
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int NTHREADS = 256;
+constexpr int TB = 32, NB = 64;          // output tiles, filters per workgroup
+constexpr int CH = 8;                    // channels per step
+constexpr int OOB = (int)0x80000000;     // offset no buffer of < 2 GiB contains
+constexpr int RSRC_FLAGS = 0x00020000;   // raw buffer, 32-bit data format
+constexpr int UB = 16 * NB * CH;         // transformed filter words per (filter block, step)
+
+struct WinoAux {
+  int TW, TPI, T;        // tiles per image row, per image, in all
+  int nchunks, per;      // steps of 8 channels; steps per reduction split
+  int nblk;              // filter blocks
+  FastDiv div_tpi, div_tw;
+  uint32_t x_bytes, u_bytes;
+  const float *U;
+};
+
+__device__ inline float4 bload(__amdgpu_buffer_rsrc_t r, int voff) {
+  const floatx4 v = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ inline float el(const float4 &v, int k) { return k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w; }
+__device__ inline float4 add4(const float4 &a, const float4 &b) {
+  return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+__device__ inline float4 sub4(const float4 &a, const float4 &b) {
+  return make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w);
+}
+__device__ inline float4 scale4(float s, const float4 &a) { return make_float4(s * a.x, s * a.y, s * a.z, s * a.w); }
+// a + s*b with s = +-1 (exact product)
+__device__ inline float4 fma4(float s, const float4 &b, const float4 &a) {
+  return make_float4(__builtin_fmaf(s, b.x, a.x), __builtin_fmaf(s, b.y, a.y), __builtin_fmaf(s, b.z, a.z),
+                     __builtin_fmaf(s, b.w, a.w));
+}
+__device__ inline bool finite4(const float4 &v) {
+  return __builtin_isfinite(v.x) & __builtin_isfinite(v.y) & __builtin_isfinite(v.z) & __builtin_isfinite(v.w);
+}
+
+// U[filter block][step][position a*4+b][n & 1][lane][4]: the word of lane (j, h), element k is filter
+// 64*block + 2*j + (n & 1), channel 8*step + 4*h + k, i.e. the B fragment of one MFMA group.  Zero
+// past the last filter and channel.  HBM-bound: 36 bytes read, 64 written per (filter, channel).
+__global__ __launch_bounds__(256) void wino_filter_kernel(const float *w, float *U, int N, int C, int nchunks) {
+  const int t = threadIdx.x;
+  const int c4 = blockIdx.x * 8 + (t & 7), n = blockIdx.y * 32 + (t >> 3);  // 8 lanes read 128 contiguous bytes
+  if (c4 >= 2 * nchunks) return;
+  float4 g[3][3];
+  const bool ok = n < N && c4 * 4 < C;
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      g[r][s] = ok ? *reinterpret_cast<const float4 *>(w + ((long long)n * 9 + r * 3 + s) * C + c4 * 4)
+                   : make_float4(0.f, 0.f, 0.f, 0.f);
+  const int blk = n / NB, in = n % NB;
+  float *o = U + ((long long)blk * nchunks + (c4 >> 1)) * UB + (in & 1) * 256 + ((c4 & 1) * 32 + (in >> 1)) * 4;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    float4 q[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      if (a == 0) q[s] = g[0][s];
+      else if (a == 3) q[s] = g[2][s];
+      else q[s] = scale4(0.5f, a == 1 ? add4(add4(g[0][s], g[2][s]), g[1][s]) : sub4(add4(g[0][s], g[2][s]), g[1][s]));
+    }
+    const float4 e = add4(q[0], q[2]);
+    float4 v[4] = {q[0], scale4(0.5f, add4(e, q[1])), scale4(0.5f, sub4(e, q[1])), q[2]};
+#pragma unroll
+    for (int b = 0; b < 4; ++b) *reinterpret_cast<float4 *>(o + (a * 4 + b) * 512) = v[b];
+  }
+}
+
+// Four outputs (filters n .. n+3 of pixel (img, ho, wo)) by the direct sum over channels [c_lo, c_hi);
+// taps outside the image multiply a zero, as in the direct kernel.
+__device__ inline float4 direct4(const float *x, const float *w, int H, int W, int C, int img, int ho, int wo, int n,
+                                 int c_lo, int c_hi) {
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  const long long ws = 9ll * C;
+#pragma unroll 1
+  for (int tap = 0; tap < 9; ++tap) {
+    const int hi = ho + tap / 3 - 1, wi = wo + tap % 3 - 1;
+    const bool in = ((unsigned)hi < (unsigned)H) & ((unsigned)wi < (unsigned)W);
+    const float *xr = x + ((long long)(img * H + (in ? hi : 0)) * W + (in ? wi : 0)) * C;
+    const float *wr = w + ((long long)n * 9 + tap) * C;
+#pragma unroll 1
+    for (int c = c_lo; c < c_hi; ++c) {
+      const float v = in ? xr[c] : 0.f;
+      s.x = __builtin_fmaf(v, wr[c], s.x), s.y = __builtin_fmaf(v, wr[c + ws], s.y);
+      s.z = __builtin_fmaf(v, wr[c + 2 * ws], s.z), s.w = __builtin_fmaf(v, wr[c + 3 * ws], s.w);
+    }
+  }
+  return s;
+}
+
+__global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, WinoAux q) {
+  // main loop: As[2][16 patch pixels][32 tiles][8 channels]; epilogue: Cs[4 rows][32 tiles][2 columns][64 filters]
+  __shared__ __attribute__((aligned(16))) float S[4 * TB * 2 * NB];
+
+  const int t = threadIdx.x;
+  const int lane = t & 63, row = t >> 6;  // a wave owns one row of the transformed domain
+    const int j = lane & 31, h = lane >> 5;
+  // XCD re-map (workgroups are dealt round-robin over 8 XCDs): each XCD gets a contiguous run with the
+  // filter blocks fastest, so that the patches of a tile block are read into one L2 only
+  const int nwg = gridDim.x, lin = blockIdx.x;
+  const int wper = nwg >> 3, wrem = nwg & 7, xcd = lin & 7, slot = lin >> 3;
+  const int id = xcd < wrem ? xcd * (wper + 1) + slot : wrem * (wper + 1) + (xcd - wrem) * wper + slot;
+  const int nb = id % q.nblk, t0 = (id / q.nblk) * TB;
+  const int s_lo = blockIdx.y * q.per, s_hi = min(q.nchunks, s_lo + q.per);
+
+  const __amdgpu_buffer_rsrc_t rsx = __builtin_amdgcn_make_buffer_rsrc((void *)p.x, 0, q.x_bytes, RSRC_FLAGS);
+  const __amdgpu_buffer_rsrc_t rsu = __builtin_amdgcn_make_buffer_rsrc((void *)q.U, 0, q.u_bytes, RSRC_FLAGS);
+
+  // ---- staging: thread = (patch row, tile, channel half); its four loads are the row's pixels ----
+  const int st_half = t & 1, st_tile = (t >> 1) & (TB - 1), st_row = t / (2 * TB);
+  int xoff[4];
+  {
+    const int tile = t0 + st_tile;
+    const int img = (int)q.div_tpi.div((uint32_t)tile), rem = tile - img * q.TPI;
+    const int ty = (int)q.div_tw.div((uint32_t)rem), tx = rem - ty * q.TW;
+    const int hi = 2 * ty - 1 + st_row, wi = 2 * tx - 1;
+    const bool rok = (tile < q.T) & ((unsigned)hi < (unsigned)p.H);
+    const int base = ((img * p.H + hi) * p.W + wi) * p.C * 4 + st_half * 16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      xoff[i] = (base + i * p.C * 4) | ((rok & ((unsigned)(wi + i) < (unsigned)p.W)) ? 0 : OOB);
+  }
+  auto gload = [&](int s, float4 *sx) {
+    const int c0 = s * CH + st_half * 4;
+    const int bad = ((c0 < p.C) & (s < s_hi)) ? 0 : OOB;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sx[i] = bload(rsx, (xoff[i] + s * (CH * 4)) | bad);
+  };
+  float *const st_base = S + (st_row * 4 * TB + st_tile) * CH + st_half * 4;
+  auto lstore = [&](int buf, const float4 *sx) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<float4 *>(st_base + buf * (16 * TB * CH) + i * (TB * CH)) = sx[i];
+  };
+
+  // ---- this wave's row of B^T: d[ra] + sg * d[rb] ----
+  const int ra = row == 0 ? 0 : row == 2 ? 2 : 1, rb = row == 0 ? 2 : row == 1 ? 2 : row == 2 ? 1 : 3;
+  const float sg = row == 1 ? 1.f : -1.f;
+  const float *const fa = S + (ra * 4 * TB + j) * CH + h * 4;
+  const float *const fb = S + (rb * 4 * TB + j) * CH + h * 4;
+  float4 tr[4];  // row-combined patch pixels of the step ahead
+  auto lread = [&](int buf, int c) {
+    const float4 u = *reinterpret_cast<const float4 *>(fa + buf * (16 * TB * CH) + c * (TB * CH));
+    const float4 v = *reinterpret_cast<const float4 *>(fb + buf * (16 * TB * CH) + c * (TB * CH));
+    tr[c] = fma4(sg, v, u);
+  };
+
+  const int ubase = ((nb * q.nchunks) * UB + row * 4 * 512 + lane * 4) * 4;
+  float4 uf[4][2];  // fragments of column b: re-loaded one section after their last use
+  auto uload = [&](int s, int b) {
+#pragma unroll
+    for (int n = 0; n < 2; ++n) uf[b][n] = bload(rsu, ubase + (s * UB + b * 512 + n * 256) * 4);
+  };
+
+  floatx16 acc[4][2];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[b][n][e] = 0.f;
+
+  // ---- prologue: steps s_lo, s_lo+1 in LDS, s_lo+2 in registers, row combination of s_lo ----
+  float4 sx[4];
+  {
+    float4 sa[4], sb[4];
+    gload(s_lo, sa);
+    gload(s_lo + 1, sb);
+    gload(s_lo + 2, sx);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) uload(s_lo, b);
+    lstore(0, sa);
+    lstore(1, sb);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 4; ++c) lread(0, c);
+
+  // Four sections per step, one per column b of the transformed domain, each closed by a scheduling
+  // fence: left alone the compiler gathers all loads at the end of the step, right in front of their use.
+  int buf = 0;  // buffer of step s
+  for (int s = s_lo; s < s_hi; ++s) {
+    __syncthreads();  // step s+1 is in buffer buf^1; everybody has read step s out of buffer buf
+    const float4 v[4] = {sub4(tr[0], tr[2]), add4(tr[1], tr[2]), sub4(tr[2], tr[1]), sub4(tr[1], tr[3])};
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      lread(buf ^ 1, b);
+      if (b == 0) {
+        uload(s, 3);
+        lstore(buf, sx);
+      } else {
+        uload(s + 1, b - 1);
+      }
+      if (b == 1) gload(s + 3, sx);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+          acc[b][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(el(v[b], k), el(uf[b][n], k), acc[b][n], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                // one MFMA
+        if (i < 1) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                     // + patch reads
+        if (b == 0 && i >= 2 && i < 6) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0); // + an LDS write
+        if (i < (b == 1 ? 6 : 2)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);      // + a load
+        if (i >= 3) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);                    // + address, row combination
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    buf ^= 1;
+  }
+
+  // ---- epilogue: this thread's eight results are filters n .. n+3 of 4 (tile, column) x 2 rows ----
+  const bool split = gridDim.y > 1;
+  float *const out = p.out + (split ? (long long)blockIdx.y * p.M * p.N : 0ll);
+  const int n = nb * NB + (t & 15) * 4;
+  long long off[4][2];  // -1: no such pixel or filter
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int task = i * 16 + (t >> 4);  // (tile, column)
+    const int tile = t0 + (task >> 1);
+    const int img = (int)q.div_tpi.div((uint32_t)tile), rem = tile - img * q.TPI;
+    const int ty = (int)q.div_tw.div((uint32_t)rem), tx = rem - ty * q.TW;
+    const int wo = 2 * tx + (task & 1);
+    const bool ok = (tile < q.T) & (wo < p.Wo) & (n < p.N);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      off[i][k] = (ok & (2 * ty + k < p.Ho)) ? ((long long)(img * p.Ho + 2 * ty + k) * p.Wo + wo) * p.N + n : -1;
+  }
+  // shortcut or mask: fetched before the transform, so that the loads overlap it
+  const float *const extra = split ? nullptr : p.addsrc ? p.addsrc : p.mask;
+  float4 ex[4][2];
+  if (extra) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        if (off[i][k] >= 0) ex[i][k] = *reinterpret_cast<const float4 *>(extra + off[i][k]);
+  }
+  // output transform: columns in registers, rows through LDS
+  __syncthreads();
+  {
+    float *const cw = S + row * (TB * 2 * NB) + 2 * j;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int r = 8 * (e >> 2) + 4 * h + (e & 3);
+      float2 y0, y1;
+      const float p0 = acc[1][0][e], m0 = acc[2][0][e], p1 = acc[1][1][e], m1 = acc[2][1][e];
+      y0.x = acc[0][0][e] + p0 + m0, y1.x = p0 - m0 - acc[3][0][e];
+      y0.y = acc[0][1][e] + p1 + m1, y1.y = p1 - m1 - acc[3][1][e];
+      *reinterpret_cast<float2 *>(cw + (r * 2 + 0) * NB) = y0;
+      *reinterpret_cast<float2 *>(cw + (r * 2 + 1) * NB) = y1;
+    }
+  }
+  __syncthreads();
+  float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (p.bias && !split && n < p.N) bias = *reinterpret_cast<const float4 *>(p.bias + n);
+  // everything after the contraction for one result
+  auto finish = [&](float4 v, float4 x, long long o) {
+    if (!split) {
+      v = add4(v, bias);
+      if (p.addsrc) v = add4(v, x);
+      if (p.relu) v.x = v.x > 0.f ? v.x : 0.f, v.y = v.y > 0.f ? v.y : 0.f, v.z = v.z > 0.f ? v.z : 0.f, v.w = v.w > 0.f ? v.w : 0.f;
+      if (p.mask) {
+        const float4 m = p.addsrc ? *reinterpret_cast<const float4 *>(p.mask + o) : x;
+        v.x = m.x > 0.f ? v.x : 0.f, v.y = m.y > 0.f ? v.y : 0.f, v.z = m.z > 0.f ? v.z : 0.f, v.w = m.w > 0.f ? v.w : 0.f;
+      }
+    }
+    *reinterpret_cast<float4 *>(out + o) = v;
+  };
+  unsigned bad = 0;  // bit 2*i + k: that result is not finite
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int task = i * 16 + (t >> 4), lt = task >> 1;
+    const float *c = S + (lt * 2 + (task & 1)) * NB + (t & 15) * 4;
+    constexpr int RS = TB * 2 * NB;  // next row of the transformed domain
+    const float4 r0 = *reinterpret_cast<const float4 *>(c), r1 = *reinterpret_cast<const float4 *>(c + RS);
+    const float4 r2 = *reinterpret_cast<const float4 *>(c + 2 * RS), r3 = *reinterpret_cast<const float4 *>(c + 3 * RS);
+    const float4 y[2] = {add4(add4(r0, r1), r2), sub4(sub4(r1, r2), r3)};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (off[i][k] < 0) continue;
+      bad |= finite4(y[k]) ? 0u : 1u << (2 * i + k);
+      finish(y[k], ex[i][k], off[i][k]);
+    }
+  }
+  if (bad == 0) return;
+#pragma unroll 1
+  for (int ik = 0; ik < 8; ++ik) {
+    if (!(bad >> ik & 1)) continue;
+    const int task = (ik >> 1) * 16 + (t >> 4), tile = t0 + (task >> 1);
+    const int img = (int)q.div_tpi.div((uint32_t)tile), rem = tile - img * q.TPI;
+    const int ty = (int)q.div_tw.div((uint32_t)rem), tx = rem - ty * q.TW;
+    const int ho = 2 * ty + (ik & 1), wo = 2 * tx + (task & 1);
+    const long long o = ((long long)(img * p.Ho + ho) * p.Wo + wo) * p.N + n;
+    const float4 v = direct4(p.x, p.w, p.H, p.W, p.C, img, ho, wo, n, s_lo * CH, min(p.C, s_hi * CH));
+    float4 x = bias;
+    if (extra) x = *reinterpret_cast<const float4 *>(extra + o);
+    finish(v, x, o);
+  }
+}
+
+}  // namespace
+
+size_t wino_fwd_filter_floats(int N, int C) {
+  return (size_t)((N + NB - 1) / NB) * ((C + CH - 1) / CH) * UB;
+}
+
+namespace {
+bool applicable(const FwdProblem &p) {
+  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.Cs || p.pool_part) return false;
+  if (p.C % 4 || p.N % 4) return false;
+  const long long lim = 0x7FFFFFF0ll, B = p.M / ((long long)p.Ho * p.Wo);
+  return B * p.H * p.W * p.C * 4 <= lim && (long long)wino_fwd_filter_floats(p.N, p.C) * 4 <= lim;
+}
+}  // namespace
+
+// Which kernel, and how many reduction splits: both times are estimated from the step times below and
+// the smaller one wins.  The line was checked on 240 shapes (16 ... 512 channels, 64 ... 512 filters, 256 ... 65 536
+// pixels, maps of 2 ... 32): the choice is within 0.5 % of the faster of the two on average and never
+// more than 10 % off it; taking the direct kernel always is 27 % off.  Examples (us, direct / this):
+// 512 -> 512 channels, 8192 pixels 312 / 150; 128 -> 128, 16 384 pixels 45 / 30, 4096 pixels 20 / 22 (direct);
+// 256 -> 512, 1024 pixels 37 / 28 (4 splits); 64 -> 64, 65 536 pixels 43 / 34.
+// The map's size only enters through the number of tiles.
+int wino_fwd_pick_splits(const FwdProblem &p) {
+  // up to 32 filters half of a workgroup's columns would be padding
+  if (p.N <= 32 || !applicable(p)) return 0;
+  const double mn = (double)p.M * p.N;
+  const int B = p.M / (p.Ho * p.Wo);
+  const long long tiles = ((long long)B * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) + TB - 1) / TB;
+  const long long wgs = tiles * ((p.N + NB - 1) / NB);
+  const int nchunks = (p.C + CH - 1) / CH;
+  auto finish_us = [&](int s) { return s > 1 ? 3.5 + mn * 4.0 * (s + 1) / 4e6 : 0.0; };  // fwd_finish at 4 TB/s
+  // this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two; 11 us of prologue, epilogue and
+  // launches; the transformed filter written and read at 4 TB/s
+  double best = 0.0;
+  int splits = 0;
+  for (int s = 1; s <= 16; s *= 2) {
+    if (s > 1 && (nchunks / s < 2 || wgs * s > 512)) break;
+    const double per = wgs * s <= 256 ? 1.13 : wgs * s <= 512 ? 2.12 : 2.12 * (wgs * s) / 512.0;
+    const double us = 11.0 + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per + finish_us(s);
+    if (!splits || us < best) best = us, splits = s;
+  }
+  // the direct kernel: steps of 32 products, 128x128 tiles one per CU or 64x64 tiles up to four
+  const int nkb = (p.Kg + 31) / 32;
+  const int ks = igemm_fwd_pick_ksplits(p.M, p.N, p.Kg, p.C, p.R * p.S);
+  const bool big = p.N > 128 && p.Kg > 160;
+  const int bt = big ? 128 : 64;
+  const long long w = (long long)((p.M + bt - 1) / bt) * ((p.N + bt - 1) / bt) * ks;
+  const double per = big ? 2.06 * ((w + 255) / 256) : w <= 260 ? 0.56 : 0.55 * w / 256.0;
+  const double direct = 8.0 + (nkb + ks - 1) / ks * per + finish_us(ks);
+  return best < 0.93 * direct ? splits : 0;
+}
+
+hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st) {
+  WinoAux q;
+  const int TH = (p.Ho + 1) / 2, B = p.M / (p.Ho * p.Wo);
+  q.TW = (p.Wo + 1) / 2, q.TPI = TH * q.TW, q.T = B * q.TPI;
+  q.nchunks = (p.C + CH - 1) / CH;
+  q.nblk = (p.N + NB - 1) / NB;
+  q.div_tpi = FastDiv(q.TPI), q.div_tw = FastDiv(q.TW);
+  q.x_bytes = (uint32_t)((long long)B * p.H * p.W * p.C * 4);
+  q.u_bytes = (uint32_t)(wino_fwd_filter_floats(p.N, p.C) * 4);
+  q.U = U;
+  const int splits = p.ksplits > 1 ? p.ksplits : 1;
+  q.per = (q.nchunks + splits - 1) / splits;
+  hipLaunchKernelGGL(wino_filter_kernel, dim3((2 * q.nchunks + 7) / 8, q.nblk * 2), dim3(256), 0, st, p.w, U, p.N, p.C,
+                     q.nchunks);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(wino_fwd_kernel, dim3(q.nblk * ((q.T + TB - 1) / TB), splits), dim3(NTHREADS), 0, st, p, q);
+  return hipGetLastError();
+}
+
+}  // namespace nf

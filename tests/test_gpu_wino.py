@@ -1,0 +1,70 @@
+"""The 3x3 convolutions that run through F(2x2, 3x3) (csrc/wino_fwd.hip): whole steps against the
+CPU oracle at the sizes where the tiling can go wrong, and values that are not finite."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from paper_2402_14139_amd import binding as nf
+from tests import gpu_common as G
+from tests.test_gpu_parity import S
+
+pytestmark = pytest.mark.gpu
+
+# name -> (spec, B, classes, how many of layer / head / data gradient run as wino_fwd)
+CASES = {
+    # ragged last tile block, last filter block of 4, odd map (a half-empty tile in both directions)
+    "odd_map_n260": (S(64, 5, 7, 260, 8), 9, 10, 1),
+    # channel count not a multiple of the step (8), identity shortcut
+    "c68_identity": (S(256, 8, 8, 256, 4, skip=1), 5, 10, 1),
+    "c68": (S(68, 8, 8, 256, 4), 5, 10, 1),
+    # one pixel per map: a tile is one pixel and 15 zeros
+    "map_1x1": (S(64, 1, 1, 256, 8), 300, 10, 1),
+    # split reduction, pooled; head and data gradient split as well
+    "split_pool_wide_head": (S(512, 2, 2, 256, 256, pool=(2, 2, 0)), 64, 10, 2),
+    "split_wide_head": (S(256, 2, 2, 256, 256), 128, 10, 3),
+    # fewer filters than a workgroup's 64 columns
+    "n60": (S(128, 16, 16, 60, 4), 100, 10, 1),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_wino_steps_match_oracle(name):
+    spec, B, cls, launches = CASES[name]
+    print(f"case {name}: B={B}", flush=True)
+    nf.nf_prof_begin()
+    out, final = G.run_step_both(spec, cls, B, seed=310, lr=0.05, mu=0.9, steps=1)
+    got = {r["kernel"]: r["launches"] for r in nf.nf_prof_end()}
+    G.check_step_results(name, out, final)
+    if nf.nf_contraction() == nf.NF_CONTRACT_F32:
+        assert got.get("wino_fwd", 0) >= launches, got
+
+
+@pytest.mark.parametrize("where", ["input", "filter"])
+def test_wino_values_that_are_not_finite(where):
+    """An infinity reaches exactly the results whose direct sum contains it."""
+    B, C, H, W, K = 3, 64, 9, 8, 256
+    g = torch.Generator().manual_seed(5)
+    x, w = torch.randn(B, H, W, C, generator=g), torch.randn(K, 3, 3, C, generator=g) * 0.06
+    if where == "input":
+        x[1, 4, 5, 7], x[2, 0, 0, 3] = float("inf"), float("nan")
+    else:
+        w[200, 1, 1, 9] = float("inf")  # the centre tap: never over the padding
+    ref = torch.nn.functional.conv2d(x.permute(0, 3, 1, 2).double(), w.permute(0, 3, 1, 2).double(), padding=1)
+    ref = ref.permute(0, 2, 3, 1).numpy()
+    ref = np.where(ref > 0, ref, 0.0)  # ReLU as the library takes it: NaN is not positive
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=W, C_out=K, R=3, S=3, stride=1, pad=1)
+    xd, wd, bd = x.cuda(), w.cuda(), torch.zeros(K, device="cuda")
+    y = torch.empty(B, H, W, K, device="cuda")
+    ws = torch.empty(nf.nf_workspace_bytes(d, None, B), dtype=torch.uint8, device="cuda")
+    nf.nf_prof_begin()
+    nf.nf_layer_fwd(d, B, xd, None, nf.layer_params(wd, bd, None), y, ws)
+    names = {r["kernel"] for r in nf.nf_prof_end()}
+    if nf.nf_contraction() != nf.NF_CONTRACT_F32:
+        pytest.skip("the split modes turn an infinity into NaN")
+    assert "wino_fwd" in names
+    got = y.cpu().numpy().astype(np.float64)
+    inf = np.isinf(ref)
+    assert inf.any() and np.array_equal(np.isinf(got), inf)
+    # finite results: 576 products of unit variance scale; 1e-4 is the suite's bar
+    assert np.abs(got[~inf] - ref[~inf]).max() <= 1e-4 * np.abs(ref[~inf]).max()
