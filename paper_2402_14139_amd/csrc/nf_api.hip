@@ -106,6 +106,18 @@ WgradProblem aux_wgrad_shape(const nf_aux_desc *a, const AuxDims &ad, int B) {
   return g;
 }
 
+// the layer's weight-gradient problem, likewise
+WgradProblem layer_wgrad_shape(const nf_layer_desc *d, const LayerDims &ld, int B) {
+  WgradProblem g;
+  std::memset((void *)&g, 0, sizeof(g));
+  g.H = d->H_in, g.W = d->W_in, g.C = d->C_in, g.R = d->R, g.S = d->S, g.stride = d->stride, g.pad = d->pad,
+  g.Ho = ld.Ho, g.Wo = ld.Wo;
+  if (d->skip_kind == 2) g.Cs = d->skip_C, g.Hs = d->skip_H, g.Ws = d->skip_W, g.ss = d->skip_stride;
+  g.P = d->C_out, g.M = B * ld.Ho * ld.Wo, g.RSC = d->R * d->S * d->C_in, g.Q = g.RSC + g.Cs;
+  g.div_howo = FastDiv(ld.Ho * ld.Wo), g.div_wo = FastDiv(ld.Wo);
+  return g;
+}
+
 HeadShape head_shape(const nf_aux_desc *a, const AuxDims &ad, int B) {
   HeadShape h;
   h.B = B, h.Hu = ad.Hu, h.Wu = ad.Wu, h.A = a->A, h.oh = a->pool_oh, h.ow = a->pool_ow, h.F = ad.F,
@@ -137,6 +149,8 @@ struct WsLayout {
   // > 0: that contraction runs as wino_fwd (fp32 mode) with this many reduction splits; the
   // transformed filter, then the partial sums of the splits, alias `part`
   int wino_layer, wino_aux, wino_dgrad;
+  // > 0: the layer's weight gradient runs as wino_wgrad (fp32 mode) with this many splits
+  int wino_wgrad;
   // head_fused == 2 only: F_n is formed from column sums left by the aux convolution's epilogue
   // (region ppart), no pooling launch
   int pool_fused;
@@ -210,6 +224,8 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
                        ? igemm_wgrad_small_splits(a->A, a->C_in, B, a->H_in)
                        : wgrad_pick_splits(a->A, Qa, B * ad.Hu * ad.Wu);
     w.splits_layer = wgrad_pick_splits(d->C_out, Kl, B * ld.Ho * ld.Wo);
+    w.wino_wgrad = wino_wgrad_pick_splits(layer_wgrad_shape(d, ld, B));
+    pwino = std::max(pwino, (size_t)w.wino_wgrad * d->C_out * w.Qld_layer);
     // split partials of the two weight gradients live side by side: one launch reduces both
     const size_t pa = (size_t)w.splits_aux * a->A * w.Qld_aux, pl = (size_t)w.splits_layer * d->C_out * w.Qld_layer;
     if (pl > pmax) pmax = pl;
@@ -232,14 +248,14 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
       if (w.pool_fused) w.ksplits_aux = 1;
     }
     w.ppart = take(w.pool_fused ? (size_t)B * ad.Hu * ad.Wu / 16 * 2 * a->A * f : 0);
-    w.part_b = take((size_t)w.splits_layer * d->C_out * f);
+    w.part_b = take((size_t)std::max(w.splits_layer, w.wino_wgrad) * d->C_out * f);
     w.part_aux = take(pa * f);
     w.part_b_aux = take((size_t)w.splits_aux * a->A * f);
   }
   if (pwino > pmax) {
     // this scratch must not push a step that the static array holds out of it
     const size_t lim = (size_t)NF_STATIC_SCRATCH_BYTES;
-    if (off + up(pmax * f) <= lim && off + up(pwino * f) > lim) w.wino_layer = w.wino_aux = w.wino_dgrad = 0;
+    if (off + up(pmax * f) <= lim && off + up(pwino * f) > lim) w.wino_layer = w.wino_aux = w.wino_dgrad = w.wino_wgrad = 0;
     else pmax = pwino;
   }
   w.part = take(pmax * f);
@@ -528,18 +544,20 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
   }
   // theta_n: weight, bias and projection gradients; nothing flows to x or x_skip
   {
-    WgradProblem g;
-    std::memset((void *)&g, 0, sizeof(g));
+    WgradProblem g = layer_wgrad_shape(d, ld, B);
     g.d = dZ, g.x = x, g.part = wsf(ws, w.part), g.part_b = wsf(ws, w.part_b);
-    g.H = d->H_in, g.W = d->W_in, g.C = d->C_in, g.R = d->R, g.S = d->S, g.stride = d->stride, g.pad = d->pad,
-    g.Ho = ld.Ho, g.Wo = ld.Wo;
-    if (d->skip_kind == 2) g.xs = xs, g.Cs = d->skip_C, g.Hs = d->skip_H, g.Ws = d->skip_W, g.ss = d->skip_stride;
-    g.P = d->C_out, g.M = B * ld.Ho * ld.Wo, g.RSC = d->R * d->S * d->C_in, g.Q = g.RSC + g.Cs, g.Qld = w.Qld_layer;
-    g.splits = w.splits_layer;
-    g.m_per_split = ((g.M + g.splits - 1) / g.splits + 31) / 32 * 32;  // whole 32-row steps
-    g.div_howo = FastDiv(ld.Ho * ld.Wo), g.div_wo = FastDiv(ld.Wo);
-    const int32_t rc = enqueue_wgrad(g, st);
-    if (rc) return rc;
+    if (d->skip_kind == 2) g.xs = xs;
+    g.Qld = w.Qld_layer;
+    int32_t rc;
+    if (w.wino_wgrad && contraction_mode() == NF_CONTRACT_F32) {
+      g.splits = w.wino_wgrad;
+      const double byts = 4.0 * ((double)g.M * g.P + (double)B * g.H * g.W * g.C + (double)g.P * g.Q);
+      NF_RUN(st, "wino_wgrad", 2.0 * g.M * g.P * g.Q, byts, launch_wino_wgrad(g, st));
+    } else {
+      g.splits = w.splits_layer;
+      g.m_per_split = ((g.M + g.splits - 1) / g.splits + 31) / 32 * 32;  // whole 32-row steps
+      if ((rc = enqueue_wgrad(g, st))) return rc;
+    }
     red.job[0] = reduce_job(g, gp->W, gp->Wp, gp->b);
   }
   red.njobs = 2;

@@ -1,5 +1,6 @@
-"""The 3x3 convolutions that run through F(2x2, 3x3) (csrc/wino_fwd.hip): whole steps against the
-CPU oracle at the sizes where the tiling can go wrong, and values that are not finite."""
+"""The 3x3 convolutions that run through F(2x2, 3x3) (csrc/wino_fwd.hip) and the weight gradients that
+run through F(3x3, 2x2) (csrc/wino_wgrad.hip): whole steps against the CPU oracle at the sizes where
+the tiling can go wrong, and values that are not finite."""
 import numpy as np
 import pytest
 import torch
@@ -68,3 +69,66 @@ def test_wino_values_that_are_not_finite(where):
     assert inf.any() and np.array_equal(np.isinf(got), inf)
     # finite results: 576 products of unit variance scale; 1e-4 is the suite's bar
     assert np.abs(got[~inf] - ref[~inf]).max() <= 1e-4 * np.abs(ref[~inf]).max()
+
+
+WGRAD_CASES = {
+    # odd maps (half-empty tiles), tiles of an image not a multiple of a step's four
+    "odd_map_13x11": (S(64, 13, 11, 128, 4), 64, 10),
+    # ragged channel (32) and filter (64) blocks, identity shortcut, pooled
+    "c36_p132_pool": (S(36, 10, 9, 132, 4, pool=(2, 2, 0)), 96, 10),
+    # narrowest map it takes, a last split shorter than the others
+    "map_4x4_last_split": (S(96, 4, 4, 256, 4), 517, 10),
+    # more than one addition to the result per split
+    "several_periods": (S(256, 8, 8, 256, 4, skip=1), 160, 10),
+}
+
+
+@pytest.mark.parametrize("name", list(WGRAD_CASES))
+def test_wino_weight_gradients_match_oracle(name):
+    spec, B, cls = WGRAD_CASES[name]
+    print(f"case {name}: B={B}", flush=True)
+    nf.nf_prof_begin()
+    out, final = G.run_step_both(spec, cls, B, seed=311, lr=0.05, mu=0.9, steps=1)
+    got = {r["kernel"] for r in nf.nf_prof_end()}
+    G.check_step_results(name, out, final)
+    if nf.nf_contraction() == nf.NF_CONTRACT_F32:
+        assert "wino_wgrad" in got, got
+
+
+def test_wino_weight_gradient_of_an_infinite_input():
+    """An infinity in the corner pixel reaches the four taps that see it, in its channel alone."""
+    B, C, H, K, cls = 64, 64, 16, 128, 10
+    g = torch.Generator(device="cuda").manual_seed(6)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=K, R=3, S=3, stride=1, pad=1)
+    a = nf.AuxDesc(C_in=K, H_in=H, W_in=H, A=8, R=3, S=3, pad=1, relu=0, pool_oh=2, pool_ow=2, n_classes=cls)
+    x, y = rn(B, H, H, C), rn(B, H, H, K).abs() + 0.1  # every pixel passes the ReLU: no zero in dL/dZ
+    labels = torch.randint(0, cls, (B,), generator=g, device="cuda", dtype=torch.int32)
+    p = [rn(K, 3, 3, C) * 0.05, rn(K), rn(8, 3, 3, K) * 0.05, rn(8), rn(cls, 32) * 0.2, rn(cls)]
+    gr = [torch.zeros_like(t) for t in p]
+    lp, ap = nf.layer_params(p[0], p[1], None), nf.aux_params(*p[2:])
+    gp, ga = nf.layer_params(gr[0], gr[1], None), nf.aux_params(*gr[2:])
+    ws = torch.empty(nf.nf_workspace_bytes(d, a, B), dtype=torch.uint8, device="cuda")
+    loss = torch.zeros(1, device="cuda")
+    res = []
+    for bad in (0.0, float("inf")):
+        if bad:
+            x[3, 0, 0, 37] = bad
+        nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, loss, ws)
+        nf.nf_prof_begin()
+        nf.nf_local_bwd_wgrad(d, a, B, x, None, y, lp, ap, gp, ga, ws)
+        names = {r["kernel"] for r in nf.nf_prof_end()}
+        res.append(gr[0].cpu().numpy().copy())
+    if nf.nf_contraction() != nf.NF_CONTRACT_F32:
+        pytest.skip("the split modes turn an infinity into NaN")
+    assert "wino_wgrad" in names
+    inf = np.zeros((K, 3, 3, C), bool)
+    inf[:, :2, :2, 37] = True
+    assert np.array_equal(np.isinf(res[1]), inf) and not np.isnan(res[1]).any()
+    # the taps of that channel that do not see it lose the pixel's old value in neither run: compare all
+    # other channels (1e-4: the suite's bar)
+    keep = np.arange(C) != 37
+    ref = res[0][..., keep]
+    assert np.abs(res[1][..., keep] - ref).max() <= 1e-4 * np.abs(ref).max()
+    tail = res[0][:, 2, :, 37]
+    assert np.abs(res[1][:, 2, :, 37] - tail).max() <= 1e-4 * np.abs(ref).max()
