@@ -359,26 +359,32 @@ bool applicable(const FwdProblem &p) {
 }  // namespace
 
 // Which kernel, and how many reduction splits: both times are estimated from the step times below and
-// the smaller one wins.  The line was checked on 240 shapes (16 ... 512 channels, 64 ... 512 filters, 256 ... 65 536
-// pixels, maps of 2 ... 32): the choice is within 0.5 % of the faster of the two on average and never
-// more than 10 % off it; taking the direct kernel always is 27 % off.  Examples (us, direct / this):
-// 512 -> 512 channels, 8192 pixels 312 / 150; 128 -> 128, 16 384 pixels 45 / 30, 4096 pixels 20 / 22 (direct);
-// 256 -> 512, 1024 pixels 37 / 28 (4 splits); 64 -> 64, 65 536 pixels 43 / 34.
-// The map's size only enters through the number of tiles.
+// the smaller one wins.  The estimates were checked on 240 shapes (16 ... 512 channels, 64 ... 512 filters,
+// 256 ... 65 536 pixels): the choice is within 0.5 % of the faster of the two on average and never more than
+// 10 % off it; taking the direct kernel always is 27 % off.  Examples (us, direct / this): 512 -> 512 channels,
+// 8192 pixels 312 / 150; 128 -> 128, 16 384 pixels 45 / 30, 4096 pixels 20 / 22 (direct); 512 -> 512, 1024 pixels
+// 52 / 40 (8 splits); 64 -> 64, 65 536 pixels 43 / 34.
+// Two lines are drawn by accuracy, not by time.  Where the direct kernel splits its reduction its sums
+// are short, and this one needs about as many splits to stay below their error (512 -> 512, 1024 pixels,
+// 8 direct splits 2.7e-7: 4 splits here 3.4e-7, 8 splits 2.5e-7).  On maps narrower than 4 most taps
+// multiply padding: the direct sum skips their rounding, the transforms do not (2x2 maps 1.5e-7
+// against 1.9e-7 ... 2.9e-7).
 int wino_fwd_pick_splits(const FwdProblem &p) {
   // up to 32 filters half of a workgroup's columns would be padding
-  if (p.N <= 32 || !applicable(p)) return 0;
+  if (p.N <= 32 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
   const double mn = (double)p.M * p.N;
   const int B = p.M / (p.Ho * p.Wo);
   const long long tiles = ((long long)B * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) + TB - 1) / TB;
   const long long wgs = tiles * ((p.N + NB - 1) / NB);
   const int nchunks = (p.C + CH - 1) / CH;
+  const int ks = igemm_fwd_pick_ksplits(p.M, p.N, p.Kg, p.C, p.R * p.S);  // of the direct kernel
   auto finish_us = [&](int s) { return s > 1 ? 3.5 + mn * 4.0 * (s + 1) / 4e6 : 0.0; };  // fwd_finish at 4 TB/s
   // this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two; 11 us of prologue, epilogue and
   // launches; the transformed filter written and read at 4 TB/s
   double best = 0.0;
   int splits = 0;
   for (int s = 1; s <= 16; s *= 2) {
+    if (4 * s < 3 * ks) continue;
     if (s > 1 && (nchunks / s < 2 || wgs * s > 512)) break;
     const double per = wgs * s <= 256 ? 1.13 : wgs * s <= 512 ? 2.12 : 2.12 * (wgs * s) / 512.0;
     const double us = 11.0 + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per + finish_us(s);
@@ -386,13 +392,12 @@ int wino_fwd_pick_splits(const FwdProblem &p) {
   }
   // the direct kernel: steps of 32 products, 128x128 tiles one per CU or 64x64 tiles up to four
   const int nkb = (p.Kg + 31) / 32;
-  const int ks = igemm_fwd_pick_ksplits(p.M, p.N, p.Kg, p.C, p.R * p.S);
   const bool big = p.N > 128 && p.Kg > 160;
   const int bt = big ? 128 : 64;
   const long long w = (long long)((p.M + bt - 1) / bt) * ((p.N + bt - 1) / bt) * ks;
   const double per = big ? 2.06 * ((w + 255) / 256) : w <= 260 ? 0.56 : 0.55 * w / 256.0;
   const double direct = 8.0 + (nkb + ks - 1) / ks * per + finish_us(ks);
-  return best < 0.93 * direct ? splits : 0;
+  return splits && best < 0.93 * direct ? splits : 0;
 }
 
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st) {

@@ -19,11 +19,11 @@ CASES = {
     # channel count not a multiple of the step (8), identity shortcut
     "c68_identity": (S(256, 8, 8, 256, 4, skip=1), 5, 10, 1),
     "c68": (S(68, 8, 8, 256, 4), 5, 10, 1),
-    # one pixel per map: a tile is one pixel and 15 zeros
-    "map_1x1": (S(64, 1, 1, 256, 8), 300, 10, 1),
-    # split reduction, pooled; head and data gradient split as well
-    "split_pool_wide_head": (S(512, 2, 2, 256, 256, pool=(2, 2, 0)), 64, 10, 2),
-    "split_wide_head": (S(256, 2, 2, 256, 256), 128, 10, 3),
+    # the narrowest map it takes, an odd one
+    "map_4x5": (S(64, 4, 5, 256, 8), 20, 10, 1),
+    # split reductions: layer (pooled), and all three of layer, head and data gradient
+    "split_pool": (S(256, 8, 8, 256, 4, pool=(2, 2, 0)), 4, 10, 1),
+    "split_wide_head": (S(256, 4, 4, 256, 256), 16, 10, 3),
     # fewer filters than a workgroup's 64 columns
     "n60": (S(128, 16, 16, 60, 4), 100, 10, 1),
 }
