@@ -264,7 +264,7 @@ __global__ __launch_bounds__(NTHREADS) void igemm_wgrad_kernel(WgradProblem p) {
   }
 }
 
-// Sum of the split partials in a fixed order, for up to two weight gradients in one launch,
+// Sum of the split partials in a fixed order, for up to three weight gradients in one launch,
 // optionally followed in place by the update line of Algorithm 2 (momentum SGD) for the tensors
 // just reduced and for up to two more whose gradient is already final.
 // Per gradient: a workgroup owns 256/ZS groups of four consecutive elements of the flattened
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(ReduceSgd r) {
   const int t = threadIdx.x;
   int b = blockIdx.x;
 #pragma unroll
-  for (int ji = 0; ji < 2; ++ji) {
+  for (int ji = 0; ji < 3; ++ji) {
     if (ji >= r.njobs) break;
     const WgradReduce &jb = r.job[ji];
     if (b < jb.main_blocks && jb.direct) {

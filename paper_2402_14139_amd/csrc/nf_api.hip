@@ -149,8 +149,9 @@ struct WsLayout {
   // > 0: that contraction runs as wino_fwd (fp32 mode) with this many reduction splits; the
   // transformed filter, then the partial sums of the splits, alias `part`
   int wino_layer, wino_aux, wino_dgrad;
-  // > 0: the layer's weight gradient runs as wino_wgrad (fp32 mode) with this many splits
-  int wino_wgrad;
+  // > 0: the layer's weight gradient runs as wino_wgrad (fp32 mode) with this many splits; the projection's,
+  // if any, is a contraction of its own with proj_splits, its partial sums behind the other ones
+  int wino_wgrad, proj_splits;
   // head_fused == 2 only: F_n is formed from column sums left by the aux convolution's epilogue
   // (region ppart), no pooling launch
   int pool_fused;
@@ -225,7 +226,9 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
                        : wgrad_pick_splits(a->A, Qa, B * ad.Hu * ad.Wu);
     w.splits_layer = wgrad_pick_splits(d->C_out, Kl, B * ld.Ho * ld.Wo);
     w.wino_wgrad = wino_wgrad_pick_splits(layer_wgrad_shape(d, ld, B));
-    pwino = std::max(pwino, (size_t)w.wino_wgrad * d->C_out * w.Qld_layer);
+    if (w.wino_wgrad && d->skip_kind == 2) w.proj_splits = wgrad_pick_splits(d->C_out, d->skip_C, B * ld.Ho * ld.Wo);
+    pwino = std::max(pwino, (size_t)w.wino_wgrad * d->C_out * (Kl - d->skip_C * (d->skip_kind == 2)) +
+                                (size_t)w.proj_splits * d->C_out * ((d->skip_C + 3) / 4 * 4));
     // split partials of the two weight gradients live side by side: one launch reduces both
     const size_t pa = (size_t)w.splits_aux * a->A * w.Qld_aux, pl = (size_t)w.splits_layer * d->C_out * w.Qld_layer;
     if (pl > pmax) pmax = pl;
@@ -371,9 +374,31 @@ int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, hipSt
   return NF_OK;
 }
 
-// by the layout's plan: wino_fwd, or the direct kernels (the split-operand modes always use those)
+// whether a contraction is carried out with the fp32 instructions in the mode in force: always in the
+// fp32 mode, in the split-operand modes where their kernels do not serve it (narrow layers)
+bool fp32_contraction(const FwdProblem &f) {
+  return contraction_mode() == NF_CONTRACT_F32 || !(igemm_fwd_fast_applicable(f) && igemm_fwd_split_applicable(f));
+}
+bool fp32_contraction(const WgradProblem &g) {
+  return contraction_mode() == NF_CONTRACT_F32 || !(igemm_wgrad_fast_applicable(g) && igemm_wgrad_split_applicable(g));
+}
+
+// by the layout's plan: wino_fwd, or the direct kernels
 int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, float *part, hipStream_t st) {
-  if (wino && contraction_mode() == NF_CONTRACT_F32) return enqueue_wino(f, out, wino, part, st);
+  if (wino && fp32_contraction(f)) {
+    FwdProblem g = f;
+    if (f.Cs) {  // the projection first, into `out`; wino_fwd adds it there (each element read by the thread that writes it)
+      FwdProblem pr;
+      std::memset((void *)&pr, 0, sizeof(pr));
+      pr.x = f.xs, pr.w = f.wp, pr.out = out;
+      pr.H = f.Hs, pr.W = f.Ws, pr.C = f.Cs, pr.N = f.N, pr.R = pr.S = 1, pr.stride = f.ss, pr.Ho = f.Ho, pr.Wo = f.Wo;
+      pr.M = f.M, pr.RSC = pr.Kg = f.Cs, pr.div_howo = f.div_howo, pr.div_wo = f.div_wo;
+      const int32_t rc = enqueue_fwd(pr, st);
+      if (rc) return rc;
+      g.Cs = 0, g.Kg = g.RSC, g.addsrc = out;
+    }
+    return enqueue_wino(g, out, wino, part, st);
+  }
   return enqueue_fwd_split(f, out, ksplits, part, st);
 }
 
@@ -423,7 +448,7 @@ int32_t run_aux_conv(const nf_aux_desc *a, const AuxDims &ad, int B, const float
                      const WsLayout &w, hipStream_t st, bool pool_partials, int *ks, const float **parts) {
   FwdProblem f = aux_fwd_problem(a, ad, B);
   f.x = y, f.w = ap->Wa, f.bias = ap->ba;
-  const bool wino = w.wino_aux && contraction_mode() == NF_CONTRACT_F32;
+  const bool wino = w.wino_aux && fp32_contraction(f);
   const int splits = wino ? w.wino_aux : igemm_fwd_fast_applicable(f) ? w.ksplits_aux : 1;
   *ks = splits > 1 ? splits : 0;
   float *const part = wsf(ws, w.part) + (wino ? wino_fwd_filter_floats(f.N, f.C) : 0);
@@ -549,10 +574,19 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
     if (d->skip_kind == 2) g.xs = xs;
     g.Qld = w.Qld_layer;
     int32_t rc;
-    if (w.wino_wgrad && contraction_mode() == NF_CONTRACT_F32) {
-      g.splits = w.wino_wgrad;
+    if (w.wino_wgrad && fp32_contraction(g)) {
+      WgradProblem pr = g;  // the projection's columns
+      g.splits = w.wino_wgrad, g.Q = g.Qld = g.RSC, g.Cs = 0;
       const double byts = 4.0 * ((double)g.M * g.P + (double)B * g.H * g.W * g.C + (double)g.P * g.Q);
       NF_RUN(st, "wino_wgrad", 2.0 * g.M * g.P * g.Q, byts, launch_wino_wgrad(g, st));
+      if (pr.Cs) {
+        pr.x = xs, pr.H = pr.Hs, pr.W = pr.Ws, pr.C = pr.Cs, pr.stride = pr.ss, pr.R = pr.S = 1, pr.pad = 0, pr.Cs = 0;
+        pr.Q = pr.RSC = pr.C, pr.Qld = (pr.Q + 3) / 4 * 4, pr.splits = w.proj_splits, pr.part_b = nullptr;
+        pr.part = g.part + (size_t)g.splits * g.P * g.Qld;
+        pr.m_per_split = ((pr.M + pr.splits - 1) / pr.splits + 31) / 32 * 32;
+        if ((rc = enqueue_wgrad(pr, st))) return rc;
+        red.job[2] = reduce_job(pr, gp->Wp, nullptr, nullptr);
+      }
     } else {
       g.splits = w.splits_layer;
       g.m_per_split = ((g.M + g.splits - 1) / g.splits + 31) / 32 * 32;  // whole 32-row steps
@@ -560,16 +594,18 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
     }
     red.job[0] = reduce_job(g, gp->W, gp->Wp, gp->b);
   }
-  red.njobs = 2;
+  red.njobs = red.job[2].part ? 3 : 2;
   double nred = 0, nsgd = 0;
-  for (int j = 0; j < 2; ++j) nred += ((double)red.job[j].splits + 1.0) * red.job[j].P * (red.job[j].Q + 1.0);
+  for (int j = 0; j < red.njobs; ++j) nred += ((double)red.job[j].splits + 1.0) * red.job[j].P * (red.job[j].Q + 1.0);
   if (sgd) {
     const bool mom = sgd->momentum != 0.f;
     red.lr = sgd->lr, red.mu = sgd->momentum;
     red.job[0].w0 = p->W, red.job[0].w1 = p->Wp, red.job[0].wb = p->b;
+    red.job[2].w0 = p->Wp;
     red.job[1].w0 = ap->Wa, red.job[1].wb = ap->ba;
     if (mom) {
       red.job[0].v0 = vp->W, red.job[0].v1 = vp->Wp, red.job[0].vb = vp->b;
+      red.job[2].v0 = vp->Wp;
       red.job[1].v0 = va->Wa, red.job[1].vb = va->ba;
     }
     if (!w.head_fused) {
@@ -577,7 +613,7 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
       red.xw[0] = ap->Wf, red.xg[0] = ga->Wf, red.xv[0] = mom ? va->Wf : nullptr, red.xn[0] = (long long)a->n_classes * ad.F;
       red.xw[1] = ap->bf, red.xg[1] = ga->bf, red.xv[1] = mom ? va->bf : nullptr, red.xn[1] = a->n_classes;
     }
-    for (int j = 0; j < 2; ++j) nsgd += (double)red.job[j].P * (red.job[j].Q + 1.0);
+    for (int j = 0; j < red.njobs; ++j) nsgd += (double)red.job[j].P * (red.job[j].Q + 1.0);
     nsgd += fc + a->n_classes;
     nsgd *= mom ? 16.0 : 8.0;  // bytes beyond the gradient write
   }

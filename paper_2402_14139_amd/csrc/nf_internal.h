@@ -73,7 +73,8 @@ hipError_t launch_igemm_fwd_split(const FwdProblem &p, bool nine, hipStream_t st
 // 3x3 / stride 1 / pad 1 through F(2x2, 3x3) in fp32 (wino_fwd.hip).  `U` is scratch for the transformed
 // filter (wino_fwd_filter_floats floats, 16-byte aligned); two launches.
 size_t wino_fwd_filter_floats(int N, int C);
-// 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none)
+// 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none).  Of a
+// problem with a projection (Cs) it serves the 3x3 part: the caller adds the projection through addsrc
 int wino_fwd_pick_splits(const FwdProblem &p);
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st);
 
@@ -106,7 +107,8 @@ bool igemm_wgrad_split_applicable(const WgradProblem &p);
 hipError_t launch_igemm_wgrad_split(const WgradProblem &p, bool nine, hipStream_t st, const char **kernel);
 // 3x3 / stride 1 / pad 1 through F(3x3, 2x2) in fp32 (wino_wgrad.hip); `splits` are ranges of 2x2 output
 // tiles there (any count is valid), m_per_split is not read
-// 0: not served or the direct kernel is faster; else the number of splits
+// 0: not served or the direct kernel is faster; else the number of splits.  Of a problem with
+// projection columns it forms the first RSC: Qld is theirs then
 int wino_wgrad_pick_splits(const WgradProblem &p);
 hipError_t launch_wino_wgrad(const WgradProblem &p, hipStream_t st);
 // 3x3 / stride 1 / pad 1 with at most 32 output channels (igemm_wgrad_small.hip): 4x4x1 MFMA with a
@@ -143,7 +145,7 @@ struct WgradReduce {
   int ZS, main_blocks, bias_blocks, vec4, direct;  // filled by the launcher
 };
 struct ReduceSgd {
-  WgradReduce job[2];
+  WgradReduce job[3];
   int njobs;
   // tensors whose gradient is final already (update only; used when lr/mu are given)
   float *xw[2];

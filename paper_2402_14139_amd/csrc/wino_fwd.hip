@@ -351,7 +351,7 @@ size_t wino_fwd_filter_floats(int N, int C) {
 
 namespace {
 bool applicable(const FwdProblem &p) {
-  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.Cs || p.pool_part) return false;
+  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.pool_part) return false;
   if (p.C % 4 || p.N % 4) return false;
   const long long lim = 0x7FFFFFF0ll, B = p.M / ((long long)p.Ho * p.Wo);
   return B * p.H * p.W * p.C * 4 <= lim && (long long)wino_fwd_filter_floats(p.N, p.C) * 4 <= lim;
@@ -370,8 +370,9 @@ bool applicable(const FwdProblem &p) {
 // multiply padding: the direct sum skips their rounding, the transforms do not (2x2 maps 1.5e-7
 // against 1.9e-7 ... 2.9e-7).
 int wino_fwd_pick_splits(const FwdProblem &p) {
-  // up to 32 filters half of a workgroup's columns would be padding
-  if (p.N <= 32 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
+  // up to 32 filters half of a workgroup's columns would be padding; below 16 channels the result's own
+  // traffic is all there is to either kernel (8 channels, 16 384 x 256 results: 17 / 14 + 5 for the filter launch)
+  if (p.N <= 32 || p.C < 16 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
   const double mn = (double)p.M * p.N;
   const int B = p.M / (p.Ho * p.Wo);
   const long long tiles = ((long long)B * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) + TB - 1) / TB;
@@ -381,13 +382,15 @@ int wino_fwd_pick_splits(const FwdProblem &p) {
   auto finish_us = [&](int s) { return s > 1 ? 3.5 + mn * 4.0 * (s + 1) / 4e6 : 0.0; };  // fwd_finish at 4 TB/s
   // this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two; 11 us of prologue, epilogue and
   // launches; the transformed filter written and read at 4 TB/s
+  // a projection shortcut is a launch of its own whose result this kernel adds (enqueue_conv)
+  const double proj_us = p.Cs ? 8.0 + 2.0 * mn * p.Cs / 90e6 + 4.0 * mn / 4e6 : 0.0;
   double best = 0.0;
   int splits = 0;
   for (int s = 1; s <= 16; s *= 2) {
     if (4 * s < 3 * ks) continue;
     if (s > 1 && (nchunks / s < 2 || wgs * s > 512)) break;
     const double per = wgs * s <= 256 ? 1.13 : wgs * s <= 512 ? 2.12 : 2.12 * (wgs * s) / 512.0;
-    const double us = 11.0 + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per + finish_us(s);
+    const double us = 11.0 + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per + finish_us(s) + proj_us;
     if (!splits || us < best) best = us, splits = s;
   }
   // the direct kernel: steps of 32 products, 128x128 tiles one per CU or 64x64 tiles up to four

@@ -326,7 +326,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_wgrad_kernel(WgradProblem p,
 
 namespace {
 bool applicable(const WgradProblem &p) {
-  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.Cs || p.C % 4 || p.P % 4) return false;
+  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.C % 4 || p.P % 4) return false;
   const long long lim = OOB_T, B = p.M / ((long long)p.Ho * p.Wo);
   return (long long)p.M * p.P * 4 <= lim && B * p.H * p.W * p.C * 4 <= lim;
 }
@@ -349,6 +349,8 @@ int wino_wgrad_pick_splits(const WgradProblem &p) {
   if (p.P <= 32 || p.M < 8192 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
   const long long T = num_tiles(p), blocks = (long long)((p.C + QB - 1) / QB) * ((p.P + PB - 1) / PB);
   auto reduce_us = [&](int s) { return s * (double)p.P * p.Q * 4.0 / 4e6; };  // at 4 TB/s
+  // the columns of a projection shortcut are a launch of their own (run_bwd)
+  const double proj_us = p.Cs ? 10.0 + 2.0 * p.M * p.P * p.Cs / 90e6 : 0.0;
   // a step of four tiles takes 1.0 us with one workgroup on a CU, 1.54 with two
   double best = 0.0;
   int splits = 0;
@@ -356,7 +358,7 @@ int wino_wgrad_pick_splits(const WgradProblem &p) {
     const int s = (int)((wgs + blocks - 1) / blocks);
     if (s > 1 && T / s < 16) break;
     const double w = (double)blocks * s;
-    const double us = 11.0 + tiles_per_split(T, s) / KT * (w <= 256 ? 1.0 : w <= 512 ? 1.54 : 1.54 * w / 512) + reduce_us(s);
+    const double us = 11.0 + tiles_per_split(T, s) / KT * (w <= 256 ? 1.0 : w <= 512 ? 1.54 : 1.54 * w / 512) + reduce_us(s) + proj_us;
     if (!splits || us < best) best = us, splits = s;
   }
   // the direct kernel: its padded contraction at the rate its tile reaches, plus ramp-up and drain

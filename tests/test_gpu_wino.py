@@ -24,6 +24,8 @@ CASES = {
     # split reductions: layer (pooled), and all three of layer, head and data gradient
     "split_pool": (S(256, 8, 8, 256, 4, pool=(2, 2, 0)), 4, 10, 1),
     "split_wide_head": (S(256, 4, 4, 256, 256), 16, 10, 3),
+    # projection shortcut: a launch of its own, added in the epilogue
+    "projection": (S(128, 8, 8, 256, 4, skip=2, skip_C=36), 130, 10, 1),
     # fewer filters than a workgroup's 64 columns
     "n60": (S(128, 16, 16, 60, 4), 100, 10, 1),
 }
@@ -78,6 +80,8 @@ WGRAD_CASES = {
     "c36_p132_pool": (S(36, 10, 9, 132, 4, pool=(2, 2, 0)), 96, 10),
     # narrowest map it takes, a last split shorter than the others
     "map_4x4_last_split": (S(96, 4, 4, 256, 4), 517, 10),
+    # projection shortcut (its columns are a launch of their own)
+    "projection": (S(128, 8, 8, 192, 4, skip=2, skip_C=68), 200, 10),
     # more than one addition to the result per split
     "several_periods": (S(256, 8, 8, 256, 4, skip=1), 160, 10),
 }
