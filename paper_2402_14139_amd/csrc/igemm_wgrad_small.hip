@@ -274,6 +274,11 @@ bool igemm_wgrad_small_applicable(const WgradProblem &p) {
   if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.Cs != 0) return false;
   // measured: from 32 output channels on the tiled MFMA kernel is faster (no padding left to save)
   if (p.Ho != p.H || p.Wo != p.W || p.P > 16 || p.P % 4 || p.C % 4) return false;
+  // Few pixels times channels: the four waves' sums, a wave's ring and its descriptors cost the same
+  // however few pixels there are (18 us for 8192 pixels x 16 channels), and the tiled kernel is done sooner
+  // although it pads P to 32 (10 us; 16 384 x 64: 18 / 12).  They meet near 3 million (16 384 x 128: equal; 16 384 x 512
+  // in favour of this one by 1.5; measured for P = 4 ... 16, both with their reduction).
+  if ((long long)p.M * p.C < (3ll << 20)) return false;
   if ((long long)p.M * p.P * 4 > lim || B * p.H * p.W * p.C * 4 > lim) return false;
   return true;
 }

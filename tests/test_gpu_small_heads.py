@@ -1,0 +1,29 @@
+"""Weight gradients of narrow heads on both sides of the line between the 4x4x1 kernel and the tiled one
+(pixels times channels, csrc/igemm_wgrad_small.hip), with ragged channel counts, against the oracle."""
+import pytest
+
+from paper_2402_14139_amd import binding as nf
+from tests import gpu_common as G
+from tests.test_gpu_parity import S
+
+pytestmark = pytest.mark.gpu
+
+# name -> (spec, B, kernel of the head's weight gradient)
+CASES = {
+    "a12_c136_above": (S(8, 16, 16, 136, 12), 93, "wgrad_small_4x4"),
+    "a4_c260_above": (S(8, 9, 7, 260, 4), 200, "wgrad_small_4x4"),
+    "a8_c132_above": (S(8, 16, 16, 132, 8), 95, "wgrad_small_4x4"),
+    "a12_c136_below": (S(8, 16, 16, 136, 12), 90, "igemm_wgrad_fast_32x128"),
+    "a16_c64_below": (S(8, 7, 5, 64, 16), 3, "igemm_wgrad_fast_32x128"),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_narrow_heads_match_oracle(name):
+    spec, B, kernel = CASES[name]
+    print(f"case {name}: B={B}", flush=True)
+    nf.nf_prof_begin()
+    out, final = G.run_step_both(spec, 10, B, seed=320, lr=0.05, mu=0.9, steps=1)
+    got = {r["kernel"] for r in nf.nf_prof_end()}
+    G.check_step_results(name, out, final)
+    assert kernel in got, got
