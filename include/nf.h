@@ -105,7 +105,10 @@ const char *nf_strerror(int32_t status);
 /* How the wide contractions (the convolution of Eq. 1 and its weight gradient in Algorithm 2, for
  * layers with at least 128 filters) are carried out.  Operands, results and accumulation are fp32
  * in both modes.
- *   NF_CONTRACT_F32     (default) fp32 matrix-core instructions (v_mfma_f32_32x32x2_f32).
+ *   NF_CONTRACT_F32     (default) fp32 matrix-core instructions (v_mfma_f32_*).  3x3 convolutions of
+ *                       stride 1 and pad 1, and their weight gradients, go through the minimal filtering
+ *                       algorithms F(2x2,3x3) / F(3x3,2x2), all in fp32, where that is faster and its
+ *                       error against 64 bits is below the direct sum's.
  *   NF_CONTRACT_BF16X6  each fp32 operand element is cut into three bfloat16 pieces that sum to it
  *                       exactly; six of the nine piece products are accumulated in fp32 by bf16
  *                       matrix-core instructions.  The three left out are together below 2^-21 of
@@ -113,7 +116,8 @@ const char *nf_strerror(int32_t status);
  *                       square, i.e. of the size of an fp32 rounding; over the reductions of this
  *                       library (36 ... 4608 terms) the measured error against fp64 equals that of
  *                       the fp32 instructions.  An operand element that is +-inf gives NaN
- *                       instead of +-inf.
+ *                       instead of +-inf.  Contractions that NF_CONTRACT_F32 carries out faster run as
+ *                       there.
  *   NF_CONTRACT_BF16X9  the same with all nine piece products: every product x*w enters the fp32
  *                       accumulation exactly, as with the fp32 instructions; 1.5x the matrix-core
  *                       work of BF16X6.

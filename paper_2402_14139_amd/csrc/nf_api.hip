@@ -149,6 +149,7 @@ struct WsLayout {
   // > 0: that contraction runs as wino_fwd (fp32 mode) with this many reduction splits; the
   // transformed filter, then the partial sums of the splits, alias `part`
   int wino_layer, wino_aux, wino_dgrad;
+  int wino_split_mode;  // 1: the scratch also serves wino_fwd in place of the six-product kernel
   // > 0: the layer's weight gradient runs as wino_wgrad (fp32 mode) with this many splits; the projection's,
   // if any, is a contraction of its own with proj_splits, its partial sums behind the other ones
   int wino_wgrad, proj_splits;
@@ -181,12 +182,20 @@ FwdProblem layer_fwd_problem(const nf_layer_desc *d, const LayerDims &ld, int B)
   return f;
 }
 
-// scratch of a forward-type contraction that runs as wino_fwd (out: elements of its result)
-size_t wino_scratch_floats(int splits, int N, int C, size_t out) {
-  return splits ? wino_fwd_filter_floats(N, C) + (splits > 1 ? splits * out : 0) : 0;
+// The six-product kernel adds two half sums, so where wino_fwd replaces it a long sum is cut in two as
+// well (512 channels: error 4.2e-7; uncut 4.4e-7, cut 3.5e-7).
+int wino_splits_split_mode(const FwdProblem &f, int splits) { return splits == 1 && f.C > 256 ? 2 : splits; }
+
+// scratch of a forward-type contraction that runs as wino_fwd (split_mode: in place of the six-product kernel)
+size_t wino_scratch_floats(int splits, const FwdProblem &f, bool split_mode) {
+  if (!splits) return 0;
+  if (split_mode && igemm_fwd_split_applicable(f)) splits = wino_splits_split_mode(f, splits);
+  return wino_fwd_filter_floats(f.N, f.C) + (splits > 1 ? (size_t)splits * f.M * f.N : 0);
 }
 
-WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B) {
+// wino = false: without the wino_* kernels and what they need beyond the direct ones
+WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B,
+                   bool wino = true) {
   WsLayout w;
   std::memset(&w, 0, sizeof(w));
   size_t off = 0;
@@ -204,8 +213,9 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
   const int Kl = d->R * d->S * d->C_in + (d->skip_kind == 2 ? d->skip_C : 0);
   w.ksplits_layer = igemm_fwd_pick_ksplits(B * ld.Ho * ld.Wo, d->C_out, Kl, d->C_in, d->R * d->S);
   size_t pmax = w.ksplits_layer > 1 ? (size_t)w.ksplits_layer * conv_out : 0;
-  w.wino_layer = wino_fwd_pick_splits(layer_fwd_problem(d, ld, B));
-  size_t pwino = wino_scratch_floats(w.wino_layer, d->C_out, d->C_in, conv_out);
+  const FwdProblem fl = layer_fwd_problem(d, ld, B);
+  w.wino_layer = wino ? wino_fwd_pick_splits(fl) : 0;
+  size_t pwino = wino_scratch_floats(w.wino_layer, fl, false), pcut = wino_scratch_floats(w.wino_layer, fl, true);
   w.ksplits_aux = w.ksplits_dgrad = 1;
   if (a) {
     const size_t u = (size_t)B * ad.Hu * ad.Wu * a->A;
@@ -225,7 +235,7 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
                        ? igemm_wgrad_small_splits(a->A, a->C_in, B, a->H_in)
                        : wgrad_pick_splits(a->A, Qa, B * ad.Hu * ad.Wu);
     w.splits_layer = wgrad_pick_splits(d->C_out, Kl, B * ld.Ho * ld.Wo);
-    w.wino_wgrad = wino_wgrad_pick_splits(layer_wgrad_shape(d, ld, B));
+    w.wino_wgrad = wino ? wino_wgrad_pick_splits(layer_wgrad_shape(d, ld, B)) : 0;
     if (w.wino_wgrad && d->skip_kind == 2) w.proj_splits = wgrad_pick_splits(d->C_out, d->skip_C, B * ld.Ho * ld.Wo);
     pwino = std::max(pwino, (size_t)w.wino_wgrad * d->C_out * (Kl - d->skip_C * (d->skip_kind == 2)) +
                                 (size_t)w.proj_splits * d->C_out * ((d->skip_C + 3) / 4 * 4));
@@ -238,10 +248,11 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     if (w.ksplits_aux > 1 && (size_t)w.ksplits_aux * u > pmax) pmax = (size_t)w.ksplits_aux * u;
     w.ksplits_dgrad = igemm_fwd_pick_ksplits(B * a->H_in * a->W_in, a->C_in, a->R * a->S * a->A, a->A, a->R * a->S);
     if (w.ksplits_dgrad > 1 && (size_t)w.ksplits_dgrad * emitted > pmax) pmax = (size_t)w.ksplits_dgrad * emitted;
-    w.wino_aux = wino_fwd_pick_splits(aux_fwd_problem(a, ad, B));
-    w.wino_dgrad = wino_fwd_pick_splits(dgrad_problem(a, ad, B));
-    pwino = std::max(pwino, wino_scratch_floats(w.wino_aux, a->A, a->C_in, u));
-    pwino = std::max(pwino, wino_scratch_floats(w.wino_dgrad, a->C_in, a->A, emitted));
+    const FwdProblem fa = aux_fwd_problem(a, ad, B), fd = dgrad_problem(a, ad, B);
+    w.wino_aux = wino ? wino_fwd_pick_splits(fa) : 0;
+    w.wino_dgrad = wino ? wino_fwd_pick_splits(fd) : 0;
+    pwino = std::max({pwino, wino_scratch_floats(w.wino_aux, fa, false), wino_scratch_floats(w.wino_dgrad, fd, false)});
+    pcut = std::max({pcut, wino_scratch_floats(w.wino_aux, fa, true), wino_scratch_floats(w.wino_dgrad, fd, true)});
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;
     if (w.head_fused == 2 && head_pool_partials_applicable(head_shape(a, ad, B))) {
       // (a reduction split in two gives way: the pooling launch it would need costs more than it gains)
@@ -255,15 +266,26 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     w.part_aux = take(pa * f);
     w.part_b_aux = take((size_t)w.splits_aux * a->A * f);
   }
-  if (pwino > pmax) {
-    // this scratch must not push a step that the static array holds out of it
+  // this scratch must not push a step that the static array holds out of it
+  const auto pushes_out = [&](size_t floats) {
     const size_t lim = (size_t)NF_STATIC_SCRATCH_BYTES;
-    if (off + up(pmax * f) <= lim && off + up(pwino * f) > lim) w.wino_layer = w.wino_aux = w.wino_dgrad = w.wino_wgrad = 0;
-    else pmax = pwino;
-  }
+    return floats > pmax && off + up(pmax * f) <= lim && off + up(floats * f) > lim;
+  };
+  if (pushes_out(pwino)) w.wino_layer = w.wino_aux = w.wino_dgrad = w.wino_wgrad = 0;
+  else pmax = std::max(pmax, pwino);
+  w.wino_split_mode = w.wino_layer + w.wino_aux + w.wino_dgrad > 0 && !pushes_out(pcut);
+  if (w.wino_split_mode) pmax = std::max(pmax, pcut);
   w.part = take(pmax * f);
   w.total = off ? off : ALIGN;
   return w;
+}
+
+// the layout a call uses in a workspace of `have` bytes: one that only holds the direct kernels (the
+// regions before the partial sums lie the same) runs those
+WsLayout ws_layout_in(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B,
+                      size_t have) {
+  const WsLayout w = ws_layout(d, ld, a, ad, B);
+  return have < w.total ? ws_layout(d, ld, a, ad, B, false) : w;
 }
 
 int32_t check_ws(const void *ws, size_t have, size_t need) {
@@ -374,18 +396,28 @@ int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, hipSt
   return NF_OK;
 }
 
-// whether a contraction is carried out with the fp32 instructions in the mode in force: always in the
-// fp32 mode, in the split-operand modes where their kernels do not serve it (narrow layers)
-bool fp32_contraction(const FwdProblem &f) {
-  return contraction_mode() == NF_CONTRACT_F32 || !(igemm_fwd_fast_applicable(f) && igemm_fwd_split_applicable(f));
+// The reduction splits with which a contraction that the layout plans as wino_fwd runs in the mode in force;
+// 0: the direct kernels.  Always so in the fp32 mode; in the split-operand modes where their kernels do not
+// serve it (narrow layers), with six piece products also where those are slower (with nine the caller
+// asks for exact products, which a transformed contraction does not form).
+int wino_splits_now(const FwdProblem &f, int splits, const WsLayout &w) {
+  const int mode = contraction_mode();
+  if (!splits || mode == NF_CONTRACT_F32 || !igemm_fwd_fast_applicable(f) || !igemm_fwd_split_applicable(f)) return splits;
+  splits = wino_splits_split_mode(f, splits);
+  return mode == NF_CONTRACT_BF16X6 && w.wino_split_mode && wino_fwd_beats_split(f, splits) ? splits : 0;
 }
-bool fp32_contraction(const WgradProblem &g) {
-  return contraction_mode() == NF_CONTRACT_F32 || !(igemm_wgrad_fast_applicable(g) && igemm_wgrad_split_applicable(g));
+// whether the layer's weight gradient, planned as wino_wgrad, runs that way in the mode in force
+bool run_wino(const WgradProblem &g, int splits) {
+  if (!splits) return false;
+  const int mode = contraction_mode();
+  return mode == NF_CONTRACT_F32 || !igemm_wgrad_fast_applicable(g) || !igemm_wgrad_split_applicable(g) ||
+         (mode == NF_CONTRACT_BF16X6 && wino_wgrad_beats_split(g, splits));
 }
 
 // by the layout's plan: wino_fwd, or the direct kernels
-int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, float *part, hipStream_t st) {
-  if (wino && fp32_contraction(f)) {
+int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, const WsLayout &w, float *part,
+                     hipStream_t st) {
+  if ((wino = wino_splits_now(f, wino, w))) {
     FwdProblem g = f;
     if (f.Cs) {  // the projection first, into `out`; wino_fwd adds it there (each element read by the thread that writes it)
       FwdProblem pr;
@@ -430,7 +462,7 @@ int32_t run_layer_fwd(const nf_layer_desc *d, const LayerDims &ld, int B, const 
   if (d->skip_kind == 1) f.addsrc = xs;
   if (d->skip_kind == 2) f.xs = xs, f.wp = p->Wp;
   float *conv_out = pooled ? wsf(ws, w.T_dZ) : y;
-  int32_t rc = enqueue_conv(f, conv_out, w.wino_layer, w.ksplits_layer, wsf(ws, w.part), st);
+  int32_t rc = enqueue_conv(f, conv_out, w.wino_layer, w.ksplits_layer, w, wsf(ws, w.part), st);
   if (rc) return rc;
   if (pooled) {
     const double pre = (double)B * ld.Ho * ld.Wo * d->C_out, post = (double)B * ld.Hp * ld.Wp * d->C_out;
@@ -448,8 +480,8 @@ int32_t run_aux_conv(const nf_aux_desc *a, const AuxDims &ad, int B, const float
                      const WsLayout &w, hipStream_t st, bool pool_partials, int *ks, const float **parts) {
   FwdProblem f = aux_fwd_problem(a, ad, B);
   f.x = y, f.w = ap->Wa, f.bias = ap->ba;
-  const bool wino = w.wino_aux && fp32_contraction(f);
-  const int splits = wino ? w.wino_aux : igemm_fwd_fast_applicable(f) ? w.ksplits_aux : 1;
+  const int wino = wino_splits_now(f, w.wino_aux, w);
+  const int splits = wino ? wino : igemm_fwd_fast_applicable(f) ? w.ksplits_aux : 1;
   *ks = splits > 1 ? splits : 0;
   float *const part = wsf(ws, w.part) + (wino ? wino_fwd_filter_floats(f.N, f.C) : 0);
   *parts = part;
@@ -558,7 +590,8 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
     FwdProblem f = dgrad_problem(a, ad, B);
     f.x = dU, f.w = wsf(ws, w.WaT);
     f.mask = pooled ? nullptr : y;
-    const int32_t rc = enqueue_conv(f, pooled ? wsf(ws, w.dY) : dZ, w.wino_dgrad, w.ksplits_dgrad, wsf(ws, w.part), st);
+    const int32_t rc = enqueue_conv(f, pooled ? wsf(ws, w.dY) : dZ, w.wino_dgrad, w.ksplits_dgrad, w, wsf(ws, w.part),
+                                    st);
     if (rc) return rc;
     if (pooled) {
       const double pre = (double)B * ld.Ho * ld.Wo * d->C_out, post = (double)B * ld.Hp * ld.Wp * d->C_out;
@@ -574,7 +607,7 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
     if (d->skip_kind == 2) g.xs = xs;
     g.Qld = w.Qld_layer;
     int32_t rc;
-    if (w.wino_wgrad && fp32_contraction(g)) {
+    if (run_wino(g, w.wino_wgrad)) {
       WgradProblem pr = g;  // the projection's columns
       g.splits = w.wino_wgrad, g.Q = g.Qld = g.RSC, g.Cs = 0;
       const double byts = 4.0 * ((double)g.M * g.P + (double)B * g.H * g.W * g.C + (double)g.P * g.Q);
@@ -716,7 +749,7 @@ int32_t local_step_impl(const nf_layer_desc *d, const nf_aux_desc *a, const nf_s
     if ((rc = check_aux_ptrs(va))) return rc;
   }
   if (!aligned16(y_out)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout(d, ld, a, ad, B);
+  const WsLayout w = use_static ? ws_layout(d, ld, a, ad, B) : ws_layout_in(d, ld, a, ad, B, ws_bytes);
   if (use_static) {
     if (w.total > (size_t)NF_STATIC_SCRATCH_BYTES) return NF_ERR_SCRATCH_LIMIT;
     if ((rc = static_scratch(&ws))) return rc;
@@ -736,6 +769,16 @@ int32_t local_step_impl(const nf_layer_desc *d, const nf_aux_desc *a, const nf_s
 }  // namespace
 
 bool prof_active() { return g_prof.on; }
+
+int32_t workspace_least_bytes(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B, size_t *out) {
+  LayerDims ld;
+  AuxDims ad = {0, 0, 0};
+  int32_t rc = check_layer(d, &ld);
+  if (!rc) rc = check_sizes(d, ld, B);
+  if (!rc && a) rc = check_aux(a, &ad);
+  if (!rc) *out = std::min(ws_layout(d, ld, a, ad, B).total, ws_layout(d, ld, a, ad, B, false).total);
+  return rc;
+}
 }  // namespace nf
 
 using namespace nf;
@@ -830,7 +873,7 @@ int32_t nf_layer_fwd(const nf_layer_desc *d, int32_t B, const float *x, const fl
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
   // the layout with a head is a superset that starts with the same regions, so a workspace
   // sized for the full step is accepted as well
-  const WsLayout w = ws_layout(d, ld, nullptr, ad, B);
+  const WsLayout w = ws_layout_in(d, ld, nullptr, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
   return run_layer_fwd(d, ld, B, x, x_skip, p, y, ws, w, static_cast<hipStream_t>(stream));
 }
@@ -848,7 +891,7 @@ int32_t nf_aux_fwd_loss(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B,
   if (!y || !labels || !loss_out) return NF_ERR_NULL;
   if ((rc = check_aux_ptrs(ap))) return rc;
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout(d, ld, a, ad, B);
+  const WsLayout w = ws_layout_in(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
   return run_aux_fwd(a, ad, B, y, labels, ap, loss_out, ws, w, static_cast<hipStream_t>(stream));
 }
@@ -867,7 +910,7 @@ int32_t nf_aux_predict(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B, 
   if ((labels == nullptr) != (n_correct == nullptr)) return NF_ERR_NULL;
   if ((rc = check_aux_ptrs(ap))) return rc;
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout(d, ld, a, ad, B);
+  const WsLayout w = ws_layout_in(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = run_aux_features(a, ad, B, y, ap, ws, w, st))) return rc;
@@ -897,7 +940,7 @@ int32_t nf_local_bwd_wgrad(const nf_layer_desc *d, const nf_aux_desc *a, int32_t
   if ((rc = check_aux_ptrs(ga))) return rc;
   if (!y) return NF_ERR_NULL;
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout(d, ld, a, ad, B);
+  const WsLayout w = ws_layout_in(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
   return run_bwd(d, ld, a, ad, B, x, x_skip, y, p, ap, gp, ga, nullptr, nullptr, nullptr, nullptr, ws, w,
                  static_cast<hipStream_t>(stream));

@@ -15,6 +15,8 @@
 
 namespace nf {
 bool prof_active();  // nf_api.hip: true between nf_prof_begin and nf_prof_end
+// nf_api.hip: least workspace the single-layer calls accept (nf_workspace_bytes: what they want)
+int32_t workspace_least_bytes(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B, size_t *out);
 }
 
 // One captured block pass (nf_block_graph_create): the instantiated graph and the device it lives on.
@@ -69,7 +71,9 @@ int32_t plan_block(const nf_block *blk, int32_t B, int32_t B_last, PlanMode mode
     if (rc) return rc;
     size_t need = 0, need_last = 0;
     if ((rc = nf_workspace_bytes(d, a, B, &need))) return rc;
+    // a partial last batch makes do with what the full ones get, if that holds its direct kernels
     if ((rc = nf_workspace_bytes(d, a, B_last, &need_last))) return rc;
+    if (need_last > need && (rc = nf::workspace_least_bytes(d, a, B_last, &need_last))) return rc;
     lws = std::max(lws, std::max(need, need_last));
     if (l > 0) {
       const nf_layer_desc &q = blk->layers[l - 1];

@@ -76,6 +76,8 @@ size_t wino_fwd_filter_floats(int N, int C);
 // 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none).  Of a
 // problem with a projection (Cs) it serves the 3x3 part: the caller adds the projection through addsrc
 int wino_fwd_pick_splits(const FwdProblem &p);
+// whether it is also faster, with the splits picked, than the split-operand kernel with six piece products
+bool wino_fwd_beats_split(const FwdProblem &p, int splits);
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st);
 
 // first-layer shapes (stem.hip): the whole reduction R*S*C <= 32 in one staging step, channel counts
@@ -110,6 +112,7 @@ hipError_t launch_igemm_wgrad_split(const WgradProblem &p, bool nine, hipStream_
 // 0: not served or the direct kernel is faster; else the number of splits.  Of a problem with
 // projection columns it forms the first RSC: Qld is theirs then
 int wino_wgrad_pick_splits(const WgradProblem &p);
+bool wino_wgrad_beats_split(const WgradProblem &p, int splits);
 hipError_t launch_wino_wgrad(const WgradProblem &p, hipStream_t st);
 // 3x3 / stride 1 / pad 1 with at most 32 output channels (igemm_wgrad_small.hip): 4x4x1 MFMA with a
 // sliding register window; `splits` are ranges of image rows there (any count is valid)

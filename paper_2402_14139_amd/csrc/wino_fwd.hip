@@ -369,28 +369,39 @@ bool applicable(const FwdProblem &p) {
 // 8 direct splits 2.7e-7: 4 splits here 3.4e-7, 8 splits 2.5e-7).  On maps narrower than 4 most taps
 // multiply padding: the direct sum skips their rounding, the transforms do not (2x2 maps 1.5e-7
 // against 1.9e-7 ... 2.9e-7).
+namespace {
+double finish_us(const FwdProblem &p, int s) {  // fwd_finish at 4 TB/s
+  return s > 1 ? 3.5 + (double)p.M * p.N * 4.0 * (s + 1) / 4e6 : 0.0;
+}
+long long workgroups(const FwdProblem &p) {
+  const int B = p.M / (p.Ho * p.Wo);
+  const long long tiles = ((long long)B * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) + TB - 1) / TB;
+  return tiles * ((p.N + NB - 1) / NB);
+}
+// this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two; 11 us of prologue, epilogue and
+// launches; the transformed filter written and read at 4 TB/s; a projection shortcut is a launch of
+// its own whose result this kernel adds (enqueue_conv)
+double wino_us(const FwdProblem &p, int s) {
+  const int nchunks = (p.C + CH - 1) / CH;
+  const long long w = workgroups(p) * s;
+  const double per = w <= 256 ? 1.13 : w <= 512 ? 2.12 : 2.12 * w / 512.0, mn = (double)p.M * p.N;
+  const double proj = p.Cs ? 8.0 + 2.0 * mn * p.Cs / 90e6 + 4.0 * mn / 4e6 : 0.0;
+  return 11.0 + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per + finish_us(p, s) + proj;
+}
+}  // namespace
+
 int wino_fwd_pick_splits(const FwdProblem &p) {
   // up to 32 filters half of a workgroup's columns would be padding; below 16 channels the result's own
   // traffic is all there is to either kernel (8 channels, 16 384 x 256 results: 17 / 14 + 5 for the filter launch)
   if (p.N <= 32 || p.C < 16 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
-  const double mn = (double)p.M * p.N;
-  const int B = p.M / (p.Ho * p.Wo);
-  const long long tiles = ((long long)B * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) + TB - 1) / TB;
-  const long long wgs = tiles * ((p.N + NB - 1) / NB);
   const int nchunks = (p.C + CH - 1) / CH;
   const int ks = igemm_fwd_pick_ksplits(p.M, p.N, p.Kg, p.C, p.R * p.S);  // of the direct kernel
-  auto finish_us = [&](int s) { return s > 1 ? 3.5 + mn * 4.0 * (s + 1) / 4e6 : 0.0; };  // fwd_finish at 4 TB/s
-  // this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two; 11 us of prologue, epilogue and
-  // launches; the transformed filter written and read at 4 TB/s
-  // a projection shortcut is a launch of its own whose result this kernel adds (enqueue_conv)
-  const double proj_us = p.Cs ? 8.0 + 2.0 * mn * p.Cs / 90e6 + 4.0 * mn / 4e6 : 0.0;
   double best = 0.0;
   int splits = 0;
   for (int s = 1; s <= 16; s *= 2) {
     if (4 * s < 3 * ks) continue;
-    if (s > 1 && (nchunks / s < 2 || wgs * s > 512)) break;
-    const double per = wgs * s <= 256 ? 1.13 : wgs * s <= 512 ? 2.12 : 2.12 * (wgs * s) / 512.0;
-    const double us = 11.0 + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per + finish_us(s) + proj_us;
+    if (s > 1 && (nchunks / s < 2 || workgroups(p) * s > 512)) break;
+    const double us = wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;
   }
   // the direct kernel: steps of 32 products, 128x128 tiles one per CU or 64x64 tiles up to four
@@ -399,8 +410,18 @@ int wino_fwd_pick_splits(const FwdProblem &p) {
   const int bt = big ? 128 : 64;
   const long long w = (long long)((p.M + bt - 1) / bt) * ((p.N + bt - 1) / bt) * ks;
   const double per = big ? 2.06 * ((w + 255) / 256) : w <= 260 ? 0.56 : 0.55 * w / 256.0;
-  const double direct = 8.0 + (nkb + ks - 1) / ks * per + finish_us(ks);
+  const double direct = 8.0 + (nkb + ks - 1) / ks * per + finish_us(p, ks);
   return splits && best < 0.93 * direct ? splits : 0;
+}
+
+// The split-operand kernel (six piece products) takes 1.4 us per step of 32 products and 128x128 tile, one
+// tile per CU.  512 -> 512 channels, 8192 pixels: 206 us, this 150 + 7; 1024 pixels in 8 splits: about 41, this
+// 43.  The error against 64 bits is no larger where this one is taken (512 channels 6.5e-7 for both,
+// 256 4.9e-7 / 4.4e-7, 128 3.5e-7 / 3.1e-7).
+bool wino_fwd_beats_split(const FwdProblem &p, int splits) {
+  const int nkb = (p.Kg + 31) / 32, ks = igemm_fwd_pick_ksplits(p.M, p.N, p.Kg, p.C, p.R * p.S);
+  const long long w = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * ks;
+  return wino_us(p, splits) < 0.93 * (8.0 + (nkb + ks - 1) / ks * 1.4 * ((w + 255) / 256) + finish_us(p, ks));
 }
 
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st) {

@@ -345,28 +345,46 @@ int tiles_per_split(long long T, int splits) { return (int)(((T + splits - 1) / 
 // transforms' own rounding would make this the less accurate one (relative error against 64 bits,
 // direct / this: 256 channels, 4x4 maps, 4096 pixels 0.85e-7 / 0.93e-7, 2x2 maps 0.9e-7 / 1.8e-7; at 8192 and more
 // pixels this one's is smaller: 1.5e-7 / 1.1e-7 with 512 channels, 1.1e-7 / 1.0e-7 with 128).
+namespace {
+double reduce_us(const WgradProblem &p, int s) { return s * (double)p.P * p.Q * 4.0 / 4e6; }  // at 4 TB/s
+long long blocks_of(const WgradProblem &p) { return (long long)((p.C + QB - 1) / QB) * ((p.P + PB - 1) / PB); }
+// a step of four tiles takes 1.0 us with one workgroup on a CU, 1.54 with two; the columns of a
+// projection shortcut are a launch of their own (run_bwd)
+double wino_us(const WgradProblem &p, int s) {
+  const double w = (double)blocks_of(p) * s;
+  const double proj = p.Cs ? 10.0 + 2.0 * p.M * p.P * p.Cs / 90e6 : 0.0;
+  return 11.0 + tiles_per_split(num_tiles(p), s) / KT * (w <= 256 ? 1.0 : w <= 512 ? 1.54 : 1.54 * w / 512) +
+         reduce_us(p, s) + proj;
+}
+// a direct kernel of 128x128 tiles: its padded contraction at the rate it reaches (flops per us), plus
+// ramp-up and drain
+double wide_us(const WgradProblem &p, double rate) {
+  const double q128 = (p.Q + 127) / 128 * 128.0, p128 = (p.P + 127) / 128 * 128.0;
+  return 14.0 + 2.0 * p.M * p128 * q128 / rate + reduce_us(p, wgrad_pick_splits(p.P, p.Q, p.M));
+}
+}  // namespace
+
 int wino_wgrad_pick_splits(const WgradProblem &p) {
   if (p.P <= 32 || p.M < 8192 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
-  const long long T = num_tiles(p), blocks = (long long)((p.C + QB - 1) / QB) * ((p.P + PB - 1) / PB);
-  auto reduce_us = [&](int s) { return s * (double)p.P * p.Q * 4.0 / 4e6; };  // at 4 TB/s
-  // the columns of a projection shortcut are a launch of their own (run_bwd)
-  const double proj_us = p.Cs ? 10.0 + 2.0 * p.M * p.P * p.Cs / 90e6 : 0.0;
-  // a step of four tiles takes 1.0 us with one workgroup on a CU, 1.54 with two
+  const long long T = num_tiles(p), blocks = blocks_of(p);
   double best = 0.0;
   int splits = 0;
   for (int wgs = 256; wgs <= 1024; wgs *= 2) {
     const int s = (int)((wgs + blocks - 1) / blocks);
     if (s > 1 && T / s < 16) break;
-    const double w = (double)blocks * s;
-    const double us = 11.0 + tiles_per_split(T, s) / KT * (w <= 256 ? 1.0 : w <= 512 ? 1.54 : 1.54 * w / 512) + reduce_us(s) + proj_us;
+    const double us = wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;
   }
-  // the direct kernel: its padded contraction at the rate its tile reaches, plus ramp-up and drain
-  const double q64 = (p.Q + 63) / 64 * 64.0, q128 = (p.Q + 127) / 128 * 128.0, p128 = (p.P + 127) / 128 * 128.0;
-  const double direct = (p.P > 64 ? 14.0 + 2.0 * p.M * p128 * q128 / 118e6 : 8.0 + 2.0 * p.M * 64 * q64 / 104e6) +
-                        reduce_us(wgrad_pick_splits(p.P, p.Q, p.M));
+  const double q64 = (p.Q + 63) / 64 * 64.0;
+  const double direct = p.P > 64 ? wide_us(p, 118e6)
+                                 : 8.0 + 2.0 * p.M * 64 * q64 / 104e6 + reduce_us(p, wgrad_pick_splits(p.P, p.Q, p.M));
   return best < 0.95 * direct ? splits : 0;
 }
+
+// The split-operand kernel (six piece products) reaches 185 TFLOP/s.  Kernel alone, us (it / this): 512 -> 512
+// channels, 8192 pixels 251 / 218, 256 -> 256, 16 384 pixels 129 / 116; error against 64 bits 1.7e-7 / 1.1e-7 and
+// 1.4e-7 / 0.9e-7.
+bool wino_wgrad_beats_split(const WgradProblem &p, int splits) { return wino_us(p, splits) < 0.95 * wide_us(p, 185e6); }
 
 hipError_t launch_wino_wgrad(const WgradProblem &p, hipStream_t st) {
   WinoWgradAux q;

@@ -136,3 +136,24 @@ def test_wino_weight_gradient_of_an_infinite_input():
     assert np.abs(res[1][..., keep] - ref).max() <= 1e-4 * np.abs(ref).max()
     tail = res[0][:, 2, :, 37]
     assert np.abs(res[1][:, 2, :, 37] - tail).max() <= 1e-4 * np.abs(ref).max()
+
+
+def test_a_workspace_for_the_direct_kernels_alone_is_enough():
+    """A workspace that holds no transformed filter runs the direct kernels, same result to rounding."""
+    B, C, H, K = 64, 64, 16, 128
+    g = torch.Generator(device="cuda").manual_seed(8)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    x, w, b = rn(B, H, H, C), rn(K, 3, 3, C) * 0.06, rn(K)
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=K, R=3, S=3, stride=1, pad=1)
+    ys, names = [], []
+    for nbytes in (nf.nf_workspace_bytes(d, None, B), 256):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        y = torch.empty(B, H, H, K, device="cuda")
+        nf.nf_prof_begin()
+        nf.nf_layer_fwd(d, B, x, None, nf.layer_params(w, b, None), y, ws)
+        names.append({r["kernel"] for r in nf.nf_prof_end()})
+        ys.append(y.cpu().numpy())
+    if nf.nf_contraction() == nf.NF_CONTRACT_F32:
+        assert "wino_fwd" in names[0] and "wino_fwd" not in names[1], names
+    # 576-term sums in two orders: a few 1e-7 of the largest value
+    assert np.abs(ys[0] - ys[1]).max() <= 5e-6 * np.abs(ys[0]).max()
