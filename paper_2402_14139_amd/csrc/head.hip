@@ -6,6 +6,7 @@
 // workgroup reductions with a fixed summation order (deterministic).
 #include "head_gamma.h"
 #include "nf_internal.h"
+#include "wino_filter.h"
 
 namespace nf {
 namespace {
@@ -541,18 +542,6 @@ __device__ inline void du_element(const HeadShape &s, int hh, int w, int av, con
   }
 }
 
-// element i of the re-laid aux filter: WaT[k][r][s][a] = Wa[a][R-1-r][S-1-s][k]
-__device__ inline void wat_element(long long i, int A, int R, int S, int K, const float *__restrict__ Wa,
-                                   float *__restrict__ WaT) {
-  const int a = (int)(i % A);
-  long long r = i / A;
-  const int sx = (int)(r % S);
-  r /= S;
-  const int rr = (int)(r % R);
-  const int k = (int)(r / R);
-  WaT[i] = Wa[(((long long)a * R + (R - 1 - rr)) * S + (S - 1 - sx)) * K + k];
-}
-
 // The whole per-sample chain of a head with a small activation map in one launch: workgroup n
 // (n < B) runs F_n, gamma_n, the loss and dL/dz, dPq and the backward through F_n and the aux ReLU
 // for sample n; the pooled features, dPq and the max-pooling selection stay in LDS between the
@@ -568,15 +557,13 @@ __global__ __launch_bounds__(HT) void head_sample_kernel(HeadShape s, float *__r
                                                          const float *__restrict__ Wf, const float *__restrict__ bf,
                                                          float *__restrict__ Pq, int32_t *__restrict__ parg,
                                                          float *__restrict__ dz, float *__restrict__ loss_n,
-                                                         float *__restrict__ dU, const float *__restrict__ Wa,
-                                                         float *__restrict__ WaT, int R, int S, int K, int CA, int NS) {
+                                                         float *__restrict__ dU, RelayJob rj, int CA, int NS) {
   extern __shared__ float sm[];
   __shared__ float red[HT * V];
   __shared__ int redi[PMAX ? HT * V : 1];
   const int t = threadIdx.x;
   if ((int)blockIdx.x >= s.B) {
-    const long long i = (long long)(blockIdx.x - s.B) * HT + t;
-    if (i < (long long)s.A * R * S * K) wat_element(i, s.A, R, S, K, Wa, WaT);
+    relay_block(rj, (int)blockIdx.x - s.B);
     return;
   }
   float *pq = sm;            // [F]
@@ -616,13 +603,11 @@ __global__ __launch_bounds__(HT) void head_wide_kernel(HeadShape s, int NS, cons
                                                        const float *__restrict__ Wf, const float *__restrict__ bf,
                                                        float *__restrict__ dz, float *__restrict__ loss_n,
                                                        const int32_t *__restrict__ parg, float *__restrict__ dU,
-                                                       const float *__restrict__ Wa, float *__restrict__ WaT, int R,
-                                                       int S, int K) {
+                                                       RelayJob rj) {
   extern __shared__ float sm[];
   const int t = threadIdx.x;
   if ((int)blockIdx.x >= s.B * NS) {
-    const long long i = (long long)(blockIdx.x - s.B * NS) * HT + t;
-    if (i < (long long)s.A * R * S * K) wat_element(i, s.A, R, S, K, Wa, WaT);
+    relay_block(rj, (int)blockIdx.x - s.B * NS);
     return;
   }
   float *pq = sm;            // [F]
@@ -696,8 +681,7 @@ __global__ __launch_bounds__(HT) void head_bwd_kernel(HeadShape s, HeadBwdJobs j
                                                       const float *__restrict__ dz, float *__restrict__ dWf,
                                                       float *__restrict__ dbf, const float *__restrict__ U,
                                                       const float *__restrict__ dPq, float *__restrict__ dU,
-                                                      const float *__restrict__ Wa, float *__restrict__ WaT, int R,
-                                                      int S, int K, const float *__restrict__ loss_n,
+                                                      RelayJob rj, const float *__restrict__ loss_n,
                                                       float *__restrict__ loss_out,
                                                       const int32_t *__restrict__ parg) {
   __shared__ float red[HT];
@@ -730,10 +714,7 @@ __global__ __launch_bounds__(HT) void head_bwd_kernel(HeadShape s, HeadBwdJobs j
   }
   b -= jb.nb_u;
   if (b < jb.nb_t) {
-    const long long total = (long long)s.A * R * S * K;
-    const long long i = (long long)b * HT + t;
-    if (i >= total) return;
-    wat_element(i, s.A, R, S, K, Wa, WaT);
+    relay_block(rj, b);
     return;
   }
   loss_mean_block(loss_n, s.B, loss_out, red);
@@ -788,6 +769,16 @@ hipError_t launch_head_fc(const HeadShape &h, const float *Pq, const int32_t *la
   return hipGetLastError();
 }
 
+RelayJob relay_job(const float *Wa, float *WaT, float *U, int A, int R, int S, int K) {
+  static_assert(HT == 256, "relay_block");
+  RelayJob j;
+  j.Wa = Wa, j.WaT = WaT, j.U = U, j.A = A, j.R = R, j.S = S, j.K = K;
+  j.nchunks = (A + WINO_CH - 1) / WINO_CH;
+  j.nb_t = (int)(((long long)A * R * S * K + HT - 1) / HT);
+  j.nb_u = U ? ((K + WINO_NB - 1) / WINO_NB * WINO_NB * 2 * j.nchunks + HT - 1) / HT : 0;
+  return j;
+}
+
 bool head_sample_applicable(const HeadShape &h) {
   // a sample's activation map of at most 4 KiB (measured: at 16 KiB per sample and 128 samples the
   // three chip-wide launches are faster than 128 workgroups doing a sample each), the linear layer
@@ -796,17 +787,17 @@ bool head_sample_applicable(const HeadShape &h) {
 }
 
 hipError_t launch_head_sample(const HeadShape &h, float *U, const float *part, int splits, const float *ba,
-                              const int32_t *labels, const float *Wf, const float *bf, float *Pq, int32_t *parg, float *dz, float *loss_n, float *dU, const float *Wa,
-                              float *WaT, int R, int S, int K, hipStream_t st) {
+                              const int32_t *labels, const float *Wf, const float *bf, float *Pq, int32_t *parg,
+                              float *dz, float *loss_n, float *dU, const RelayJob &rj, hipStream_t st) {
   const int V = h.A % 4 == 0 ? 4 : 1;
   int CA, NS;
   pool_lanes(h, V, &CA, &NS);
-  const unsigned nb_t = Wa ? (unsigned)(((long long)h.A * R * S * K + HT - 1) / HT) : 0;
+  const unsigned nb_t = (unsigned)(rj.nb_t + rj.nb_u);
   const dim3 grid((unsigned)h.B + nb_t);
   const size_t lds = (size_t)(2 * h.F + h.Cls + 8) * sizeof(float) + (h.pmax ? (size_t)h.F * sizeof(int) : 0);
 #define NF_HS(V_, P_)                                                                                              \
   hipLaunchKernelGGL((head_sample_kernel<V_, P_>), grid, dim3(HT), lds, st, h, U, part, splits, ba, labels, Wf, bf, Pq, \
-                     parg, dz, loss_n, dU, Wa, WaT, R, S, K, CA, NS)
+                     parg, dz, loss_n, dU, rj, CA, NS)
   if (h.pmax) {
     if (V == 4) NF_HS(4, true);
     else NF_HS(1, true);
@@ -832,22 +823,22 @@ bool head_pool_partials_applicable(const HeadShape &h) {
 
 hipError_t launch_head_wide(const HeadShape &h, const float *U, float *Pq, const float *ppart, const int32_t *labels,
                             const float *Wf, const float *bf, float *dz, float *loss_n, const int32_t *parg,
-                            float *dU, const float *Wa, float *WaT, int R, int S, int K, hipStream_t st) {
+                            float *dU, const RelayJob &rj, hipStream_t st) {
   const int V = h.A % 4 == 0 ? 4 : 1;
   // slices per sample: about 768 workgroups in all, at least 1024 values of dU each
   const long long per_sample = (long long)h.Hu * h.Wu * h.A;
   int NS = (768 + h.B - 1) / h.B;
   if (NS > per_sample / 1024) NS = (int)(per_sample / 1024);
   if (NS < 1) NS = 1;
-  const unsigned nb_t = Wa ? (unsigned)(((long long)h.A * R * S * K + HT - 1) / HT) : 0;
+  const unsigned nb_t = (unsigned)(rj.nb_t + rj.nb_u);
   const dim3 grid((unsigned)(h.B * NS) + nb_t);
   const size_t lds = (size_t)(2 * h.F + h.Cls + 8) * sizeof(float);
   if (V == 4)
     hipLaunchKernelGGL(head_wide_kernel<4>, grid, dim3(HT), lds, st, h, NS, U, Pq, ppart, labels, Wf, bf, dz, loss_n, parg, dU,
-                       Wa, WaT, R, S, K);
+                       rj);
   else
     hipLaunchKernelGGL(head_wide_kernel<1>, grid, dim3(HT), lds, st, h, NS, U, Pq, ppart, labels, Wf, bf, dz, loss_n, parg, dU,
-                       Wa, WaT, R, S, K);
+                       rj);
   return hipGetLastError();
 }
 
@@ -879,8 +870,8 @@ hipError_t launch_loss_mean(const float *loss_n, int B, float *loss_out, hipStre
 }
 
 hipError_t launch_head_bwd(const HeadShape &h, const float *Pq, const float *dz, float *dWf, float *dbf,
-                           const float *U, const float *dPq, float *dU, const float *Wa, float *WaT, int R, int S,
-                           int K, const float *loss_n, float *loss_out, const int32_t *parg, hipStream_t st) {
+                           const float *U, const float *dPq, float *dU, const RelayJob &rj, const float *loss_n,
+                           float *loss_out, const int32_t *parg, hipStream_t st) {
   HeadBwdJobs jb;
   GammaJob gj;
   gj.F = h.F, gj.Cls = h.Cls, gj.loss_out = nullptr;
@@ -889,13 +880,13 @@ hipError_t launch_head_bwd(const HeadShape &h, const float *Pq, const float *dz,
   const int V = h.A % 4 == 0 ? 4 : 1;
   const long long total = (long long)h.B * h.Hu * h.Wu * (h.A / V);
   jb.nb_u = (int)((total + HT - 1) / HT);
-  jb.nb_t = Wa ? (int)(((long long)h.A * R * S * K + HT - 1) / HT) : 0;
+  jb.nb_t = rj.nb_t + rj.nb_u;
   const dim3 grid((unsigned)(jb.nb_w + jb.nb_u + jb.nb_t + (loss_out ? 1 : 0)));
   if (V == 4)
-    hipLaunchKernelGGL(head_bwd_kernel<4>, grid, dim3(HT), 0, st, h, jb, Pq, dz, dWf, dbf, U, dPq, dU, Wa, WaT, R, S, K,
+    hipLaunchKernelGGL(head_bwd_kernel<4>, grid, dim3(HT), 0, st, h, jb, Pq, dz, dWf, dbf, U, dPq, dU, rj,
                        loss_n, loss_out, parg);
   else
-    hipLaunchKernelGGL(head_bwd_kernel<1>, grid, dim3(HT), 0, st, h, jb, Pq, dz, dWf, dbf, U, dPq, dU, Wa, WaT, R, S, K,
+    hipLaunchKernelGGL(head_bwd_kernel<1>, grid, dim3(HT), 0, st, h, jb, Pq, dz, dWf, dbf, U, dPq, dU, rj,
                        loss_n, loss_out, parg);
   return hipGetLastError();
 }

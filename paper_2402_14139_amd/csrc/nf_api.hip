@@ -139,6 +139,7 @@ FwdProblem aux_fwd_problem(const nf_aux_desc *a, const AuxDims &ad, int B) {
 
 struct WsLayout {
   size_t T_dZ, arg, U, Pq, parg, dz, loss_n, dPq, dU, WaT, dY, part, part_b, part_aux, part_b_aux, ppart, total;
+  size_t Ud;  // transformed filter of the data gradient (wino_dgrad)
   int splits_aux, splits_layer, Qld_aux, Qld_layer;
   // reduction splits of the forward-type contractions (1 = none); their partial sums alias `part`
   int ksplits_aux, ksplits_layer, ksplits_dgrad;
@@ -251,6 +252,7 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     const FwdProblem fa = aux_fwd_problem(a, ad, B), fd = dgrad_problem(a, ad, B);
     w.wino_aux = wino ? wino_fwd_pick_splits(fa) : 0;
     w.wino_dgrad = wino ? wino_fwd_pick_splits(fd) : 0;
+    w.Ud = take(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0);
     pwino = std::max({pwino, wino_scratch_floats(w.wino_aux, fa, false), wino_scratch_floats(w.wino_dgrad, fd, false)});
     pcut = std::max({pcut, wino_scratch_floats(w.wino_aux, fa, true), wino_scratch_floats(w.wino_dgrad, fd, true)});
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;
@@ -267,12 +269,14 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     w.part_b_aux = take((size_t)w.splits_aux * a->A * f);
   }
   // this scratch must not push a step that the static array holds out of it
+  const size_t extra = up(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0);
+  const size_t direct = off - extra + up(pmax * f);
   const auto pushes_out = [&](size_t floats) {
     const size_t lim = (size_t)NF_STATIC_SCRATCH_BYTES;
-    return floats > pmax && off + up(pmax * f) <= lim && off + up(floats * f) > lim;
+    return direct <= lim && off + up(std::max(floats, pmax) * f) > lim;
   };
-  if (pushes_out(pwino)) w.wino_layer = w.wino_aux = w.wino_dgrad = w.wino_wgrad = 0;
-  else pmax = std::max(pmax, pwino);
+  if (wino && pushes_out(pwino)) return ws_layout(d, ld, a, ad, B, false);
+  pmax = std::max(pmax, pwino);
   w.wino_split_mode = w.wino_layer + w.wino_aux + w.wino_dgrad > 0 && !pushes_out(pcut);
   if (w.wino_split_mode) pmax = std::max(pmax, pcut);
   w.part = take(pmax * f);
@@ -281,7 +285,7 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
 }
 
 // the layout a call uses in a workspace of `have` bytes: one that only holds the direct kernels (the
-// regions before the partial sums lie the same) runs those
+// regions that one call leaves for the next lie the same) runs those
 WsLayout ws_layout_in(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B,
                       size_t have) {
   const WsLayout w = ws_layout(d, ld, a, ad, B);
@@ -381,15 +385,16 @@ int32_t enqueue_fwd_split(FwdProblem f, float *out, int ksplits, float *part, hi
 }
 
 // the same contraction through wino_fwd (flops of the dense formula; scratch: the transformed filter,
-// then the partial sums of the splits)
-int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, hipStream_t st) {
+// then the partial sums of the splits; filter: the transformed filter where an earlier launch left it)
+int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, float *filter, hipStream_t st) {
   const double B = (double)f.M / ((double)f.Ho * f.Wo), mn = (double)f.M * f.N;
   double elems = B * f.H * f.W * f.C + (double)f.N * f.Kg + mn;
   const float *bias = f.bias, *addsrc = f.addsrc, *mask = f.mask;
   if (splits <= 1 && (addsrc || mask)) elems += mn;
   float *part = scratch + wino_fwd_filter_floats(f.N, f.C);
   f.ksplits = splits, f.out = splits > 1 ? part : out;
-  NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, 4.0 * elems, launch_wino_fwd(f, scratch, st));
+  NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, 4.0 * elems,
+         launch_wino_fwd(f, filter ? filter : scratch, filter != nullptr, st));
   if (splits > 1)
     NF_RUN(st, "fwd_finish", 0.0, 4.0 * mn * (splits + 1.0 + (addsrc ? 1.0 : 0.0) + (mask ? 1.0 : 0.0)),
            launch_fwd_finish(part, splits, f.M, f.N, bias, addsrc, mask, f.relu, out, st));
@@ -416,7 +421,7 @@ bool run_wino(const WgradProblem &g, int splits) {
 
 // by the layout's plan: wino_fwd, or the direct kernels
 int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, const WsLayout &w, float *part,
-                     hipStream_t st) {
+                     hipStream_t st, float *filter = nullptr) {
   if ((wino = wino_splits_now(f, wino, w))) {
     FwdProblem g = f;
     if (f.Cs) {  // the projection first, into `out`; wino_fwd adds it there (each element read by the thread that writes it)
@@ -429,7 +434,7 @@ int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, con
       if (rc) return rc;
       g.Cs = 0, g.Kg = g.RSC, g.addsrc = out;
     }
-    return enqueue_wino(g, out, wino, part, st);
+    return enqueue_wino(g, out, wino, part, filter, st);
   }
   return enqueue_fwd_split(f, out, ksplits, part, st);
 }
@@ -490,7 +495,7 @@ int32_t run_aux_conv(const nf_aux_desc *a, const AuxDims &ad, int B, const float
   if (pool_partials) f.pool_part = wsf(ws, w.ppart), f.pool_split = ad.Wu == 16 ? 1 : 0;
   if (!wino) return enqueue_fwd(f, st);
   const double mn = (double)f.M * f.N, byts = 4.0 * ((double)B * f.H * f.W * f.C + (double)f.N * f.Kg + mn);
-  NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, byts, launch_wino_fwd(f, wsf(ws, w.part), st));
+  NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, byts, launch_wino_fwd(f, wsf(ws, w.part), false, st));
   return NF_OK;
 }
 
@@ -512,6 +517,12 @@ int32_t run_aux_features(const nf_aux_desc *a, const AuxDims &ad, int B, const f
   return NF_OK;
 }
 
+// the re-lay of beta_n's filter that rides on a head launch; where the data gradient is planned as wino_fwd
+// its transformed form too (both: the mode in force may change before the data gradient is enqueued)
+RelayJob head_relay(const nf_aux_desc *a, const nf_aux_params *ap, void *ws, const WsLayout &w) {
+  return relay_job(ap->Wa, wsf(ws, w.WaT), w.wino_dgrad ? wsf(ws, w.Ud) : nullptr, a->A, a->R, a->S, a->C_in);
+}
+
 // loss_out == nullptr: the batch mean is left to the backward launch that follows (run_bwd)
 int32_t run_aux_fwd(const nf_aux_desc *a, const AuxDims &ad, int B, const float *y, const int32_t *labels,
                     const nf_aux_params *ap, float *loss_out, void *ws, const WsLayout &w, hipStream_t st) {
@@ -530,7 +541,7 @@ int32_t run_aux_fwd(const nf_aux_desc *a, const AuxDims &ad, int B, const float 
            4.0 * ((3.0 + ks) * u + 2.0 * B * fc + (double)B * (ad.F + a->n_classes + 1.0)) + 8.0 * wa,
            launch_head_sample(hs, wsf(ws, w.U), parts, ks, ap->ba, labels, ap->Wf, ap->bf, wsf(ws, w.Pq),
                               reinterpret_cast<int32_t *>(wsf(ws, w.parg)), wsf(ws, w.dz), wsf(ws, w.loss_n),
-                              wsf(ws, w.dU), ap->Wa, wsf(ws, w.WaT), a->R, a->S, a->C_in, st));
+                              wsf(ws, w.dU), head_relay(a, ap, ws, w), st));
     if (loss_out) NF_RUN(st, "loss_mean", 0.0, 4.0 * B, launch_loss_mean(wsf(ws, w.loss_n), B, loss_out, st));
     return NF_OK;
   }
@@ -542,8 +553,8 @@ int32_t run_aux_fwd(const nf_aux_desc *a, const AuxDims &ad, int B, const float 
     const double u = (double)B * ad.Hu * ad.Wu * a->A, wa = (double)a->A * a->R * a->S * a->C_in;
     NF_RUN(st, "head_wide", 4.0 * B * fc, 4.0 * (2.0 * u + (double)B * (ad.F + a->n_classes + 1.0)) + 8.0 * wa,
            launch_head_wide(hs, wsf(ws, w.U), wsf(ws, w.Pq), w.pool_fused ? wsf(ws, w.ppart) : nullptr, labels, ap->Wf, ap->bf, wsf(ws, w.dz), wsf(ws, w.loss_n),
-                            reinterpret_cast<const int32_t *>(wsf(ws, w.parg)), wsf(ws, w.dU), ap->Wa, wsf(ws, w.WaT),
-                            a->R, a->S, a->C_in, st));
+                            reinterpret_cast<const int32_t *>(wsf(ws, w.parg)), wsf(ws, w.dU),
+                            head_relay(a, ap, ws, w), st));
     if (loss_out) NF_RUN(st, "loss_mean", 0.0, 4.0 * B, launch_loss_mean(wsf(ws, w.loss_n), B, loss_out, st));
     return NF_OK;
   }
@@ -570,8 +581,8 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
   const double wa = (double)a->A * a->R * a->S * a->C_in;
   if (!w.head_fused)
     NF_RUN(st, "head_bwd", 2.0 * B * fc, 4.0 * (fc + (double)B * (2.0 * ad.F + a->n_classes) + 2.0 * u) + 8.0 * wa,
-           launch_head_bwd(hs, wsf(ws, w.Pq), wsf(ws, w.dz), ga->Wf, ga->bf, wsf(ws, w.U), wsf(ws, w.dPq), dU, ap->Wa,
-                           wsf(ws, w.WaT), a->R, a->S, a->C_in, wsf(ws, w.loss_n), loss_out,
+           launch_head_bwd(hs, wsf(ws, w.Pq), wsf(ws, w.dz), ga->Wf, ga->bf, wsf(ws, w.U), wsf(ws, w.dPq), dU,
+                           head_relay(a, ap, ws, w), wsf(ws, w.loss_n), loss_out,
                            reinterpret_cast<const int32_t *>(wsf(ws, w.parg)), st));
   // beta_n: weight + bias gradient
   {
@@ -590,8 +601,10 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
     FwdProblem f = dgrad_problem(a, ad, B);
     f.x = dU, f.w = wsf(ws, w.WaT);
     f.mask = pooled ? nullptr : y;
+    // by a head launch of this call; a forward call of its own may have had a workspace without the region
+    const bool filter_ready = sgd || !w.head_fused;
     const int32_t rc = enqueue_conv(f, pooled ? wsf(ws, w.dY) : dZ, w.wino_dgrad, w.ksplits_dgrad, w, wsf(ws, w.part),
-                                    st);
+                                    st, filter_ready ? wsf(ws, w.Ud) : nullptr);
     if (rc) return rc;
     if (pooled) {
       const double pre = (double)B * ld.Ho * ld.Wo * d->C_out, post = (double)B * ld.Hp * ld.Wp * d->C_out;

@@ -78,7 +78,8 @@ size_t wino_fwd_filter_floats(int N, int C);
 int wino_fwd_pick_splits(const FwdProblem &p);
 // whether it is also faster, with the splits picked, than the split-operand kernel with six piece products
 bool wino_fwd_beats_split(const FwdProblem &p, int splits);
-hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st);
+// (filter_ready: U holds the transformed filter already, one launch)
+hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, hipStream_t st);
 
 // first-layer shapes (stem.hip): the whole reduction R*S*C <= 32 in one staging step, channel counts
 // that are not multiples of 4; launch_igemm_fwd / launch_igemm_wgrad pick them when applicable
@@ -162,6 +163,17 @@ struct ReduceSgd {
 };
 hipError_t launch_wgrad_reduce_sgd(const ReduceSgd &r, hipStream_t st);
 
+// Re-lay of the aux filter for the data gradient as extra workgroups of a head launch (wino_filter.h):
+// WaT[k][r][s][a] = Wa[a][R-1-r][S-1-s][k], and with U (3x3 only, wino_fwd_filter_floats(K, A) floats) its
+// transformed form for wino_fwd
+struct RelayJob {
+  const float *Wa;
+  float *WaT, *U;
+  int A, R, S, K;
+  int nchunks, nb_t, nb_u;
+};
+RelayJob relay_job(const float *Wa, float *WaT, float *U, int A, int R, int S, int K);
+
 // ---- head (Eq. 2 after the aux conv, Eq. 3) ----
 struct HeadShape {
   int B, Hu, Wu, A, oh, ow, F, Cls, relu;
@@ -186,16 +198,14 @@ hipError_t launch_count_hits(const int32_t *hit, int B, int32_t *out, bool accum
 // Whole per-sample chain of the head in one launch, one workgroup per sample, for heads whose
 // activation map is small (head_sample_applicable): F_n, gamma_n, the loss and dL/dz, dPq and the
 // backward through F_n and the aux ReLU (dU).  Leaves Pq, dz, loss_n (and the max-pooling
-// selection) in global memory for the batch-reducing jobs (GammaJob).  Extra workgroups re-lay the
-// aux filter for the data gradient when Wa is given: WaT[k][r][s][a] = Wa[a][R-1-r][S-1-s][k].
+// selection) in global memory for the batch-reducing jobs (GammaJob).  Extra workgroups run the RelayJob.
 bool head_sample_applicable(const HeadShape &h);
 hipError_t launch_head_sample(const HeadShape &h, float *U, const float *part, int splits, const float *ba,
                               const int32_t *labels, const float *Wf, const float *bf, float *Pq, int32_t *parg,
-                              float *dz, float *loss_n, float *dU, const float *Wa, float *WaT, int R, int S, int K,
-                              hipStream_t st);
+                              float *dz, float *loss_n, float *dU, const RelayJob &rj, hipStream_t st);
 // Everything after F_n for a large activation map in one launch (head_wide_applicable: a linear
 // layer of at most 16384 weights): gamma_n, loss, dL/dz, dPq recomputed per slice of a sample, dU,
-// and the re-laid aux filter when Wa is given.  Reads Pq (and the max-pooling selection) left by
+// and the RelayJob.  Reads Pq (and the max-pooling selection) left by
 // launch_head_pool; leaves dz and loss_n for the batch-reducing jobs (GammaJob).
 // `ppart` (or null): column sums per 16 pixels from the aux convolution's epilogue
 // (FwdProblem::pool_part, head_pool_partials_applicable); then F_n is formed here as well and Pq written.
@@ -203,12 +213,12 @@ bool head_wide_applicable(const HeadShape &h);
 bool head_pool_partials_applicable(const HeadShape &h);
 hipError_t launch_head_wide(const HeadShape &h, const float *U, float *Pq, const float *ppart, const int32_t *labels,
                             const float *Wf, const float *bf, float *dz, float *loss_n, const int32_t *parg,
-                            float *dU, const float *Wa, float *WaT, int R, int S, int K, hipStream_t st);
-// one launch: dWf, dbf; dU (pool + aux ReLU backward); WaT[k][r][s][a] = Wa[a][R-1-r][S-1-s][k] when Wa
-// is given; the batch-mean loss when loss_out is given
+                            float *dU, const RelayJob &rj, hipStream_t st);
+// one launch: dWf, dbf; dU (pool + aux ReLU backward); the RelayJob; the batch-mean loss when loss_out is
+// given
 hipError_t launch_head_bwd(const HeadShape &h, const float *Pq, const float *dz, float *dWf, float *dbf,
-                           const float *U, const float *dPq, float *dU, const float *Wa, float *WaT, int R, int S,
-                           int K, const float *loss_n, float *loss_out, const int32_t *parg, hipStream_t st);
+                           const float *U, const float *dPq, float *dU, const RelayJob &rj, const float *loss_n,
+                           float *loss_out, const int32_t *parg, hipStream_t st);
 
 // ---- elementwise / data movement ----
 hipError_t launch_maxpool_fwd(const float *T, float *Y, uint8_t *arg, int B, int Ho, int Wo, int K, int Hp,

@@ -31,7 +31,7 @@
 // A value that is not finite anywhere in a tile makes neighbours of the transformed domain NaN that
 // the direct sum would leave finite (or infinite): a thread that finds one among its results
 // forms those results again by the direct sum.
-#include "nf_internal.h"
+#include "wino_filter.h"
 
 namespace nf {
 namespace {
@@ -40,11 +40,11 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int NTHREADS = 256;
-constexpr int TB = 32, NB = 64;          // output tiles, filters per workgroup
-constexpr int CH = 8;                    // channels per step
+constexpr int TB = 32, NB = WINO_NB;     // output tiles, filters per workgroup
+constexpr int CH = WINO_CH;              // channels per step
 constexpr int OOB = (int)0x80000000;     // offset no buffer of < 2 GiB contains
 constexpr int RSRC_FLAGS = 0x00020000;   // raw buffer, 32-bit data format
-constexpr int UB = 16 * NB * CH;         // transformed filter words per (filter block, step)
+constexpr int UB = WINO_UB;
 
 struct WinoAux {
   int TW, TPI, T;        // tiles per image row, per image, in all
@@ -66,7 +66,6 @@ __device__ inline float4 add4(const float4 &a, const float4 &b) {
 __device__ inline float4 sub4(const float4 &a, const float4 &b) {
   return make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w);
 }
-__device__ inline float4 scale4(float s, const float4 &a) { return make_float4(s * a.x, s * a.y, s * a.z, s * a.w); }
 // a + s*b with s = +-1 (exact product)
 __device__ inline float4 fma4(float s, const float4 &b, const float4 &a) {
   return make_float4(__builtin_fmaf(s, b.x, a.x), __builtin_fmaf(s, b.y, a.y), __builtin_fmaf(s, b.z, a.z),
@@ -76,9 +75,8 @@ __device__ inline bool finite4(const float4 &v) {
   return __builtin_isfinite(v.x) & __builtin_isfinite(v.y) & __builtin_isfinite(v.z) & __builtin_isfinite(v.w);
 }
 
-// U[filter block][step][position a*4+b][n & 1][lane][4]: the word of lane (j, h), element k is filter
-// 64*block + 2*j + (n & 1), channel 8*step + 4*h + k, i.e. the B fragment of one MFMA group.  Zero
-// past the last filter and channel.  HBM-bound: 36 bytes read, 64 written per (filter, channel).
+// The transformed filter, zero past the last filter and channel.  HBM-bound: 36 bytes read, 64 written per
+// (filter, channel); 5-8 us.
 __global__ __launch_bounds__(256) void wino_filter_kernel(const float *w, float *U, int N, int C, int nchunks) {
   const int t = threadIdx.x;
   const int c4 = blockIdx.x * 8 + (t & 7), n = blockIdx.y * 32 + (t >> 3);  // 8 lanes read 128 contiguous bytes
@@ -91,22 +89,7 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(const float *w, float 
     for (int s = 0; s < 3; ++s)
       g[r][s] = ok ? *reinterpret_cast<const float4 *>(w + ((long long)n * 9 + r * 3 + s) * C + c4 * 4)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
-  const int blk = n / NB, in = n % NB;
-  float *o = U + ((long long)blk * nchunks + (c4 >> 1)) * UB + (in & 1) * 256 + ((c4 & 1) * 32 + (in >> 1)) * 4;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    float4 q[3];
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      if (a == 0) q[s] = g[0][s];
-      else if (a == 3) q[s] = g[2][s];
-      else q[s] = scale4(0.5f, a == 1 ? add4(add4(g[0][s], g[2][s]), g[1][s]) : sub4(add4(g[0][s], g[2][s]), g[1][s]));
-    }
-    const float4 e = add4(q[0], q[2]);
-    float4 v[4] = {q[0], scale4(0.5f, add4(e, q[1])), scale4(0.5f, sub4(e, q[1])), q[2]};
-#pragma unroll
-    for (int b = 0; b < 4; ++b) *reinterpret_cast<float4 *>(o + (a * 4 + b) * 512) = v[b];
-  }
+  wino_filter_store(g, U, n, c4, nchunks);
 }
 
 // Four outputs (filters n .. n+3 of pixel (img, ho, wo)) by the direct sum over channels [c_lo, c_hi);
@@ -424,7 +407,7 @@ bool wino_fwd_beats_split(const FwdProblem &p, int splits) {
   return wino_us(p, splits) < 0.93 * (8.0 + (nkb + ks - 1) / ks * 1.4 * ((w + 255) / 256) + finish_us(p, ks));
 }
 
-hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st) {
+hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, hipStream_t st) {
   WinoAux q;
   const int TH = (p.Ho + 1) / 2, B = p.M / (p.Ho * p.Wo);
   q.TW = (p.Wo + 1) / 2, q.TPI = TH * q.TW, q.T = B * q.TPI;
@@ -436,10 +419,12 @@ hipError_t launch_wino_fwd(const FwdProblem &p, float *U, hipStream_t st) {
   q.U = U;
   const int splits = p.ksplits > 1 ? p.ksplits : 1;
   q.per = (q.nchunks + splits - 1) / splits;
-  hipLaunchKernelGGL(wino_filter_kernel, dim3((2 * q.nchunks + 7) / 8, q.nblk * 2), dim3(256), 0, st, p.w, U, p.N, p.C,
-                     q.nchunks);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (!filter_ready) {
+    hipLaunchKernelGGL(wino_filter_kernel, dim3((2 * q.nchunks + 7) / 8, q.nblk * 2), dim3(256), 0, st, p.w, U, p.N, p.C,
+                       q.nchunks);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(wino_fwd_kernel, dim3(q.nblk * ((q.T + TB - 1) / TB), splits), dim3(NTHREADS), 0, st, p, q);
   return hipGetLastError();
 }

@@ -33,7 +33,10 @@ CASES = {
 
 @pytest.mark.parametrize("name", list(CASES))
 def test_wino_steps_match_oracle(name):
-    spec, B, cls, launches = CASES[name]
+    wino_step(name, *CASES[name])
+
+
+def wino_step(name, spec, B, cls, launches):
     print(f"case {name}: B={B}", flush=True)
     nf.nf_prof_begin()
     out, final = G.run_step_both(spec, cls, B, seed=310, lr=0.05, mu=0.9, steps=1)
@@ -71,6 +74,46 @@ def test_wino_values_that_are_not_finite(where):
     assert inf.any() and np.array_equal(np.isinf(got), inf)
     # finite results: 576 products of unit variance scale; 1e-4 is the suite's bar
     assert np.abs(got[~inf] - ref[~inf]).max() <= 1e-4 * np.abs(ref[~inf]).max()
+
+
+# data gradients whose transformed filter comes from a head launch: the per-sample head, the wide one and the
+# backward of a wide linear layer; channels of the head and of the layer that are not multiples of 8 and 64
+DGRAD_CASES = {
+    "head_sample_a20_k132": (S(8, 7, 7, 132, 20), 150, 10, 1),
+    "head_wide_a20_k60": (S(8, 16, 16, 60, 20), 240, 10, 1),
+    "head_wide_a32_k200_pool": (S(8, 20, 20, 200, 32, pool=(2, 2, 0)), 80, 10, 1),
+    "head_bwd_a36_k68": (S(8, 12, 12, 68, 36), 200, 130, 1),
+}
+
+
+@pytest.mark.parametrize("name", list(DGRAD_CASES))
+def test_wino_data_gradients_match_oracle(name):
+    wino_step(name, *DGRAD_CASES[name])
+
+
+def test_backward_in_a_larger_workspace_than_the_forward_call():
+    """A head call whose workspace holds the direct kernels alone leaves no transformed filter; the
+    backward call in one that holds everything forms its own."""
+    B, H, K, A, cls = 128, 16, 64, 32, 10
+    g = torch.Generator(device="cuda").manual_seed(8)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    d = nf.LayerDesc(C_in=8, H_in=H, W_in=H, C_out=K, R=3, S=3, stride=1, pad=1)
+    a = nf.AuxDesc(C_in=K, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=1, pool_oh=2, pool_ow=2, n_classes=cls)
+    x, y = rn(B, H, H, 8), rn(B, H, H, K).relu()
+    labels = torch.randint(0, cls, (B,), generator=g, device="cuda", dtype=torch.int32)
+    p = [rn(K, 3, 3, 8) * 0.1, rn(K), rn(A, 3, 3, K) * 0.05, rn(A), rn(cls, 4 * A) * 0.2, rn(cls)]
+    lp, ap = nf.layer_params(p[0], p[1], None), nf.aux_params(*p[2:])
+    need = nf.nf_workspace_bytes(d, a, B)
+    loss, res = torch.zeros(1, device="cuda"), []
+    for fwd_bytes in (need, need - 16 * 64 * 32 * 4):
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")  # NaN wherever nothing is written
+        gr = [torch.zeros_like(t) for t in p]
+        nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, loss, ws[:fwd_bytes])
+        nf.nf_local_bwd_wgrad(d, a, B, x, None, y, lp, ap, nf.layer_params(gr[0], gr[1], None), nf.aux_params(*gr[2:]), ws)
+        res.append(gr[0].cpu().numpy().copy())
+    assert np.abs(res[0]).max() > 0
+    # (the head's sums may be cut differently: 1e-4 is the suite's bar)
+    assert np.abs(res[1] - res[0]).max() <= 1e-4 * np.abs(res[0]).max()
 
 
 WGRAD_CASES = {
