@@ -420,7 +420,7 @@ int igemm_fwd_pick_ksplits(int M, int N, int Kg, int C, int taps) {
     if (s > 16) s = 16;
     return s > 1 ? s : 1;
   }
-  // tile shape as launch_igemm_fwd_fast picks it
+  // at least one 128x128 (up to 128 columns or five steps of 32 products: 64x64) tile per CU
   const int bm = (N > 128 && Kg > 160) ? 128 : 64, bn = bm;
   const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   if (tiles >= 192) return 1;
@@ -428,6 +428,17 @@ int igemm_fwd_pick_ksplits(int M, int N, int Kg, int C, int taps) {
   if (s > nkb / 8) s = nkb / 8;
   if (s > 32) s = 32;
   return s > 1 ? s : 1;
+}
+
+// 64x64 tiles (four workgroups per CU hide each other's loads and barriers; same sums in the same order, so
+// the same bits) unless the 128x128 ones fill the chip twice over and the reduction is long: there the
+// operands' traffic, twice as much with the small tile, is what counts.  Measured, us, 128x128 / 64x64:
+// 512x512 results of 4608 products in 16 parts 31.6 / 30.4, 512x256 in 18 29.2 / 23.4, 128x512 26.7 / 17.0;
+// 1x1, 8192x256 of 256 33.4 / 18.5, 65 536x512 of 512 317 / 310; 12 544x160 of 4800 (48 columns less padding)
+// 307 / 229; 8192x512 of 2304 (256 big tiles) 158 / 157, 32 768x512 (1024) 562 / 587, 16 384x512 of 4608 549 / 580.
+bool igemm_fwd_tile128(int M, int N, int Kg, int ksplits) {
+  const long long w = (long long)((M + 127) / 128) * ((N + 127) / 128) * (ksplits > 1 ? ksplits : 1);
+  return N > 128 && (N + 63) / 64 % 2 == 0 && Kg >= 2048 && w >= 512;
 }
 
 bool fwd_pool_partials_applicable(const FwdProblem &p) {
@@ -457,14 +468,11 @@ hipError_t launch_igemm_fwd_fast(const FwdProblem &p, hipStream_t st, const char
   q.xs_bytes = p.Cs ? (uint32_t)(B * p.Hs * p.Ws * p.Cs * 4) : 0;
   q.wp_bytes = p.Cs ? (uint32_t)((long long)p.N * p.Cs * 4) : 0;
   q.nkb_conv = q.nkb_proj = 0;  // set per tile configuration
-  if (p.N > 128 && p.Kg > 160) {
+  if (igemm_fwd_tile128(p.M, p.N, p.Kg, p.ksplits)) {
     *kernel = "igemm_fwd_fast_128x128";
     return launch_cfg<128, 128, 32, 2, 2, 32>(p, q, st);
   }
   if (p.N > 32) {
-    // at most 128 columns, or one to five reduction steps (bound by the output stream): small
-    // tiles keep more workgroups in flight (measured 7-9 % faster than 128x64 at N = 64, 4 %
-    // faster than 128x128 at N = 128)
     *kernel = "igemm_fwd_fast_64x64";
     return launch_cfg<64, 64, 32, 2, 2, 32>(p, q, st);
   }

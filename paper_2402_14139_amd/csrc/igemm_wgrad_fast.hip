@@ -357,6 +357,17 @@ bool igemm_wgrad_fast_applicable(const WgradProblem &p) {
   return true;
 }
 
+// 64x64 tiles (the same sums in the same order) where the 128x128 ones, two per CU, leave an eighth of the chip or
+// more without work in their rounds, or pad the result by more than a tenth.  Measured, us, 128x128 / 64x64
+// (workgroups of the former): 512x4608 over 256 rows (288) 31.0 / 24.5, 512 rows (432) 36.0 / 34.2, 128x1152 over 4096
+// (288) 30.8 / 23.4, 256x256 over 2048 (64) 17.8 / 10.0; 160x4800 over 12 544 258 / 211; but 384x6400 over 288 (450)
+// 26.8 / 27.3, 512x2304 over 1024 (504) 32.3 / 33.2, over 32 768 (504) 591 / 640.
+bool igemm_wgrad_tile64(int P, int Q, int splits) {
+  const auto up = [](long long n, long long m) { return (n + m - 1) / m; };
+  const long long w = up(P, 128) * up(Q, 128) * splits, rounds = up(w, 512);
+  return 8 * w < 7 * 512 * rounds || 10 * up(P, 64) * up(Q, 64) < 9 * 4 * up(P, 128) * up(Q, 128);
+}
+
 hipError_t launch_igemm_wgrad_fast(const WgradProblem &p0, hipStream_t st, const char **kernel) {
   if (contraction_mode() != NF_CONTRACT_F32 && igemm_wgrad_split_applicable(p0))
     return launch_igemm_wgrad_split(p0, contraction_mode() == NF_CONTRACT_BF16X9, st, kernel);
@@ -365,7 +376,7 @@ hipError_t launch_igemm_wgrad_fast(const WgradProblem &p0, hipStream_t st, const
   p.d_bytes = (uint32_t)((long long)p.M * p.P * 4);
   p.x_bytes = (uint32_t)(B * p.H * p.W * p.C * 4);
   p.xs_bytes = p.Cs ? (uint32_t)(B * p.Hs * p.Ws * p.Cs * 4) : 0;
-  if (p.P > 64) {
+  if (p.P > 64 && !igemm_wgrad_tile64(p.P, p.Q, p.splits)) {
     *kernel = "igemm_wgrad_fast_128x128";
     return launch_cfg<128, 128, 2, 2>(p, st);
   }

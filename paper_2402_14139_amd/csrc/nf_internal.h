@@ -50,6 +50,8 @@ struct FwdProblem {
 bool fwd_pool_partials_applicable(const FwdProblem &p);
 // how many reduction splits a skinny forward-type contraction should use (1 = none)
 int igemm_fwd_pick_ksplits(int M, int N, int Kg, int C, int taps);
+// whether the direct kernel takes 128x128 tiles (more than 32 filters: 64x64 otherwise)
+bool igemm_fwd_tile128(int M, int N, int Kg, int ksplits);
 // out[m][n] = act(sum_z part[z][m][n] + bias[n] + addsrc[m][n]) zeroed where mask[m][n] <= 0:
 // the epilogue of a forward-type contraction whose reduction was split
 hipError_t launch_fwd_finish(const float *part, int splits, long long M, int N, const float *bias,
@@ -100,6 +102,8 @@ struct WgradProblem {
 };
 // chooses the tile shape for (P,Q); reports how many splits of M it wants
 int wgrad_pick_splits(int P, int Q, int M);
+// whether igemm_wgrad_fast takes 64x64 tiles for more than 64 filters (128x128 otherwise)
+bool igemm_wgrad_tile64(int P, int Q, int splits);
 hipError_t launch_igemm_wgrad(const WgradProblem &p, hipStream_t st, const char **kernel);
 // software-pipelined buffer-load variant (igemm_wgrad_fast.hip); launch_igemm_wgrad picks it when applicable
 bool igemm_wgrad_fast_applicable(const WgradProblem &p);

@@ -389,7 +389,7 @@ int wino_fwd_pick_splits(const FwdProblem &p) {
   }
   // the direct kernel: steps of 32 products, 128x128 tiles one per CU or 64x64 tiles up to four
   const int nkb = (p.Kg + 31) / 32;
-  const bool big = p.N > 128 && p.Kg > 160;
+  const bool big = igemm_fwd_tile128(p.M, p.N, p.Kg, ks);
   const int bt = big ? 128 : 64;
   const long long w = (long long)((p.M + bt - 1) / bt) * ((p.N + bt - 1) / bt) * ks;
   const double per = big ? 2.06 * ((w + 255) / 256) : w <= 260 ? 0.56 : 0.55 * w / 256.0;

@@ -375,9 +375,11 @@ int wino_wgrad_pick_splits(const WgradProblem &p) {
     const double us = wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;
   }
-  const double q64 = (p.Q + 63) / 64 * 64.0;
-  const double direct = p.P > 64 ? wide_us(p, 118e6)
-                                 : 8.0 + 2.0 * p.M * 64 * q64 / 104e6 + reduce_us(p, wgrad_pick_splits(p.P, p.Q, p.M));
+  const int sd = wgrad_pick_splits(p.P, p.Q, p.M);
+  const double p64 = (p.P + 63) / 64 * 64.0, q64 = (p.Q + 63) / 64 * 64.0;
+  const double direct = p.P > 64 && !igemm_wgrad_tile64(p.P, p.Q, sd)
+                            ? wide_us(p, 118e6)
+                            : 8.0 + 2.0 * p.M * p64 * q64 / 104e6 + reduce_us(p, sd);
   return best < 0.95 * direct ? splits : 0;
 }
 

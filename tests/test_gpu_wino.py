@@ -15,17 +15,17 @@ pytestmark = pytest.mark.gpu
 # name -> (spec, B, classes, how many of layer / head / data gradient run as wino_fwd)
 CASES = {
     # ragged last tile block, last filter block of 4, odd map (a half-empty tile in both directions)
-    "odd_map_n260": (S(64, 5, 7, 260, 8), 9, 10, 1),
+    "odd_map_n260": (S(64, 5, 7, 260, 8), 221, 10, 1),
     # channel count not a multiple of the step (8), identity shortcut
-    "c68_identity": (S(256, 8, 8, 256, 4, skip=1), 5, 10, 1),
-    "c68": (S(68, 8, 8, 256, 4), 5, 10, 1),
+    "c68_identity": (S(256, 8, 8, 256, 4, skip=1), 25, 10, 1),
+    "c68": (S(68, 8, 8, 256, 4), 64, 10, 1),
     # the narrowest map it takes, an odd one
-    "map_4x5": (S(64, 4, 5, 256, 8), 20, 10, 1),
+    "map_4x5": (S(64, 4, 5, 256, 8), 317, 10, 1),
     # split reductions: layer (pooled), and all three of layer, head and data gradient
-    "split_pool": (S(256, 8, 8, 256, 4, pool=(2, 2, 0)), 4, 10, 1),
-    "split_wide_head": (S(256, 4, 4, 256, 256), 16, 10, 3),
+    "split_pool": (S(256, 8, 8, 256, 4, pool=(2, 2, 0)), 25, 10, 1),
+    "split_wide_head": (S(256, 4, 4, 256, 256), 94, 10, 3),
     # projection shortcut: a launch of its own, added in the epilogue
-    "projection": (S(128, 8, 8, 256, 4, skip=2, skip_C=36), 130, 10, 1),
+    "projection": (S(128, 8, 8, 256, 4, skip=2, skip_C=36), 260, 10, 1),
     # fewer filters than a workgroup's 64 columns
     "n60": (S(128, 16, 16, 60, 4), 100, 10, 1),
 }
@@ -49,7 +49,7 @@ def wino_step(name, spec, B, cls, launches):
 @pytest.mark.parametrize("where", ["input", "filter"])
 def test_wino_values_that_are_not_finite(where):
     """An infinity reaches exactly the results whose direct sum contains it."""
-    B, C, H, W, K = 3, 64, 9, 8, 256
+    B, C, H, W, K = 83, 64, 9, 8, 256
     g = torch.Generator().manual_seed(5)
     x, w = torch.randn(B, H, W, C, generator=g), torch.randn(K, 3, 3, C, generator=g) * 0.06
     if where == "input":
@@ -79,7 +79,7 @@ def test_wino_values_that_are_not_finite(where):
 # data gradients whose transformed filter comes from a head launch: the per-sample head, the wide one and the
 # backward of a wide linear layer; channels of the head and of the layer that are not multiples of 8 and 64
 DGRAD_CASES = {
-    "head_sample_a20_k132": (S(8, 7, 7, 132, 20), 150, 10, 1),
+    "head_sample_a20_k132": (S(8, 7, 7, 132, 20), 453, 10, 1),
     "head_wide_a20_k60": (S(8, 16, 16, 60, 20), 240, 10, 1),
     "head_wide_a32_k200_pool": (S(8, 20, 20, 200, 32, pool=(2, 2, 0)), 80, 10, 1),
     "head_bwd_a36_k68": (S(8, 12, 12, 68, 36), 200, 130, 1),
@@ -118,9 +118,9 @@ def test_backward_in_a_larger_workspace_than_the_forward_call():
 
 WGRAD_CASES = {
     # odd maps (half-empty tiles), tiles of an image not a multiple of a step's four
-    "odd_map_13x11": (S(64, 13, 11, 128, 4), 64, 10),
+    "odd_map_13x11": (S(64, 13, 11, 128, 4), 90, 10),
     # ragged channel (32) and filter (64) blocks, identity shortcut, pooled
-    "c36_p132_pool": (S(36, 10, 9, 132, 4, pool=(2, 2, 0)), 96, 10),
+    "c36_p132_pool": (S(36, 10, 9, 132, 4, pool=(2, 2, 0)), 574, 10),
     # narrowest map it takes, a last split shorter than the others
     "map_4x4_last_split": (S(96, 4, 4, 256, 4), 517, 10),
     # projection shortcut (its columns are a launch of their own)
