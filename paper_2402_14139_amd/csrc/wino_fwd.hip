@@ -71,8 +71,10 @@ __device__ inline float4 fma4(float s, const float4 &b, const float4 &a) {
   return make_float4(__builtin_fmaf(s, b.x, a.x), __builtin_fmaf(s, b.y, a.y), __builtin_fmaf(s, b.z, a.z),
                      __builtin_fmaf(s, b.w, a.w));
 }
-__device__ inline bool finite4(const float4 &v) {
-  return __builtin_isfinite(v.x) & __builtin_isfinite(v.y) & __builtin_isfinite(v.z) & __builtin_isfinite(v.w);
+// bit e: component e is not finite
+__device__ inline unsigned bad4(const float4 &v) {
+  return (__builtin_isfinite(v.x) ? 0u : 1u) | (__builtin_isfinite(v.y) ? 0u : 2u) | (__builtin_isfinite(v.z) ? 0u : 4u) |
+         (__builtin_isfinite(v.w) ? 0u : 8u);
 }
 
 // The transformed filter, zero past the last filter and channel.  HBM-bound: 36 bytes read, 64 written per
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(const float *w, float 
 // Four outputs (filters n .. n+3 of pixel (img, ho, wo)) by the direct sum over channels [c_lo, c_hi);
 // taps outside the image multiply a zero, as in the direct kernel.
 __device__ inline float4 direct4(const float *x, const float *w, int H, int W, int C, int img, int ho, int wo, int n,
-                                 int c_lo, int c_hi) {
+                                 int c_lo, int c_hi, unsigned want) {
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   const long long ws = 9ll * C;
 #pragma unroll 1
@@ -105,10 +107,17 @@ __device__ inline float4 direct4(const float *x, const float *w, int H, int W, i
     const float *xr = x + ((long long)(img * H + (in ? hi : 0)) * W + (in ? wi : 0)) * C;
     const float *wr = w + ((long long)n * 9 + tap) * C;
 #pragma unroll 1
-    for (int c = c_lo; c < c_hi; ++c) {
-      const float v = in ? xr[c] : 0.f;
-      s.x = __builtin_fmaf(v, wr[c], s.x), s.y = __builtin_fmaf(v, wr[c + ws], s.y);
-      s.z = __builtin_fmaf(v, wr[c + 2 * ws], s.z), s.w = __builtin_fmaf(v, wr[c + 3 * ws], s.w);
+    for (int c = c_lo; c < c_hi; c += 4) {
+      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f), v = in ? *reinterpret_cast<const float4 *>(xr + c) : z;
+      auto dot = [&](int k, float a) {
+        const float4 g = *reinterpret_cast<const float4 *>(wr + k * ws + c);
+        return __builtin_fmaf(v.w, g.w, __builtin_fmaf(v.z, g.z, __builtin_fmaf(v.y, g.y, __builtin_fmaf(v.x, g.x, a))));
+      };
+      s.x = dot(0, s.x), s.y = dot(1, s.y), s.z = dot(2, s.z), s.w = dot(3, s.w);
+      // a NaN stays one: filters that have become NaN, as in a network that has diverged, cost a step of this
+      const unsigned nan = (__builtin_isnan(s.x) ? 1u : 0u) | (__builtin_isnan(s.y) ? 2u : 0u) |
+                           (__builtin_isnan(s.z) ? 4u : 0u) | (__builtin_isnan(s.w) ? 8u : 0u);
+      if ((nan & want) == want) return s;
     }
   }
   return s;
@@ -282,7 +291,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
   float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
   if (p.bias && !split && n < p.N) bias = *reinterpret_cast<const float4 *>(p.bias + n);
   // everything after the contraction for one result
-  auto finish = [&](float4 v, float4 x, long long o) {
+  auto finish = [&](float4 v, float4 x, long long o) -> float4 {
     if (!split) {
       v = add4(v, bias);
       if (p.addsrc) v = add4(v, x);
@@ -292,9 +301,20 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
         v.x = m.x > 0.f ? v.x : 0.f, v.y = m.y > 0.f ? v.y : 0.f, v.z = m.z > 0.f ? v.z : 0.f, v.w = m.w > 0.f ? v.w : 0.f;
       }
     }
-    *reinterpret_cast<float4 *>(out + o) = v;
+    return v;
   };
-  unsigned bad = 0;  // bit 2*i + k: that result is not finite
+  // results whose bits are not in `skip` (a projection's result, read as addsrc, may lie where they go)
+  auto store = [&](const float4 &v, long long o, unsigned skip) {
+    if (!skip) {
+      *reinterpret_cast<float4 *>(out + o) = v;
+      return;
+    }
+    if (!(skip & 1u)) out[o] = v.x;
+    if (!(skip & 2u)) out[o + 1] = v.y;
+    if (!(skip & 4u)) out[o + 2] = v.z;
+    if (!(skip & 8u)) out[o + 3] = v.w;
+  };
+  unsigned bad = 0;  // four bits from 4*(2*i + k): which of those results are not finite
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int task = i * 16 + (t >> 4), lt = task >> 1;
@@ -306,23 +326,25 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       if (off[i][k] < 0) continue;
-      bad |= finite4(y[k]) ? 0u : 1u << (2 * i + k);
-      finish(y[k], ex[i][k], off[i][k]);
+      const unsigned b = bad4(y[k]);
+      bad |= b << (4 * (2 * i + k));
+      store(finish(y[k], ex[i][k], off[i][k]), off[i][k], b);
     }
   }
   if (bad == 0) return;
 #pragma unroll 1
   for (int ik = 0; ik < 8; ++ik) {
-    if (!(bad >> ik & 1)) continue;
+    const unsigned want = bad >> (4 * ik) & 15u;
+    if (!want) continue;
     const int task = (ik >> 1) * 16 + (t >> 4), tile = t0 + (task >> 1);
     const int img = (int)q.div_tpi.div((uint32_t)tile), rem = tile - img * q.TPI;
     const int ty = (int)q.div_tw.div((uint32_t)rem), tx = rem - ty * q.TW;
     const int ho = 2 * ty + (ik & 1), wo = 2 * tx + (task & 1);
     const long long o = ((long long)(img * p.Ho + ho) * p.Wo + wo) * p.N + n;
-    const float4 v = direct4(p.x, p.w, p.H, p.W, p.C, img, ho, wo, n, s_lo * CH, min(p.C, s_hi * CH));
+    const float4 v = direct4(p.x, p.w, p.H, p.W, p.C, img, ho, wo, n, s_lo * CH, min(p.C, s_hi * CH), want);
     float4 x = bias;
     if (extra) x = *reinterpret_cast<const float4 *>(extra + o);
-    finish(v, x, o);
+    store(finish(v, x, o), o, ~want & 15u);
   }
 }
 

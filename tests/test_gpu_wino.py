@@ -76,6 +76,58 @@ def test_wino_values_that_are_not_finite(where):
     assert np.abs(got[~inf] - ref[~inf]).max() <= 1e-4 * np.abs(ref[~inf]).max()
 
 
+def test_wino_values_that_are_not_finite_beside_a_projection():
+    """The projection's sums lie where the results go: a result formed again still has its own."""
+    B, C, H, K, Cs = 260, 128, 8, 256, 36
+    g = torch.Generator(device="cuda").manual_seed(13)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    x, xs, w, b, wp = rn(B, H, H, C), rn(B, 2 * H, 2 * H, Cs), rn(K, 3, 3, C) * 0.04, rn(K), rn(K, Cs) * 0.2
+    x[7, 3, 4, 5] = float("inf")
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=K, R=3, S=3, stride=1, pad=1, skip_kind=2, skip_C=Cs,
+                     skip_H=2 * H, skip_W=2 * H, skip_stride=2)
+    need, ys, names = nf.nf_workspace_bytes(d, None, B), [], []
+    for nbytes in (need, need - 256):  # the second one only holds the direct kernels
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        y = torch.full((B, H, H, K), -1.0, device="cuda")
+        nf.nf_prof_begin()
+        nf.nf_layer_fwd(d, B, x, xs, nf.layer_params(w, b, wp), y, ws)
+        names.append({r["kernel"] for r in nf.nf_prof_end()})
+        ys.append(y)
+    if nf.nf_contraction() != nf.NF_CONTRACT_F32:
+        pytest.skip("the split modes turn an infinity into NaN")
+    assert "wino_fwd" in names[0] and "wino_fwd" not in names[1], names
+    inf = torch.isinf(ys[1])
+    assert inf.any() and torch.equal(torch.isinf(ys[0]), inf) and not torch.isnan(ys[0]).any()
+    # 1188-term sums in two orders: a few 1e-7 of the largest value
+    assert (ys[0] - ys[1])[~inf].abs().max() <= 5e-6 * ys[1][~inf].abs().max()
+
+
+def test_wino_results_of_filters_that_are_nan():
+    """Whole filters of NaN, some beside finite ones in the group of four that a thread forms again."""
+    B, C, H, K = 48, 64, 16, 256
+    g = torch.Generator(device="cuda").manual_seed(12)
+    x, w = torch.randn(B, H, H, C, generator=g, device="cuda"), torch.randn(K, 3, 3, C, generator=g, device="cuda") * 0.06
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=K, R=3, S=3, stride=1, pad=1)
+    b, ys = torch.full((K,), 30.0, device="cuda"), []  # every finite result positive: ReLU passes it
+    ws = torch.empty(nf.nf_workspace_bytes(d, None, B), dtype=torch.uint8, device="cuda")
+    bad = torch.zeros(K, dtype=torch.bool, device="cuda")
+    bad[8:16], bad[21], bad[40:43] = True, True, True
+    for nan in (False, True):
+        if nan:
+            w[bad] = float("nan")
+        y = torch.empty(B, H, H, K, device="cuda")
+        nf.nf_prof_begin()
+        nf.nf_layer_fwd(d, B, x, None, nf.layer_params(w, b, None), y, ws)
+        names = {r["kernel"] for r in nf.nf_prof_end()}
+        ys.append(y)
+    if nf.nf_contraction() == nf.NF_CONTRACT_F32:
+        assert "wino_fwd" in names
+    assert (ys[1][..., bad] == 0).all()  # ReLU as the library takes it: NaN is not positive
+    assert (ys[0] > 0).all()
+    # 576-term sums in two orders where a neighbour was NaN: a few 1e-7 of the largest value
+    assert (ys[1] - ys[0])[..., ~bad].abs().max() <= 5e-6 * ys[0].abs().max()
+
+
 # data gradients whose transformed filter comes from a head launch: the per-sample head, the wide one and the
 # backward of a wide linear layer; channels of the head and of the layer that are not multiples of 8 and 64
 DGRAD_CASES = {
