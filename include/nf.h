@@ -116,8 +116,8 @@ const char *nf_strerror(int32_t status);
  *                       square, i.e. of the size of an fp32 rounding; over the reductions of this
  *                       library (36 ... 4608 terms) the measured error against fp64 equals that of
  *                       the fp32 instructions.  An operand element that is +-inf gives NaN
- *                       instead of +-inf.  Contractions that NF_CONTRACT_F32 carries out faster run as
- *                       there.
+ *                       instead of +-inf.  Weight gradients that NF_CONTRACT_F32 carries out faster
+ *                       run as there.
  *   NF_CONTRACT_BF16X9  the same with all nine piece products: every product x*w enters the fp32
  *                       accumulation exactly, as with the fp32 instructions; 1.5x the matrix-core
  *                       work of BF16X6.
@@ -129,7 +129,8 @@ int32_t nf_contraction(int32_t mode);
 /* Emitted sizes: conv output (Ho,Wo) and post-pool (Hp,Wp).  Any out pointer may be NULL. */
 int32_t nf_layer_out_dims(const nf_layer_desc *d, int32_t *Ho, int32_t *Wo, int32_t *Hp, int32_t *Wp);
 
-/* Bytes of workspace the calls below need for this (layer, head, batch).  `a` may be NULL
+/* Bytes of workspace the calls below want for this (layer, head, batch); single-layer calls also take a
+ * smaller one that still holds the direct contraction kernels, and run those.  `a` may be NULL
  * when only nf_layer_fwd will be called. */
 int32_t nf_workspace_bytes(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B, size_t *out);
 
@@ -201,7 +202,7 @@ int32_t nf_local_step(const nf_layer_desc *d, const nf_aux_desc *a, const nf_sgd
  * allocates nothing (no hipMalloc / hipFree, no allocating library routine).
  * A (layer, head, B) whose nf_workspace_bytes exceeds NF_STATIC_SCRATCH_BYTES is rejected with
  * NF_ERR_SCRATCH_LIMIT before anything is enqueued (a 512-channel 3x3 layer at batch 512 on 4x4
- * maps needs 89 MiB, the largest layer of the VGG-16-style workload 115 MiB).
+ * maps needs 89 MiB, the largest layer of the VGG-16-style workload 124.6 MiB).
  * Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU (two
  * streams, two threads) race; order them on one stream.  The array keeps the previous call's
  * contents, which is harmless: every region is written by the step before it is read.  The

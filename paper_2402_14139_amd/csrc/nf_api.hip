@@ -150,7 +150,6 @@ struct WsLayout {
   // > 0: that contraction runs as wino_fwd (fp32 mode) with this many reduction splits; the
   // transformed filter, then the partial sums of the splits, alias `part`
   int wino_layer, wino_aux, wino_dgrad;
-  int wino_split_mode;  // 1: the scratch also serves wino_fwd in place of the six-product kernel
   // > 0: the layer's weight gradient runs as wino_wgrad (fp32 mode) with this many splits; the projection's,
   // if any, is a contraction of its own with proj_splits, its partial sums behind the other ones
   int wino_wgrad, proj_splits;
@@ -183,14 +182,9 @@ FwdProblem layer_fwd_problem(const nf_layer_desc *d, const LayerDims &ld, int B)
   return f;
 }
 
-// The six-product kernel adds two half sums, so where wino_fwd replaces it a long sum is cut in two as
-// well (512 channels: error 4.2e-7; uncut 4.4e-7, cut 3.5e-7).
-int wino_splits_split_mode(const FwdProblem &f, int splits) { return splits == 1 && f.C > 256 ? 2 : splits; }
-
-// scratch of a forward-type contraction that runs as wino_fwd (split_mode: in place of the six-product kernel)
-size_t wino_scratch_floats(int splits, const FwdProblem &f, bool split_mode) {
+// scratch of a forward-type contraction that runs as wino_fwd
+size_t wino_scratch_floats(int splits, const FwdProblem &f) {
   if (!splits) return 0;
-  if (split_mode && igemm_fwd_split_applicable(f)) splits = wino_splits_split_mode(f, splits);
   return wino_fwd_filter_floats(f.N, f.C) + (splits > 1 ? (size_t)splits * f.M * f.N : 0);
 }
 
@@ -216,7 +210,7 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
   size_t pmax = w.ksplits_layer > 1 ? (size_t)w.ksplits_layer * conv_out : 0;
   const FwdProblem fl = layer_fwd_problem(d, ld, B);
   w.wino_layer = wino ? wino_fwd_pick_splits(fl) : 0;
-  size_t pwino = wino_scratch_floats(w.wino_layer, fl, false), pcut = wino_scratch_floats(w.wino_layer, fl, true);
+  size_t pwino = wino_scratch_floats(w.wino_layer, fl);
   w.ksplits_aux = w.ksplits_dgrad = 1;
   if (a) {
     const size_t u = (size_t)B * ad.Hu * ad.Wu * a->A;
@@ -253,8 +247,7 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     w.wino_aux = wino ? wino_fwd_pick_splits(fa) : 0;
     w.wino_dgrad = wino ? wino_fwd_pick_splits(fd) : 0;
     w.Ud = take(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0);
-    pwino = std::max({pwino, wino_scratch_floats(w.wino_aux, fa, false), wino_scratch_floats(w.wino_dgrad, fd, false)});
-    pcut = std::max({pcut, wino_scratch_floats(w.wino_aux, fa, true), wino_scratch_floats(w.wino_dgrad, fd, true)});
+    pwino = std::max({pwino, wino_scratch_floats(w.wino_aux, fa), wino_scratch_floats(w.wino_dgrad, fd)});
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;
     if (w.head_fused == 2 && head_pool_partials_applicable(head_shape(a, ad, B))) {
       // (a reduction split in two gives way: the pooling launch it would need costs more than it gains)
@@ -277,8 +270,6 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
   };
   if (wino && pushes_out(pwino)) return ws_layout(d, ld, a, ad, B, false);
   pmax = std::max(pmax, pwino);
-  w.wino_split_mode = w.wino_layer + w.wino_aux + w.wino_dgrad > 0 && !pushes_out(pcut);
-  if (w.wino_split_mode) pmax = std::max(pmax, pcut);
   w.part = take(pmax * f);
   w.total = off ? off : ALIGN;
   return w;
@@ -402,14 +393,11 @@ int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, float
 }
 
 // The reduction splits with which a contraction that the layout plans as wino_fwd runs in the mode in force;
-// 0: the direct kernels.  Always so in the fp32 mode; in the split-operand modes where their kernels do not
-// serve it (narrow layers), with six piece products also where those are slower (with nine the caller
-// asks for exact products, which a transformed contraction does not form).
-int wino_splits_now(const FwdProblem &f, int splits, const WsLayout &w) {
-  const int mode = contraction_mode();
-  if (!splits || mode == NF_CONTRACT_F32 || !igemm_fwd_fast_applicable(f) || !igemm_fwd_split_applicable(f)) return splits;
-  splits = wino_splits_split_mode(f, splits);
-  return mode == NF_CONTRACT_BF16X6 && w.wino_split_mode && wino_fwd_beats_split(f, splits) ? splits : 0;
+// 0: the direct kernels.  The split-operand modes keep their kernels where those serve it: a ReLU decision that
+// is a tie to within rounding falls as that mode's sums have it.
+int wino_splits_now(const FwdProblem &f, int splits) {
+  return contraction_mode() == NF_CONTRACT_F32 || !igemm_fwd_fast_applicable(f) || !igemm_fwd_split_applicable(f) ? splits
+                                                                                                                  : 0;
 }
 // whether the layer's weight gradient, planned as wino_wgrad, runs that way in the mode in force
 bool run_wino(const WgradProblem &g, int splits) {
@@ -420,9 +408,9 @@ bool run_wino(const WgradProblem &g, int splits) {
 }
 
 // by the layout's plan: wino_fwd, or the direct kernels
-int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, const WsLayout &w, float *part,
-                     hipStream_t st, float *filter = nullptr) {
-  if ((wino = wino_splits_now(f, wino, w))) {
+int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, float *part, hipStream_t st,
+                     float *filter = nullptr) {
+  if ((wino = wino_splits_now(f, wino))) {
     FwdProblem g = f;
     if (f.Cs) {  // the projection first, into `out`; wino_fwd adds it there (each element read by the thread that writes it)
       FwdProblem pr;
@@ -467,7 +455,7 @@ int32_t run_layer_fwd(const nf_layer_desc *d, const LayerDims &ld, int B, const 
   if (d->skip_kind == 1) f.addsrc = xs;
   if (d->skip_kind == 2) f.xs = xs, f.wp = p->Wp;
   float *conv_out = pooled ? wsf(ws, w.T_dZ) : y;
-  int32_t rc = enqueue_conv(f, conv_out, w.wino_layer, w.ksplits_layer, w, wsf(ws, w.part), st);
+  int32_t rc = enqueue_conv(f, conv_out, w.wino_layer, w.ksplits_layer, wsf(ws, w.part), st);
   if (rc) return rc;
   if (pooled) {
     const double pre = (double)B * ld.Ho * ld.Wo * d->C_out, post = (double)B * ld.Hp * ld.Wp * d->C_out;
@@ -485,7 +473,7 @@ int32_t run_aux_conv(const nf_aux_desc *a, const AuxDims &ad, int B, const float
                      const WsLayout &w, hipStream_t st, bool pool_partials, int *ks, const float **parts) {
   FwdProblem f = aux_fwd_problem(a, ad, B);
   f.x = y, f.w = ap->Wa, f.bias = ap->ba;
-  const int wino = wino_splits_now(f, w.wino_aux, w);
+  const int wino = wino_splits_now(f, w.wino_aux);
   const int splits = wino ? wino : igemm_fwd_fast_applicable(f) ? w.ksplits_aux : 1;
   *ks = splits > 1 ? splits : 0;
   float *const part = wsf(ws, w.part) + (wino ? wino_fwd_filter_floats(f.N, f.C) : 0);
@@ -603,7 +591,7 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
     f.mask = pooled ? nullptr : y;
     // by a head launch of this call; a forward call of its own may have had a workspace without the region
     const bool filter_ready = sgd || !w.head_fused;
-    const int32_t rc = enqueue_conv(f, pooled ? wsf(ws, w.dY) : dZ, w.wino_dgrad, w.ksplits_dgrad, w, wsf(ws, w.part),
+    const int32_t rc = enqueue_conv(f, pooled ? wsf(ws, w.dY) : dZ, w.wino_dgrad, w.ksplits_dgrad, wsf(ws, w.part),
                                     st, filter_ready ? wsf(ws, w.Ud) : nullptr);
     if (rc) return rc;
     if (pooled) {

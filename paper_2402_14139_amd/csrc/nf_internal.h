@@ -78,8 +78,6 @@ size_t wino_fwd_filter_floats(int N, int C);
 // 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none).  Of a
 // problem with a projection (Cs) it serves the 3x3 part: the caller adds the projection through addsrc
 int wino_fwd_pick_splits(const FwdProblem &p);
-// whether it is also faster, with the splits picked, than the split-operand kernel with six piece products
-bool wino_fwd_beats_split(const FwdProblem &p, int splits);
 // (filter_ready: U holds the transformed filter already, one launch)
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, hipStream_t st);
 

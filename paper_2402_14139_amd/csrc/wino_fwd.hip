@@ -419,16 +419,6 @@ int wino_fwd_pick_splits(const FwdProblem &p) {
   return splits && best < 0.93 * direct ? splits : 0;
 }
 
-// The split-operand kernel (six piece products) takes 1.4 us per step of 32 products and 128x128 tile, one
-// tile per CU.  512 -> 512 channels, 8192 pixels: 206 us, this 150 + 7; 1024 pixels in 8 splits: about 41, this
-// 43.  The error against 64 bits is no larger where this one is taken (512 channels 6.5e-7 for both,
-// 256 4.9e-7 / 4.4e-7, 128 3.5e-7 / 3.1e-7).
-bool wino_fwd_beats_split(const FwdProblem &p, int splits) {
-  const int nkb = (p.Kg + 31) / 32, ks = igemm_fwd_pick_ksplits(p.M, p.N, p.Kg, p.C, p.R * p.S);
-  const long long w = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * ks;
-  return wino_us(p, splits) < 0.93 * (8.0 + (nkb + ks - 1) / ks * 1.4 * ((w + 255) / 256) + finish_us(p, ks));
-}
-
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, hipStream_t st) {
   WinoAux q;
   const int TH = (p.Ho + 1) / 2, B = p.M / (p.Ho * p.Wo);
