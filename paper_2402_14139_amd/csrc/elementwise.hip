@@ -112,13 +112,13 @@ __global__ __launch_bounds__(ET) void maxpool_bwd_kernel(const float *__restrict
 }
 
 // ---- epilogue of a split forward-type contraction: sum of the parts in order, bias, identity
-// shortcut, ReLU, mask (Eq. 1 after the convolution; data gradient of beta_n) ----
+// shortcut, ReLU, mask (Eq. 1 after the convolution; data gradient of beta_n).  `addsrc` may be `out` (a
+// projection's sums lie where the results go): a thread reads its elements before it stores them ----
 template <int V>
 __global__ __launch_bounds__(ET) void fwd_finish_kernel(const float *__restrict__ part, int splits, long long total,
                                                         int N, const float *__restrict__ bias,
-                                                        const float *__restrict__ addsrc,
-                                                        const float *__restrict__ mask, int relu,
-                                                        float *__restrict__ out) {
+                                                        const float *addsrc, const float *__restrict__ mask, int relu,
+                                                        float *out) {
   const long long i = ((long long)blockIdx.x * ET + threadIdx.x) * V;
   if (i >= total) return;
   float v[V];

@@ -53,7 +53,7 @@ int igemm_fwd_pick_ksplits(int M, int N, int Kg, int C, int taps);
 // whether the direct kernel takes 128x128 tiles (more than 32 filters: 64x64 otherwise)
 bool igemm_fwd_tile128(int M, int N, int Kg, int ksplits);
 // out[m][n] = act(sum_z part[z][m][n] + bias[n] + addsrc[m][n]) zeroed where mask[m][n] <= 0:
-// the epilogue of a forward-type contraction whose reduction was split
+// the epilogue of a forward-type contraction whose reduction was split.  addsrc may be out
 hipError_t launch_fwd_finish(const float *part, int splits, long long M, int N, const float *bias,
                              const float *addsrc, const float *mask, int relu, float *out, hipStream_t st);
 // `*kernel` receives a static string naming the tile configuration that was launched

@@ -46,6 +46,29 @@ def wino_step(name, spec, B, cls, launches):
         assert got.get("wino_fwd", 0) >= launches, got
 
 
+# name -> (spec, B, whether the 3x3 part's reduction is split)
+PROJECTIONS = {
+    # its sums lie in the output, where fwd_finish adds the parts of the 3x3 convolution to them
+    "split_4": (S(256, 8, 8, 256, 8, skip=2, skip_C=128), 64, True),
+    "split_2_pool": (S(256, 8, 8, 256, 8, pool=(2, 2, 0), skip=2, skip_C=128), 128, True),
+    # channels that are not a multiple of 4: the general kernel, the first-layer kernel
+    "skip_c34_split": (S(512, 4, 4, 512, 4, skip=2, skip_C=34), 128, True),
+    "skip_c10": (S(128, 8, 8, 256, 4, skip=2, skip_C=10), 260, False),
+}
+
+
+@pytest.mark.parametrize("name", list(PROJECTIONS))
+def test_wino_beside_a_projection_matches_oracle(name):
+    spec, B, split = PROJECTIONS[name]
+    print(f"case {name}: B={B}", flush=True)
+    nf.nf_prof_begin()
+    out, final = G.run_step_both(spec, 10, B, seed=312, lr=0.05, mu=0.9, steps=1)
+    got = {r["kernel"] for r in nf.nf_prof_end()}
+    G.check_step_results(name, out, final)
+    if nf.nf_contraction() == nf.NF_CONTRACT_F32:
+        assert "wino_fwd" in got and ("fwd_finish" in got) == split, got
+
+
 @pytest.mark.parametrize("where", ["input", "filter"])
 def test_wino_values_that_are_not_finite(where):
     """An infinity reaches exactly the results whose direct sum contains it."""
