@@ -193,12 +193,13 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
                    bool wino = true) {
   WsLayout w;
   std::memset(&w, 0, sizeof(w));
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
+  size_t off = 0, least = 0;  // least: the same regions as the direct kernels need them
+  auto take_or = [&](size_t bytes, size_t direct_bytes) {
     const size_t at = off;
-    off += up(bytes);
+    off += up(bytes), least += up(direct_bytes);
     return at;
   };
+  auto take = [&](size_t bytes) { return take_or(bytes, bytes); };
   const size_t f = sizeof(float);
   const bool pooled = d->pool_kind != 0;
   const size_t conv_out = (size_t)B * ld.Ho * ld.Wo * d->C_out, emitted = (size_t)B * ld.Hp * ld.Wp * d->C_out;
@@ -246,7 +247,7 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     const FwdProblem fa = aux_fwd_problem(a, ad, B), fd = dgrad_problem(a, ad, B);
     w.wino_aux = wino ? wino_fwd_pick_splits(fa) : 0;
     w.wino_dgrad = wino ? wino_fwd_pick_splits(fd) : 0;
-    w.Ud = take(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0);
+    w.Ud = take_or(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0, 0);
     pwino = std::max({pwino, wino_scratch_floats(w.wino_aux, fa), wino_scratch_floats(w.wino_dgrad, fd)});
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;
     if (w.head_fused == 2 && head_pool_partials_applicable(head_shape(a, ad, B))) {
@@ -257,18 +258,14 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
       if (w.pool_fused) w.ksplits_aux = 1;
     }
     w.ppart = take(w.pool_fused ? (size_t)B * ad.Hu * ad.Wu / 16 * 2 * a->A * f : 0);
-    w.part_b = take((size_t)std::max(w.splits_layer, w.wino_wgrad) * d->C_out * f);
+    w.part_b = take_or((size_t)std::max(w.splits_layer, w.wino_wgrad) * d->C_out * f, (size_t)w.splits_layer * d->C_out * f);
     w.part_aux = take(pa * f);
     w.part_b_aux = take((size_t)w.splits_aux * a->A * f);
   }
   // this scratch must not push a step that the static array holds out of it
-  const size_t extra = up(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0);
-  const size_t direct = off - extra + up(pmax * f);
-  const auto pushes_out = [&](size_t floats) {
-    const size_t lim = (size_t)NF_STATIC_SCRATCH_BYTES;
-    return direct <= lim && off + up(std::max(floats, pmax) * f) > lim;
-  };
-  if (wino && pushes_out(pwino)) return ws_layout(d, ld, a, ad, B, false);
+  const size_t lim = (size_t)NF_STATIC_SCRATCH_BYTES;
+  if (wino && least + up(pmax * f) <= lim && off + up(std::max(pmax, pwino) * f) > lim)
+    return ws_layout(d, ld, a, ad, B, false);
   pmax = std::max(pmax, pwino);
   w.part = take(pmax * f);
   w.total = off ? off : ALIGN;

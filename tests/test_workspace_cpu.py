@@ -31,3 +31,31 @@ def test_no_layer_is_pushed_out_of_the_static_scratch(cfg_name):
             d = nf.LayerDesc(**spec.layer_desc_fields())
             a = nf.AuxDesc(**spec.aux_desc_fields(cfg.n_classes))
             assert nf.nf_workspace_bytes(d, a, blk.batch) <= nf.NF_STATIC_SCRATCH_BYTES, (cfg_name, spec.name)
+
+
+def layer(C, H, W, K, A, R, pool, skip, classes):
+    """(layer, head) descriptors; pool 0 / 2 (2x2) / 3 (3x3, stride 2), skip 0 / 1 (identity) / 2 (projection of C/2)."""
+    pk, ps, pp = {0: (0, 0, 0), 2: (2, 2, 0), 3: (3, 2, 1)}[pool]
+    Hp, Wp = ((n + 2 * pp - pk) // ps + 1 if pool else n for n in (H, W))
+    sk = {0: (0, 0, 0, 0), 1: (K, H, W, 1), 2: (C // 2, 2 * H, 2 * W, 2)}[skip]
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=W, C_out=K, R=R, S=R, stride=1, pad=R // 2, pool_kind=int(pool > 0), pool_k=pk,
+                     pool_stride=ps, pool_pad=pp, skip_kind=skip, skip_C=sk[0], skip_H=sk[1], skip_W=sk[2], skip_stride=sk[3])
+    return d, nf.AuxDesc(C_in=K, H_in=Hp, W_in=Wp, A=A, R=3, S=3, pad=1, relu=1, pool_oh=2, pool_ow=2, n_classes=classes)
+
+
+# (layer, batch) whose direct kernels' scratch, the last figure, is just below the static array's size and whose
+# transformed contractions would need more
+NEAR_THE_LIMIT = [
+    ((64, 22, 22, 192, 64, 3, 0, 0, 10), 166, 134197248),
+    ((192, 10, 10, 96, 128, 3, 0, 0, 10), 535, 134217472),
+    ((32, 6, 6, 384, 5, 3, 0, 0, 100), 1839, 134175232),
+    ((64, 4, 4, 512, 8, 3, 0, 1, 200), 2728, 134205440),
+    ((32, 7, 7, 512, 5, 3, 2, 0, 10), 871, 134208256),
+    ((32, 20, 20, 256, 16, 3, 3, 2, 10), 178, 134206208),
+]
+
+
+@pytest.mark.parametrize("shape,B,direct", NEAR_THE_LIMIT)
+def test_what_the_direct_kernels_fit_is_not_pushed_out(shape, B, direct):
+    assert direct <= nf.NF_STATIC_SCRATCH_BYTES
+    assert nf.nf_workspace_bytes(*layer(*shape), B) <= nf.NF_STATIC_SCRATCH_BYTES
