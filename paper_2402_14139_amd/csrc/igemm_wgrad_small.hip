@@ -268,30 +268,43 @@ inline SmallShape small_shape(int P, int C) {
 
 }  // namespace
 
-bool igemm_wgrad_small_applicable(const WgradProblem &p) {
+namespace {
+bool served(const WgradProblem &p) {
   // operands below 1 GiB: the kernel marks "no data" with bit 30 of a byte offset
   const long long lim = 0x3FFFFFF0ll, B = p.M / ((long long)p.Ho * p.Wo);
   if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.Cs != 0) return false;
   // measured: from 32 output channels on the tiled MFMA kernel is faster (no padding left to save)
   if (p.Ho != p.H || p.Wo != p.W || p.P > 16 || p.P % 4 || p.C % 4) return false;
+  return (long long)p.M * p.P * 4 <= lim && B * p.H * p.W * p.C * 4 <= lim;
+}
+// split count (image-row ranges): about two workgroups per CU over all chunks, at least 4 image
+// rows per workgroup (one per wave)
+int small_splits(int P, int C, int rows) {
+  const SmallShape sh = small_shape(P, C);
+  const int chunks = ((C + 64 * sh.V - 1) / (64 * sh.V)) * ((P + 4 * sh.G - 1) / (4 * sh.G));
+  int S = 256 / (chunks > 0 ? chunks : 1);  // one workgroup per CU (measured: 128 and 512 are slower)
+  if (S > rows / 4) S = rows / 4;
+  return S > 1 ? S : 1;
+}
+}  // namespace
+
+bool igemm_wgrad_small_applicable(const WgradProblem &p) {
   // Few pixels times channels: the four waves' sums, a wave's ring and its descriptors cost the same
   // however few pixels there are (18 us for 8192 pixels x 16 channels), and the tiled kernel is done sooner
   // although it pads P to 32 (10 us; 16 384 x 64: 18 / 12).  They meet near 3 million (16 384 x 128: equal; 16 384 x 512
   // in favour of this one by 1.5; measured for P = 4 ... 16, both with their reduction).
-  if ((long long)p.M * p.C < (3ll << 20)) return false;
-  if ((long long)p.M * p.P * 4 > lim || B * p.H * p.W * p.C * 4 > lim) return false;
-  return true;
+  return served(p) && (long long)p.M * p.C >= (3ll << 20);
 }
 
-// split count (image-row ranges): about two workgroups per CU over all chunks, at least 4 image
-// rows per workgroup (one per wave)
-int igemm_wgrad_small_splits(int P, int C, int B, int H) {
-  const SmallShape sh = small_shape(P, C);
-  const int chunks = ((C + 64 * sh.V - 1) / (64 * sh.V)) * ((P + 4 * sh.G - 1) / (4 * sh.G));
-  const int rows = B * H;
-  int S = 256 / (chunks > 0 ? chunks : 1);  // one workgroup per CU (measured: 128 and 512 are slower)
-  if (S > rows / 4) S = rows / 4;
-  return S > 1 ? S : 1;
+// The tiled kernel may want more splits than this one; a workspace sized for this one's holds it with as many
+// (any count is valid for either).
+int wgrad_head_splits(const WgradProblem &p, int *least) {
+  const int tiled = wgrad_pick_splits(p.P, p.Q, p.M);
+  if (!served(p)) return *least = tiled;
+  const int small = small_splits(p.P, p.C, p.M / p.Wo);
+  if (igemm_wgrad_small_applicable(p)) return *least = small;
+  *least = tiled < small ? tiled : small;
+  return tiled;
 }
 
 hipError_t launch_igemm_wgrad_small(const WgradProblem &p0, hipStream_t st, const char **kernel) {

@@ -188,12 +188,13 @@ size_t wino_scratch_floats(int splits, const FwdProblem &f) {
   return wino_fwd_filter_floats(f.N, f.C) + (splits > 1 ? (size_t)splits * f.M * f.N : 0);
 }
 
-// wino = false: without the wino_* kernels and what they need beyond the direct ones
+// wino = false: without the wino_* kernels and what they need beyond the direct ones, and with the fewest
+// splits of the head's weight gradient
 WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B,
                    bool wino = true) {
   WsLayout w;
   std::memset(&w, 0, sizeof(w));
-  size_t off = 0, least = 0;  // least: the same regions as the direct kernels need them
+  size_t off = 0, least = 0;  // least: the same regions with wino = false
   auto take_or = [&](size_t bytes, size_t direct_bytes) {
     const size_t at = off;
     off += up(bytes), least += up(direct_bytes);
@@ -227,16 +228,16 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     const int Qa = a->R * a->S * a->C_in;
     w.Qld_aux = (Qa + 3) / 4 * 4;
     w.Qld_layer = (Kl + 3) / 4 * 4;
-    w.splits_aux = igemm_wgrad_small_applicable(aux_wgrad_shape(a, ad, B))
-                       ? igemm_wgrad_small_splits(a->A, a->C_in, B, a->H_in)
-                       : wgrad_pick_splits(a->A, Qa, B * ad.Hu * ad.Wu);
+    int aux_least = 0;
+    w.splits_aux = wgrad_head_splits(aux_wgrad_shape(a, ad, B), &aux_least);
+    if (!wino) w.splits_aux = aux_least;
     w.splits_layer = wgrad_pick_splits(d->C_out, Kl, B * ld.Ho * ld.Wo);
     w.wino_wgrad = wino ? wino_wgrad_pick_splits(layer_wgrad_shape(d, ld, B)) : 0;
     if (w.wino_wgrad && d->skip_kind == 2) w.proj_splits = wgrad_pick_splits(d->C_out, d->skip_C, B * ld.Ho * ld.Wo);
     pwino = std::max(pwino, (size_t)w.wino_wgrad * d->C_out * (Kl - d->skip_C * (d->skip_kind == 2)) +
                                 (size_t)w.proj_splits * d->C_out * ((d->skip_C + 3) / 4 * 4));
     // split partials of the two weight gradients live side by side: one launch reduces both
-    const size_t pa = (size_t)w.splits_aux * a->A * w.Qld_aux, pl = (size_t)w.splits_layer * d->C_out * w.Qld_layer;
+    const size_t pa = (size_t)a->A * w.Qld_aux, pl = (size_t)w.splits_layer * d->C_out * w.Qld_layer;
     if (pl > pmax) pmax = pl;
     // partials of the aux forward are dead before the backward; those of the data gradient are
     // dead before the layer's weight gradient overwrites them
@@ -259,8 +260,8 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     }
     w.ppart = take(w.pool_fused ? (size_t)B * ad.Hu * ad.Wu / 16 * 2 * a->A * f : 0);
     w.part_b = take_or((size_t)std::max(w.splits_layer, w.wino_wgrad) * d->C_out * f, (size_t)w.splits_layer * d->C_out * f);
-    w.part_aux = take(pa * f);
-    w.part_b_aux = take((size_t)w.splits_aux * a->A * f);
+    w.part_aux = take_or(w.splits_aux * pa * f, aux_least * pa * f);
+    w.part_b_aux = take_or((size_t)w.splits_aux * a->A * f, (size_t)aux_least * a->A * f);
   }
   // this scratch must not push a step that the static array holds out of it
   const size_t lim = (size_t)NF_STATIC_SCRATCH_BYTES;

@@ -120,7 +120,8 @@ hipError_t launch_wino_wgrad(const WgradProblem &p, hipStream_t st);
 // 3x3 / stride 1 / pad 1 with at most 32 output channels (igemm_wgrad_small.hip): 4x4x1 MFMA with a
 // sliding register window; `splits` are ranges of image rows there (any count is valid)
 bool igemm_wgrad_small_applicable(const WgradProblem &p);
-int igemm_wgrad_small_splits(int P, int C, int B, int H);
+// splits of a head's weight gradient, whichever kernel it takes; *least: how many it makes do with
+int wgrad_head_splits(const WgradProblem &p, int *least);
 hipError_t launch_igemm_wgrad_small(const WgradProblem &p, hipStream_t st, const char **kernel);
 // gamma_n's gradient as a job of extra workgroups (head_gamma.h): dWf = dz^T Pq, dbf = column sums of
 // dz, optionally followed by the update of Wf / bf; plus the batch mean of the per-sample losses.

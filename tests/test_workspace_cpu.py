@@ -52,6 +52,10 @@ NEAR_THE_LIMIT = [
     ((64, 4, 4, 512, 8, 3, 0, 1, 200), 2728, 134205440),
     ((32, 7, 7, 512, 5, 3, 2, 0, 10), 871, 134208256),
     ((32, 20, 20, 256, 16, 3, 3, 2, 10), 178, 134206208),
+    # heads of few filters, whose weight gradient takes more splits than it needs
+    ((512, 56, 56, 4, 16, 5, 2, 0, 200), 641, 134208512),
+    ((28, 31, 32, 4, 16, 5, 3, 0, 10), 2319, 134188288),
+    ((32, 59, 59, 4, 12, 3, 2, 0, 200), 850, 134099456),
 ]
 
 
