@@ -130,8 +130,9 @@ int32_t nf_contraction(int32_t mode);
 int32_t nf_layer_out_dims(const nf_layer_desc *d, int32_t *Ho, int32_t *Wo, int32_t *Hp, int32_t *Wp);
 
 /* Bytes of workspace the calls below want for this (layer, head, batch); single-layer calls also take a
- * smaller one that still holds the direct contraction kernels, and run those.  `a` may be NULL
- * when only nf_layer_fwd will be called. */
+ * smaller one that still holds the direct contraction kernels, and run those where the others do not fit.
+ * At most NF_STATIC_SCRATCH_BYTES where that holds the direct kernels.  `a` may be NULL when only
+ * nf_layer_fwd will be called. */
 int32_t nf_workspace_bytes(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B, size_t *out);
 
 /* Where two intermediates of the step live inside the workspace (byte offset and size), for
@@ -202,7 +203,7 @@ int32_t nf_local_step(const nf_layer_desc *d, const nf_aux_desc *a, const nf_sgd
  * allocates nothing (no hipMalloc / hipFree, no allocating library routine).
  * A (layer, head, B) whose nf_workspace_bytes exceeds NF_STATIC_SCRATCH_BYTES is rejected with
  * NF_ERR_SCRATCH_LIMIT before anything is enqueued (a 512-channel 3x3 layer at batch 512 on 4x4
- * maps needs 89 MiB, the largest layer of the VGG-16-style workload 124.6 MiB).
+ * maps needs 89 MiB, the largest layer of the VGG-16-style workload 108 MiB).
  * Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU (two
  * streams, two threads) race; order them on one stream.  The array keeps the previous call's
  * contents, which is harmless: every region is written by the step before it is read.  The

@@ -156,6 +156,17 @@ struct WsLayout {
   // head_fused == 2 only: F_n is formed from column sums left by the aux convolution's epilogue
   // (region ppart), no pooling launch
   int pool_fused;
+  int aux_least;  // how few splits the head's weight gradient makes do with
+  size_t least;   // `total` of the layout that gives up all it can (WsPlan)
+  // floats of scratch in `part` that the direct kernels, and each contraction as planned, need
+  size_t part_direct, part_layer, part_aux_fwd, part_dgrad, part_wgrad;
+};
+
+// What a layout may use.  All of it by default; a workspace too small for that gets a layout that does without some.
+struct WsPlan {
+  bool layer = true, aux = true, dgrad = true;  // wino_fwd for that contraction
+  int wgrad_splits = INT32_MAX;                 // most splits of wino_wgrad (0: the direct kernels)
+  bool aux_least = false;                       // the fewest splits for the head's weight gradient
 };
 
 // data gradient of beta_n: the forward-type contraction of dU with the re-laid filter (pointers left null)
@@ -188,16 +199,14 @@ size_t wino_scratch_floats(int splits, const FwdProblem &f) {
   return wino_fwd_filter_floats(f.N, f.C) + (splits > 1 ? (size_t)splits * f.M * f.N : 0);
 }
 
-// wino = false: without the wino_* kernels and what they need beyond the direct ones, and with the fewest
-// splits of the head's weight gradient
-WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B,
-                   bool wino = true) {
+WsLayout ws_layout_of(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B,
+                      const WsPlan &pl) {
   WsLayout w;
   std::memset(&w, 0, sizeof(w));
-  size_t off = 0, least = 0;  // least: the same regions with wino = false
-  auto take_or = [&](size_t bytes, size_t direct_bytes) {
+  size_t off = 0, least = 0;
+  auto take_or = [&](size_t bytes, size_t least_bytes) {
     const size_t at = off;
-    off += up(bytes), least += up(direct_bytes);
+    off += up(bytes), least += up(least_bytes);
     return at;
   };
   auto take = [&](size_t bytes) { return take_or(bytes, bytes); };
@@ -211,8 +220,8 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
   w.ksplits_layer = igemm_fwd_pick_ksplits(B * ld.Ho * ld.Wo, d->C_out, Kl, d->C_in, d->R * d->S);
   size_t pmax = w.ksplits_layer > 1 ? (size_t)w.ksplits_layer * conv_out : 0;
   const FwdProblem fl = layer_fwd_problem(d, ld, B);
-  w.wino_layer = wino ? wino_fwd_pick_splits(fl) : 0;
-  size_t pwino = wino_scratch_floats(w.wino_layer, fl);
+  w.wino_layer = pl.layer ? wino_fwd_pick_splits(fl) : 0;
+  w.part_layer = wino_scratch_floats(w.wino_layer, fl);
   w.ksplits_aux = w.ksplits_dgrad = 1;
   if (a) {
     const size_t u = (size_t)B * ad.Hu * ad.Wu * a->A;
@@ -228,17 +237,16 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     const int Qa = a->R * a->S * a->C_in;
     w.Qld_aux = (Qa + 3) / 4 * 4;
     w.Qld_layer = (Kl + 3) / 4 * 4;
-    int aux_least = 0;
-    w.splits_aux = wgrad_head_splits(aux_wgrad_shape(a, ad, B), &aux_least);
-    if (!wino) w.splits_aux = aux_least;
+    w.splits_aux = wgrad_head_splits(aux_wgrad_shape(a, ad, B), &w.aux_least);
+    if (pl.aux_least) w.splits_aux = w.aux_least;
     w.splits_layer = wgrad_pick_splits(d->C_out, Kl, B * ld.Ho * ld.Wo);
-    w.wino_wgrad = wino ? wino_wgrad_pick_splits(layer_wgrad_shape(d, ld, B)) : 0;
+    w.wino_wgrad = wino_wgrad_pick_splits(layer_wgrad_shape(d, ld, B), pl.wgrad_splits);
     if (w.wino_wgrad && d->skip_kind == 2) w.proj_splits = wgrad_pick_splits(d->C_out, d->skip_C, B * ld.Ho * ld.Wo);
-    pwino = std::max(pwino, (size_t)w.wino_wgrad * d->C_out * (Kl - d->skip_C * (d->skip_kind == 2)) +
-                                (size_t)w.proj_splits * d->C_out * ((d->skip_C + 3) / 4 * 4));
+    w.part_wgrad = (size_t)w.wino_wgrad * d->C_out * (Kl - d->skip_C * (d->skip_kind == 2)) +
+                   (size_t)w.proj_splits * d->C_out * ((d->skip_C + 3) / 4 * 4);
     // split partials of the two weight gradients live side by side: one launch reduces both
-    const size_t pa = (size_t)a->A * w.Qld_aux, pl = (size_t)w.splits_layer * d->C_out * w.Qld_layer;
-    if (pl > pmax) pmax = pl;
+    const size_t pa = (size_t)a->A * w.Qld_aux, pw = (size_t)w.splits_layer * d->C_out * w.Qld_layer;
+    if (pw > pmax) pmax = pw;
     // partials of the aux forward are dead before the backward; those of the data gradient are
     // dead before the layer's weight gradient overwrites them
     w.ksplits_aux = igemm_fwd_pick_ksplits(B * ad.Hu * ad.Wu, a->A, Qa, a->C_in, a->R * a->S);
@@ -246,10 +254,10 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     w.ksplits_dgrad = igemm_fwd_pick_ksplits(B * a->H_in * a->W_in, a->C_in, a->R * a->S * a->A, a->A, a->R * a->S);
     if (w.ksplits_dgrad > 1 && (size_t)w.ksplits_dgrad * emitted > pmax) pmax = (size_t)w.ksplits_dgrad * emitted;
     const FwdProblem fa = aux_fwd_problem(a, ad, B), fd = dgrad_problem(a, ad, B);
-    w.wino_aux = wino ? wino_fwd_pick_splits(fa) : 0;
-    w.wino_dgrad = wino ? wino_fwd_pick_splits(fd) : 0;
+    w.wino_aux = pl.aux ? wino_fwd_pick_splits(fa) : 0;
+    w.wino_dgrad = pl.dgrad ? wino_fwd_pick_splits(fd) : 0;
     w.Ud = take_or(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0, 0);
-    pwino = std::max({pwino, wino_scratch_floats(w.wino_aux, fa), wino_scratch_floats(w.wino_dgrad, fd)});
+    w.part_aux_fwd = wino_scratch_floats(w.wino_aux, fa), w.part_dgrad = wino_scratch_floats(w.wino_dgrad, fd);
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;
     if (w.head_fused == 2 && head_pool_partials_applicable(head_shape(a, ad, B))) {
       // (a reduction split in two gives way: the pooling launch it would need costs more than it gains)
@@ -260,25 +268,47 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
     }
     w.ppart = take(w.pool_fused ? (size_t)B * ad.Hu * ad.Wu / 16 * 2 * a->A * f : 0);
     w.part_b = take_or((size_t)std::max(w.splits_layer, w.wino_wgrad) * d->C_out * f, (size_t)w.splits_layer * d->C_out * f);
-    w.part_aux = take_or(w.splits_aux * pa * f, aux_least * pa * f);
-    w.part_b_aux = take_or((size_t)w.splits_aux * a->A * f, (size_t)aux_least * a->A * f);
+    w.part_aux = take_or(w.splits_aux * pa * f, w.aux_least * pa * f);
+    w.part_b_aux = take_or((size_t)w.splits_aux * a->A * f, (size_t)w.aux_least * a->A * f);
   }
-  // this scratch must not push a step that the static array holds out of it
-  const size_t lim = (size_t)NF_STATIC_SCRATCH_BYTES;
-  if (wino && least + up(pmax * f) <= lim && off + up(std::max(pmax, pwino) * f) > lim)
-    return ws_layout(d, ld, a, ad, B, false);
-  pmax = std::max(pmax, pwino);
-  w.part = take(pmax * f);
+  w.part_direct = pmax, w.least = std::max(least + up(pmax * f), ALIGN);
+  w.part = take(std::max({pmax, w.part_layer, w.part_aux_fwd, w.part_dgrad, w.part_wgrad}) * f);
   w.total = off ? off : ALIGN;
   return w;
 }
 
-// the layout a call uses in a workspace of `have` bytes: one that only holds the direct kernels (the
-// regions that one call leaves for the next lie the same) runs those
-WsLayout ws_layout_in(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B,
-                      size_t have) {
-  const WsLayout w = ws_layout(d, ld, a, ad, B);
-  return have < w.total ? ws_layout(d, ld, a, ad, B, false) : w;
+// What a layout that is too large does without next: of the contractions that share `part` the one that needs most
+// of it (the weight gradient takes fewer splits first, then all go back to the direct kernels), then what has a
+// region of its own.  False: nothing is left to give up.
+bool give_up(WsPlan *pl, const WsLayout &w) {
+  const size_t m = std::max({w.part_layer, w.part_aux_fwd, w.part_dgrad, w.part_wgrad});
+  if (m > w.part_direct) {
+    if (w.part_wgrad == m) pl->wgrad_splits = w.wino_wgrad - 1;
+    else if (w.part_layer == m) pl->layer = false;
+    else if (w.part_aux_fwd == m) pl->aux = false;
+    else pl->dgrad = false;
+  } else if (w.splits_aux > w.aux_least) {
+    pl->aux_least = true;
+  } else if (w.wino_dgrad) {
+    pl->dgrad = false;
+  } else if (w.wino_wgrad) {
+    pl->wgrad_splits = w.wino_wgrad - 1;
+  } else {
+    return false;
+  }
+  return true;
+}
+
+// The layout a call uses in a workspace of `have` bytes (by default what it wants).  A step that the static array
+// could hold is never planned past its size, and a smaller workspace that holds the direct kernels is enough: either
+// gives up what does not fit and no more.  (The regions that one call leaves for the next lie the same in all layouts.)
+WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *a, const AuxDims &ad, int B,
+                   size_t have = SIZE_MAX) {
+  WsPlan pl;
+  WsLayout w = ws_layout_of(d, ld, a, ad, B, pl);
+  const size_t lim = w.least <= (size_t)NF_STATIC_SCRATCH_BYTES ? std::min(have, (size_t)NF_STATIC_SCRATCH_BYTES) : have;
+  while (w.total > lim && give_up(&pl, w)) w = ws_layout_of(d, ld, a, ad, B, pl);
+  return w;
 }
 
 int32_t check_ws(const void *ws, size_t have, size_t need) {
@@ -748,7 +778,7 @@ int32_t local_step_impl(const nf_layer_desc *d, const nf_aux_desc *a, const nf_s
     if ((rc = check_aux_ptrs(va))) return rc;
   }
   if (!aligned16(y_out)) return NF_ERR_BAD_DESC;
-  const WsLayout w = use_static ? ws_layout(d, ld, a, ad, B) : ws_layout_in(d, ld, a, ad, B, ws_bytes);
+  const WsLayout w = use_static ? ws_layout(d, ld, a, ad, B) : ws_layout(d, ld, a, ad, B, ws_bytes);
   if (use_static) {
     if (w.total > (size_t)NF_STATIC_SCRATCH_BYTES) return NF_ERR_SCRATCH_LIMIT;
     if ((rc = static_scratch(&ws))) return rc;
@@ -775,7 +805,7 @@ int32_t workspace_least_bytes(const nf_layer_desc *d, const nf_aux_desc *a, int3
   int32_t rc = check_layer(d, &ld);
   if (!rc) rc = check_sizes(d, ld, B);
   if (!rc && a) rc = check_aux(a, &ad);
-  if (!rc) *out = std::min(ws_layout(d, ld, a, ad, B).total, ws_layout(d, ld, a, ad, B, false).total);
+  if (!rc) *out = ws_layout_of(d, ld, a, ad, B, WsPlan()).least;
   return rc;
 }
 }  // namespace nf
@@ -872,7 +902,7 @@ int32_t nf_layer_fwd(const nf_layer_desc *d, int32_t B, const float *x, const fl
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
   // the layout with a head is a superset that starts with the same regions, so a workspace
   // sized for the full step is accepted as well
-  const WsLayout w = ws_layout_in(d, ld, nullptr, ad, B, ws_bytes);
+  const WsLayout w = ws_layout(d, ld, nullptr, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
   return run_layer_fwd(d, ld, B, x, x_skip, p, y, ws, w, static_cast<hipStream_t>(stream));
 }
@@ -890,7 +920,7 @@ int32_t nf_aux_fwd_loss(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B,
   if (!y || !labels || !loss_out) return NF_ERR_NULL;
   if ((rc = check_aux_ptrs(ap))) return rc;
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout_in(d, ld, a, ad, B, ws_bytes);
+  const WsLayout w = ws_layout(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
   return run_aux_fwd(a, ad, B, y, labels, ap, loss_out, ws, w, static_cast<hipStream_t>(stream));
 }
@@ -909,7 +939,7 @@ int32_t nf_aux_predict(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B, 
   if ((labels == nullptr) != (n_correct == nullptr)) return NF_ERR_NULL;
   if ((rc = check_aux_ptrs(ap))) return rc;
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout_in(d, ld, a, ad, B, ws_bytes);
+  const WsLayout w = ws_layout(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = run_aux_features(a, ad, B, y, ap, ws, w, st))) return rc;
@@ -939,7 +969,7 @@ int32_t nf_local_bwd_wgrad(const nf_layer_desc *d, const nf_aux_desc *a, int32_t
   if ((rc = check_aux_ptrs(ga))) return rc;
   if (!y) return NF_ERR_NULL;
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout_in(d, ld, a, ad, B, ws_bytes);
+  const WsLayout w = ws_layout(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
   return run_bwd(d, ld, a, ad, B, x, x_skip, y, p, ap, gp, ga, nullptr, nullptr, nullptr, nullptr, ws, w,
                  static_cast<hipStream_t>(stream));

@@ -112,9 +112,9 @@ bool igemm_wgrad_split_applicable(const WgradProblem &p);
 hipError_t launch_igemm_wgrad_split(const WgradProblem &p, bool nine, hipStream_t st, const char **kernel);
 // 3x3 / stride 1 / pad 1 through F(3x3, 2x2) in fp32 (wino_wgrad.hip); `splits` are ranges of 2x2 output
 // tiles there (any count is valid), m_per_split is not read
-// 0: not served or the direct kernel is faster; else the number of splits.  Of a problem with
-// projection columns it forms the first RSC: Qld is theirs then
-int wino_wgrad_pick_splits(const WgradProblem &p);
+// 0: not served or the direct kernel is faster; else the number of splits, at most `most`.  Of a problem
+// with projection columns it forms the first RSC: Qld is theirs then
+int wino_wgrad_pick_splits(const WgradProblem &p, int most);
 bool wino_wgrad_beats_split(const WgradProblem &p, int splits);
 hipError_t launch_wino_wgrad(const WgradProblem &p, hipStream_t st);
 // 3x3 / stride 1 / pad 1 with at most 32 output channels (igemm_wgrad_small.hip): 4x4x1 MFMA with a

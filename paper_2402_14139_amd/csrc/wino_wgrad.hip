@@ -364,14 +364,14 @@ double wide_us(const WgradProblem &p, double rate) {
 }
 }  // namespace
 
-int wino_wgrad_pick_splits(const WgradProblem &p) {
+int wino_wgrad_pick_splits(const WgradProblem &p, int most) {
   if (p.P <= 32 || p.M < 8192 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
   const long long T = num_tiles(p), blocks = blocks_of(p);
   double best = 0.0;
   int splits = 0;
   for (int wgs = 256; wgs <= 1024; wgs *= 2) {
     const int s = (int)((wgs + blocks - 1) / blocks);
-    if (s > 1 && T / s < 16) break;
+    if (s > most || (s > 1 && T / s < 16)) break;
     const double us = wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;
   }
@@ -380,7 +380,7 @@ int wino_wgrad_pick_splits(const WgradProblem &p) {
   const double direct = p.P > 64 && !igemm_wgrad_tile64(p.P, p.Q, sd)
                             ? wide_us(p, 118e6)
                             : 8.0 + 2.0 * p.M * p64 * q64 / 104e6 + reduce_us(p, sd);
-  return best < 0.95 * direct ? splits : 0;
+  return splits && best < 0.95 * direct ? splits : 0;
 }
 
 // The split-operand kernel (six piece products) reaches 185 TFLOP/s.  Kernel alone, us (it / this): 512 -> 512

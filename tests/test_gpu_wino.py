@@ -275,3 +275,39 @@ def test_a_workspace_for_the_direct_kernels_alone_is_enough():
         assert "wino_fwd" in names[0] and "wino_fwd" not in names[1], names
     # 576-term sums in two orders: a few 1e-7 of the largest value
     assert np.abs(ys[0] - ys[1]).max() <= 5e-6 * np.abs(ys[0]).max()
+
+
+def test_workspaces_between_the_least_and_the_full_plan():
+    """Each gives up what does not fit and no more, and all give the same gradients to rounding.  (Wanted
+    here: 122 MB, as much as lets the step stay in the static array; the direct kernels need 111 MB.)"""
+    B, H, C, A, cls = 176, 32, 64, 32, 100
+    g = torch.Generator(device="cuda").manual_seed(14)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=C, R=3, S=3, stride=1, pad=1)
+    # no ReLU in the head and a given activation: no decision that rounding could turn
+    a = nf.AuxDesc(C_in=C, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=0, pool_oh=2, pool_ow=2, n_classes=cls)
+    x, y = rn(B, H, H, C).relu(), rn(B, H, H, C).relu()
+    labels = torch.randint(0, cls, (B,), generator=g, device="cuda", dtype=torch.int32)
+    p = [rn(C, 3, 3, C) * 0.06, rn(C), rn(A, 3, 3, C) * 0.06, rn(A), rn(cls, 4 * A) * 0.2, rn(cls)]
+    lp, ap, loss = nf.layer_params(p[0], p[1], None), nf.aux_params(*p[2:]), torch.zeros(1, device="cuda")
+    want = nf.nf_workspace_bytes(d, a, B)
+    names, grads = [], []
+    for nbytes in (want, want - 256, 111600000 // 256 * 256, 111288576, 111288576 - 256):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        gr = [torch.zeros_like(t) for t in p]
+        if nbytes < 111288576:
+            with pytest.raises(Exception, match="workspace"):
+                nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, loss, ws)
+            break
+        nf.nf_prof_begin()
+        nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, loss, ws)
+        nf.nf_local_bwd_wgrad(d, a, B, x, None, y, lp, ap, nf.layer_params(gr[0], gr[1], None), nf.aux_params(*gr[2:]), ws)
+        names.append({r["kernel"] for r in nf.nf_prof_end()})
+        grads.append([t.double() for t in gr])
+    if nf.nf_contraction() == nf.NF_CONTRACT_F32:
+        assert [[k in n for k in ("wino_wgrad", "wino_fwd")] for n in names] == [[True, True], [False, True], [False, True],
+                                                                                [False, False]], names
+    for other in grads[1:]:
+        for u, v in zip(grads[0], other):
+            # sums of 180 224 products in other orders: some 1e-7 of the norm each
+            assert (u - v).norm() <= 2e-6 * u.norm()

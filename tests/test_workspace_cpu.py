@@ -63,3 +63,18 @@ NEAR_THE_LIMIT = [
 def test_what_the_direct_kernels_fit_is_not_pushed_out(shape, B, direct):
     assert direct <= nf.NF_STATIC_SCRATCH_BYTES
     assert nf.nf_workspace_bytes(*layer(*shape), B) <= nf.NF_STATIC_SCRATCH_BYTES
+
+
+# (layer, batch) whose full plan is larger than the static array: what fits of it stays (the last figure: the
+# scratch of the direct kernels)
+BETWEEN = [
+    ((64, 56, 56, 64, 32, 3, 0, 0, 100), 64, 118730752),
+    ((64, 32, 32, 64, 32, 3, 0, 0, 100), 176, 111288576),
+    ((64, 32, 32, 64, 32, 3, 0, 0, 100), 216, 132972800),
+    ((64, 32, 32, 64, 64, 3, 0, 0, 100), 128, 117668352),
+]
+
+
+@pytest.mark.parametrize("shape,B,direct", BETWEEN)
+def test_a_plan_that_does_not_fit_gives_up_a_part(shape, B, direct):
+    assert direct < nf.nf_workspace_bytes(*layer(*shape), B) <= nf.NF_STATIC_SCRATCH_BYTES
