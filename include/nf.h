@@ -242,7 +242,8 @@ typedef struct {
 } nf_block;
 
 /* Workspace of the two block calls at batch size B: two input batches (double buffer), every
- * layer's emitted batch, and the largest single-layer workspace. */
+ * layer's emitted batch, and the largest single-layer workspace.  It serves smaller batches too, also where
+ * those would ask for more (the kernels planned for them want more scratch; they take those that fit). */
 int32_t nf_block_workspace_bytes(const nf_block *blk, int32_t B, size_t *out);
 
 /* One pass of the block over n_items cached samples in batches of B (the last one may be

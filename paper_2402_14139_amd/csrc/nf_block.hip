@@ -35,7 +35,7 @@ struct BlockPlan {
   std::vector<size_t> y_off;  // emitted batch of every layer
   std::vector<int64_t> y_elems;
   size_t xin_off[2], lab_off[2];
-  size_t layer_ws_off, layer_ws_bytes;
+  size_t layer_ws_off, layer_ws_bytes, layer_ws_least;  // (the least: what every layer accepts)
   size_t total;
   int64_t se_in, se_out;
 };
@@ -55,7 +55,7 @@ int32_t plan_block(const nf_block *blk, int32_t B, int32_t B_last, PlanMode mode
   const int n = blk->n_layers;
   pl->y_off.assign(n, 0);
   pl->y_elems.assign(n, 0);
-  size_t off = 0, lws = 0;
+  size_t off = 0, lws = 0, lws_least = 0;
   const nf_layer_desc &d0 = blk->layers[0];
   pl->se_in = (int64_t)d0.C_in * d0.H_in * d0.W_in;
   if (pl->se_in <= 0) return NF_ERR_BAD_DESC;
@@ -69,12 +69,12 @@ int32_t plan_block(const nf_block *blk, int32_t B, int32_t B_last, PlanMode mode
     int32_t Hp = 0, Wp = 0;
     int32_t rc = nf_layer_out_dims(d, nullptr, nullptr, &Hp, &Wp);
     if (rc) return rc;
-    size_t need = 0, need_last = 0;
+    size_t need = 0, least = 0, least_last = 0;
     if ((rc = nf_workspace_bytes(d, a, B, &need))) return rc;
+    if ((rc = nf::workspace_least_bytes(d, a, B, &least))) return rc;
     // a partial last batch makes do with what the full ones get, if that holds its direct kernels
-    if ((rc = nf_workspace_bytes(d, a, B_last, &need_last))) return rc;
-    if (need_last > need && (rc = nf::workspace_least_bytes(d, a, B_last, &need_last))) return rc;
-    lws = std::max(lws, std::max(need, need_last));
+    if ((rc = nf::workspace_least_bytes(d, a, B_last, &least_last))) return rc;
+    lws = std::max({lws, need, least_last}), lws_least = std::max({lws_least, least, least_last});
     if (l > 0) {
       const nf_layer_desc &q = blk->layers[l - 1];
       int32_t qh = 0, qw = 0;
@@ -109,9 +109,25 @@ int32_t plan_block(const nf_block *blk, int32_t B, int32_t B_last, PlanMode mode
     pl->y_off[l] = off, off += up((size_t)B * pl->y_elems[l] * sizeof(float));
   }
   pl->se_out = pl->y_elems[n - 1];
-  pl->layer_ws_off = off, pl->layer_ws_bytes = lws, off += up(lws);
+  pl->layer_ws_off = off, pl->layer_ws_bytes = lws, pl->layer_ws_least = lws_least, off += up(lws);
   pl->total = off;
   return NF_OK;
+}
+
+// The plan for a workspace of `have` bytes.  What a layer wants depends on the kernels planned for the batch and does
+// not only grow with it; a workspace of the size that a larger batch asks for is enough all the same: the layers get
+// what it holds of their scratch.
+int32_t plan_block_in(const nf_block *blk, int32_t B, int32_t B_last, PlanMode mode, size_t have, BlockPlan *pl) {
+  const int32_t rc = plan_block(blk, B, B_last, mode, pl);
+  if (rc || have >= pl->total || have < pl->layer_ws_off + up(pl->layer_ws_least)) return rc;
+  BlockPlan q;
+  for (int32_t b = B + 1; plan_block(blk, b, b, mode, &q) == NF_OK && q.layer_ws_off <= have; ++b)
+    if (q.total <= have) {
+      pl->layer_ws_bytes = (have - pl->layer_ws_off) / ALIGN * ALIGN;
+      pl->total = pl->layer_ws_off + pl->layer_ws_bytes;
+      break;
+    }
+  return rc;
 }
 
 inline float *at(void *ws, size_t off) { return reinterpret_cast<float *>(static_cast<char *>(ws) + off); }
@@ -171,7 +187,7 @@ int32_t nf_block_train_epoch(const nf_block *blk, const nf_sgd_desc *s, int32_t 
   const int64_t n_batches = (n_items + B - 1) / B;
   const int32_t B_last = (int32_t)(n_items - (n_batches - 1) * B);
   BlockPlan pl;
-  int32_t rc = plan_block(blk, B, B_last, PLAN_TRAIN, &pl);
+  int32_t rc = plan_block_in(blk, B, B_last, PLAN_TRAIN, ws_bytes, &pl);
   if (rc) return rc;
   if (s->momentum != 0.f) {
     if (!blk->vp || !blk->va) return NF_ERR_NULL;
@@ -301,7 +317,7 @@ int32_t nf_block_fill_cache(const nf_block *blk, int32_t B, int64_t n_items, con
   const int64_t n_batches = (n_items + B - 1) / B;
   const int32_t B_last = (int32_t)(n_items - (n_batches - 1) * B);
   BlockPlan pl;
-  int32_t rc = plan_block(blk, B, B_last, PLAN_FWD, &pl);
+  int32_t rc = plan_block_in(blk, B, B_last, PLAN_FWD, ws_bytes, &pl);
   if (rc) return rc;
   if (!aligned16(cache_in) || !aligned16(cache_out)) return NF_ERR_BAD_DESC;
   if (!ws || (reinterpret_cast<uintptr_t>(ws) & (ALIGN - 1)) || ws_bytes < pl.total) return NF_ERR_WORKSPACE;
@@ -337,7 +353,7 @@ int32_t nf_block_evaluate(const nf_block *blk, int32_t exit_layer, int32_t B, in
   const int64_t n_batches = (n_items + B - 1) / B;
   const int32_t B_last = (int32_t)(n_items - (n_batches - 1) * B);
   BlockPlan pl;
-  int32_t rc = plan_block(blk, B, B_last, PLAN_EVAL, &pl);
+  int32_t rc = plan_block_in(blk, B, B_last, PLAN_EVAL, ws_bytes, &pl);
   if (rc) return rc;
   if (!aligned16(cache)) return NF_ERR_BAD_DESC;
   if (!ws || (reinterpret_cast<uintptr_t>(ws) & (ALIGN - 1)) || ws_bytes < pl.total) return NF_ERR_WORKSPACE;

@@ -469,3 +469,24 @@ def test_block_graph_keeps_the_contraction_mode_of_its_creation():
         nf.nf_contraction(start)
         for h, _, _ in graphs.values():
             nf.nf_block_graph_destroy(h)
+
+
+def test_a_workspace_sized_for_a_larger_batch_serves_a_smaller_one():
+    """What a layer wants does not only grow with the batch: here 69 MiB at 90 samples, 56 at 104.  A pass over
+    batches of 90 in the block workspace of 104 takes the kernels that fit there."""
+    spec, cls, B, B_ws = workloads.LayerSpec("l0", 32, 32, 32, 64, A=8), 10, 90, 104
+    X, lab, _, params = _gen([spec], cls, B, 51)
+    x, labels = torch.from_numpy(layout.act_to_lib(X)).cuda(), torch.from_numpy(lab).cuda()
+    res, want = [], {}
+    for b in (B, B_ws):
+        blk = GpuBlock([spec], [-1], cls, params, b, False)
+        want[b] = blk.ws.numel()
+        before, losses = blk.state(), torch.zeros(1, 1, device="cuda")
+        nf.nf_block_train_epoch(blk.blk, 0.05, 0.0, B, B, x, labels, B, None, losses, blk.ws)
+        res.append((losses, [u - v for u, v in zip(blk.state(), before)]))
+    if nf.nf_contraction() == nf.NF_CONTRACT_F32:
+        assert want[B_ws] < want[B]
+    assert (res[0][0] - res[1][0]).abs().max() <= 1e-5 * res[0][0].abs().max()
+    for u, v in zip(res[0][1], res[1][1]):
+        # the update of each tensor; a rectified value that is a tie may fall either way (1e-4 of a gradient)
+        assert (u - v).norm() <= 1e-3 * u.norm()
