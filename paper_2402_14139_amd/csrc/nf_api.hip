@@ -307,7 +307,13 @@ WsLayout ws_layout(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_des
   WsPlan pl;
   WsLayout w = ws_layout_of(d, ld, a, ad, B, pl);
   const size_t lim = w.least <= (size_t)NF_STATIC_SCRATCH_BYTES ? std::min(have, (size_t)NF_STATIC_SCRATCH_BYTES) : have;
-  while (w.total > lim && give_up(&pl, w)) w = ws_layout_of(d, ld, a, ad, B, pl);
+  // the partial sums of wino_wgrad at most double a layer's scratch: memory is what the method is there to save (512 ->
+  // 64 channels, 16x16, batch 39, projection: 44.3 MiB and 161 us a step with them, 15.2 and 169 without; 33x33, batch 9:
+  // 39.4 and 144, half of the splits 21.4 and 147.5; 384 -> 60, 20x20, batch 27: 44.8 and 157, without 22.2 and 145)
+  const auto swollen = [&] {
+    return w.part_wgrad > std::max({w.part_direct, w.part_layer, w.part_aux_fwd, w.part_dgrad}) && w.total > 2 * w.least;
+  };
+  while ((w.total > lim || swollen()) && give_up(&pl, w)) w = ws_layout_of(d, ld, a, ad, B, pl);
   return w;
 }
 

@@ -78,3 +78,11 @@ BETWEEN = [
 @pytest.mark.parametrize("shape,B,direct", BETWEEN)
 def test_a_plan_that_does_not_fit_gives_up_a_part(shape, B, direct):
     assert direct < nf.nf_workspace_bytes(*layer(*shape), B) <= nf.NF_STATIC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("shape,B,direct", [((512, 16, 16, 64, 4, 3, 0, 2, 10), 39, 11084544),
+                                            ((384, 6, 6, 60, 5, 3, 0, 2, 100), 380, 12166144),
+                                            ((512, 33, 33, 64, 4, 3, 0, 0, 10), 9, 11777024)])
+def test_scratch_at_most_doubles(shape, B, direct):
+    """Partial sums of the transformed weight gradient against what the direct kernels need."""
+    assert nf.nf_workspace_bytes(*layer(*shape), B) <= 2 * direct
