@@ -291,9 +291,13 @@ int small_splits(int P, int C, int rows) {
 bool igemm_wgrad_small_applicable(const WgradProblem &p) {
   // Few pixels times channels: the four waves' sums, a wave's ring and its descriptors cost the same
   // however few pixels there are (18 us for 8192 pixels x 16 channels), and the tiled kernel is done sooner
-  // although it pads P to 32 (10 us; 16 384 x 64: 18 / 12).  They meet near 3 million (16 384 x 128: equal; 16 384 x 512
-  // in favour of this one by 1.5; measured for P = 4 ... 16, both with their reduction).
-  return served(p) && (long long)p.M * p.C >= (3ll << 20);
+  // although it pads P to 32 (10 us).  Where they meet depends on how well this one fills its lanes: with up to 8 filters
+  // and 128 channels or more it gives a lane several channels (us with the reduction, this / tiled: 13 568 pixels x
+  // 200 channels, 8 filters 29.1 / 33.4; 5696 x 256 25.7 / 23.3), otherwise a wave takes 64 channels (32 768 x 64, 16 filters
+  // 35.4 / 35.8; 22 784 x 64 34.9 / 28.7), padded where they are not a multiple of 64 (28 392 x 96, 12 filters 42.6 / 39.1;
+  // 16 384 x 136 36.3 / 32.3; both equal near 3 million).
+  const long long line = p.P <= 8 && p.C >= 128 ? 1300000 : p.C % 64 == 0 ? 1700000 : 3ll << 20;
+  return served(p) && (long long)p.M * p.C >= line;
 }
 
 // The tiled kernel may want more splits than this one; a workspace sized for this one's holds it with as many

@@ -27,3 +27,24 @@ def test_narrow_heads_match_oracle(name):
     got = {r["kernel"] for r in nf.nf_prof_end()}
     G.check_step_results(name, out, final)
     assert kernel in got, got
+
+
+# The line lies lower where the 4x4x1 kernel fills its lanes (few filters beside 128 channels or more) or its waves (64s)
+LOWER_CASES = {
+    "a8_c200_above": (S(8, 8, 8, 200, 8), 102, "wgrad_small_4x4"),
+    "a8_c200_below": (S(8, 8, 8, 200, 8), 101, "igemm_wgrad_fast_32x128"),
+    "a16_c64_above": (S(8, 16, 16, 64, 16), 104, "wgrad_small_4x4"),
+    "a16_c64_below_1_7m": (S(8, 16, 16, 64, 16), 103, "igemm_wgrad_fast_32x128"),
+    "a12_c100": (S(8, 13, 11, 100, 12), 130, "igemm_wgrad_fast_32x128"),
+}
+
+
+@pytest.mark.parametrize("name", list(LOWER_CASES))
+def test_the_line_where_the_lanes_are_full(name):
+    spec, B, kernel = LOWER_CASES[name]
+    print(f"case {name}: B={B}", flush=True)
+    nf.nf_prof_begin()
+    out, final = G.run_step_both(spec, 10, B, seed=321, lr=0.05, mu=0.9, steps=1)
+    got = {r["kernel"] for r in nf.nf_prof_end()}
+    G.check_step_results(name, out, final)
+    assert kernel in got, got
