@@ -35,7 +35,9 @@ LOWER_CASES = {
     "a8_c200_below": (S(8, 8, 8, 200, 8), 101, "igemm_wgrad_fast_32x128"),
     "a16_c64_above": (S(8, 16, 16, 64, 16), 104, "wgrad_small_4x4"),
     "a16_c64_below_1_7m": (S(8, 16, 16, 64, 16), 103, "igemm_wgrad_fast_32x128"),
+    # the tiled kernel with splits of at most 192 rows: the last one short, and nearly as many as the other kernel's
     "a12_c100": (S(8, 13, 11, 100, 12), 130, "igemm_wgrad_fast_32x128"),
+    "a4_c36_many_splits": (S(8, 16, 16, 36, 4), 320, "igemm_wgrad_fast_32x128"),
 }
 
 
