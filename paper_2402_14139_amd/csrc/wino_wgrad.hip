@@ -28,6 +28,8 @@
 //
 // A value that is not finite makes NaN of neighbours that the direct sum would leave finite or
 // infinite: a workgroup that finds one among its results forms them again by the direct sum.
+#include <cmath>
+
 #include "nf_internal.h"
 
 namespace nf {
@@ -340,7 +342,8 @@ int tiles_per_split(long long T, int splits) { return (int)(((T + splits - 1) / 
 // with the reading of its partial sums) and the smaller one wins.  Examples (us, direct / this, kernel +
 // reduction): 512 -> 512 channels, 8192 pixels 328 + 19 / 216 + 17; 256 -> 256, 16 384 pixels 172 + 17 / 115 + 18;
 // 128 -> 128, 16 384 pixels 55 + 14 / 40 + 14; 64 -> 64, 65 536 pixels 53 + 11 / 36 + 11; 16 384 pixels 20 + 10 / 22 + 12
-// (direct).  Left to the direct kernel whatever the time: up to 32 filters (half the tile would be
+// (direct).  (On 220 random shapes of 4 ... 512 channels it was chosen 118 times, 0.75 of the direct time on average, and
+// once by mistake, 3 % slower; the 128x128 kernel is up to a tenth faster than its estimate, hence its larger margin.)  Left to the direct kernel whatever the time: up to 32 filters (half the tile would be
 // padding); fewer than 8192 pixels and maps narrower than 4, where the direct sums are short and the
 // transforms' own rounding would make this the less accurate one (relative error against 64 bits,
 // direct / this: 256 channels, 4x4 maps, 4096 pixels 0.85e-7 / 0.93e-7, 2x2 maps 0.9e-7 / 1.8e-7; at 8192 and more
@@ -353,8 +356,9 @@ long long blocks_of(const WgradProblem &p) { return (long long)((p.C + QB - 1) /
 double wino_us(const WgradProblem &p, int s) {
   const double w = (double)blocks_of(p) * s;
   const double proj = p.Cs ? 10.0 + 2.0 * p.M * p.P * p.Cs / 90e6 : 0.0;
-  return 11.0 + tiles_per_split(num_tiles(p), s) / KT * (w <= 256 ? 1.0 : w <= 512 ? 1.54 : 1.54 * w / 512) +
-         reduce_us(p, s) + proj;
+  const double full = std::floor(w / 512), rest = w - 512 * full;  // rounds of two workgroups per CU
+  const double rounds = 1.54 * full + (rest > 256 ? 1.54 : rest > 0 ? 1.0 : 0.0);
+  return 11.0 + tiles_per_split(num_tiles(p), s) / KT * rounds + reduce_us(p, s) + proj;
 }
 // a direct kernel of 128x128 tiles: its padded contraction at the rate it reaches (flops per us), plus
 // ramp-up and drain
@@ -370,17 +374,17 @@ int wino_wgrad_pick_splits(const WgradProblem &p, int most) {
   double best = 0.0;
   int splits = 0;
   for (int wgs = 256; wgs <= 1024; wgs *= 2) {
-    const int s = (int)((wgs + blocks - 1) / blocks);
+    // (rounded down: 516 workgroups for 512 places take a second round of the chip)
+    const int s = (int)(wgs > blocks ? wgs / blocks : 1);
     if (s > most || (s > 1 && T / s < 16)) break;
     const double us = wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;
   }
   const int sd = wgrad_pick_splits(p.P, p.Q, p.M);
   const double p64 = (p.P + 63) / 64 * 64.0, q64 = (p.Q + 63) / 64 * 64.0;
-  const double direct = p.P > 64 && !igemm_wgrad_tile64(p.P, p.Q, sd)
-                            ? wide_us(p, 118e6)
-                            : 8.0 + 2.0 * p.M * p64 * q64 / 104e6 + reduce_us(p, sd);
-  return splits && best < 0.95 * direct ? splits : 0;
+  const bool wide = p.P > 64 && !igemm_wgrad_tile64(p.P, p.Q, sd);
+  const double direct = wide ? wide_us(p, 118e6) : 8.0 + 2.0 * p.M * p64 * q64 / 104e6 + reduce_us(p, sd);
+  return splits && best < (wide ? 0.95 : 0.975) * direct ? splits : 0;
 }
 
 // The split-operand kernel (six piece products) reaches 185 TFLOP/s.  Kernel alone, us (it / this): 512 -> 512

@@ -86,3 +86,12 @@ def test_a_plan_that_does_not_fit_gives_up_a_part(shape, B, direct):
 def test_scratch_at_most_doubles(shape, B, direct):
     """Partial sums of the transformed weight gradient against what the direct kernels need."""
     assert nf.nf_workspace_bytes(*layer(*shape), B) <= 2 * direct
+
+
+@pytest.mark.parametrize("shape,B,planned", [((180, 34, 34, 128, 4, 3, 0, 0, 10), 62, 78599936),
+                                             ((336, 13, 13, 128, 4, 3, 0, 0, 10), 52, 41464320),
+                                             ((72, 21, 21, 48, 4, 3, 0, 0, 10), 167, 39490304)])
+def test_splits_of_the_weight_gradient_fill_whole_rounds(shape, B, planned):
+    """12, 22 and 3 blocks of filters and channels: 42, 11 and 170 splits make 504, 242 and 510 workgroups for
+    512 or 256 places.  One more split (the scratch would show it) leaves a second round to a handful."""
+    assert nf.nf_workspace_bytes(*layer(*shape), B) <= planned
