@@ -31,6 +31,8 @@
 // A value that is not finite anywhere in a tile makes neighbours of the transformed domain NaN that
 // the direct sum would leave finite (or infinite): a thread that finds one among its results
 // forms those results again by the direct sum.
+#include <algorithm>
+
 #include "wino_filter.h"
 
 namespace nf {
@@ -364,9 +366,9 @@ bool applicable(const FwdProblem &p) {
 }  // namespace
 
 // Which kernel, and how many reduction splits: both times are estimated from the step times below and
-// the smaller one wins.  The estimates were checked on 240 shapes (16 ... 512 channels, 64 ... 512 filters,
-// 256 ... 65 536 pixels): the choice is within 0.5 % of the faster of the two on average and never more than
-// 10 % off it; taking the direct kernel always is 27 % off.  Examples (us, direct / this): 512 -> 512 channels,
+// the smaller one wins.  Of 440 random shapes for which this kernel is chosen (16 ... 512 channels, 36 ... 512 filters) it
+// takes 0.63 of the direct kernels' time in all, and is the slower one for 7, by 14 % at most (reductions split in two or
+// four, whose direct form the estimate has a tenth too slow).  Examples (us, direct / this): 512 -> 512 channels,
 // 8192 pixels 312 / 150; 128 -> 128, 16 384 pixels 45 / 30, 4096 pixels 20 / 22 (direct); 512 -> 512, 1024 pixels
 // 52 / 40 (8 splits); 64 -> 64, 65 536 pixels 43 / 34.
 // Two lines are drawn by accuracy, not by time.  Where the direct kernel splits its reduction its sums
@@ -383,15 +385,17 @@ long long workgroups(const FwdProblem &p) {
   const long long tiles = ((long long)B * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) + TB - 1) / TB;
   return tiles * ((p.N + NB - 1) / NB);
 }
-// this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two; 11 us of prologue, epilogue and
-// launches; the transformed filter written and read at 4 TB/s; a projection shortcut is a launch of
+// this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two, in rounds of 512 workgroups; 11 us of
+// prologue, epilogue and launches, 3 us for each further round; the transformed filter written and read at 4 TB/s; a projection shortcut is a launch of
 // its own whose result this kernel adds (enqueue_conv)
 double wino_us(const FwdProblem &p, int s) {
   const int nchunks = (p.C + CH - 1) / CH;
   const long long w = workgroups(p) * s;
-  const double per = w <= 256 ? 1.13 : w <= 512 ? 2.12 : 2.12 * w / 512.0, mn = (double)p.M * p.N;
+  const long long full = w / 512, rest = w % 512;
+  const double per = 2.12 * full + (rest > 256 ? 2.12 : rest > 0 ? 1.13 : 0.0), mn = (double)p.M * p.N;
   const double proj = p.Cs ? 8.0 + 2.0 * mn * p.Cs / 90e6 + 4.0 * mn / 4e6 : 0.0;
-  return 11.0 + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per + finish_us(p, s) + proj;
+  return 11.0 + 3.0 * (full + (rest > 0) - 1) + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per +
+         finish_us(p, s) + proj;
 }
 }  // namespace
 
@@ -409,13 +413,15 @@ int wino_fwd_pick_splits(const FwdProblem &p) {
     const double us = wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;
   }
-  // the direct kernel: steps of 32 products, 128x128 tiles one per CU or 64x64 tiles up to four
+  // the direct kernel: steps of 32 products, 128x128 tiles one per CU, or 64x64 ones up to four, in rounds
+  // of 1024 workgroups (2 us for each further one)
   const int nkb = (p.Kg + 31) / 32;
   const bool big = igemm_fwd_tile128(p.M, p.N, p.Kg, ks);
   const int bt = big ? 128 : 64;
   const long long w = (long long)((p.M + bt - 1) / bt) * ((p.N + bt - 1) / bt) * ks;
-  const double per = big ? 2.06 * ((w + 255) / 256) : w <= 260 ? 0.56 : 0.55 * w / 256.0;
-  const double direct = 8.0 + (nkb + ks - 1) / ks * per + finish_us(p, ks);
+  const long long full = w / 1024, rest = w % 1024;
+  const double per = big ? 2.06 * ((w + 255) / 256) : 2.2 * full + (rest > 0 ? std::max(0.56, 0.55 * rest / 256.0) : 0.0);
+  const double direct = 8.0 + (big ? 0.0 : 2.0 * (full + (rest > 0) - 1)) + (nkb + ks - 1) / ks * per + finish_us(p, ks);
   return splits && best < 0.93 * direct ? splits : 0;
 }
 
