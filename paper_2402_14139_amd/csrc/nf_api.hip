@@ -539,8 +539,9 @@ int32_t run_aux_features(const nf_aux_desc *a, const AuxDims &ad, int B, const f
   return NF_OK;
 }
 
-// the re-lay of beta_n's filter that rides on a head launch; where the data gradient is planned as wino_fwd
-// its transformed form too (both: the mode in force may change before the data gradient is enqueued)
+// the re-lay of beta_n's filter that rides on a head launch; where this call's data gradient runs as wino_fwd
+// (w.wino_dgrad, settled by the entry point) its transformed form too (both: the mode in force may still change
+// before the data gradient is enqueued)
 RelayJob head_relay(const nf_aux_desc *a, const nf_aux_params *ap, void *ws, const WsLayout &w) {
   return relay_job(ap->Wa, wsf(ws, w.WaT), w.wino_dgrad ? wsf(ws, w.Ud) : nullptr, a->A, a->R, a->S, a->C_in);
 }
@@ -784,13 +785,14 @@ int32_t local_step_impl(const nf_layer_desc *d, const nf_aux_desc *a, const nf_s
     if ((rc = check_aux_ptrs(va))) return rc;
   }
   if (!aligned16(y_out)) return NF_ERR_BAD_DESC;
-  const WsLayout w = use_static ? ws_layout(d, ld, a, ad, B) : ws_layout(d, ld, a, ad, B, ws_bytes);
+  WsLayout w = use_static ? ws_layout(d, ld, a, ad, B) : ws_layout(d, ld, a, ad, B, ws_bytes);
   if (use_static) {
     if (w.total > (size_t)NF_STATIC_SCRATCH_BYTES) return NF_ERR_SCRATCH_LIMIT;
     if ((rc = static_scratch(&ws))) return rc;
   } else if ((rc = check_ws(ws, ws_bytes, w.total))) {
     return rc;
   }
+  w.wino_dgrad = wino_splits_now(dgrad_problem(a, ad, B), w.wino_dgrad);
   hipStream_t st = static_cast<hipStream_t>(stream);
   // Algorithm 2: forward with the current weights (this y_out is what the next layer reads),
   // head + loss, local gradients, update.
@@ -926,8 +928,9 @@ int32_t nf_aux_fwd_loss(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B,
   if (!y || !labels || !loss_out) return NF_ERR_NULL;
   if ((rc = check_aux_ptrs(ap))) return rc;
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout(d, ld, a, ad, B, ws_bytes);
+  WsLayout w = ws_layout(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
+  w.wino_dgrad = 0;  // the backward call forms its own transformed filter: this one's workspace may not have held it
   return run_aux_fwd(a, ad, B, y, labels, ap, loss_out, ws, w, static_cast<hipStream_t>(stream));
 }
 
@@ -975,8 +978,9 @@ int32_t nf_local_bwd_wgrad(const nf_layer_desc *d, const nf_aux_desc *a, int32_t
   if ((rc = check_aux_ptrs(ga))) return rc;
   if (!y) return NF_ERR_NULL;
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
-  const WsLayout w = ws_layout(d, ld, a, ad, B, ws_bytes);
+  WsLayout w = ws_layout(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
+  w.wino_dgrad = wino_splits_now(dgrad_problem(a, ad, B), w.wino_dgrad);
   return run_bwd(d, ld, a, ad, B, x, x_skip, y, p, ap, gp, ga, nullptr, nullptr, nullptr, nullptr, ws, w,
                  static_cast<hipStream_t>(stream));
 }

@@ -311,3 +311,21 @@ def test_workspaces_between_the_least_and_the_full_plan():
         for u, v in zip(grads[0], other):
             # sums of 180 224 products in other orders: some 1e-7 of the norm each
             assert (u - v).norm() <= 2e-6 * u.norm()
+
+
+@pytest.mark.parametrize("B,H,K,A,cls", [(128, 16, 64, 32, 10), (453, 7, 132, 20, 10)])
+def test_a_head_call_of_its_own_leaves_no_transformed_filter(B, H, K, A, cls):
+    """Nothing would read it: the backward call forms its own.  (The wide head and the per-sample one.)"""
+    g = torch.Generator(device="cuda").manual_seed(15)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    d = nf.LayerDesc(C_in=8, H_in=H, W_in=H, C_out=K, R=3, S=3, stride=1, pad=1)
+    a = nf.AuxDesc(C_in=K, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=1, pool_oh=2, pool_ow=2, n_classes=cls)
+    labels = torch.randint(0, cls, (B,), generator=g, device="cuda", dtype=torch.int32)
+    ap = nf.aux_params(rn(A, 3, 3, K) * 0.05, rn(A), rn(cls, 4 * A) * 0.2, rn(cls))
+    y, written = rn(B, H, H, K).relu(), []
+    need = nf.nf_workspace_bytes(d, a, B)
+    for nbytes in (need, need - 16 * 64 * -(-K // 64) * 8 * -(-A // 8) * 4):  # the second one has no room for it
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+        nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, torch.zeros(1, device="cuda"), ws)
+        written.append(int((ws.view(torch.int32) != -1).sum()))
+    assert written[0] == written[1], written
