@@ -295,8 +295,9 @@ bool igemm_wgrad_small_applicable(const WgradProblem &p) {
   // and 128 channels or more it gives a lane several channels (us with the reduction, this / tiled: 13 568 pixels x
   // 200 channels, 8 filters 29.1 / 33.4; 5696 x 256 25.7 / 23.3), otherwise a wave takes 64 channels (32 768 x 64, 16 filters
   // 35.4 / 35.8; 22 784 x 64 34.9 / 28.7), padded where they are not a multiple of 64 (28 392 x 96, 12 filters 42.6 / 39.1;
-  // 16 384 x 136 36.3 / 32.3; both equal near 3 million).
-  const long long line = p.P <= 8 && p.C >= 128 ? 1300000 : p.C % 64 == 0 ? 1700000 : 3ll << 20;
+  // 16 384 x 136 36.3 / 32.3; both equal near 3 million).  A layer of so few filters has the tiled kernel's splits, with
+  // which this one is slow (8136 pixels x 256 channels, 8 filters 29 / 20).
+  const long long line = !p.head ? 3ll << 20 : p.P <= 8 && p.C >= 128 ? 1300000 : p.C % 64 == 0 ? 1700000 : 3ll << 20;
   return served(p) && (long long)p.M * p.C >= line;
 }
 

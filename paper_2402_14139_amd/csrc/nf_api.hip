@@ -101,7 +101,7 @@ WgradProblem aux_wgrad_shape(const nf_aux_desc *a, const AuxDims &ad, int B) {
   std::memset((void *)&g, 0, sizeof(g));
   g.H = a->H_in, g.W = a->W_in, g.C = a->C_in, g.R = a->R, g.S = a->S, g.stride = 1, g.pad = a->pad, g.Ho = ad.Hu,
   g.Wo = ad.Wu;
-  g.P = a->A, g.M = B * ad.Hu * ad.Wu, g.RSC = a->R * a->S * a->C_in, g.Q = g.RSC;
+  g.P = a->A, g.M = B * ad.Hu * ad.Wu, g.RSC = a->R * a->S * a->C_in, g.Q = g.RSC, g.head = 1;
   g.div_howo = FastDiv(ad.Hu * ad.Wu), g.div_wo = FastDiv(ad.Wu);
   return g;
 }

@@ -95,6 +95,7 @@ struct WgradProblem {
   int Cs, Hs, Ws, ss;
   int P, M, RSC, Q, Qld;
   int splits, m_per_split;
+  int head;  // a head's: wgrad_head_splits chose the splits
   FastDiv div_howo, div_wo;
   uint32_t d_bytes, x_bytes, xs_bytes;  // filled by the launcher for the buffer-load variant
 };

@@ -50,3 +50,12 @@ def test_the_line_where_the_lanes_are_full(name):
     got = {r["kernel"] for r in nf.nf_prof_end()}
     G.check_step_results(name, out, final)
     assert kernel in got, got
+
+
+def test_a_narrow_layer_keeps_the_tiled_kernel():
+    """A layer of 8 filters (2.1 million pixels times channels) has that kernel's splits, a head of 8 would not."""
+    nf.nf_prof_begin()
+    out, final = G.run_step_both(S(256, 6, 6, 8, 80), 10, 226, seed=322, lr=0.05, mu=0.9, steps=1)
+    got = {r["kernel"] for r in nf.nf_prof_end()}
+    G.check_step_results("narrow_layer", out, final)
+    assert "wgrad_small_4x4" not in got and "igemm_wgrad_fast_32x128" in got, got
