@@ -203,7 +203,7 @@ int32_t nf_local_step(const nf_layer_desc *d, const nf_aux_desc *a, const nf_sgd
  * allocates nothing (no hipMalloc / hipFree, no allocating library routine).
  * A (layer, head, B) whose nf_workspace_bytes exceeds NF_STATIC_SCRATCH_BYTES is rejected with
  * NF_ERR_SCRATCH_LIMIT before anything is enqueued (a 512-channel 3x3 layer at batch 512 on 4x4
- * maps needs 89 MiB, the largest layer of the VGG-16-style workload 108 MiB).
+ * maps needs 89 MiB, the largest layer of the VGG-16-style workload 115 MiB).
  * Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU (two
  * streams, two threads) race; order them on one stream.  The array keeps the previous call's
  * contents, which is harmless: every region is written by the step before it is read.  The
