@@ -220,7 +220,7 @@ WsLayout ws_layout_of(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_
   w.ksplits_layer = igemm_fwd_pick_ksplits(B * ld.Ho * ld.Wo, d->C_out, Kl, d->C_in, d->R * d->S);
   size_t pmax = w.ksplits_layer > 1 ? (size_t)w.ksplits_layer * conv_out : 0;
   const FwdProblem fl = layer_fwd_problem(d, ld, B);
-  w.wino_layer = pl.layer ? wino_fwd_pick_splits(fl) : 0;
+  w.wino_layer = pl.layer ? wino_fwd_pick_splits(fl, 16) : 0;
   w.part_layer = wino_scratch_floats(w.wino_layer, fl);
   w.ksplits_aux = w.ksplits_dgrad = 1;
   if (a) {
@@ -254,8 +254,10 @@ WsLayout ws_layout_of(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_
     w.ksplits_dgrad = igemm_fwd_pick_ksplits(B * a->H_in * a->W_in, a->C_in, a->R * a->S * a->A, a->A, a->R * a->S);
     if (w.ksplits_dgrad > 1 && (size_t)w.ksplits_dgrad * emitted > pmax) pmax = (size_t)w.ksplits_dgrad * emitted;
     const FwdProblem fa = aux_fwd_problem(a, ad, B), fd = dgrad_problem(a, ad, B);
-    w.wino_aux = pl.aux ? wino_fwd_pick_splits(fa) : 0;
-    w.wino_dgrad = pl.dgrad ? wino_fwd_pick_splits(fd) : 0;
+    // (no more parts than the direct kernel's: a pooling launch adds them, few workgroups of it where samples are few; 7
+    // samples of 32x31, 128 -> 80 channels: pooling 12 us unsplit, 31 with two parts)
+    w.wino_aux = pl.aux ? wino_fwd_pick_splits(fa, w.ksplits_aux) : 0;
+    w.wino_dgrad = pl.dgrad ? wino_fwd_pick_splits(fd, 16) : 0;
     w.Ud = take_or(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0, 0);
     w.part_aux_fwd = wino_scratch_floats(w.wino_aux, fa), w.part_dgrad = wino_scratch_floats(w.wino_dgrad, fd);
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;

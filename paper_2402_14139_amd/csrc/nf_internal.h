@@ -75,9 +75,9 @@ hipError_t launch_igemm_fwd_split(const FwdProblem &p, bool nine, hipStream_t st
 // 3x3 / stride 1 / pad 1 through F(2x2, 3x3) in fp32 (wino_fwd.hip).  `U` is scratch for the transformed
 // filter (wino_fwd_filter_floats floats, 16-byte aligned); two launches.
 size_t wino_fwd_filter_floats(int N, int C);
-// 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none).  Of a
-// problem with a projection (Cs) it serves the 3x3 part: the caller adds the projection through addsrc
-int wino_fwd_pick_splits(const FwdProblem &p);
+// 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none), at most `most`.
+// Of a problem with a projection (Cs) it serves the 3x3 part: the caller adds the projection through addsrc
+int wino_fwd_pick_splits(const FwdProblem &p, int most);
 // (filter_ready: U holds the transformed filter already, one launch)
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, hipStream_t st);
 

@@ -399,7 +399,7 @@ double wino_us(const FwdProblem &p, int s) {
 }
 }  // namespace
 
-int wino_fwd_pick_splits(const FwdProblem &p) {
+int wino_fwd_pick_splits(const FwdProblem &p, int most) {
   // up to 32 filters half of a workgroup's columns would be padding; below 16 channels the result's own
   // traffic is all there is to either kernel (8 channels, 16 384 x 256 results: 17 / 14 + 5 for the filter launch)
   if (p.N <= 32 || p.C < 16 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
@@ -409,6 +409,7 @@ int wino_fwd_pick_splits(const FwdProblem &p) {
   int splits = 0;
   for (int s = 1; s <= 16; s *= 2) {
     if (4 * s < 3 * ks) continue;
+    if (s > most) break;
     if (s > 1 && (nchunks / s < 2 || workgroups(p) * s > 512)) break;
     const double us = wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;

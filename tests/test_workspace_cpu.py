@@ -95,3 +95,9 @@ def test_splits_of_the_weight_gradient_fill_whole_rounds(shape, B, planned):
     """12, 22 and 3 blocks of filters and channels: 42, 11 and 170 splits make 504, 242 and 510 workgroups for
     512 or 256 places.  One more split (the scratch would show it) leaves a second round to a handful."""
     assert nf.nf_workspace_bytes(*layer(*shape), B) <= planned
+
+
+def test_a_head_takes_no_more_parts_than_its_direct_kernel():
+    """7 samples of 32x31: the direct head convolution is not cut, and a pooling launch with 28 windows would add the
+    parts of a cut one (the scratch would show them)."""
+    assert nf.nf_workspace_bytes(*layer(4, 32, 31, 128, 80, 1, 0, 0, 10), 7) <= 28820480
