@@ -828,7 +828,8 @@ RelayJob relay_job(const float *Wa, float *WaT, float *U, int A, int R, int S, i
   j.Wa = Wa, j.WaT = WaT, j.U = U, j.A = A, j.R = R, j.S = S, j.K = K;
   j.nchunks = (A + WINO_CH - 1) / WINO_CH;
   j.nb_t = (int)(((long long)A * R * S * K + HT - 1) / HT);
-  j.nb_u = U ? ((K + WINO_NB - 1) / WINO_NB * WINO_NB * 2 * j.nchunks + HT - 1) / HT : 0;
+  const int nb = wino_nb(K);
+  j.nb_u = U ? ((K + nb - 1) / nb * nb * 2 * j.nchunks + HT - 1) / HT : 0;
   return j;
 }
 

@@ -156,6 +156,7 @@ struct WsLayout {
   // head_fused == 2 only: F_n is formed from column sums left by the aux convolution's epilogue
   // (region ppart), no pooling launch
   int pool_fused;
+  float *aux_filter;  // the head's transformed filter where the layer's launch left it (set by nf_local_step)
   int aux_least;  // how few splits the head's weight gradient makes do with
   size_t least;   // `total` of the layout that gives up all it can (WsPlan)
   // floats of scratch in `part` that the direct kernels, and each contraction as planned, need
@@ -193,6 +194,10 @@ FwdProblem layer_fwd_problem(const nf_layer_desc *d, const LayerDims &ld, int B)
   return f;
 }
 
+// Whether the region of dU, which no launch before the head's convolution is done writes, holds that convolution's
+// transformed filter: then nf_local_step has the layer's filter launch form it there
+bool filter_in_dU(const FwdProblem &f) { return wino_fwd_filter_floats(f.N, f.C) <= (size_t)f.M * f.N; }
+
 // scratch of a forward-type contraction that runs as wino_fwd
 size_t wino_scratch_floats(int splits, const FwdProblem &f) {
   if (!splits) return 0;
@@ -220,7 +225,7 @@ WsLayout ws_layout_of(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_
   w.ksplits_layer = igemm_fwd_pick_ksplits(B * ld.Ho * ld.Wo, d->C_out, Kl, d->C_in, d->R * d->S);
   size_t pmax = w.ksplits_layer > 1 ? (size_t)w.ksplits_layer * conv_out : 0;
   const FwdProblem fl = layer_fwd_problem(d, ld, B);
-  w.wino_layer = pl.layer ? wino_fwd_pick_splits(fl, 16) : 0;
+  w.wino_layer = pl.layer ? wino_fwd_pick_splits(fl, w.ksplits_layer, 16) : 0;
   w.part_layer = wino_scratch_floats(w.wino_layer, fl);
   w.ksplits_aux = w.ksplits_dgrad = 1;
   if (a) {
@@ -254,12 +259,9 @@ WsLayout ws_layout_of(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_
     w.ksplits_dgrad = igemm_fwd_pick_ksplits(B * a->H_in * a->W_in, a->C_in, a->R * a->S * a->A, a->A, a->R * a->S);
     if (w.ksplits_dgrad > 1 && (size_t)w.ksplits_dgrad * emitted > pmax) pmax = (size_t)w.ksplits_dgrad * emitted;
     const FwdProblem fa = aux_fwd_problem(a, ad, B), fd = dgrad_problem(a, ad, B);
-    // (no more parts than the direct kernel's: a pooling launch adds them, few workgroups of it where samples are few; 7
-    // samples of 32x31, 128 -> 80 channels: pooling 12 us unsplit, 31 with two parts)
-    w.wino_aux = pl.aux ? wino_fwd_pick_splits(fa, w.ksplits_aux) : 0;
-    w.wino_dgrad = pl.dgrad ? wino_fwd_pick_splits(fd, 16) : 0;
+    w.wino_dgrad = pl.dgrad ? wino_fwd_pick_splits(fd, w.ksplits_dgrad, 16, true) : 0;
     w.Ud = take_or(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0, 0);
-    w.part_aux_fwd = wino_scratch_floats(w.wino_aux, fa), w.part_dgrad = wino_scratch_floats(w.wino_dgrad, fd);
+    w.part_dgrad = wino_scratch_floats(w.wino_dgrad, fd);
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;
     if (w.head_fused == 2 && head_pool_partials_applicable(head_shape(a, ad, B))) {
       // (a reduction split in two gives way: the pooling launch it would need costs more than it gains)
@@ -268,6 +270,10 @@ WsLayout ws_layout_of(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_
       w.pool_fused = fwd_pool_partials_applicable(fp) ? 1 : 0;
       if (w.pool_fused) w.ksplits_aux = 1;
     }
+    // (no more parts than the direct kernel's: a pooling launch adds them, few workgroups of it where samples are few; 7
+    // samples of 32x31, 128 -> 80 channels: pooling 12 us unsplit, 31 with two parts)
+    w.wino_aux = pl.aux ? wino_fwd_pick_splits(fa, w.ksplits_aux, w.ksplits_aux, w.wino_layer && filter_in_dU(fa)) : 0;
+    w.part_aux_fwd = wino_scratch_floats(w.wino_aux, fa);
     w.ppart = take(w.pool_fused ? (size_t)B * ad.Hu * ad.Wu / 16 * 2 * a->A * f : 0);
     w.part_b = take_or((size_t)std::max(w.splits_layer, w.wino_wgrad) * d->C_out * f, (size_t)w.splits_layer * d->C_out * f);
     w.part_aux = take_or(w.splits_aux * pa * f, w.aux_least * pa * f);
@@ -411,17 +417,22 @@ int32_t enqueue_fwd_split(FwdProblem f, float *out, int ksplits, float *part, hi
   return enqueue_fwd(f, st);
 }
 
+// its variant of 32 filters is another kernel
+const char *wino_name(int N) { return N <= 32 ? "wino_fwd_32" : "wino_fwd"; }
+
 // the same contraction through wino_fwd (flops of the dense formula; scratch: the transformed filter,
-// then the partial sums of the splits; filter: the transformed filter where an earlier launch left it)
-int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, float *filter, hipStream_t st) {
+// then the partial sums of the splits; filter: the transformed filter where an earlier launch left it; also: a
+// filter to transform beside this one's)
+int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, float *filter, const WinoFilter *also,
+                     hipStream_t st) {
   const double B = (double)f.M / ((double)f.Ho * f.Wo), mn = (double)f.M * f.N;
   double elems = B * f.H * f.W * f.C + (double)f.N * f.Kg + mn;
   const float *bias = f.bias, *addsrc = f.addsrc, *mask = f.mask;
   if (splits <= 1 && (addsrc || mask)) elems += mn;
   float *part = scratch + wino_fwd_filter_floats(f.N, f.C);
   f.ksplits = splits, f.out = splits > 1 ? part : out;
-  NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, 4.0 * elems,
-         launch_wino_fwd(f, filter ? filter : scratch, filter != nullptr, st));
+  NF_RUN(st, wino_name(f.N), 2.0 * mn * f.Kg, 4.0 * elems,
+         launch_wino_fwd(f, filter ? filter : scratch, filter != nullptr, also, st));
   if (splits > 1)
     NF_RUN(st, "fwd_finish", 0.0, 4.0 * mn * (splits + 1.0 + (addsrc ? 1.0 : 0.0) + (mask ? 1.0 : 0.0)),
            launch_fwd_finish(part, splits, f.M, f.N, bias, addsrc, mask, f.relu, out, st));
@@ -443,9 +454,10 @@ bool run_wino(const WgradProblem &g, int splits) {
          (mode == NF_CONTRACT_BF16X6 && wino_wgrad_beats_split(g, splits));
 }
 
-// by the layout's plan: wino_fwd, or the direct kernels
+// by the layout's plan: wino_fwd, or the direct kernels.  `also`: a filter that wino_fwd's launch transforms on its
+// way; *formed says whether it did
 int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, float *part, hipStream_t st,
-                     float *filter = nullptr) {
+                     float *filter = nullptr, const WinoFilter *also = nullptr, bool *formed = nullptr) {
   if ((wino = wino_splits_now(f, wino))) {
     FwdProblem g = f;
     if (f.Cs) {  // the projection first, into `out`; wino_fwd adds it there (each element read by the thread that writes it)
@@ -458,7 +470,8 @@ int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, flo
       if (rc) return rc;
       g.Cs = 0, g.Kg = g.RSC, g.addsrc = out;
     }
-    return enqueue_wino(g, out, wino, part, filter, st);
+    if (also) *formed = true;
+    return enqueue_wino(g, out, wino, part, filter, also, st);
   }
   return enqueue_fwd_split(f, out, ksplits, part, st);
 }
@@ -484,14 +497,15 @@ WgradReduce reduce_job(const WgradProblem &g, float *out0, float *out1, float *o
 }
 
 int32_t run_layer_fwd(const nf_layer_desc *d, const LayerDims &ld, int B, const float *x, const float *xs,
-                      const nf_layer_params *p, float *y, void *ws, const WsLayout &w, hipStream_t st) {
+                      const nf_layer_params *p, float *y, void *ws, const WsLayout &w, hipStream_t st,
+                      const WinoFilter *also = nullptr, bool *formed = nullptr) {
   const bool pooled = d->pool_kind != 0;
   FwdProblem f = layer_fwd_problem(d, ld, B);
   f.x = x, f.w = p->W, f.bias = p->b;
   if (d->skip_kind == 1) f.addsrc = xs;
   if (d->skip_kind == 2) f.xs = xs, f.wp = p->Wp;
   float *conv_out = pooled ? wsf(ws, w.T_dZ) : y;
-  int32_t rc = enqueue_conv(f, conv_out, w.wino_layer, w.ksplits_layer, wsf(ws, w.part), st);
+  int32_t rc = enqueue_conv(f, conv_out, w.wino_layer, w.ksplits_layer, wsf(ws, w.part), st, nullptr, also, formed);
   if (rc) return rc;
   if (pooled) {
     const double pre = (double)B * ld.Ho * ld.Wo * d->C_out, post = (double)B * ld.Hp * ld.Wp * d->C_out;
@@ -519,7 +533,9 @@ int32_t run_aux_conv(const nf_aux_desc *a, const AuxDims &ad, int B, const float
   if (pool_partials) f.pool_part = wsf(ws, w.ppart), f.pool_split = ad.Wu == 16 ? 1 : 0;
   if (!wino) return enqueue_fwd(f, st);
   const double mn = (double)f.M * f.N, byts = 4.0 * ((double)B * f.H * f.W * f.C + (double)f.N * f.Kg + mn);
-  NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, byts, launch_wino_fwd(f, wsf(ws, w.part), false, st));
+  NF_RUN(st, wino_name(f.N), 2.0 * mn * f.Kg, byts,
+         launch_wino_fwd(f, w.aux_filter ? w.aux_filter : wsf(ws, w.part), w.aux_filter != nullptr,
+                         nullptr, st));
   return NF_OK;
 }
 
@@ -798,7 +814,12 @@ int32_t local_step_impl(const nf_layer_desc *d, const nf_aux_desc *a, const nf_s
   hipStream_t st = static_cast<hipStream_t>(stream);
   // Algorithm 2: forward with the current weights (this y_out is what the next layer reads),
   // head + loss, local gradients, update.
-  if ((rc = run_layer_fwd(d, ld, B, x, x_skip, p, y_out, ws, w, st))) return rc;
+  const FwdProblem fa = aux_fwd_problem(a, ad, B);
+  const WinoFilter also = {ap->Wa, wsf(ws, w.dU), fa.N, fa.C};
+  const bool share = wino_splits_now(fa, w.wino_aux) && filter_in_dU(fa);
+  bool formed = false;
+  if ((rc = run_layer_fwd(d, ld, B, x, x_skip, p, y_out, ws, w, st, share ? &also : nullptr, &formed))) return rc;
+  if (formed) w.aux_filter = wsf(ws, w.dU);
   // the batch-mean loss rides on the head's backward launch
   if ((rc = run_aux_fwd(a, ad, B, y_out, labels, ap, nullptr, ws, w, st))) return rc;
   // ... and the update on the launch that finishes the weight gradients

@@ -76,10 +76,18 @@ hipError_t launch_igemm_fwd_split(const FwdProblem &p, bool nine, hipStream_t st
 // filter (wino_fwd_filter_floats floats, 16-byte aligned); two launches.
 size_t wino_fwd_filter_floats(int N, int C);
 // 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none), at most `most`.
+// `direct`: the direct kernel's.  `ready`: an earlier launch transforms the filter on its way.
 // Of a problem with a projection (Cs) it serves the 3x3 part: the caller adds the projection through addsrc
-int wino_fwd_pick_splits(const FwdProblem &p, int most);
-// (filter_ready: U holds the transformed filter already, one launch)
-hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, hipStream_t st);
+int wino_fwd_pick_splits(const FwdProblem &p, int direct, int most, bool ready = false);
+// A filter [N][3][3][C] and where its transformed form goes
+struct WinoFilter {
+  const float *w;
+  float *U;
+  int N, C;
+};
+// (filter_ready: U holds the transformed filter already, one launch; `also`: a filter transformed by the same
+// launch as this one's)
+hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, const WinoFilter *also, hipStream_t st);
 
 // first-layer shapes (stem.hip): the whole reduction R*S*C <= 32 in one staging step, channel counts
 // that are not multiples of 4; launch_igemm_fwd / launch_igemm_wgrad pick them when applicable

@@ -5,17 +5,20 @@
 
 namespace nf {
 
-// U[filter block of 64][step of 8 channels][position a*4+b][n & 1][lane][4]: the word of lane (j, h), element
-// k is filter 64*block + 2*j + (n & 1), channel 8*step + 4*h + k, i.e. the B fragment of one MFMA group.
-constexpr int WINO_NB = 64, WINO_CH = 8, WINO_UB = 16 * WINO_NB * WINO_CH;  // words per (filter block, step)
+// U[filter block of nb][step of 8 channels][position a*4+b][n][lane][4], nb = 64: the word of lane (j, h), element
+// k is filter 64*block + 2*j + n, channel 8*step + 4*h + k, i.e. the B fragment of one MFMA group; nb = 32: one
+// fragment (no n), filter 32*block + j.
+constexpr int WINO_CH = 8;
+// Filters per workgroup of wino_fwd: 64, or 32 where those would be half padding (wino_fwd.hip)
+__host__ __device__ inline int wino_nb(int N) { return N <= 32 ? 32 : 64; }
 
 // U = G g G^T for four consecutive channels 4*c4 .. +3 of filter n, g[r][s] holding their taps
-__device__ inline void wino_filter_store(const float4 (&g)[3][3], float *U, int n, int c4, int nchunks) {
+__device__ inline void wino_filter_store(const float4 (&g)[3][3], float *U, int n, int c4, int nchunks, int nb) {
   auto add = [](const float4 &a, const float4 &b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
   auto sub = [](const float4 &a, const float4 &b) { return make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w); };
   auto half = [](const float4 &a) { return make_float4(0.5f * a.x, 0.5f * a.y, 0.5f * a.z, 0.5f * a.w); };
-  const int in = n % WINO_NB;
-  float *o = U + ((long long)(n / WINO_NB) * nchunks + (c4 >> 1)) * WINO_UB + (in & 1) * 256 + ((c4 & 1) * 32 + (in >> 1)) * 4;
+  const int in = n & (nb - 1), two = nb >> 6, pos = nb * WINO_CH;  // words per position
+  float *o = U + ((long long)(n / nb) * nchunks + (c4 >> 1)) * (16 * pos) + (in & two) * 256 + ((c4 & 1) * 32 + (in >> two)) * 4;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     float4 q[3];
@@ -28,7 +31,7 @@ __device__ inline void wino_filter_store(const float4 (&g)[3][3], float *U, int 
     const float4 e = add(q[0], q[2]);
     const float4 v[4] = {q[0], half(add(e, q[1])), half(sub(e, q[1])), q[2]};
 #pragma unroll
-    for (int b = 0; b < 4; ++b) *reinterpret_cast<float4 *>(o + (a * 4 + b) * 512) = v[b];
+    for (int b = 0; b < 4; ++b) *reinterpret_cast<float4 *>(o + (a * 4 + b) * pos) = v[b];
   }
 }
 
@@ -49,7 +52,7 @@ __device__ inline void relay_block(const RelayJob &j, int b) {
     j.WaT[i] = j.Wa[(((long long)a * j.R + (j.R - 1 - rr)) * j.S + (j.S - 1 - ss)) * j.K + k];
     return;
   }
-  const int i = (b - j.nb_t) * 256 + threadIdx.x, nk = (j.K + WINO_NB - 1) / WINO_NB * WINO_NB;
+  const int nb = wino_nb(j.K), i = (b - j.nb_t) * 256 + threadIdx.x, nk = (j.K + nb - 1) / nb * nb;
   const int k = i % nk, c4 = i / nk;
   if (c4 >= 2 * j.nchunks) return;
   float4 g[3][3];
@@ -66,7 +69,7 @@ __device__ inline void relay_block(const RelayJob &j, int b) {
       }
       g[r][s] = make_float4(v[0], v[1], v[2], v[3]);
     }
-  wino_filter_store(g, j.U, k, c4, j.nchunks);
+  wino_filter_store(g, j.U, k, c4, j.nchunks, nb);
 }
 
 }  // namespace nf

@@ -28,6 +28,13 @@
 // 43 / 35; 128 -> 128, 32 768 pixels 80 / 48; 256 -> 256, 16 384 pixels 155 / 83; 512 -> 512, 8192 pixels 312 / 150
 // (a step of 8 channels takes 2.1 us on a CU with two workgroups, 0.87 of it MFMAs).
 //
+// Up to 32 filters (the heads' usual width) a variant of 32 per workgroup runs, half of whose columns would be
+// padding otherwise: 64 accumulators, three workgroups per CU, the same patches and transforms for half of the
+// MFMAs, so a step of 16 MFMAs takes 1.3 us with two workgroups on a CU where they alone take 0.9.  In front of the head's
+// pooling its epilogue leaves the sums over 16 pixels that the direct kernel's does.  Measured (us, the direct kernel
+// of 64x32 tiles / this, without the filter's launch): 64 channels, 65 536 pixels 30.2 / 19.5, 128 channels, 16 384 pixels 17.1 /
+// 12.3; a 64-channel step with a 32-wide head 175.1 / 166.5.
+//
 // A value that is not finite anywhere in a tile makes neighbours of the transformed domain NaN that
 // the direct sum would leave finite (or infinite): a thread that finds one among its results
 // forms those results again by the direct sum.
@@ -42,11 +49,10 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int NTHREADS = 256;
-constexpr int TB = 32, NB = WINO_NB;     // output tiles, filters per workgroup
+constexpr int TB = 32;                   // output tiles per workgroup
 constexpr int CH = WINO_CH;              // channels per step
 constexpr int OOB = (int)0x80000000;     // offset no buffer of < 2 GiB contains
 constexpr int RSRC_FLAGS = 0x00020000;   // raw buffer, 32-bit data format
-constexpr int UB = WINO_UB;
 
 struct WinoAux {
   int TW, TPI, T;        // tiles per image row, per image, in all
@@ -79,21 +85,29 @@ __device__ inline unsigned bad4(const float4 &v) {
          (__builtin_isfinite(v.w) ? 0u : 8u);
 }
 
-// The transformed filter, zero past the last filter and channel.  HBM-bound: 36 bytes read, 64 written per
-// (filter, channel); 5-8 us.
-__global__ __launch_bounds__(256) void wino_filter_kernel(const float *w, float *U, int N, int C, int nchunks) {
+// One or two transformed filters, zero past the last filter and channel.  HBM-bound: 36 bytes read, 64 written per
+// (filter, channel); 5-8 us, most of it the launch: the head's filter rides on its layer's (64 -> 64 channels, batch
+// 64, 32-wide head: a launch of 4.5 us less).
+struct FilterJobs {
+  WinoFilter f[2];
+  int nchunks[2], bx[2], blocks0;  // steps of 8 channels; blocks along the channels; blocks of job 0
+};
+__global__ __launch_bounds__(256) void wino_filter_kernel(FilterJobs js) {
+  const int k = (int)blockIdx.x >= js.blocks0, b = blockIdx.x - (k ? js.blocks0 : 0);
+  const WinoFilter f = js.f[k];
+  const int nchunks = js.nchunks[k], bx = js.bx[k];
   const int t = threadIdx.x;
-  const int c4 = blockIdx.x * 8 + (t & 7), n = blockIdx.y * 32 + (t >> 3);  // 8 lanes read 128 contiguous bytes
+  const int c4 = b % bx * 8 + (t & 7), n = b / bx * 32 + (t >> 3);  // 8 lanes read 128 contiguous bytes
   if (c4 >= 2 * nchunks) return;
   float4 g[3][3];
-  const bool ok = n < N && c4 * 4 < C;
+  const bool ok = n < f.N && c4 * 4 < f.C;
 #pragma unroll
   for (int r = 0; r < 3; ++r)
 #pragma unroll
     for (int s = 0; s < 3; ++s)
-      g[r][s] = ok ? *reinterpret_cast<const float4 *>(w + ((long long)n * 9 + r * 3 + s) * C + c4 * 4)
+      g[r][s] = ok ? *reinterpret_cast<const float4 *>(f.w + ((long long)n * 9 + r * 3 + s) * f.C + c4 * 4)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
-  wino_filter_store(g, U, n, c4, nchunks);
+  wino_filter_store(g, f.U, n, c4, nchunks, wino_nb(f.N));
 }
 
 // Four outputs (filters n .. n+3 of pixel (img, ho, wo)) by the direct sum over channels [c_lo, c_hi);
@@ -125,13 +139,17 @@ __device__ inline float4 direct4(const float *x, const float *w, int H, int W, i
   return s;
 }
 
-__global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, WinoAux q) {
-  // main loop: As[2][16 patch pixels][32 tiles][8 channels]; epilogue: Cs[4 rows][32 tiles][2 columns][64 filters]
-  __shared__ __attribute__((aligned(16))) float S[4 * TB * 2 * NB];
+// NF: MFMA columns of 32 filters per workgroup (2, or 1 for few filters)
+template <int NF>
+__global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(FwdProblem p, WinoAux q) {
+  constexpr int NB = 32 * NF, UP = NB * CH, UB = 16 * UP;  // filters; words of U per position and per step
+  constexpr int AW = 2 * 16 * TB * CH, CW = 4 * TB * 2 * NB;
+  // main loop: As[2][16 patch pixels][32 tiles][8 channels]; epilogue: Cs[4 rows][32 tiles][2 columns][NB filters]
+  __shared__ __attribute__((aligned(16))) float S[AW > CW ? AW : CW];
 
   const int t = threadIdx.x;
   const int lane = t & 63, row = t >> 6;  // a wave owns one row of the transformed domain
-    const int j = lane & 31, h = lane >> 5;
+  const int j = lane & 31, h = lane >> 5;
   // XCD re-map (workgroups are dealt round-robin over 8 XCDs): each XCD gets a contiguous run with the
   // filter blocks fastest, so that the patches of a tile block are read into one L2 only
   const int nwg = gridDim.x, lin = blockIdx.x;
@@ -181,18 +199,18 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
     tr[c] = fma4(sg, v, u);
   };
 
-  const int ubase = ((nb * q.nchunks) * UB + row * 4 * 512 + lane * 4) * 4;
-  float4 uf[4][2];  // fragments of column b: re-loaded one section after their last use
+  const int ubase = ((nb * q.nchunks) * UB + row * 4 * UP + lane * 4) * 4;
+  float4 uf[4][NF];  // fragments of column b: re-loaded one section after their last use
   auto uload = [&](int s, int b) {
 #pragma unroll
-    for (int n = 0; n < 2; ++n) uf[b][n] = bload(rsu, ubase + (s * UB + b * 512 + n * 256) * 4);
+    for (int n = 0; n < NF; ++n) uf[b][n] = bload(rsu, ubase + (s * UB + b * UP + n * 256) * 4);
   };
 
-  floatx16 acc[4][2];
+  floatx16 acc[4][NF];
 #pragma unroll
   for (int b = 0; b < 4; ++b)
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < NF; ++n)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[b][n][e] = 0.f;
 
@@ -232,29 +250,44 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
 #pragma unroll
       for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
+        for (int n = 0; n < NF; ++n)
           acc[b][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(el(v[b], k), el(uf[b][n], k), acc[b][n], 0, 0, 0);
+      if constexpr (NF == 2) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                // one MFMA
-        if (i < 1) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                     // + patch reads
-        if (b == 0 && i >= 2 && i < 6) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0); // + an LDS write
-        if (i < (b == 1 ? 6 : 2)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);      // + a load
-        if (i >= 3) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);                    // + address, row combination
+        for (int i = 0; i < 8; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                // one MFMA
+          if (i < 1) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                     // + patch reads
+          if (b == 0 && i >= 2 && i < 6) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0); // + an LDS write
+          if (i < (b == 1 ? 6 : 2)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);      // + a load
+          if (i >= 3) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);                    // + address, row combination
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          if (i < 1) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+          if (b == 0 && i >= 1 && i < 3) __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);
+          if (b == 1 || i < 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+          if (b == 1 && i == 3) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+          if (i >= 1) __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     buf ^= 1;
   }
 
-  // ---- epilogue: this thread's eight results are filters n .. n+3 of 4 (tile, column) x 2 rows ----
+  // ---- epilogue: this thread's results are filters n .. n+3 of NT (tile, column) x 2 rows ----
+  constexpr int NG = NB / 4, NT = 64 * NG / NTHREADS;
   const bool split = gridDim.y > 1;
   float *const out = p.out + (split ? (long long)blockIdx.y * p.M * p.N : 0ll);
-  const int n = nb * NB + (t & 15) * 4;
-  long long off[4][2];  // -1: no such pixel or filter
+  const int n = nb * NB + (t % NG) * 4;
+  // (NF = 1: a wave takes 8 consecutive tiles, what p.pool_part sums)
+  auto task_of = [&](int i) { return NF == 2 ? i * 16 + (t >> 4) : row * 16 + i * 8 + (lane >> 3); };  // (tile, column)
+  long long off[NT][2];  // -1: no such pixel or filter
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int task = i * 16 + (t >> 4);  // (tile, column)
+  for (int i = 0; i < NT; ++i) {
+    const int task = task_of(i);
     const int tile = t0 + (task >> 1);
     const int img = (int)q.div_tpi.div((uint32_t)tile), rem = tile - img * q.TPI;
     const int ty = (int)q.div_tw.div((uint32_t)rem), tx = rem - ty * q.TW;
@@ -266,10 +299,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
   }
   // shortcut or mask: fetched before the transform, so that the loads overlap it
   const float *const extra = split ? nullptr : p.addsrc ? p.addsrc : p.mask;
-  float4 ex[4][2];
+  float4 ex[NT][2];
   if (extra) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
       for (int k = 0; k < 2; ++k)
         if (off[i][k] >= 0) ex[i][k] = *reinterpret_cast<const float4 *>(extra + off[i][k]);
@@ -277,16 +310,22 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
   // output transform: columns in registers, rows through LDS
   __syncthreads();
   {
-    float *const cw = S + row * (TB * 2 * NB) + 2 * j;
+    float *const cw = S + row * (TB * 2 * NB) + NF * j;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int r = 8 * (e >> 2) + 4 * h + (e & 3);
-      float2 y0, y1;
-      const float p0 = acc[1][0][e], m0 = acc[2][0][e], p1 = acc[1][1][e], m1 = acc[2][1][e];
-      y0.x = acc[0][0][e] + p0 + m0, y1.x = p0 - m0 - acc[3][0][e];
-      y0.y = acc[0][1][e] + p1 + m1, y1.y = p1 - m1 - acc[3][1][e];
-      *reinterpret_cast<float2 *>(cw + (r * 2 + 0) * NB) = y0;
-      *reinterpret_cast<float2 *>(cw + (r * 2 + 1) * NB) = y1;
+      float y0[NF], y1[NF];
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        const float pl = acc[1][f][e], mi = acc[2][f][e];
+        y0[f] = acc[0][f][e] + pl + mi, y1[f] = pl - mi - acc[3][f][e];
+      }
+      if constexpr (NF == 2) {
+        *reinterpret_cast<float2 *>(cw + (r * 2 + 0) * NB) = make_float2(y0[0], y0[1]);
+        *reinterpret_cast<float2 *>(cw + (r * 2 + 1) * NB) = make_float2(y1[0], y1[1]);
+      } else {
+        cw[(r * 2 + 0) * NB] = y0[0], cw[(r * 2 + 1) * NB] = y1[0];
+      }
     }
   }
   __syncthreads();
@@ -317,28 +356,65 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
     if (!(skip & 8u)) out[o + 3] = v.w;
   };
   unsigned bad = 0;  // four bits from 4*(2*i + k): which of those results are not finite
+  float4 ps[NF == 1 ? NT : 1][2];  // what each stored, for p.pool_part
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int task = i * 16 + (t >> 4), lt = task >> 1;
-    const float *c = S + (lt * 2 + (task & 1)) * NB + (t & 15) * 4;
+  for (int i = 0; i < NT; ++i) {
+    const int task = task_of(i), lt = task >> 1;
+    const float *c = S + (lt * 2 + (task & 1)) * NB + (t % NG) * 4;
     constexpr int RS = TB * 2 * NB;  // next row of the transformed domain
     const float4 r0 = *reinterpret_cast<const float4 *>(c), r1 = *reinterpret_cast<const float4 *>(c + RS);
     const float4 r2 = *reinterpret_cast<const float4 *>(c + 2 * RS), r3 = *reinterpret_cast<const float4 *>(c + 3 * RS);
     const float4 y[2] = {add4(add4(r0, r1), r2), sub4(sub4(r1, r2), r3)};
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
+      if constexpr (NF == 1) ps[i][k] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (off[i][k] < 0) continue;
       const unsigned b = bad4(y[k]);
       bad |= b << (4 * (2 * i + k));
-      store(finish(y[k], ex[i][k], off[i][k]), off[i][k], b);
+      const float4 v = finish(y[k], ex[i][k], off[i][k]);
+      if constexpr (NF == 1) ps[i][k] = v;
+      store(v, off[i][k], b);
     }
   }
-  if (bad == 0) return;
+  // sums over 16 consecutive pixels for the head's pooling: the wave's eight tiles are 16 pixels of two image
+  // rows, its first four (i = 0) their first 8 (lanes along the columns pairwise, then the halves: a fixed order)
+  auto pool = [&] {
+    if constexpr (NF == 1) {
+      const int tile = t0 + row * 8;
+      if (tile >= q.T) return;  // (whole wave; its tiles lie in one tile row)
+      const int img = (int)q.div_tpi.div((uint32_t)tile), rem = tile - img * q.TPI;
+      const int ty = (int)q.div_tw.div((uint32_t)rem), tx = rem - ty * q.TW;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        float4 s[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          s[i] = ps[i][k];
+#pragma unroll
+          for (int o = 8; o < 64; o *= 2)
+            s[i] = add4(s[i], make_float4(__shfl_xor(s[i].x, o, 64), __shfl_xor(s[i].y, o, 64),
+                                          __shfl_xor(s[i].z, o, 64), __shfl_xor(s[i].w, o, 64)));
+        }
+        if (lane >= NG || n >= p.N) continue;
+        float *const dst = p.pool_part + (((long long)(img * p.Ho + 2 * ty + k) * p.Wo + 2 * tx) >> 4) * 2 * p.N + n;
+        *reinterpret_cast<float4 *>(dst) = p.pool_split ? s[0] : add4(s[0], s[1]);
+        if (p.pool_split) *reinterpret_cast<float4 *>(dst + p.N) = s[1];
+      }
+    }
+  };
+  if (p.pool_part) {  // with results formed again in their place
+    if (!__ballot(bad != 0)) {
+      pool();
+      return;
+    }
+  } else if (bad == 0) {
+    return;
+  }
 #pragma unroll 1
-  for (int ik = 0; ik < 8; ++ik) {
+  for (int ik = 0; ik < 2 * NT; ++ik) {
     const unsigned want = bad >> (4 * ik) & 15u;
     if (!want) continue;
-    const int task = (ik >> 1) * 16 + (t >> 4), tile = t0 + (task >> 1);
+    const int task = task_of(ik >> 1), tile = t0 + (task >> 1);
     const int img = (int)q.div_tpi.div((uint32_t)tile), rem = tile - img * q.TPI;
     const int ty = (int)q.div_tw.div((uint32_t)rem), tx = rem - ty * q.TW;
     const int ho = 2 * ty + (ik & 1), wo = 2 * tx + (task & 1);
@@ -346,19 +422,33 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_kernel(FwdProblem p, Win
     const float4 v = direct4(p.x, p.w, p.H, p.W, p.C, img, ho, wo, n, s_lo * CH, min(p.C, s_hi * CH), want);
     float4 x = bias;
     if (extra) x = *reinterpret_cast<const float4 *>(extra + o);
-    store(finish(v, x, o), o, ~want & 15u);
+    const float4 f = finish(v, x, o);
+    store(f, o, ~want & 15u);
+    if constexpr (NF == 1) {
+#pragma unroll
+      for (int k = 0; k < 2 * NT; ++k)
+        if (k == ik) {
+          float4 &s = ps[k >> 1][k & 1];
+          if (want & 1u) s.x = f.x;
+          if (want & 2u) s.y = f.y;
+          if (want & 4u) s.z = f.z;
+          if (want & 8u) s.w = f.w;
+        }
+    }
   }
+  if (p.pool_part) pool();
 }
 
 }  // namespace
 
 size_t wino_fwd_filter_floats(int N, int C) {
-  return (size_t)((N + NB - 1) / NB) * ((C + CH - 1) / CH) * UB;
+  const int nb = wino_nb(N);
+  return (size_t)((N + nb - 1) / nb) * ((C + CH - 1) / CH) * (16 * nb * CH);
 }
 
 namespace {
 bool applicable(const FwdProblem &p) {
-  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.pool_part) return false;
+  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1) return false;
   if (p.C % 4 || p.N % 4) return false;
   const long long lim = 0x7FFFFFF0ll, B = p.M / ((long long)p.Ho * p.Wo);
   return B * p.H * p.W * p.C * 4 <= lim && (long long)wino_fwd_filter_floats(p.N, p.C) * 4 <= lim;
@@ -383,7 +473,8 @@ double finish_us(const FwdProblem &p, int s) {  // fwd_finish at 4 TB/s
 long long workgroups(const FwdProblem &p) {
   const int B = p.M / (p.Ho * p.Wo);
   const long long tiles = ((long long)B * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) + TB - 1) / TB;
-  return tiles * ((p.N + NB - 1) / NB);
+  const int nb = wino_nb(p.N);
+  return tiles * ((p.N + nb - 1) / nb);
 }
 // this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two, in rounds of 512 workgroups; 11 us of
 // prologue, epilogue and launches, 3 us for each further round; the transformed filter written and read at 4 TB/s; a projection shortcut is a launch of
@@ -397,23 +488,40 @@ double wino_us(const FwdProblem &p, int s) {
   return 11.0 + 3.0 * (full + (rest > 0) - 1) + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per +
          finish_us(p, s) + proj;
 }
+// its variant of 32 filters: 0.8, 1.4 and 2.1 us per step with one, two and three workgroups on a CU, 6 us of prologue,
+// epilogue and launch, 4.5 us for a filter launch of its own; the direct kernel of 64x32 tiles in its place 0.3 us per step
+// and workgroup on a CU.  On 36 random shapes (17 ... 32 filters, 16 ... 512 channels) this one is chosen 10 times and is the
+// faster one each time, by 3 to 33 % (us, direct / this with its filter launch: 64 -> 32, 204 800 pixels 72.5 / 50.1; 16 -> 28, 174 592
+// pixels 29.2 / 22.6; 64 -> 32, 16 384 pixels 12.0 / 14.7, direct); its error is the smaller one on all 36 (64 -> 32 2.9e-7 / 2.1e-7)
+double narrow_us(const FwdProblem &p, int s, bool ready) {
+  const int nchunks = (p.C + CH - 1) / CH;
+  const long long w = workgroups(p) * s, full = w / 768, rest = w % 768;
+  const double per = 2.1 * full + (rest > 512 ? 2.1 : rest > 256 ? 1.4 : rest > 0 ? 0.8 : 0.0);
+  return (ready ? 6.0 : 10.5) + 3.0 * (full + (rest > 0) - 1) + (nchunks + s - 1) / s * per + finish_us(p, s);
+}
+double narrow_direct_us(const FwdProblem &p, int ks) {
+  const int nkb = (p.Kg + 31) / 32;
+  const long long w = (long long)((p.M + 63) / 64) * ks;
+  return 7.3 + (nkb + ks - 1) / ks * 0.3 * ((w + 255) / 256) + finish_us(p, ks);
+}
 }  // namespace
 
-int wino_fwd_pick_splits(const FwdProblem &p, int most) {
-  // up to 32 filters half of a workgroup's columns would be padding; below 16 channels the result's own
+int wino_fwd_pick_splits(const FwdProblem &p, int ks, int most, bool ready) {
+  // up to 16 filters half of a workgroup's columns would be padding; below 16 channels the result's own
   // traffic is all there is to either kernel (8 channels, 16 384 x 256 results: 17 / 14 + 5 for the filter launch)
-  if (p.N <= 32 || p.C < 16 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
+  if (p.N <= 16 || p.C < 16 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
   const int nchunks = (p.C + CH - 1) / CH;
-  const int ks = igemm_fwd_pick_ksplits(p.M, p.N, p.Kg, p.C, p.R * p.S);  // of the direct kernel
+  const bool narrow = wino_nb(p.N) == 32;
   double best = 0.0;
   int splits = 0;
   for (int s = 1; s <= 16; s *= 2) {
     if (4 * s < 3 * ks) continue;
     if (s > most) break;
     if (s > 1 && (nchunks / s < 2 || workgroups(p) * s > 512)) break;
-    const double us = wino_us(p, s);
+    const double us = narrow ? narrow_us(p, s, ready) : wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;
   }
+  if (narrow) return splits && best < 0.93 * narrow_direct_us(p, ks) ? splits : 0;
   // the direct kernel: steps of 32 products, 128x128 tiles one per CU, or 64x64 ones up to four, in rounds
   // of 1024 workgroups (2 us for each further one)
   const int nkb = (p.Kg + 31) / 32;
@@ -426,25 +534,37 @@ int wino_fwd_pick_splits(const FwdProblem &p, int most) {
   return splits && best < 0.93 * direct ? splits : 0;
 }
 
-hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, hipStream_t st) {
+hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, const WinoFilter *also, hipStream_t st) {
   WinoAux q;
   const int TH = (p.Ho + 1) / 2, B = p.M / (p.Ho * p.Wo);
   q.TW = (p.Wo + 1) / 2, q.TPI = TH * q.TW, q.T = B * q.TPI;
   q.nchunks = (p.C + CH - 1) / CH;
-  q.nblk = (p.N + NB - 1) / NB;
+  const int nb = wino_nb(p.N);
+  q.nblk = (p.N + nb - 1) / nb;
   q.div_tpi = FastDiv(q.TPI), q.div_tw = FastDiv(q.TW);
   q.x_bytes = (uint32_t)((long long)B * p.H * p.W * p.C * 4);
   q.u_bytes = (uint32_t)(wino_fwd_filter_floats(p.N, p.C) * 4);
   q.U = U;
   const int splits = p.ksplits > 1 ? p.ksplits : 1;
   q.per = (q.nchunks + splits - 1) / splits;
-  if (!filter_ready) {
-    hipLaunchKernelGGL(wino_filter_kernel, dim3((2 * q.nchunks + 7) / 8, q.nblk * 2), dim3(256), 0, st, p.w, U, p.N, p.C,
-                       q.nchunks);
+  if (!filter_ready || also) {
+    FilterJobs js;
+    int blocks = js.blocks0 = 0, n = 0;
+    for (int k = 0; k < 2; ++k) {
+      if (k == 0 ? filter_ready : !also) continue;
+      const WinoFilter f = k ? *also : WinoFilter{p.w, U, p.N, p.C};
+      const int fnb = wino_nb(f.N);
+      js.f[n] = f, js.nchunks[n] = (f.C + CH - 1) / CH, js.bx[n] = (2 * js.nchunks[n] + 7) / 8;
+      blocks += js.bx[n] * ((f.N + fnb - 1) / fnb) * (fnb / 32);
+      if (n++ == 0) js.blocks0 = blocks;
+    }
+    hipLaunchKernelGGL(wino_filter_kernel, dim3(blocks), dim3(256), 0, st, js);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(wino_fwd_kernel, dim3(q.nblk * ((q.T + TB - 1) / TB), splits), dim3(NTHREADS), 0, st, p, q);
+  const dim3 grid(q.nblk * ((q.T + TB - 1) / TB), splits);
+  if (nb == 64) hipLaunchKernelGGL(wino_fwd_kernel<2>, grid, dim3(NTHREADS), 0, st, p, q);
+  else hipLaunchKernelGGL(wino_fwd_kernel<1>, grid, dim3(NTHREADS), 0, st, p, q);
   return hipGetLastError();
 }
 
