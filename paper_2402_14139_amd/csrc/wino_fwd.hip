@@ -63,8 +63,8 @@ struct WinoAux {
   const float *U;
 };
 
-__device__ inline float4 bload(__amdgpu_buffer_rsrc_t r, int voff) {
-  const floatx4 v = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+__device__ inline float4 bload(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  const floatx4 v = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
   return make_float4(v.x, v.y, v.z, v.w);
 }
 __device__ inline float el(const float4 &v, int k) { return k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w; }
@@ -175,11 +175,20 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
     for (int i = 0; i < 4; ++i)
       xoff[i] = (base + i * p.C * 4) | ((rok & ((unsigned)(wi + i) < (unsigned)p.W)) ? 0 : OOB);
   }
-  auto gload = [&](int s, float4 *sx) {
-    const int c0 = s * CH + st_half * 4;
-    const int bad = ((c0 < p.C) & (s < s_hi)) ? 0 : OOB;
+  // A load's offset is a lane's constant and a scalar that advances: no vector arithmetic beside the MFMAs (54 -> 35
+  // vector instructions a step; 512 -> 512 channels, 8192 pixels: workgroups end after 162 / 154 us).  Steps past the
+  // end load the last one again, which nothing reads.  The upper half of a last step of four channels is out of range.
+  const int half_step = (p.C % CH) ? q.nchunks - 1 : -1;
+  auto last = [&](int s) { return s < s_hi ? s : s_hi - 1; };
+  auto halve = [&](int s) {  // in front of gload(s)
+    if (last(s) == half_step) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sx[i] = bload(rsx, (xoff[i] + s * (CH * 4)) | bad);
+      for (int i = 0; i < 4; ++i) xoff[i] |= st_half ? OOB : 0;
+    }
+  };
+  auto gload = [&](int s, float4 *sx) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sx[i] = bload(rsx, xoff[i], last(s) * (CH * 4));
   };
   float *const st_base = S + (st_row * 4 * TB + st_tile) * CH + st_half * 4;
   auto lstore = [&](int buf, const float4 *sx) {
@@ -203,7 +212,7 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
   float4 uf[4][NF];  // fragments of column b: re-loaded one section after their last use
   auto uload = [&](int s, int b) {
 #pragma unroll
-    for (int n = 0; n < NF; ++n) uf[b][n] = bload(rsu, ubase + (s * UB + b * UP + n * 256) * 4);
+    for (int n = 0; n < NF; ++n) uf[b][n] = bload(rsu, ubase + (b * UP + n * 256) * 4, last(s) * (UB * 4));
   };
 
   floatx16 acc[4][NF];
@@ -218,8 +227,11 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
   float4 sx[4];
   {
     float4 sa[4], sb[4];
+    halve(s_lo);
     gload(s_lo, sa);
+    halve(s_lo + 1);
     gload(s_lo + 1, sb);
+    halve(s_lo + 2);
     gload(s_lo + 2, sx);
 #pragma unroll
     for (int b = 0; b < 3; ++b) uload(s_lo, b);
@@ -234,6 +246,7 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
   // fence: left alone the compiler gathers all loads at the end of the step, right in front of their use.
   int buf = 0;  // buffer of step s
   for (int s = s_lo; s < s_hi; ++s) {
+    halve(s + 3);
     __syncthreads();  // step s+1 is in buffer buf^1; everybody has read step s out of buffer buf
     const float4 v[4] = {sub4(tr[0], tr[2]), add4(tr[1], tr[2]), sub4(tr[2], tr[1]), sub4(tr[1], tr[3])};
     __builtin_amdgcn_sched_barrier(0);
