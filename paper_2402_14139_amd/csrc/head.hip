@@ -19,6 +19,15 @@ __device__ inline void adaptive_window(int i, int L, int O, int &lo, int &hi) {
   hi = ((i + 1) * L + O - 1) / O;
 }
 
+// 1 / elements of the window that pooled feature f averages; 1 for max pooling
+__device__ inline float pool_scale(const HeadShape &s, int f) {
+  if (s.scale != 0.f) return s.scale;  // the same for all
+  const int cell = (int)s.div_a.div((uint32_t)f), ci = (int)s.div_ow.div((uint32_t)cell), cj = cell - ci * s.ow;
+  const int h0 = (int)s.div_oh.div((uint32_t)(ci * s.Hu)), h1 = (int)s.div_oh.div((uint32_t)((ci + 1) * s.Hu + s.oh - 1));
+  const int w0 = (int)s.div_ow.div((uint32_t)(cj * s.Wu)), w1 = (int)s.div_ow.div((uint32_t)((cj + 1) * s.Wu + s.ow - 1));
+  return 1.f / (float)((h1 - h0) * (w1 - w0));
+}
+
 __device__ inline float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -28,6 +37,23 @@ __device__ inline float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
+}
+
+// V consecutive floats: channels of one element of the head's activation, features of a row of Wf
+template <int V>
+struct Chan {
+  float v[V];
+};
+template <int V>
+__device__ inline Chan<V> load_chan(const float *__restrict__ at) {
+  Chan<V> c;
+  if constexpr (V == 4) {
+    const float4 x = *reinterpret_cast<const float4 *>(at);
+    c.v[0] = x.x, c.v[1] = x.y, c.v[2] = x.z, c.v[3] = x.w;
+  } else {
+    c.v[0] = at[0];
+  }
+  return c;
 }
 
 // F_n: adaptive average pool (PMAX: adaptive max pool, which also records the flat position
@@ -171,10 +197,82 @@ __global__ __launch_bounds__(HT) void head_pool_kernel(HeadShape s, float *__res
                       red, redi, nullptr, nullptr, 0);
 }
 
-// Logits of one sample (all threads of a workgroup): z[q] = bf[q] + sum_f Wf[q][f] * pq[f], pq staged in
-// LDS.  zp: HT floats of LDS.  Ends with a barrier.
-__device__ inline void logits_sample(const HeadShape &s, const float *pq, float *z, float *zp,
-                                     const float *__restrict__ Wf, const float *__restrict__ bf) {
+// Logits of one sample (all threads of a workgroup): z[q] = bf[q] + sum_f Wf[q][f] * pq[f], pq staged in LDS; ends
+// with a barrier.  L lanes per class read its row in whole 16-byte groups side by side and hold eight running
+// sums each, added in a tree, so that a result is 8 * L sums of F / (8 * L) products (relative error against 64 bits,
+// 1024 features, 100 classes, L = 8: 1.0e-7; two sums of 512 2.1e-7).  NQ classes per thread at a time, 16 / NQ groups of a
+// row: sixteen loads are in flight together.  What bounds it is the latency of those loads and, with several
+// workgroups on a CU, the lines they touch (one thread per class and part of a row touched a line per lane: 128 features, 100
+// classes, three workgroups on a CU 5.2 us, this 3.6; a single one, 64 features, 100 classes: 4.8 / 5.5 in the exit's launch).
+template <int L, int NQ>
+__device__ inline void logits_tree(const HeadShape &s, const float *pq, float *z, const float *__restrict__ Wf,
+                                   const float *__restrict__ bf) {
+  constexpr int G = HT / L, NH = 16 / NQ;  // classes side by side; groups of a row in flight
+  const int l = threadIdx.x & (L - 1), g = threadIdx.x / L;
+  for (int q0 = 0; q0 < s.Cls; q0 += G * NQ) {
+    float acc[NQ][8];
+    const float *wr[NQ];
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+      wr[k] = Wf + (long long)min(q0 + k * G + g, s.Cls - 1) * s.F;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[k][e] = 0.f;
+    }
+    if ((s.F & 3) == 0) {
+      for (int f1 = 0; f1 < s.F; f1 += 4 * L * NH) {
+        const int f0 = f1 + 4 * l;
+        float4 w[NH][NQ];
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+          const int f = f0 + h * 4 * L;
+          if (f1 + h * 4 * L < s.F)  // (the same for all lanes)
+#pragma unroll
+            for (int k = 0; k < NQ; ++k)
+              if (q0 + k * G < s.Cls) w[h][k] = *reinterpret_cast<const float4 *>(wr[k] + (f < s.F ? f : 0));
+        }
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+          const int f = f0 + h * 4 * L, o = 4 * (h & 1);
+          const bool ok = f < s.F;
+          if (f1 + h * 4 * L >= s.F) break;
+          const float4 x = *reinterpret_cast<const float4 *>(pq + (ok ? f : 0));
+#pragma unroll
+          for (int k = 0; k < NQ; ++k) {
+            if (q0 + k * G >= s.Cls) break;
+            acc[k][o] = ok ? acc[k][o] + w[h][k].x * x.x : acc[k][o];
+            acc[k][o + 1] = ok ? acc[k][o + 1] + w[h][k].y * x.y : acc[k][o + 1];
+            acc[k][o + 2] = ok ? acc[k][o + 2] + w[h][k].z * x.z : acc[k][o + 2];
+            acc[k][o + 3] = ok ? acc[k][o + 3] + w[h][k].w * x.w : acc[k][o + 3];
+          }
+        }
+      }
+    } else {
+      for (int f0 = l; f0 < s.F; f0 += 8 * L)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int f = f0 + e * L;
+          if (f >= s.F) break;
+#pragma unroll
+          for (int k = 0; k < NQ; ++k) acc[k][e] += wr[k][f] * pq[f];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+      if (q0 + k * G >= s.Cls) break;
+      float v = ((acc[k][0] + acc[k][1]) + (acc[k][2] + acc[k][3])) + ((acc[k][4] + acc[k][5]) + (acc[k][6] + acc[k][7]));
+#pragma unroll
+      for (int m = L / 2; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+      const int q = q0 + k * G + g;
+      if (l == 0 && q < s.Cls) z[q] = v + (bf ? bf[q] : 0.f);
+    }
+  }
+  __syncthreads();
+}
+
+// The same for few features, whose rows are a line or two: fewer instructions, each run once (head_sample, 32 features, 100
+// classes, with dpq_few: 10.6 us, 11.9 with the form above; the other one from 128 features on).  zp: HT floats of LDS.
+__device__ inline void logits_few(const HeadShape &s, const float *pq, float *z, float *zp,
+                                  const float *__restrict__ Wf, const float *__restrict__ bf) {
   const int t = threadIdx.x;
   // logits: P threads per class, each over a contiguous 1/P of the features (P a power of two with
   // P * Cls <= 256 and whole 16-byte groups per part), so that one batch of independent loads per
@@ -224,12 +322,21 @@ __device__ inline void logits_sample(const HeadShape &s, const float *pq, float 
   __syncthreads();
 }
 
-// out[f] = sum_q dz[q] * Wf[q][f] (z holds dz; all threads of a workgroup).  With fewer features than
+// Few classes: more lanes each, one class per thread.  (The exit's logits always take logits_tree<8, 4>.)
+__device__ inline void logits_sample(const HeadShape &s, const float *pq, float *z, float *zp, const float *__restrict__ Wf,
+                                     const float *__restrict__ bf) {
+  if (s.F < 128) logits_few(s, pq, z, zp, Wf, bf);
+  else if (s.Cls > 64) logits_tree<8, 4>(s, pq, z, Wf, bf);
+  else if (s.Cls > 16) logits_tree<8, 2>(s, pq, z, Wf, bf);
+  else logits_tree<16, 1>(s, pq, z, Wf, bf);
+}
+
+// out[f] = pool_scale(f) * sum_q dz[q] * Wf[q][f] (z holds dz; all threads of a workgroup).  With fewer features than
 // threads the classes are cut into P ranges, one per group of F threads, and the P sums added in
 // order through zp: a chain of Cls / P loads instead of Cls (head_sample, 16 features, 100 classes, with
 // the pooling tree: 12.9 -> 10.7 us).
-__device__ inline void dpq_sample(const HeadShape &s, const float *z, float *zp, const float *__restrict__ Wf,
-                                  float *out) {
+__device__ inline void dpq_few(const HeadShape &s, const float *z, float *zp, const float *__restrict__ Wf,
+                               float *out) {
   const int t = threadIdx.x;
   int P = 1;
   while (2 * P * s.F <= HT && 32 * P <= s.Cls) P *= 2;  // at least 16 classes each
@@ -238,7 +345,7 @@ __device__ inline void dpq_sample(const HeadShape &s, const float *z, float *zp,
       float acc = 0.f;
 #pragma unroll 10
       for (int q = 0; q < s.Cls; ++q) acc += z[q] * Wf[(long long)q * s.F + f];
-      out[f] = acc;
+      out[f] = acc * pool_scale(s, f);
     }
     return;
   }
@@ -254,24 +361,72 @@ __device__ inline void dpq_sample(const HeadShape &s, const float *z, float *zp,
   if (t < s.F) {
     float acc = zp[t];
     for (int k = 1; k < P; ++k) acc += zp[k * s.F + t];
-    out[t] = acc;
+    out[t] = acc * pool_scale(s, t);
   }
+}
+
+// The same from 128 features on: V features per thread (4: 16-byte loads),
+// and the classes cut into P ranges, one per group of F / V threads, their sums added in order through zp (HT * 4
+// floats): a chain of Cls / P loads instead of Cls (128 features, 100 classes: 2.5 us with two ranges and single
+// floats, 2.1 so).
+__device__ inline void dpq_many(const HeadShape &s, const float *z, float *zp, const float *__restrict__ Wf,
+                                float *out) {
+  constexpr int V = 4, NB = 14;  // (a hundred classes in eight ranges are one batch)
+  const int t = threadIdx.x, FG = s.F / V;
+  int P = 1;
+  while (P < 16 && 2 * P * FG <= HT && 8 * P <= s.Cls) P *= 2;  // at least 4 classes each
+  const int qn = (s.Cls + P - 1) / P;
+  for (int i = t; i < FG * P; i += HT) {  // (once where P > 1)
+    const int part = i / FG, f = (i - part * FG) * V;
+    const int q1 = min(s.Cls, (part + 1) * qn);
+    float acc[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[e] = 0.f;
+    const float *const wf = Wf + f;
+    for (int q0 = part * qn; q0 < q1; q0 += NB) {  // a batch of loads in flight, the last few of them repeated
+      Chan<V> w[NB];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) w[u] = load_chan<V>(wf + min(q0 + u, q1 - 1) * s.F);
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const float d = z[min(q0 + u, q1 - 1)];
+#pragma unroll
+        for (int e = 0; e < V; ++e) acc[e] = q0 + u < q1 ? acc[e] + d * w[u].v[e] : acc[e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) (P == 1 ? out : zp + part * s.F)[f + e] = acc[e];
+  }
+  __syncthreads();
+  for (int f = t; f < s.F; f += HT) {
+    float acc = P == 1 ? out[f] : zp[f];
+    for (int k = 1; k < P; ++k) acc += zp[k * s.F + f];
+    out[f] = acc * pool_scale(s, f);
+  }
+}
+__device__ inline void dpq_sample(const HeadShape &s, const float *z, float *zp, const float *__restrict__ Wf,
+                                  float *out) {
+  if (s.F < 128 || (s.F & 3)) dpq_few(s, z, zp, Wf, out);
+  else dpq_many(s, z, zp, Wf, out);
 }
 
 // gamma_n and Eq. 3 for one sample (all threads of a workgroup): logits (the pooled features pq[F]
 // already staged in LDS), log-sum-exp, per-sample loss, dL/dz, and -- the
 // sample's dz being at hand -- the gradient w.r.t. the pooled features
-// dPq[f] = sum_q dz[q] * Wf[q][f], stored to dPq_out (global row of the sample, or an LDS array).
+// dPq[f] = sum_q dz[q] * Wf[q][f], divided by the elements that f averages and stored to dPq_out (global row of the sample, or an LDS array).
 // z: Cls floats of LDS, red: 8 floats of LDS.  write = false: dz and the loss are formed but not
 // stored (a workgroup that only needs dPq of a sample another workgroup reports).
+// after_logits is called once the linear layer has been read (loads that may run under the rest).
+template <class Fn>
 __device__ inline void fc_loss_sample(const HeadShape &s, int n, const float *pq, float *z, float *red,
                                       const int32_t *__restrict__ labels, const float *__restrict__ Wf,
                                       const float *__restrict__ bf, float *__restrict__ dz,
-                                      float *__restrict__ loss_n, float *dPq_out, bool write = true) {
+                                      float *__restrict__ loss_n, float *dPq_out, bool write, Fn after_logits) {
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
-  __shared__ float zp[HT];
+  __shared__ __attribute__((aligned(16))) float zp[HT * 4];
   logits_sample(s, pq, z, zp, Wf, bf);
+  after_logits();
 
   if (s.mse) {
     // squared error against the one-hot label, mean over the classes (the batch mean follows)
@@ -325,14 +480,14 @@ __global__ __launch_bounds__(HT) void head_fc_kernel(HeadShape s, const float *_
                                                      const float *__restrict__ Wf, const float *__restrict__ bf,
                                                      float *__restrict__ dz, float *__restrict__ loss_n,
                                                      float *__restrict__ dPq) {
-  extern __shared__ float sm[];
+  extern __shared__ __attribute__((aligned(16))) float sm[];
   float *pq = sm;           // [F]
   float *z = pq + s.F;      // [Cls]
   float *red = z + s.Cls;   // [8]
   const int n = blockIdx.x, t = threadIdx.x;
   for (int f = t; f < s.F; f += HT) pq[f] = Pq[(long long)n * s.F + f];
   __syncthreads();
-  fc_loss_sample(s, n, pq, z, red, labels, Wf, bf, dz, loss_n, dPq + (long long)n * s.F);
+  fc_loss_sample(s, n, pq, z, red, labels, Wf, bf, dz, loss_n, dPq + (long long)n * s.F, true, [] {});
 }
 
 // The same step for wide heads (many pooled features): G samples per workgroup share every load
@@ -348,7 +503,7 @@ __global__ __launch_bounds__(WT) void head_fc_wide_kernel(HeadShape s, const flo
                                                           const float *__restrict__ Wf,
                                                           const float *__restrict__ bf, float *__restrict__ dz,
                                                           float *__restrict__ loss_n, float *__restrict__ dPq) {
-  extern __shared__ float sm[];
+  extern __shared__ __attribute__((aligned(16))) float sm[];
   float *pq = sm;               // [G][F]
   float *z = pq + G * s.F;      // [G][Cls]
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -420,6 +575,7 @@ __global__ __launch_bounds__(WT) void head_fc_wide_kernel(HeadShape s, const flo
   }
   __syncthreads();
   for (int f = t; f < s.F; f += WT) {
+    const float scale = pool_scale(s, f);
     float acc[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g] = 0.f;
@@ -431,63 +587,8 @@ __global__ __launch_bounds__(WT) void head_fc_wide_kernel(HeadShape s, const flo
     }
 #pragma unroll
     for (int g = 0; g < G; ++g)
-      if (g < ng) dPq[(long long)(n0 + g) * s.F + f] = acc[g];
+      if (g < ng) dPq[(long long)(n0 + g) * s.F + f] = acc[g] * scale;
   }
-}
-
-// Logits of one sample for the exit, which reports them: 8 lanes per class with eight running sums each,
-// added in a tree, so that a result is 64 sums of F / 64 products (relative error against 64 bits, 1024 features, 100
-// classes: 1.0e-7; with logits_sample, two sums of 512, 2.1e-7).  Four classes per thread at a time: their loads are
-// in flight together (100 samples, 64 features, 100 classes: 17.0 us with one wavefront per class after the
-// other, 5.5 so; logits_sample took 4.8).
-__device__ inline void exit_logits_sample(const HeadShape &s, const float *pq, float *z, const float *__restrict__ Wf,
-                                          const float *__restrict__ bf) {
-  constexpr int L = 8, NQ = 4, G = HT / L;  // lanes per class, classes per thread, classes side by side
-  const int l = threadIdx.x & (L - 1), g = threadIdx.x / L;
-  for (int q0 = 0; q0 < s.Cls; q0 += G * NQ) {
-    float acc[NQ][8];
-    const float *wr[NQ];
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-      wr[k] = Wf + (long long)min(q0 + k * G + g, s.Cls - 1) * s.F;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[k][e] = 0.f;
-    }
-    if ((s.F & 3) == 0) {
-      for (int f0 = 4 * l; f0 < s.F; f0 += 8 * L)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int f = f0 + h * 4 * L;
-          if (f >= s.F) break;
-          float4 w[NQ];
-#pragma unroll
-          for (int k = 0; k < NQ; ++k) w[k] = *reinterpret_cast<const float4 *>(wr[k] + f);
-#pragma unroll
-          for (int k = 0; k < NQ; ++k) {
-            acc[k][4 * h] += w[k].x * pq[f], acc[k][4 * h + 1] += w[k].y * pq[f + 1];
-            acc[k][4 * h + 2] += w[k].z * pq[f + 2], acc[k][4 * h + 3] += w[k].w * pq[f + 3];
-          }
-        }
-    } else {
-      for (int f0 = l; f0 < s.F; f0 += 8 * L)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int f = f0 + e * L;
-          if (f >= s.F) break;
-#pragma unroll
-          for (int k = 0; k < NQ; ++k) acc[k][e] += wr[k][f] * pq[f];
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-      float v = ((acc[k][0] + acc[k][1]) + (acc[k][2] + acc[k][3])) + ((acc[k][4] + acc[k][5]) + (acc[k][6] + acc[k][7]));
-#pragma unroll
-      for (int m = L / 2; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
-      const int q = q0 + k * G + g;
-      if (l == 0 && q < s.Cls) z[q] = v + (bf ? bf[q] : 0.f);
-    }
-  }
-  __syncthreads();
 }
 
 // Forward-only head for early-exit evaluation: one sample per workgroup; logits, then the arg-max
@@ -498,7 +599,7 @@ __global__ __launch_bounds__(HT) void head_predict_kernel(HeadShape s, const flo
                                                           const float *__restrict__ bf,
                                                           float *__restrict__ logits_out, int32_t *__restrict__ pred,
                                                           int32_t *__restrict__ hit) {
-  extern __shared__ float sm[];
+  extern __shared__ __attribute__((aligned(16))) float sm[];
   __shared__ float rv[HT];
   __shared__ int ri[HT];
   float *pq = sm;          // [F]
@@ -506,7 +607,7 @@ __global__ __launch_bounds__(HT) void head_predict_kernel(HeadShape s, const flo
   const int n = blockIdx.x, t = threadIdx.x;
   for (int f = t; f < s.F; f += HT) pq[f] = Pq[(long long)n * s.F + f];
   __syncthreads();
-  exit_logits_sample(s, pq, z, Wf, bf);
+  logits_tree<8, 4>(s, pq, z, Wf, bf);
   if (logits_out)
     for (int q = t; q < s.Cls; q += HT) logits_out[(long long)n * s.Cls + q] = z[q];
   float best = -INFINITY;
@@ -550,44 +651,32 @@ __global__ __launch_bounds__(HT) void loss_mean_kernel(const float *__restrict__
   loss_mean_block(loss_n, B, out, red);
 }
 
-// dU for V consecutive channels of one element (n, hh, w, av): F_n backward + aux ReLU mask.
+// dU for V consecutive channels u of one element (n, hh, w, av): F_n backward + aux ReLU mask.
 // dpq points at the sample's dPq[F] (global or LDS), pargn at its selection record (max pooling).
 template <int V>
-__device__ inline void du_element(const HeadShape &s, int hh, int w, int av, const float *__restrict__ u_at,
-                                  const float *dpq, const int32_t *pargn, float *__restrict__ du_at) {
-  float u[V], acc[V];
-  if constexpr (V == 4) {
-    const float4 t4 = *reinterpret_cast<const float4 *>(u_at);
-    u[0] = t4.x, u[1] = t4.y, u[2] = t4.z, u[3] = t4.w;
-  } else {
-    u[0] = u_at[0];
-  }
+__device__ inline void du_element(const HeadShape &s, int hh, int w, int av, const Chan<V> &u, const float *dpq,
+                                  const int32_t *pargn, float *__restrict__ du_at) {
+  float acc[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) acc[e] = 0.f;
-  for (int ci = 0; ci < s.oh; ++ci) {
-    int h0, h1;
-    adaptive_window(ci, s.Hu, s.oh, h0, h1);
-    if (hh < h0 || hh >= h1) continue;
-    for (int cj = 0; cj < s.ow; ++cj) {
-      int w0, w1;
-      adaptive_window(cj, s.Wu, s.ow, w0, w1);
-      if (w < w0 || w >= w1) continue;
+  // the windows that hold row hh and column w: floor(i L / O) <= hh < ceil((i + 1) L / O)
+  const int ci0 = (int)s.div_hu.div((uint32_t)(hh * s.oh)), ci1 = (int)s.div_hu.div((uint32_t)((hh + 1) * s.oh - 1));
+  const int cj0 = (int)s.div_wu.div((uint32_t)(w * s.ow)), cj1 = (int)s.div_wu.div((uint32_t)((w + 1) * s.ow - 1));
+  for (int ci = ci0; ci <= ci1; ++ci)
+    for (int cj = cj0; cj <= cj1; ++cj) {
       const int fo = (ci * s.ow + cj) * s.A + av * V;
-      const float *src = dpq + fo;
       if (s.pmax) {  // max pooling hands the gradient to the element it selected
 #pragma unroll
         for (int e = 0; e < V; ++e)
-          if (pargn[fo + e] == hh * s.Wu + w) acc[e] += src[e];
+          if (pargn[fo + e] == hh * s.Wu + w) acc[e] += dpq[fo + e];
       } else {
-        const float inv = 1.f / (float)((h1 - h0) * (w1 - w0));
 #pragma unroll
-        for (int e = 0; e < V; ++e) acc[e] += src[e] * inv;
+        for (int e = 0; e < V; ++e) acc[e] += dpq[fo + e];
       }
     }
-  }
 #pragma unroll
   for (int e = 0; e < V; ++e)
-    if (s.relu && !(u[e] > 0.f)) acc[e] = 0.f;
+    if (s.relu && !(u.v[e] > 0.f)) acc[e] = 0.f;
   if constexpr (V == 4) {
     *reinterpret_cast<float4 *>(du_at) = make_float4(acc[0], acc[1], acc[2], acc[3]);
   } else {
@@ -611,7 +700,7 @@ __global__ __launch_bounds__(HT) void head_sample_kernel(HeadShape s, float *__r
                                                          float *__restrict__ Pq, int32_t *__restrict__ parg,
                                                          float *__restrict__ dz, float *__restrict__ loss_n,
                                                          float *__restrict__ dU, RelayJob rj, int CA, int NS) {
-  extern __shared__ float sm[];
+  extern __shared__ __attribute__((aligned(16))) float sm[];
   __shared__ float red[HT * V];
   __shared__ int redi[PMAX ? HT * V : 1];
   const int t = threadIdx.x;
@@ -630,14 +719,14 @@ __global__ __launch_bounds__(HT) void head_sample_kernel(HeadShape s, float *__r
     pool_pairs<V, PMAX>(s, (long long)n * cells + c0, (long long)(n + 1) * cells, U, part, splits, ba, Pq, parg, CA,
                         NS, red, redi, pq, PMAX ? pargl : nullptr, (long long)n * cells);
   __syncthreads();  // (with splits > 0 the sample's U was formed and written on the way: visible to the workgroup)
-  fc_loss_sample(s, n, pq, z, red8, labels, Wf, bf, dz, loss_n, dpq);
+  fc_loss_sample(s, n, pq, z, red8, labels, Wf, bf, dz, loss_n, dpq, true, [] {});
   __syncthreads();
   const int AV = s.A / V, per_n = s.Hu * s.Wu * AV;
   const long long base = (long long)n * per_n;
   for (int i = t; i < per_n; i += HT) {
-    const int av = i % AV, r = i / AV;
-    const int w = r % s.Wu, hh = r / s.Wu;
-    du_element<V>(s, hh, w, av, U + (base + i) * V, dpq, PMAX ? pargl : nullptr, dU + (base + i) * V);
+    const int r = (int)s.div_av.div((uint32_t)i), av = i - r * AV;
+    const int hh = (int)s.div_wu.div((uint32_t)r), w = r - hh * s.Wu;
+    du_element<V>(s, hh, w, av, load_chan<V>(U + (base + i) * V), dpq, PMAX ? pargl : nullptr, dU + (base + i) * V);
   }
 }
 
@@ -650,14 +739,14 @@ __global__ __launch_bounds__(HT) void head_sample_kernel(HeadShape s, float *__r
 // here too (and Pq stored by slice 0) from the column sums the aux convolution's epilogue left.
 // Dynamic LDS: 2*F + Cls + 8 floats.
 template <int V>
-__global__ __launch_bounds__(HT) void head_wide_kernel(HeadShape s, int NS, const float *__restrict__ U,
+__global__ __launch_bounds__(HT, 3) void head_wide_kernel(HeadShape s, int NS, const float *__restrict__ U,
                                                        float *__restrict__ Pq, const float *__restrict__ ppart,
                                                        const int32_t *__restrict__ labels,
                                                        const float *__restrict__ Wf, const float *__restrict__ bf,
                                                        float *__restrict__ dz, float *__restrict__ loss_n,
                                                        const int32_t *__restrict__ parg, float *__restrict__ dU,
                                                        RelayJob rj) {
-  extern __shared__ float sm[];
+  extern __shared__ __attribute__((aligned(16))) float sm[];
   const int t = threadIdx.x;
   if ((int)blockIdx.x >= s.B * NS) {
     relay_block(rj, (int)blockIdx.x - s.B * NS);
@@ -676,25 +765,39 @@ __global__ __launch_bounds__(HT) void head_wide_kernel(HeadShape s, int NS, cons
     const int gpr = s.Wu >> 4;                // 16-pixel groups per image row
     const int gph = split ? 1 : (gpr >> 1);   // ... per half row
     const float inv = 1.f / (float)((s.Hu >> 1) * (s.Wu >> 1));
-    for (int f = t; f < s.F; f += HT) {
+    // The partials of a feature go to P threads (one batch of loads each where that many threads are left); their sums
+    // are added in order.
+    __shared__ float pp[HT];
+    const int np = (s.Hu >> 1) * gph;
+    int P = 1;
+    while (P < 8 && 2 * P * s.F <= HT && 4 * P <= np) P *= 2;
+    const int ni = (np + P - 1) / P;
+    for (int k = t; k < s.F * P; k += HT) {  // (once where P > 1)
+      const int part = k / s.F, f = k - part * s.F;
       const int cell = f / s.A, a = f - cell * s.A;
       const int ci = cell >> 1, cj = cell & 1;
       // partial i of the cell: image row ci*Hu/2 + i / gph, group i % gph of the half row; loaded
       // eight at a time (independent loads), added in order
-      const int np = (s.Hu >> 1) * gph;
       const float *src = ppart + (split ? cj : 0) * s.A + a;
+      const int e1 = min(np, (part + 1) * ni);
       float acc = 0.f;
-      for (int i0 = 0; i0 < np; i0 += 8) {
+      for (int e0 = part * ni; e0 < e1; e0 += 8) {
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const int i = i0 + u, hr = i / gph;
+          const int i = e0 + u, hr = i / gph;
           const long long r16 = ((long long)n * s.Hu + ci * (s.Hu >> 1) + hr) * gpr + (split ? 0 : cj * gph + (i - hr * gph));
-          v[u] = i < np ? src[r16 * 2 * s.A] : 0.f;
+          v[u] = i < e1 ? src[r16 * 2 * s.A] : 0.f;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc += v[u];
       }
+      (P == 1 ? pq : pp)[k] = acc;
+    }
+    if (P > 1) __syncthreads();
+    for (int f = t; f < s.F; f += HT) {  // (without parts each thread reads what it wrote)
+      float acc = P == 1 ? pq[f] : pp[f];
+      for (int k = 1; k < P; ++k) acc += pp[k * s.F + f];
       pq[f] = acc * inv;
       if (sl == 0) Pq[(long long)n * s.F + f] = acc * inv;
     }
@@ -702,18 +805,29 @@ __global__ __launch_bounds__(HT) void head_wide_kernel(HeadShape s, int NS, cons
     for (int f = t; f < s.F; f += HT) pq[f] = Pq[(long long)n * s.F + f];
   }
   __syncthreads();
-  fc_loss_sample(s, n, pq, z, red8, labels, Wf, bf, dz, loss_n, dpq, sl == 0);
-  __syncthreads();
+  // the slice's first elements of U: their loads run under the softmax
+  constexpr int AHEAD = 4;
   const int AV = s.A / V, per_n = s.Hu * s.Wu * AV;
   const int per_sl = (per_n + NS - 1) / NS;
-  const int i1 = min(per_n, (sl + 1) * per_sl);
+  const int i0 = sl * per_sl + t, i1 = min(per_n, (sl + 1) * per_sl);
   const long long base = (long long)n * per_n;
-  for (int i = sl * per_sl + t; i < i1; i += HT) {
-    const int av = i % AV, r = i / AV;
-    const int w = r % s.Wu, hh = r / s.Wu;
-    du_element<V>(s, hh, w, av, U + (base + i) * V, dpq, s.pmax ? parg + (long long)n * s.F : nullptr,
-                  dU + (base + i) * V);
-  }
+  const float *const un = U + base * V;
+  Chan<V> ahead[AHEAD];
+  auto prefetch = [&] {
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) ahead[k] = load_chan<V>(un + min(i0 + k * HT, per_n - 1) * V);
+  };
+  fc_loss_sample(s, n, pq, z, red8, labels, Wf, bf, dz, loss_n, dpq, sl == 0, prefetch);
+  __syncthreads();
+  auto element = [&](int i, const Chan<V> &u) {
+    const int r = (int)s.div_av.div((uint32_t)i), av = i - r * AV;
+    const int hh = (int)s.div_wu.div((uint32_t)r), w = r - hh * s.Wu;
+    du_element<V>(s, hh, w, av, u, dpq, s.pmax ? parg + (long long)n * s.F : nullptr, dU + (base + i) * V);
+  };
+#pragma unroll
+  for (int k = 0; k < AHEAD; ++k)
+    if (i0 + k * HT < i1) element(i0 + k * HT, ahead[k]);
+  for (int i = i0 + AHEAD * HT; i < i1; i += HT) element(i, load_chan<V>(U + (base + i) * V));
 }
 
 // Backward of the head after the softmax in one launch (gradient line of Algorithm 2); the
@@ -755,13 +869,12 @@ __global__ __launch_bounds__(HT) void head_bwd_kernel(HeadShape s, HeadBwdJobs j
     const long long total = (long long)s.B * s.Hu * s.Wu * AV;
     const long long i = (long long)b * HT + t;
     if (i >= total) return;
-    const int av = (int)(i % AV);
-    long long r = i / AV;
-    const int w = (int)(r % s.Wu);
-    r /= s.Wu;
-    const int hh = (int)(r % s.Hu);
-    const int n = (int)(r / s.Hu);
-    du_element<V>(s, hh, w, av, U + i * V, dPq + (long long)n * s.F, s.pmax ? parg + (long long)n * s.F : nullptr,
+    // pixels of all samples fit 31 bits, channel groups of all of them may not
+    long long r0 = i / AV;
+    if (total <= 0x7FFFFFFFll) r0 = s.div_av.div((uint32_t)i);
+    const int r = (int)r0, av = (int)(i - r0 * AV), row = (int)s.div_wu.div((uint32_t)r), w = r - row * s.Wu;
+    const int n = (int)s.div_hu.div((uint32_t)row), hh = row - n * s.Hu;
+    du_element<V>(s, hh, w, av, load_chan<V>(U + i * V), dPq + (long long)n * s.F, s.pmax ? parg + (long long)n * s.F : nullptr,
                   dU + i * V);
     return;
   }
@@ -879,9 +992,10 @@ hipError_t launch_head_wide(const HeadShape &h, const float *U, float *Pq, const
                             const float *Wf, const float *bf, float *dz, float *loss_n, const int32_t *parg,
                             float *dU, const RelayJob &rj, hipStream_t st) {
   const int V = h.A % 4 == 0 ? 4 : 1;
-  // slices per sample: about 768 workgroups in all, at least 1024 values of dU each
+  // slices per sample: about 512 workgroups in all (768: 13.7 us for 64 samples of 32x32 pixels, 32 filters, 512: 13.0, 384:
+  // 14.2), at least 1024 values of dU each
   const long long per_sample = (long long)h.Hu * h.Wu * h.A;
-  int NS = (768 + h.B - 1) / h.B;
+  int NS = (512 + h.B - 1) / h.B;
   if (NS > per_sample / 1024) NS = (int)(per_sample / 1024);
   if (NS < 1) NS = 1;
   const unsigned nb_t = (unsigned)(rj.nb_t + rj.nb_u);

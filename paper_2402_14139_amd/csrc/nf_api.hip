@@ -122,6 +122,9 @@ HeadShape head_shape(const nf_aux_desc *a, const AuxDims &ad, int B) {
   HeadShape h;
   h.B = B, h.Hu = ad.Hu, h.Wu = ad.Wu, h.A = a->A, h.oh = a->pool_oh, h.ow = a->pool_ow, h.F = ad.F,
   h.Cls = a->n_classes, h.relu = a->relu, h.pmax = a->head_pool == 1, h.mse = a->loss_kind == 1;
+  h.scale = h.pmax ? 1.f : ad.Hu % a->pool_oh || ad.Wu % a->pool_ow ? 0.f : 1.f / (float)(ad.Hu / a->pool_oh * (ad.Wu / a->pool_ow));
+  h.div_hu = FastDiv(ad.Hu), h.div_wu = FastDiv(ad.Wu), h.div_a = FastDiv(a->A);
+  h.div_av = FastDiv(a->A % 4 ? a->A : a->A / 4), h.div_oh = FastDiv(a->pool_oh), h.div_ow = FastDiv(a->pool_ow);
   return h;
 }
 

@@ -191,6 +191,8 @@ struct HeadShape {
   int B, Hu, Wu, A, oh, ow, F, Cls, relu;
   int pmax;  // F_n: 0 adaptive average pool, 1 adaptive max pool
   int mse;   // loss: 0 softmax cross-entropy, 1 mean squared error against the one-hot label
+  float scale;  // 1 / elements of a pooling window where all have as many, 1 for max pooling; 0: they differ
+  FastDiv div_hu, div_wu, div_a, div_av, div_oh, div_ow;  // av: channel groups of 4, or single channels where A is no multiple
 };
 // Pq = adaptive average pool of U.  With splits > 0, U is first formed from the raw partial sums
 // part[splits][B*Hu*Wu*A] of the aux convolution: U = act(sum_z part[z] + ba) (written out).
