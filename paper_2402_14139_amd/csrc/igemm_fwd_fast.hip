@@ -13,6 +13,7 @@
 //   - LDS fragment reads of sub-step ks+1 are issued before the MFMAs of sub-step ks;
 //   - MFMA shape is a template parameter: 32x32x2 for the wide contractions, 16x16x4 for
 //     the skinny ones (auxiliary heads with at most 16 filters).
+#include <algorithm>
 #include <type_traits>
 
 #include "nf_internal.h"
@@ -33,6 +34,8 @@ struct FastAux {
   int nkb_conv, nkb_proj;
   FastDiv div_taps;
   int kb_per;  // reduction steps per split (gridDim.y splits; every split but the last gets this many)
+  int imgs;    // position tiles (PM): images, and tiles of them per output position
+  FastDiv div_tpp;
 };
 
 __device__ inline float4 bload(__amdgpu_buffer_rsrc_t r, int voff) {
@@ -67,7 +70,11 @@ struct Mfma<16> {
 // of BK): step kb = (channel chunk, tap) with the tap fastest, so that the shifted reads of one
 // channel chunk by the R*S taps are neighbours in time and hit in L2 instead of re-streaming x from
 // the fabric once per tap (measured: less than half of the fetched bytes).
-template <int BM, int BN, int BK, int WM, int WN, int MF, int MODE, bool SCHED, bool TI>
+// PM (with TI, modes 0 and 2): a tile is BM images at ONE output position, so that a tap lies over the padding for all of its
+// rows or for none, and its steps are left out: 4 of 9 remain on 2x2 maps, 6.25 on average on 4x4 ones.  The others keep
+// their order and their split, so the sums are the same bits.  (Padding contributes nothing: an infinite weight over it, which
+// used to make a NaN of 0 * inf, is not read.)
+template <int BM, int BN, int BK, int WM, int WN, int MF, int MODE, bool SCHED, bool TI, bool PM>
 __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem p, FastAux q) {
   constexpr bool PROJ = MODE == 1, EPI = MODE == 2;
   using MM = Mfma<MF>;
@@ -97,6 +104,20 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
+  static_assert(!PM || (TI && MODE != 1), "steps of one tap");
+  // PM: the position, this tile's first image, and the taps [r0, r0 + nr) x [s0, s0 + ns) inside the image
+  int pos = 0, img0 = 0, hi0 = 0, wi0 = 0, r0 = 0, nr = 0, s0 = 0, ns = 0;
+  if constexpr (PM) {
+    pos = (int)q.div_tpp.div((uint32_t)tile_m), img0 = (tile_m - pos * (int)q.div_tpp.d) * BM;
+    const int ho = (int)p.div_wo.div((uint32_t)pos);
+    hi0 = ho * p.stride - p.pad, wi0 = (pos - ho * p.Wo) * p.stride - p.pad;
+    r0 = max(0, -hi0), nr = max(0, min(p.R, p.H - hi0) - r0), s0 = max(0, -wi0), ns = max(0, min(p.S, p.W - wi0) - s0);
+  }
+  // the output row of tile row r, or -1
+  auto row_of = [&](int r) {
+    if constexpr (PM) return img0 + r < q.imgs ? (img0 + r) * (int)p.div_howo.d + pos : -1;
+    return m0 + r < p.M ? m0 + r : -1;
+  };
 
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)p.x, 0, q.x_bytes, RSRC_FLAGS);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)p.w, 0, q.w_bytes, RSRC_FLAGS);
@@ -111,7 +132,10 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
   for (int i = 0; i < PA; ++i) {
     const int m = m0 + row0 + RPP * i;
     abase[i] = 0, sbase[i] = OOB, amask[i] = 0;
-    if (m < p.M) {
+    if constexpr (PM) {
+      const int img = img0 + row0 + RPP * i;
+      abase[i] = img < q.imgs ? ((img * p.H + hi0) * p.W + wi0) * p.C * 4 : OOB;
+    } else if (m < p.M) {
       const int img = (int)p.div_howo.div((uint32_t)m);
       const int rem = m - img * p.Ho * p.Wo;
       const int ho = (int)p.div_wo.div((uint32_t)rem);
@@ -138,14 +162,42 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
   // Two register sets of staged chunks: global loads run two reduction steps ahead of the MFMAs.
   float4 ra[2][PA], rb[2][PB];
   // this workgroup's share of the reduction: steps [kb0, kb_end)
-  const int kb0 = blockIdx.y * q.kb_per;
-  const int kb_end = min(q.nkb_conv + q.nkb_proj, kb0 + q.kb_per);
+  int kb0 = blockIdx.y * q.kb_per;
+  int kb_end = min(q.nkb_conv + q.nkb_proj, kb0 + q.kb_per);
+  // PM: steps are counted without the ones left out; the channel chunk and tap of the next step to load
+  int ncc = 0, nrr = 0, nss = 0;
+  if constexpr (PM) {
+    const int taps = p.R * p.S, nv = nr * ns;
+    auto before = [&](int kb) {  // how many of the steps before kb remain
+      const int cc = (int)q.div_taps.div((uint32_t)kb), tap = kb - cc * taps, r = (int)q.div_s.div((uint32_t)tap);
+      const int full = min(max(r - r0, 0), nr) * ns;
+      return cc * nv + full + ((r >= r0 && r < r0 + nr) ? min(max(tap - r * p.S - s0, 0), ns) : 0);
+    };
+    kb0 = before(kb0), kb_end = before(kb_end);
+    if (nv) {
+      ncc = kb0 / nv;
+      const int rest = kb0 - ncc * nv, r = rest / ns;
+      nrr = r, nss = rest - r * ns;
+    }
+  }
 
   // Branch-free gather of step kb into register set `set`.  Steps past the end, the padding of the
   // reduction axis, taps outside the image and rows past M or N all become the out-of-range
   // offset.  The projection steps (kb >= nkb_conv) read the shortcut tensor and its 1x1 filter
   // through a uniform select of the buffer descriptor.
   auto gload = [&](int kb, int set) {
+    if constexpr (PM) {  // steps are asked for one after the other; an offset of OOB and more stays out of range
+      const int bad = kb < kb_end ? 0 : OOB;
+      const int r = r0 + nrr, sx = s0 + nss, c4 = (ncc * BK + ch * 4) * 4;
+      const int offx = (r * p.W + sx) * p.C * 4 + c4, offw = (r * p.S + sx) * p.C * 4 + c4;
+      if (++nss == ns) nss = 0, ++nrr;
+      if (nrr == nr) nrr = 0, ++ncc;
+#pragma unroll
+      for (int i = 0; i < PA; ++i) ra[set][i] = bload(rx, (abase[i] + offx) | bad);
+#pragma unroll
+      for (int i = 0; i < PB; ++i) rb[set][i] = bload(rw, (bbase[i] + offw) | bad);
+      return;
+    }
     int kg, tap, c;
     bool in;
     if constexpr (TI) {  // step kb = (channel chunk, tap): the tap is uniform over the step
@@ -289,8 +341,8 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
       for (int a = 0; a < MT; ++a)
 #pragma unroll
         for (int e = 0; e < MM::NACC; ++e) {
-          const int m = m0 + wm * TM + a * MF + MM::row(e, g);
-          epi[a][b][e] = (n < p.N && m < p.M) ? src[(long long)m * p.N + n] : 0.f;
+          const int m = row_of(wm * TM + a * MF + MM::row(e, g));
+          epi[a][b][e] = (n < p.N && m >= 0) ? src[(long long)m * p.N + n] : 0.f;
         }
     }
   }
@@ -319,8 +371,8 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
       for (int a = 0; a < MT; ++a)
 #pragma unroll
         for (int e = 0; e < MM::NACC; ++e) {
-          const int m = m0 + wm * TM + a * MF + MM::row(e, g);
-          if (m < p.M) part[(long long)m * p.N + n] = acc[a][b][e];
+          const int m = row_of(wm * TM + a * MF + MM::row(e, g));
+          if (m >= 0) part[(long long)m * p.N + n] = acc[a][b][e];
         }
     }
     return;
@@ -336,8 +388,8 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
     for (int a = 0; a < MT; ++a) {
 #pragma unroll
       for (int e = 0; e < MM::NACC; ++e) {
-        const int m = m0 + wm * TM + a * MF + MM::row(e, g);
-        if (m >= p.M) continue;
+        const int m = row_of(wm * TM + a * MF + MM::row(e, g));
+        if (m < 0) continue;
         const long long o = (long long)m * p.N + n;
         float v = acc[a][b][e] + bias;
         if (p.addsrc) v += EPI ? epi[EPI ? a : 0][EPI ? b : 0][EPI ? e : 0] : p.addsrc[o];
@@ -373,9 +425,27 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
   }
 }
 
+// Whether tiles of one output position pay (PM): the steps that remain over all tiles of bm images against those of tiles of bm
+// consecutive rows.  At most 85 of 100 must remain: a position that does not fill its last tile, and rows of a tile that lie an
+// image apart, cost something.  Measured (us, without / with): 128 images on 2x2 maps, 512 -> 512 channels 26.9 / 16.2, 512 -> 256
+// 21.1 / 14.3, 256 -> 512 18.8 / 11.4 (4 of 9 remain); a 4-wide head on 4x4 maps of 512 channels, 512 images 17.5 / 15.4 (25 of
+// 36); an 8-wide one on 8x8 maps of 256 channels, 256 images 17.6 / 15.6 (121 of 144).
+bool position_tiles(const FwdProblem &p, int bm) {
+  const int pos = p.Ho * p.Wo;
+  if (p.Cs || p.pool_part || p.R * p.S == 1 || pos > 64) return false;
+  auto inside = [](int out, int in, int taps, int stride, int pad) {  // (output, tap) pairs inside the image, one direction
+    int n = 0;
+    for (int o = 0; o < out; ++o) n += std::max(0, std::min(taps, in + pad - o * stride) - std::max(0, pad - o * stride));
+    return n;
+  };
+  const long long remain = (long long)inside(p.Ho, p.H, p.R, p.stride, p.pad) * inside(p.Wo, p.W, p.S, p.stride, p.pad);
+  const long long tpp = (p.M / pos + bm - 1) / bm, rows = (p.M + bm - 1) / bm;
+  return 100 * remain * tpp <= 85 * rows * p.R * p.S;
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int MF>
 hipError_t launch_cfg(const FwdProblem &p, FastAux q, hipStream_t st) {
-  const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
+  int tiles_m = (p.M + BM - 1) / BM;
   constexpr bool SCHED = MF == 32;
   q.nkb_conv = (p.RSC + BK - 1) / BK;
   q.nkb_proj = p.Cs ? (p.Cs + BK - 1) / BK : 0;
@@ -383,21 +453,30 @@ hipError_t launch_cfg(const FwdProblem &p, FastAux q, hipStream_t st) {
   const int nkb = q.nkb_conv + q.nkb_proj;
   const int splits = p.ksplits > 1 ? p.ksplits : 1;
   q.kb_per = (nkb + splits - 1) / splits;
-  const dim3 grid((unsigned)tiles, (unsigned)splits), block(WM * WN * 64);
   // exactly one of addsrc / mask, no projection, no split: prefetch it (MODE 2)
   const bool epi = !q.nkb_proj && splits == 1 && ((p.addsrc != nullptr) != (p.mask != nullptr));
   const int mode = q.nkb_proj ? 1 : epi ? 2 : 0;
-  const bool ti = p.C % BK == 0 && p.R * p.S > 1;
-#define NF_LAUNCH(MODE_, TI_) \
-  hipLaunchKernelGGL((igemm_fwd_fast_kernel<BM, BN, BK, WM, WN, MF, MODE_, SCHED, TI_>), grid, block, 0, st, p, q)
-  if (ti) {
-    if (mode == 1) NF_LAUNCH(1, true);
-    else if (mode == 2) NF_LAUNCH(2, true);
-    else NF_LAUNCH(0, true);
+  const bool ti = p.C % BK == 0 && p.R * p.S > 1, pm = BM == 64 && ti && position_tiles(p, BM);
+  if (pm) {
+    q.imgs = p.M / (p.Ho * p.Wo), q.div_tpp = FastDiv((q.imgs + BM - 1) / BM);
+    tiles_m = p.Ho * p.Wo * (int)q.div_tpp.d;
+  }
+  const dim3 grid((unsigned)(tiles_m * ((p.N + BN - 1) / BN)), (unsigned)splits), block(WM * WN * 64);
+#define NF_LAUNCH(MODE_, TI_, PM_) \
+  hipLaunchKernelGGL((igemm_fwd_fast_kernel<BM, BN, BK, WM, WN, MF, MODE_, SCHED, TI_, PM_>), grid, block, 0, st, p, q)
+  if (pm) {
+    if constexpr (BM == 64) {
+      if (mode == 2) NF_LAUNCH(2, true, true);
+      else NF_LAUNCH(0, true, true);
+    }
+  } else if (ti) {
+    if (mode == 1) NF_LAUNCH(1, true, false);
+    else if (mode == 2) NF_LAUNCH(2, true, false);
+    else NF_LAUNCH(0, true, false);
   } else {
-    if (mode == 1) NF_LAUNCH(1, false);
-    else if (mode == 2) NF_LAUNCH(2, false);
-    else NF_LAUNCH(0, false);
+    if (mode == 1) NF_LAUNCH(1, false, false);
+    else if (mode == 2) NF_LAUNCH(2, false, false);
+    else NF_LAUNCH(0, false, false);
   }
 #undef NF_LAUNCH
   return hipGetLastError();
@@ -468,7 +547,7 @@ hipError_t launch_igemm_fwd_fast(const FwdProblem &p, hipStream_t st, const char
   q.xs_bytes = p.Cs ? (uint32_t)(B * p.Hs * p.Ws * p.Cs * 4) : 0;
   q.wp_bytes = p.Cs ? (uint32_t)((long long)p.N * p.Cs * 4) : 0;
   q.nkb_conv = q.nkb_proj = 0;  // set per tile configuration
-  if (igemm_fwd_tile128(p.M, p.N, p.Kg, p.ksplits)) {
+  if (igemm_fwd_tile128(p.M, p.N, p.Kg, p.ksplits) && !(p.C % 32 == 0 && position_tiles(p, 64))) {
     *kernel = "igemm_fwd_fast_128x128";
     return launch_cfg<128, 128, 32, 2, 2, 32>(p, q, st);
   }
