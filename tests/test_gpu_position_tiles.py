@@ -1,4 +1,4 @@
-"""Direct contractions on small maps in tiles of one output position (csrc/igemm_fwd_fast.hip): taps over the padding are
+"""Direct contractions on small maps by output position (csrc/igemm_fwd_fast.hip, csrc/igemm_wgrad_fast.hip): taps over the padding are
 left out.  Against the oracle, at the edges of the rule: batches around whole tiles, maps of one to eight pixels, strides,
 5x5 filters, reductions cut in parts that begin and end between the taps of a channel chunk."""
 import pytest
