@@ -10,21 +10,31 @@ namespace {
 
 constexpr int ET = 256;
 
+// (image, row, column, channel group) of element i of an NHWC tensor: multiply-high divisions (64-bit ones, of
+// about a hundred instructions each, took longer than the memory: maxpool_bwd of 64x32x32x128 15.7 us with them)
+struct Nhwc {
+  FastDiv c, w, h;  // channel groups, columns, rows
+  bool small;       // every element index fits 31 bits (pixels always do)
+  Nhwc(int kv, int w_, int h_, long long total) : c(kv), w(w_), h(h_), small(total <= 0x7FFFFFFFll) {}
+  __device__ inline void of(long long i, int &n, int &row, int &col, int &cg) const {
+    const uint32_t px = small ? c.div((uint32_t)i) : (uint32_t)(i / c.d);
+    cg = (int)(i - (long long)px * c.d);
+    const uint32_t r = w.div(px);
+    col = (int)(px - r * w.d);
+    n = (int)h.div(r), row = (int)(r - (uint32_t)n * h.d);
+  }
+};
+
 // ---- P_n: max-pool over NHWC, records the window-local index of the first maximum ----
 template <int V>
 __global__ __launch_bounds__(ET) void maxpool_fwd_kernel(const float *__restrict__ T, float *__restrict__ Y,
                                                          uint8_t *__restrict__ arg, int B, int Ho, int Wo, int K,
-                                                         int Hp, int Wp, int pk, int ps, int pp) {
-  const int KV = K / V;
-  const long long total = (long long)B * Hp * Wp * KV;
+                                                         int Hp, int Wp, int pk, int ps, int pp, Nhwc at) {
+  const long long total = (long long)B * Hp * Wp * (K / V);
   const long long i = (long long)blockIdx.x * ET + threadIdx.x;
   if (i >= total) return;
-  const int kv = (int)(i % KV);
-  long long r = i / KV;
-  const int jw = (int)(r % Wp);
-  r /= Wp;
-  const int ih = (int)(r % Hp);
-  const int n = (int)(r / Hp);
+  int n, ih, jw, kv;
+  at.of(i, n, ih, jw, kv);
   float best[V];
   int bi[V];
 #pragma unroll
@@ -64,17 +74,12 @@ template <int V>
 __global__ __launch_bounds__(ET) void maxpool_bwd_kernel(const float *__restrict__ dY, const float *__restrict__ Y,
                                                          const uint8_t *__restrict__ arg, float *__restrict__ dZ,
                                                          int B, int Ho, int Wo, int K, int Hp, int Wp, int pk,
-                                                         int ps, int pp) {
-  const int KV = K / V;
-  const long long total = (long long)B * Ho * Wo * KV;
+                                                         int ps, int pp, Nhwc at) {
+  const long long total = (long long)B * Ho * Wo * (K / V);
   const long long i = (long long)blockIdx.x * ET + threadIdx.x;
   if (i >= total) return;
-  const int kv = (int)(i % KV);
-  long long r = i / KV;
-  const int ww = (int)(r % Wo);
-  r /= Wo;
-  const int hh = (int)(r % Ho);
-  const int n = (int)(r / Ho);
+  int n, hh, ww, kv;
+  at.of(i, n, hh, ww, kv);
   float acc[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) acc[e] = 0.f;
@@ -108,6 +113,46 @@ __global__ __launch_bounds__(ET) void maxpool_bwd_kernel(const float *__restrict
     *reinterpret_cast<float4 *>(dZ + oz) = make_float4(acc[0], acc[1], acc[2], acc[3]);
   } else {
     dZ[oz] = acc[0];
+  }
+}
+
+// The same for 2x2 windows with stride 2: a thread reads one pooled cell once and writes the window's four pixels (and, at
+// the rim of odd maps, the zeros beside them).  HBM-bound: 64x32x32x128 9.3 us (52 MB).
+template <int V>
+__global__ __launch_bounds__(ET) void maxpool2_bwd_kernel(const float *__restrict__ dY, const float *__restrict__ Y,
+                                                          const uint8_t *__restrict__ arg, float *__restrict__ dZ,
+                                                          long long total, int Ho, int Wo, int K, int Hp, int Wp,
+                                                          Nhwc at) {
+  const long long i = (long long)blockIdx.x * ET + threadIdx.x;
+  if (i >= total) return;
+  int n, ih, jw, kv;
+  at.of(i, n, ih, jw, kv);
+  float g[V];
+  int a[V];
+  if constexpr (V == 4) {
+    const uint32_t a4 = reinterpret_cast<const uint32_t *>(arg)[i];
+    const float4 y4 = reinterpret_cast<const float4 *>(Y)[i], d4 = reinterpret_cast<const float4 *>(dY)[i];
+    const float yv[4] = {y4.x, y4.y, y4.z, y4.w}, dv[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) g[e] = yv[e] > 0.f ? dv[e] : 0.f, a[e] = (int)((a4 >> (8 * e)) & 0xffu);
+  } else {
+    g[0] = Y[i] > 0.f ? dY[i] : 0.f, a[0] = arg[i];
+  }
+  float *const out = dZ + (((long long)n * Ho + 2 * ih) * Wo + 2 * jw) * K + (long long)kv * V;
+  const int rows = ih + 1 == Hp ? Ho - 2 * ih : 2, cols = jw + 1 == Wp ? Wo - 2 * jw : 2;
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
+      if (u >= rows || v >= cols) continue;
+      const int local = (u < 2 && v < 2) ? 2 * u + v : -1;
+      float *const o = out + ((long long)u * Wo + v) * K;
+      if constexpr (V == 4)
+        *reinterpret_cast<float4 *>(o) = make_float4(a[0] == local ? g[0] : 0.f, a[1] == local ? g[1] : 0.f,
+                                                     a[2] == local ? g[2] : 0.f, a[3] == local ? g[3] : 0.f);
+      else
+        o[0] = a[0] == local ? g[0] : 0.f;
+    }
   }
 }
 
@@ -209,23 +254,38 @@ inline unsigned nblocks(long long total) { return (unsigned)((total + ET - 1) / 
 
 hipError_t launch_maxpool_fwd(const float *T, float *Y, uint8_t *arg, int B, int Ho, int Wo, int K, int Hp, int Wp,
                               int pk, int ps, int pp, hipStream_t st) {
-  if (K % 4 == 0)
-    hipLaunchKernelGGL(maxpool_fwd_kernel<4>, dim3(nblocks((long long)B * Hp * Wp * (K / 4))), dim3(ET), 0, st, T, Y,
-                       arg, B, Ho, Wo, K, Hp, Wp, pk, ps, pp);
+  const int V = K % 4 == 0 ? 4 : 1;
+  const long long total = (long long)B * Hp * Wp * (K / V);
+  const Nhwc at(K / V, Wp, Hp, total);
+  if (V == 4)
+    hipLaunchKernelGGL(maxpool_fwd_kernel<4>, dim3(nblocks(total)), dim3(ET), 0, st, T, Y, arg, B, Ho, Wo, K, Hp, Wp, pk, ps,
+                       pp, at);
   else
-    hipLaunchKernelGGL(maxpool_fwd_kernel<1>, dim3(nblocks((long long)B * Hp * Wp * K)), dim3(ET), 0, st, T, Y, arg,
-                       B, Ho, Wo, K, Hp, Wp, pk, ps, pp);
+    hipLaunchKernelGGL(maxpool_fwd_kernel<1>, dim3(nblocks(total)), dim3(ET), 0, st, T, Y, arg, B, Ho, Wo, K, Hp, Wp, pk, ps,
+                       pp, at);
   return hipGetLastError();
 }
 
 hipError_t launch_maxpool_bwd(const float *dY, const float *Y, const uint8_t *arg, float *dZ, int B, int Ho, int Wo,
                               int K, int Hp, int Wp, int pk, int ps, int pp, hipStream_t st) {
-  if (K % 4 == 0)
-    hipLaunchKernelGGL(maxpool_bwd_kernel<4>, dim3(nblocks((long long)B * Ho * Wo * (K / 4))), dim3(ET), 0, st, dY, Y,
-                       arg, dZ, B, Ho, Wo, K, Hp, Wp, pk, ps, pp);
+  const int V = K % 4 == 0 ? 4 : 1;
+  if (pk == 2 && ps == 2 && pp == 0) {
+    const long long total = (long long)B * Hp * Wp * (K / V);
+    const Nhwc at(K / V, Wp, Hp, total);
+    if (V == 4)
+      hipLaunchKernelGGL(maxpool2_bwd_kernel<4>, dim3(nblocks(total)), dim3(ET), 0, st, dY, Y, arg, dZ, total, Ho, Wo, K, Hp, Wp, at);
+    else
+      hipLaunchKernelGGL(maxpool2_bwd_kernel<1>, dim3(nblocks(total)), dim3(ET), 0, st, dY, Y, arg, dZ, total, Ho, Wo, K, Hp, Wp, at);
+    return hipGetLastError();
+  }
+  const long long total = (long long)B * Ho * Wo * (K / V);
+  const Nhwc at(K / V, Wo, Ho, total);
+  if (V == 4)
+    hipLaunchKernelGGL(maxpool_bwd_kernel<4>, dim3(nblocks(total)), dim3(ET), 0, st, dY, Y, arg, dZ, B, Ho, Wo, K, Hp, Wp, pk,
+                       ps, pp, at);
   else
-    hipLaunchKernelGGL(maxpool_bwd_kernel<1>, dim3(nblocks((long long)B * Ho * Wo * K)), dim3(ET), 0, st, dY, Y, arg,
-                       dZ, B, Ho, Wo, K, Hp, Wp, pk, ps, pp);
+    hipLaunchKernelGGL(maxpool_bwd_kernel<1>, dim3(nblocks(total)), dim3(ET), 0, st, dY, Y, arg, dZ, B, Ho, Wo, K, Hp, Wp, pk,
+                       ps, pp, at);
   return hipGetLastError();
 }
 
