@@ -429,7 +429,7 @@ const char *wino_name(int N) { return N <= 32 ? "wino_fwd_32" : "wino_fwd"; }
 int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, float *filter, const WinoFilter *also,
                      hipStream_t st) {
   const double B = (double)f.M / ((double)f.Ho * f.Wo), mn = (double)f.M * f.N;
-  double elems = B * f.H * f.W * f.C + (double)f.N * f.Kg + mn;
+  double elems = B * f.H * f.W * f.C + (double)f.N * f.Kg + (f.max_arg ? 1.25 * B * f.Hp * f.Wp * f.N : mn);
   const float *bias = f.bias, *addsrc = f.addsrc, *mask = f.mask;
   if (splits <= 1 && (addsrc || mask)) elems += mn;
   float *part = scratch + wino_fwd_filter_floats(f.N, f.C);
@@ -507,6 +507,14 @@ int32_t run_layer_fwd(const nf_layer_desc *d, const LayerDims &ld, int B, const 
   f.x = x, f.w = p->W, f.bias = p->b;
   if (d->skip_kind == 1) f.addsrc = xs;
   if (d->skip_kind == 2) f.xs = xs, f.wp = p->Wp;
+  // an output tile of wino_fwd is a 2x2 window: pooled in its epilogue.  (A projection's sums need the unpooled result.)
+  const bool in_epilogue = pooled && d->pool_k == 2 && d->pool_stride == 2 && d->pool_pad == 0 && !f.Cs && w.wino_layer == 1 &&
+                           wino_splits_now(f, w.wino_layer) == 1;
+  if (in_epilogue) {
+    f.max_arg = reinterpret_cast<uint8_t *>(wsf(ws, w.arg)), f.Hp = ld.Hp, f.Wp = ld.Wp;
+    if (formed) *formed = also != nullptr;
+    return enqueue_wino(f, y, 1, wsf(ws, w.part), nullptr, also, st);
+  }
   float *conv_out = pooled ? wsf(ws, w.T_dZ) : y;
   int32_t rc = enqueue_conv(f, conv_out, w.wino_layer, w.ksplits_layer, wsf(ws, w.part), st, nullptr, also, formed);
   if (rc) return rc;

@@ -45,6 +45,10 @@ struct FwdProblem {
   // (pool_split only).  Null: not formed.
   float *pool_part;
   int pool_split;
+  // 2x2 max pooling in the epilogue (wino_fwd, reduction not split): out is [images][Hp][Wp][N] then, max_arg its recorded
+  // selections.  Null: not formed.
+  uint8_t *max_arg;
+  int Hp, Wp;
 };
 // whether launch_igemm_fwd would run `p` on a tile that can form pool_part (M a multiple of 64)
 bool fwd_pool_partials_applicable(const FwdProblem &p);
