@@ -566,7 +566,8 @@ double wino_us(const FwdProblem &p, int s) {
          finish_us(p, s) + proj;
 }
 // its variant of 32 filters: 0.8, 1.4 and 2.1 us per step with one, two and three workgroups on a CU, 6 us of prologue,
-// epilogue and launch, 4.5 us for a filter launch of its own; the direct kernel of 64x32 tiles in its place 0.3 us per step
+// epilogue and launch, 6.5 us for a filter launch of its own (4.5 us and, in a chain of dependent layers, the gap in front of it: a
+// forward sweep of four layers of 32 channels on 40x43 maps, batch 39, 299 us, with two launches a layer 310); the direct kernel of 64x32 tiles in its place 0.3 us per step
 // and workgroup on a CU.  On 36 random shapes (17 ... 32 filters, 16 ... 512 channels) this one is chosen 10 times and is the
 // faster one each time, by 3 to 33 % (us, direct / this with its filter launch: 64 -> 32, 204 800 pixels 72.5 / 50.1; 16 -> 28, 174 592
 // pixels 29.2 / 22.6; 64 -> 32, 16 384 pixels 12.0 / 14.7, direct); its error is the smaller one on all 36 (64 -> 32 2.9e-7 / 2.1e-7)
@@ -574,7 +575,7 @@ double narrow_us(const FwdProblem &p, int s, bool ready) {
   const int nchunks = (p.C + CH - 1) / CH;
   const long long w = workgroups(p) * s, full = w / 768, rest = w % 768;
   const double per = 2.1 * full + (rest > 512 ? 2.1 : rest > 256 ? 1.4 : rest > 0 ? 0.8 : 0.0);
-  return (ready ? 6.0 : 10.5) + 3.0 * (full + (rest > 0) - 1) + (nchunks + s - 1) / s * per + finish_us(p, s);
+  return (ready ? 6.0 : 12.5) + 3.0 * (full + (rest > 0) - 1) + (nchunks + s - 1) / s * per + finish_us(p, s);
 }
 double narrow_direct_us(const FwdProblem &p, int ks) {
   const int nkb = (p.Kg + 31) / 32;
