@@ -113,11 +113,9 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
     hi0 = ho * p.stride - p.pad, wi0 = (pos - ho * p.Wo) * p.stride - p.pad;
     r0 = max(0, -hi0), nr = max(0, min(p.R, p.H - hi0) - r0), s0 = max(0, -wi0), ns = max(0, min(p.S, p.W - wi0) - s0);
   }
-  // the output row of tile row r, or -1
-  auto row_of = [&](int r) {
-    if constexpr (PM) return img0 + r < q.imgs ? (img0 + r) * (int)p.div_howo.d + pos : -1;
-    return m0 + r < p.M ? m0 + r : -1;
-  };
+  // the output row of tile row r, and whether there is one
+  auto row_of = [&](int r) { return PM ? (img0 + r) * (int)p.div_howo.d + pos : m0 + r; };
+  auto row_ok = [&](int r) { return PM ? img0 + r < q.imgs : m0 + r < p.M; };
 
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)p.x, 0, q.x_bytes, RSRC_FLAGS);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)p.w, 0, q.w_bytes, RSRC_FLAGS);
@@ -341,8 +339,8 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
       for (int a = 0; a < MT; ++a)
 #pragma unroll
         for (int e = 0; e < MM::NACC; ++e) {
-          const int m = row_of(wm * TM + a * MF + MM::row(e, g));
-          epi[a][b][e] = (n < p.N && m >= 0) ? src[(long long)m * p.N + n] : 0.f;
+          const int r = wm * TM + a * MF + MM::row(e, g), m = row_of(r);
+          epi[a][b][e] = (n < p.N && row_ok(r)) ? src[(long long)m * p.N + n] : 0.f;
         }
     }
   }
@@ -371,8 +369,8 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
       for (int a = 0; a < MT; ++a)
 #pragma unroll
         for (int e = 0; e < MM::NACC; ++e) {
-          const int m = row_of(wm * TM + a * MF + MM::row(e, g));
-          if (m >= 0) part[(long long)m * p.N + n] = acc[a][b][e];
+          const int r = wm * TM + a * MF + MM::row(e, g), m = row_of(r);
+          if (row_ok(r)) part[(long long)m * p.N + n] = acc[a][b][e];
         }
     }
     return;
@@ -388,8 +386,8 @@ __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem 
     for (int a = 0; a < MT; ++a) {
 #pragma unroll
       for (int e = 0; e < MM::NACC; ++e) {
-        const int m = row_of(wm * TM + a * MF + MM::row(e, g));
-        if (m < 0) continue;
+        const int r = wm * TM + a * MF + MM::row(e, g), m = row_of(r);
+        if (!row_ok(r)) continue;
         const long long o = (long long)m * p.N + n;
         float v = acc[a][b][e] + bias;
         if (p.addsrc) v += EPI ? epi[EPI ? a : 0][EPI ? b : 0][EPI ? e : 0] : p.addsrc[o];
