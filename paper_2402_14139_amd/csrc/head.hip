@@ -198,16 +198,15 @@ __global__ __launch_bounds__(HT) void head_pool_kernel(HeadShape s, float *__res
 }
 
 // Logits of one sample (all threads of a workgroup): z[q] = bf[q] + sum_f Wf[q][f] * pq[f], pq staged in LDS; ends
-// with a barrier.  L lanes per class read its row in whole 16-byte groups side by side and hold eight running
-// sums each, added in a tree, so that a result is 8 * L sums of F / (8 * L) products (relative error against 64 bits,
-// 1024 features, 100 classes, L = 8: 1.0e-7; two sums of 512 2.1e-7).  NQ classes per thread at a time, 16 / NQ groups of a
-// row: sixteen loads are in flight together.  What bounds it is the latency of those loads and, with several
-// workgroups on a CU, the lines they touch (one thread per class and part of a row touched a line per lane: 128 features, 100
-// classes, three workgroups on a CU 5.2 us, this 3.6; a single one, 64 features, 100 classes: 4.8 / 5.5 in the exit's launch).
-template <int L, int NQ>
-__device__ inline void logits_tree(const HeadShape &s, const float *pq, float *z, const float *__restrict__ Wf,
-                                   const float *__restrict__ bf) {
-  constexpr int G = HT / L, NH = 16 / NQ;  // classes side by side; groups of a row in flight
+// with a barrier.  8 lanes per class with eight running sums each,
+// added in a tree, so that a result is 64 sums of F / 64 products (relative error against 64 bits, 1024 features, 100
+// classes: 1.0e-7; with two sums of 512 2.1e-7).  Four classes per thread at a time: their loads are
+// in flight together (100 samples, 64 features, 100 classes: 17.0 us with one wavefront per class after the
+// other, 5.5 so; logits_few took 4.8).  What bounds it is the latency of its loads and, with several workgroups on a CU, the
+// lines they touch: 128 features, 100 classes, three workgroups on a CU 3.3 us, logits_few, whose lanes each read another row, 5.2.
+__device__ inline void logits_lanes8(const HeadShape &s, const float *pq, float *z, const float *__restrict__ Wf,
+                                     const float *__restrict__ bf) {
+  constexpr int L = 8, NQ = 4, G = HT / L;  // lanes per class, classes per thread, classes side by side
   const int l = threadIdx.x & (L - 1), g = threadIdx.x / L;
   for (int q0 = 0; q0 < s.Cls; q0 += G * NQ) {
     float acc[NQ][8];
@@ -219,33 +218,20 @@ __device__ inline void logits_tree(const HeadShape &s, const float *pq, float *z
       for (int e = 0; e < 8; ++e) acc[k][e] = 0.f;
     }
     if ((s.F & 3) == 0) {
-      for (int f1 = 0; f1 < s.F; f1 += 4 * L * NH) {
-        const int f0 = f1 + 4 * l;
-        float4 w[NH][NQ];
+      for (int f0 = 4 * l; f0 < s.F; f0 += 8 * L)
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
+        for (int h = 0; h < 2; ++h) {
           const int f = f0 + h * 4 * L;
-          if (f1 + h * 4 * L < s.F)  // (the same for all lanes)
+          if (f >= s.F) break;
+          float4 w[NQ];
 #pragma unroll
-            for (int k = 0; k < NQ; ++k)
-              if (q0 + k * G < s.Cls) w[h][k] = *reinterpret_cast<const float4 *>(wr[k] + (f < s.F ? f : 0));
-        }
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {
-          const int f = f0 + h * 4 * L, o = 4 * (h & 1);
-          const bool ok = f < s.F;
-          if (f1 + h * 4 * L >= s.F) break;
-          const float4 x = *reinterpret_cast<const float4 *>(pq + (ok ? f : 0));
+          for (int k = 0; k < NQ; ++k) w[k] = *reinterpret_cast<const float4 *>(wr[k] + f);
 #pragma unroll
           for (int k = 0; k < NQ; ++k) {
-            if (q0 + k * G >= s.Cls) break;
-            acc[k][o] = ok ? acc[k][o] + w[h][k].x * x.x : acc[k][o];
-            acc[k][o + 1] = ok ? acc[k][o + 1] + w[h][k].y * x.y : acc[k][o + 1];
-            acc[k][o + 2] = ok ? acc[k][o + 2] + w[h][k].z * x.z : acc[k][o + 2];
-            acc[k][o + 3] = ok ? acc[k][o + 3] + w[h][k].w * x.w : acc[k][o + 3];
+            acc[k][4 * h] += w[k].x * pq[f], acc[k][4 * h + 1] += w[k].y * pq[f + 1];
+            acc[k][4 * h + 2] += w[k].z * pq[f + 2], acc[k][4 * h + 3] += w[k].w * pq[f + 3];
           }
         }
-      }
     } else {
       for (int f0 = l; f0 < s.F; f0 += 8 * L)
 #pragma unroll
@@ -258,7 +244,6 @@ __device__ inline void logits_tree(const HeadShape &s, const float *pq, float *z
     }
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
-      if (q0 + k * G >= s.Cls) break;
       float v = ((acc[k][0] + acc[k][1]) + (acc[k][2] + acc[k][3])) + ((acc[k][4] + acc[k][5]) + (acc[k][6] + acc[k][7]));
 #pragma unroll
       for (int m = L / 2; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
@@ -266,6 +251,44 @@ __device__ inline void logits_tree(const HeadShape &s, const float *pq, float *z
       if (l == 0 && q < s.Cls) z[q] = v + (bf ? bf[q] : 0.f);
     }
   }
+  __syncthreads();
+}
+
+// The same for up to 16 classes: 16 lanes and one class per thread, sixteen loads in flight (1024 features, 10 classes 2.8 us,
+// logits_few 5.1).
+__device__ inline void logits_lanes16(const HeadShape &s, const float *pq, float *z, const float *__restrict__ Wf,
+                                      const float *__restrict__ bf) {
+  constexpr int L = 16, NH = 16;
+  const int l = threadIdx.x & (L - 1), q = threadIdx.x / L;
+  const float *const wr = Wf + (long long)min(q, s.Cls - 1) * s.F;
+  float acc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  if ((s.F & 3) == 0) {
+    for (int f1 = 0; f1 < s.F; f1 += 4 * L * NH) {
+      float4 w[NH];
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        const int f = f1 + 4 * l + h * 4 * L;
+        if (f1 + h * 4 * L < s.F) w[h] = *reinterpret_cast<const float4 *>(wr + (f < s.F ? f : 0));  // (all lanes or none)
+      }
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        const int f = f1 + 4 * l + h * 4 * L, o = 4 * (h & 1);
+        if (f1 + h * 4 * L >= s.F) break;
+        const bool ok = f < s.F;
+        const float4 x = *reinterpret_cast<const float4 *>(pq + (ok ? f : 0));
+        acc[o] = ok ? acc[o] + w[h].x * x.x : acc[o], acc[o + 1] = ok ? acc[o + 1] + w[h].y * x.y : acc[o + 1];
+        acc[o + 2] = ok ? acc[o + 2] + w[h].z * x.z : acc[o + 2], acc[o + 3] = ok ? acc[o + 3] + w[h].w * x.w : acc[o + 3];
+      }
+    }
+  } else {
+    for (int f = l, e = 0; f < s.F; f += L, e ^= 1) (e ? acc[1] : acc[0]) += wr[f] * pq[f];
+  }
+  float v = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+#pragma unroll
+  for (int m = L / 2; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+  if (l == 0 && q < s.Cls) z[q] = v + (bf ? bf[q] : 0.f);
   __syncthreads();
 }
 
@@ -322,16 +345,14 @@ __device__ inline void logits_few(const HeadShape &s, const float *pq, float *z,
   __syncthreads();
 }
 
-// Few classes: more lanes each, one class per thread.  (The exit's logits always take logits_tree<8, 4>.)  FEW: launches of a
-// workgroup per sample, about one on a CU, where the simple form is the faster one (head_fc, 128 features, 200 classes: 12.1 /
-// 13.2 us).
+// FEW: launches of one workgroup per sample, about one on a CU, where the simple form is the faster one (head_fc, 128 features,
+// 200 classes: 12.1 / 13.2 us).
 template <bool FEW>
 __device__ inline void logits_sample(const HeadShape &s, const float *pq, float *z, float *zp, const float *__restrict__ Wf,
                                      const float *__restrict__ bf) {
   if (FEW || s.F < 128) logits_few(s, pq, z, zp, Wf, bf);
-  else if (s.Cls > 64) logits_tree<8, 4>(s, pq, z, Wf, bf);
-  else if (s.Cls > 16) logits_tree<8, 2>(s, pq, z, Wf, bf);
-  else logits_tree<16, 1>(s, pq, z, Wf, bf);
+  else if (s.Cls > 16) logits_lanes8(s, pq, z, Wf, bf);
+  else logits_lanes16(s, pq, z, Wf, bf);
 }
 
 // out[f] = pool_scale(f) * sum_q dz[q] * Wf[q][f] (z holds dz; all threads of a workgroup).  With fewer features than
@@ -611,7 +632,7 @@ __global__ __launch_bounds__(HT) void head_predict_kernel(HeadShape s, const flo
   const int n = blockIdx.x, t = threadIdx.x;
   for (int f = t; f < s.F; f += HT) pq[f] = Pq[(long long)n * s.F + f];
   __syncthreads();
-  logits_tree<8, 4>(s, pq, z, Wf, bf);
+  logits_lanes8(s, pq, z, Wf, bf);
   if (logits_out)
     for (int q = t; q < s.Cls; q += HT) logits_out[(long long)n * s.Cls + q] = z[q];
   float best = -INFINITY;
