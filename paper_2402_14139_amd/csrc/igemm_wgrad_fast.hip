@@ -14,11 +14,11 @@
 #include <type_traits>
 
 #include "nf_internal.h"
+#include "stem_wgrad.h"
 
 namespace nf {
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int BKM = 32;  // reduction rows staged per step
@@ -35,6 +35,13 @@ struct PositionRows {
   FastDiv div_imgs;
   int bias_tile;  // the column tile of a tap that every position sees
 };
+
+struct TileGrid {
+  int x, y, z;  // column tiles, row tiles, splits
+};
+
+// LDS of a tile: two steps of both operands' rows and of the row table
+constexpr int lds_floats(int bp, int bq) { return 2 * BKM * ((bp + 4) + (bq + 4) + 4); }
 
 template <int N>
 struct Frag;
@@ -66,7 +73,8 @@ struct Frag<4> {
 // split is a range of the rows that remain (a tap at the rim has shorter ones than the one in the centre, which forms the
 // bias gradient).  (Padding contributes nothing: an infinite gradient beside it, which used to make a NaN of inf * 0, is not read.)
 template <int BP, int BQ, int WP, int WQ, int PROJ, bool PM>
-__global__ __launch_bounds__(NTHREADS, 2) void igemm_wgrad_fast_kernel(WgradProblem p, PositionRows q) {
+__device__ __forceinline__ void wgrad_tile(const WgradProblem &p, const PositionRows &q, const TileGrid &grid, int lin,
+                                           float *lds) {
   static_assert(!PM || (PROJ == 0 && BP == BQ), "one table entry serves a row of both operands");
   constexpr int TP = BP / WP, TQ = BQ / WQ;
   constexpr int PT = TP / 32, QT = TQ / 32;
@@ -78,9 +86,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void igemm_wgrad_fast_kernel(WgradProb
   static_assert(NP >= 1 && NQ >= 1 && RP * NP == BKM && RQ * NQ == BKM, "staging");
   constexpr int NSS = BKM / 4;  // sub-steps per step: two MFMA k-slices (4 reduction rows) each
 
-  __shared__ __attribute__((aligned(16))) float Ds[2][BKM][LDP];
-  __shared__ __attribute__((aligned(16))) float Xs[2][BKM][LDQ];
-  __shared__ int4 Rt[2][BKM];
+  static_assert(lds_floats(BP, BQ) == 2 * BKM * (LDP + LDQ + 4), "staged rows and the table");
+  float(*const Ds)[BKM][LDP] = reinterpret_cast<float(*)[BKM][LDP]>(lds);
+  float(*const Xs)[BKM][LDQ] = reinterpret_cast<float(*)[BKM][LDQ]>(lds + 2 * BKM * LDP);
+  int4(*const Rt)[BKM] = reinterpret_cast<int4(*)[BKM]>(lds + 2 * BKM * (LDP + LDQ));
 
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
@@ -90,9 +99,8 @@ __global__ __launch_bounds__(NTHREADS, 2) void igemm_wgrad_fast_kernel(WgradProb
   // index is re-mapped so that each XCD gets a contiguous run of (split, p-tile, q-tile) with the
   // tiles fastest: all tiles of one split read the same rows of D and X, which then come from that
   // XCD's L2 once instead of from every L2.
-  const int gx = gridDim.x, gy = gridDim.y;
-  const int nwg = gx * gy * (int)gridDim.z;
-  const int lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+  const int gx = grid.x, gy = grid.y;
+  const int nwg = gx * gy * grid.z;
   const int per = nwg >> 3, rem = nwg & 7, xcd = lin & 7, slot = lin >> 3;
   const int log_id = xcd < rem ? xcd * (per + 1) + slot : rem * (per + 1) + (xcd - rem) * per + slot;
   const int bx = log_id % gx, byz = log_id / gx, by = byz % gy, bz = byz / gy;
@@ -128,7 +136,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void igemm_wgrad_fast_kernel(WgradProb
     const int nh = max(0, to(tr, p.H, p.Ho) - ho0);
     nw = max(0, to(ts, p.W, p.Wo) - wo0);
     const int rows = nh * nw * (int)q.div_imgs.d;
-    const int per = ((rows + (int)gridDim.z - 1) / (int)gridDim.z + BKM - 1) / BKM * BKM;
+    const int per = ((rows + grid.z - 1) / grid.z + BKM - 1) / BKM * BKM;
     m_begin = bz * per, m_end = min(rows, m_begin + per);
     magic = nw ? 65535 / nw + 1 : 0;  // i * magic >> 16 = i / nw for i, nw <= 64
   }
@@ -376,6 +384,60 @@ __global__ __launch_bounds__(NTHREADS, 2) void igemm_wgrad_fast_kernel(WgradProb
   }
 }
 
+template <int BP, int BQ, int WP, int WQ, int PROJ, bool PM>
+__global__ __launch_bounds__(NTHREADS, 2) void igemm_wgrad_fast_kernel(WgradProblem p, PositionRows q) {
+  __shared__ __attribute__((aligned(16))) float lds[lds_floats(BP, BQ)];
+  const TileGrid grid = {(int)gridDim.x, (int)gridDim.y, (int)gridDim.z};
+  wgrad_tile<BP, BQ, WP, WQ, PROJ, PM>(p, q, grid, blockIdx.x + grid.x * (blockIdx.y + grid.y * blockIdx.z), lds);
+}
+
+// ---- a head's weight gradient and its layer's in one launch ----
+// Both wait for the head (the layer's for the data gradient, too) and neither reads what the other writes.  In launches of their
+// own each ramps up and drains a chip that it often leaves partly idle (a batch of small images: 1-100 workgroups of 7-14 us, 4-5 us of
+// gap after each).  The layer's workgroups come first, the head's fill in beside and behind them: the same tiles, splits and sums.
+// One kernel per pair of variants: each tile's loop is compiled as in its own kernel, and LDS and registers are the larger
+// of two.  (One kernel that branches over all variants had 20-25 % more vector instructions in its loops, and three workgroups on a CU
+// where these have four: 8 images of 32x32, 3 -> 16 channels, 41.6 us a step, but 3 -> 64 channels, 128 images 293.)  A step, two launches /
+// one, us: 8 images 47.1 / 41.0; 512 -> 512 channels on 2x2 maps, 512 images, 64-wide head 166.3 / 156.5, batch 128, 256-wide head
+// 139.3 / 133; 96 -> 48 channels, 5x5, 32x32, 64 images 448 / 437.
+enum Form { F64, F64_POS, F32, F64_PROJ, F_STEM, F_NONE };  // 64x64, 32x128 (by PROJ, PM), stem_wgrad; a head's are the first three
+
+struct WgradPair {
+  WgradProblem p[2];  // the layer's, the head's
+  PositionRows q[2];
+  TileGrid grid[2];
+  int head_at;  // the head's first workgroup: a multiple of 8, so that both grids' indices lie on the XCDs as in launches of their own
+};
+
+constexpr int form_lds(int form) {
+  return form == F_STEM ? STEM_WGRAD_LDS : form == F32 ? lds_floats(32, 128) : lds_floats(64, 64);
+}
+template <int FORM>
+__device__ __forceinline__ void form_tile(const WgradProblem &p, const PositionRows &q, const TileGrid &g, int lin, float *lds) {
+  if constexpr (FORM == F64) wgrad_tile<64, 64, 2, 2, 0, false>(p, q, g, lin, lds);
+  if constexpr (FORM == F64_POS) wgrad_tile<64, 64, 2, 2, 0, true>(p, q, g, lin, lds);
+  if constexpr (FORM == F32) wgrad_tile<32, 128, 1, 4, 0, false>(p, q, g, lin, lds);
+  if constexpr (FORM == F64_PROJ) wgrad_tile<64, 64, 2, 2, 2, false>(p, q, g, lin, lds);
+  if constexpr (FORM == F_STEM) stem_wgrad_tile<true>(p, lin % g.y, lin / g.y, lds);
+}
+template <int LAYER, int HEAD>
+__global__ __launch_bounds__(NTHREADS, 2) void wgrad_pair_kernel(WgradPair a) {
+  constexpr int FL = form_lds(LAYER), FH = form_lds(HEAD);
+  __shared__ __attribute__((aligned(16))) float lds[FL > FH ? FL : FH];
+  const int lin = blockIdx.x;
+  if (lin >= a.head_at)
+    form_tile<HEAD>(a.p[1], a.q[1], a.grid[1], lin - a.head_at, lds);
+  else if (lin < a.grid[0].x * a.grid[0].y * a.grid[0].z)
+    form_tile<LAYER>(a.p[0], a.q[0], a.grid[0], lin, lds);
+}
+
+void fill_bytes(WgradProblem *p) {
+  const long long B = p->M / ((long long)p->Ho * p->Wo);
+  p->d_bytes = (uint32_t)((long long)p->M * p->P * 4);
+  p->x_bytes = (uint32_t)(B * p->H * p->W * p->C * 4);
+  p->xs_bytes = p->Cs ? (uint32_t)(B * p->Hs * p->Ws * p->Cs * 4) : 0;
+}
+
 // Whether the rows of padding are left out (PM): at most 85 of 100 remain, and some tap sees every position.  Measured (us,
 // with all rows / without), 128 images on 2x2 maps (4 of 9 remain): 512x4608 in three splits 34.4 / 24.4, 256x4608 in four 20.0 / 13.9.
 bool position_rows(const WgradProblem &p, int bq, PositionRows *q) {
@@ -395,6 +457,55 @@ bool position_rows(const WgradProblem &p, int bq, PositionRows *q) {
   if (all_r < 0 || all_s < 0) return false;
   q->div_imgs = FastDiv(p.M / (p.Ho * p.Wo)), q->bias_tile = (all_r * p.S + all_s) * (p.C / bq);
   return 100ll * nr * ns <= 85ll * p.Ho * p.Wo * p.R * p.S;
+}
+
+// which of a pair's variants serves a problem (F_NONE: another kernel), and its grid
+int pair_form(WgradProblem *p, PositionRows *q, TileGrid *g) {
+  q->bias_tile = 0;
+  if (igemm_wgrad_small_applicable(*p)) return F_NONE;
+  if (igemm_wgrad_fast_applicable(*p)) {
+    if (contraction_mode() != NF_CONTRACT_F32 && igemm_wgrad_split_applicable(*p)) return F_NONE;
+    if (p->P > 64 && !igemm_wgrad_tile64(p->P, p->Q, p->splits)) return F_NONE;
+    const bool narrow = p->P <= 32;
+    const int bp = narrow ? 32 : 64, bq = narrow ? 128 : 64;
+    if (p->Cs && (narrow || p->RSC % bq)) return F_NONE;
+    fill_bytes(p);
+    *g = {(p->Q + bq - 1) / bq, (p->P + bp - 1) / bp, p->splits};
+    return narrow ? F32 : position_rows(*p, bq, q) ? F64_POS : p->Cs ? F64_PROJ : F64;
+  }
+  if (!stem_wgrad_applicable(*p) || p->P % 4) return F_NONE;
+  *g = {1, (p->P + 63) / 64, p->splits};
+  return F_STEM;
+}
+
+long long tiles(const TileGrid &g) { return (long long)g.x * g.y * g.z; }
+
+typedef void (*PairKernel)(WgradPair);
+template <int LAYER>
+PairKernel pair_kernel_of(int head) {
+  return head == F64       ? wgrad_pair_kernel<LAYER, F64>
+         : head == F64_POS ? wgrad_pair_kernel<LAYER, F64_POS>
+         : head == F32     ? wgrad_pair_kernel<LAYER, F32>
+                           : nullptr;
+}
+
+PairKernel make_pair(const WgradProblem &layer, const WgradProblem &head, WgradPair *a) {
+  a->p[0] = layer, a->p[1] = head;
+  const int fl = pair_form(&a->p[0], &a->q[0], &a->grid[0]), fh = pair_form(&a->p[1], &a->q[1], &a->grid[1]);
+  if (fl == F_NONE || fh > F32) return nullptr;
+  a->head_at = (int)((tiles(a->grid[0]) + 7) / 8 * 8);
+  // Of 64x64 tiles four reside on a CU, of the others (LDS, registers) three, and so of a pair that holds one.  A pair of those
+  // that leaves a small second round of long tiles is no faster than two launches (step, us, two / one: 1020 workgroups of 14.5 GFLOP
+  // 359 / 372, 1022 of 2.6 121.7 / 131.3, 1024 of 1.2 102.2 / 105.6, but 867 of 1.1 79.7 / 77.0, 1122 of 0.6 79.2 / 75.0).  Of
+  // 82 random pairs all others gained, 2-11 us.
+  const bool three = fl == F32 || fl == F64_PROJ || fh == F32;
+  const double flops = 2.0 * ((double)layer.M * layer.P * layer.Q + (double)head.M * head.P * head.Q);
+  if (three && tiles(a->grid[0]) + tiles(a->grid[1]) > 3 * 256 && flops > 1e9) return nullptr;
+  return fl == F64       ? pair_kernel_of<F64>(fh)
+         : fl == F64_POS ? pair_kernel_of<F64_POS>(fh)
+         : fl == F32     ? pair_kernel_of<F32>(fh)
+         : fl == F_STEM  ? pair_kernel_of<F_STEM>(fh)
+                         : pair_kernel_of<F64_PROJ>(fh);
 }
 
 template <int BP, int BQ, int WP, int WQ>
@@ -442,10 +553,7 @@ hipError_t launch_igemm_wgrad_fast(const WgradProblem &p0, hipStream_t st, const
   if (contraction_mode() != NF_CONTRACT_F32 && igemm_wgrad_split_applicable(p0))
     return launch_igemm_wgrad_split(p0, contraction_mode() == NF_CONTRACT_BF16X9, st, kernel);
   WgradProblem p = p0;
-  const long long B = p.M / ((long long)p.Ho * p.Wo);
-  p.d_bytes = (uint32_t)((long long)p.M * p.P * 4);
-  p.x_bytes = (uint32_t)(B * p.H * p.W * p.C * 4);
-  p.xs_bytes = p.Cs ? (uint32_t)(B * p.Hs * p.Ws * p.Cs * 4) : 0;
+  fill_bytes(&p);
   if (p.P > 64 && !igemm_wgrad_tile64(p.P, p.Q, p.splits)) {
     *kernel = "igemm_wgrad_fast_128x128";
     return launch_cfg<128, 128, 2, 2>(p, st);
@@ -456,6 +564,19 @@ hipError_t launch_igemm_wgrad_fast(const WgradProblem &p0, hipStream_t st, const
   }
   *kernel = "igemm_wgrad_fast_32x128";
   return launch_cfg<32, 128, 1, 4>(p, st);
+}
+
+bool wgrad_pair_applicable(const WgradProblem &layer, const WgradProblem &head) {
+  WgradPair a;
+  return make_pair(layer, head, &a) != nullptr;
+}
+
+hipError_t launch_wgrad_pair(const WgradProblem &layer, const WgradProblem &head, hipStream_t st) {
+  WgradPair a;
+  const PairKernel kernel = make_pair(layer, head, &a);
+  if (!kernel) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(a.head_at + tiles(a.grid[1]))), dim3(NTHREADS), 0, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace nf

@@ -637,17 +637,25 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
                            head_relay(a, ap, ws, w), wsf(ws, w.loss_n), loss_out,
                            reinterpret_cast<const int32_t *>(wsf(ws, w.parg)), st));
   // beta_n: weight + bias gradient
-  {
-    WgradProblem g = aux_wgrad_shape(a, ad, B);
-    g.d = dU, g.x = y, g.part = wsf(ws, w.part_aux), g.part_b = wsf(ws, w.part_b_aux);
-    g.Qld = w.Qld_aux;
-    g.splits = w.splits_aux;
-    g.m_per_split = ((g.M + g.splits - 1) / g.splits + 31) / 32 * 32;  // whole 32-row steps
-    g.div_howo = FastDiv(ad.Hu * ad.Wu), g.div_wo = FastDiv(ad.Wu);
-    const int32_t rc = enqueue_wgrad(g, st);
-    if (rc) return rc;
-    red.job[1] = reduce_job(g, ga->Wa, nullptr, ga->ba);
-  }
+  WgradProblem gh = aux_wgrad_shape(a, ad, B);
+  gh.d = dU, gh.x = y, gh.part = wsf(ws, w.part_aux), gh.part_b = wsf(ws, w.part_b_aux);
+  gh.Qld = w.Qld_aux;
+  gh.splits = w.splits_aux;
+  gh.m_per_split = ((gh.M + gh.splits - 1) / gh.splits + 31) / 32 * 32;  // whole 32-row steps
+  gh.div_howo = FastDiv(ad.Hu * ad.Wu), gh.div_wo = FastDiv(ad.Wu);
+  red.job[1] = reduce_job(gh, ga->Wa, nullptr, ga->ba);
+  // theta_n: weight, bias and projection gradients; nothing flows to x or x_skip
+  WgradProblem g = layer_wgrad_shape(d, ld, B);
+  g.d = dZ, g.x = x, g.part = wsf(ws, w.part), g.part_b = wsf(ws, w.part_b);
+  if (d->skip_kind == 2) g.xs = xs;
+  g.Qld = w.Qld_layer;
+  g.splits = w.splits_layer;
+  g.m_per_split = ((g.M + g.splits - 1) / g.splits + 31) / 32 * 32;  // whole 32-row steps
+  const bool wino = run_wino(g, w.wino_wgrad);
+  // one launch for both where that serves them, after the data gradient.  (A measurement times each kernel by itself.)
+  const bool pair = !wino && !prof_active() && wgrad_pair_applicable(g, gh);
+  int32_t rc;
+  if (!pair && (rc = enqueue_wgrad(gh, st))) return rc;
   // beta_n: data gradient w.r.t. the emitted activation, layer ReLU mask fused when un-pooled
   {
     FwdProblem f = dgrad_problem(a, ad, B);
@@ -655,9 +663,9 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
     f.mask = pooled ? nullptr : y;
     // by a head launch of this call; a forward call of its own may have had a workspace without the region
     const bool filter_ready = sgd || !w.head_fused;
-    const int32_t rc = enqueue_conv(f, pooled ? wsf(ws, w.dY) : dZ, w.wino_dgrad, w.ksplits_dgrad, wsf(ws, w.part),
-                                    st, filter_ready ? wsf(ws, w.Ud) : nullptr);
-    if (rc) return rc;
+    if ((rc = enqueue_conv(f, pooled ? wsf(ws, w.dY) : dZ, w.wino_dgrad, w.ksplits_dgrad, wsf(ws, w.part),
+                           st, filter_ready ? wsf(ws, w.Ud) : nullptr)))
+      return rc;
     if (pooled) {
       const double pre = (double)B * ld.Ho * ld.Wo * d->C_out, post = (double)B * ld.Hp * ld.Wp * d->C_out;
       NF_RUN(st, "maxpool_bwd", 0.0, 4.0 * pre + 9.0 * post,
@@ -665,33 +673,25 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
                                 ld.Wo, d->C_out, ld.Hp, ld.Wp, d->pool_k, d->pool_stride, d->pool_pad, st));
     }
   }
-  // theta_n: weight, bias and projection gradients; nothing flows to x or x_skip
-  {
-    WgradProblem g = layer_wgrad_shape(d, ld, B);
-    g.d = dZ, g.x = x, g.part = wsf(ws, w.part), g.part_b = wsf(ws, w.part_b);
-    if (d->skip_kind == 2) g.xs = xs;
-    g.Qld = w.Qld_layer;
-    int32_t rc;
-    if (run_wino(g, w.wino_wgrad)) {
-      WgradProblem pr = g;  // the projection's columns
-      g.splits = w.wino_wgrad, g.Q = g.Qld = g.RSC, g.Cs = 0;
-      const double byts = 4.0 * ((double)g.M * g.P + (double)B * g.H * g.W * g.C + (double)g.P * g.Q);
-      NF_RUN(st, "wino_wgrad", 2.0 * g.M * g.P * g.Q, byts, launch_wino_wgrad(g, st));
-      if (pr.Cs) {
-        pr.x = xs, pr.H = pr.Hs, pr.W = pr.Ws, pr.C = pr.Cs, pr.stride = pr.ss, pr.R = pr.S = 1, pr.pad = 0, pr.Cs = 0;
-        pr.Q = pr.RSC = pr.C, pr.Qld = (pr.Q + 3) / 4 * 4, pr.splits = w.proj_splits, pr.part_b = nullptr;
-        pr.part = g.part + (size_t)g.splits * g.P * g.Qld;
-        pr.m_per_split = ((pr.M + pr.splits - 1) / pr.splits + 31) / 32 * 32;
-        if ((rc = enqueue_wgrad(pr, st))) return rc;
-        red.job[2] = reduce_job(pr, gp->Wp, nullptr, nullptr);
-      }
-    } else {
-      g.splits = w.splits_layer;
-      g.m_per_split = ((g.M + g.splits - 1) / g.splits + 31) / 32 * 32;  // whole 32-row steps
-      if ((rc = enqueue_wgrad(g, st))) return rc;
+  if (wino) {
+    WgradProblem pr = g;  // the projection's columns
+    g.splits = w.wino_wgrad, g.Q = g.Qld = g.RSC, g.Cs = 0;
+    const double byts = 4.0 * ((double)g.M * g.P + (double)B * g.H * g.W * g.C + (double)g.P * g.Q);
+    NF_RUN(st, "wino_wgrad", 2.0 * g.M * g.P * g.Q, byts, launch_wino_wgrad(g, st));
+    if (pr.Cs) {
+      pr.x = xs, pr.H = pr.Hs, pr.W = pr.Ws, pr.C = pr.Cs, pr.stride = pr.ss, pr.R = pr.S = 1, pr.pad = 0, pr.Cs = 0;
+      pr.Q = pr.RSC = pr.C, pr.Qld = (pr.Q + 3) / 4 * 4, pr.splits = w.proj_splits, pr.part_b = nullptr;
+      pr.part = g.part + (size_t)g.splits * g.P * g.Qld;
+      pr.m_per_split = ((pr.M + pr.splits - 1) / pr.splits + 31) / 32 * 32;
+      if ((rc = enqueue_wgrad(pr, st))) return rc;
+      red.job[2] = reduce_job(pr, gp->Wp, nullptr, nullptr);
     }
-    red.job[0] = reduce_job(g, gp->W, gp->Wp, gp->b);
+  } else if (pair) {
+    NF_HIP(launch_wgrad_pair(g, gh, st));
+  } else if ((rc = enqueue_wgrad(g, st))) {
+    return rc;
   }
+  red.job[0] = reduce_job(g, gp->W, gp->Wp, gp->b);
   red.njobs = red.job[2].part ? 3 : 2;
   double nred = 0, nsgd = 0;
   for (int j = 0; j < red.njobs; ++j) nred += ((double)red.job[j].splits + 1.0) * red.job[j].P * (red.job[j].Q + 1.0);

@@ -119,6 +119,9 @@ hipError_t launch_igemm_wgrad(const WgradProblem &p, hipStream_t st, const char 
 // software-pipelined buffer-load variant (igemm_wgrad_fast.hip); launch_igemm_wgrad picks it when applicable
 bool igemm_wgrad_fast_applicable(const WgradProblem &p);
 hipError_t launch_igemm_wgrad_fast(const WgradProblem &p, hipStream_t st, const char **kernel);
+// a layer's weight gradient and its head's in one launch (igemm_wgrad_fast.hip), the same tiles and sums as in two
+bool wgrad_pair_applicable(const WgradProblem &layer, const WgradProblem &head);
+hipError_t launch_wgrad_pair(const WgradProblem &layer, const WgradProblem &head, hipStream_t st);
 // fp32 weight gradient on the bf16 matrix cores through three-way split operands
 // (igemm_wgrad_split.hip); launch_igemm_wgrad_fast hands over to it in the NF_CONTRACT_BF16X* modes
 bool igemm_wgrad_split_applicable(const WgradProblem &p);
