@@ -852,7 +852,13 @@ __global__ __launch_bounds__(HT, 3) void head_wide_kernel(HeadShape s, int NS, c
 #pragma unroll
   for (int k = 0; k < AHEAD; ++k)
     if (i0 + k * HT < i1) element(i0 + k * HT, ahead[k]);
-  for (int i = i0 + AHEAD * HT; i < i1; i += HT) element(i, load_chan<V>(U + (base + i) * V));
+  for (int c = i0 + AHEAD * HT; c < i1; c += AHEAD * HT) {  // as many loads in flight, or each waits for the store before it
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) ahead[k] = load_chan<V>(un + min(c + k * HT, per_n - 1) * V);
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+      if (c + k * HT < i1) element(c + k * HT, ahead[k]);
+  }
 }
 
 // Backward of the head after the softmax in one launch (gradient line of Algorithm 2); the
@@ -1004,7 +1010,14 @@ hipError_t launch_head_sample(const HeadShape &h, float *U, const float *part, i
 bool head_wide_applicable(const HeadShape &h) {
   // the linear layer small enough to be recomputed by every slice of a sample (its weights read
   // from L2 by every workgroup); wider ones share the weights between samples (head_fc_wide_kernel)
-  return !head_sample_applicable(h) && (long long)h.F * h.Cls <= 16384 && h.F <= 1024 && h.Cls <= 1024;
+  // Wide rows are read side by side (logits_sample): from 256 features and 100 classes on, on maps of up to 256 pixels, one launch is
+  // faster than three, too (step, us, three / one: 64 samples of 16x16 pixels, 64 filters, 200 classes 114.2 / 100.7, 100 classes 101.8 /
+  // 95.2; 100 of 14x14, 200 classes 139.2 / 128.1, 37 of 7x7 80.5 / 66.9; 80 filters, 100 classes, 256 of 16x16 260 / 253).
+  // Not so on larger maps (80 filters, 60 classes, 500 of 32x32 1518 / 1525), with 512 features (37 classes, 100 of 14x14 153 / 156) or
+  // fewer classes (80 filters, 60, 256 of 16x16, gradients alone 236.6 / 238.8), and with 128 features, where the launches it saves are
+  // short, only for some (32 filters, 200 classes, 64 of 16x16 from 32 channels 88.9 / 84.0, gradients from 128 102.6 / 107.1).
+  const bool rows = h.A % 4 == 0 && h.F >= 256 && h.F <= 320 && h.Cls >= 100 && h.Cls <= 200 && h.Hu * h.Wu <= 256;
+  return !head_sample_applicable(h) && (rows || (long long)h.F * h.Cls <= 16384) && h.F <= 1024 && h.Cls <= 1024;
 }
 
 bool head_pool_partials_applicable(const HeadShape &h) {

@@ -224,8 +224,8 @@ bool head_sample_applicable(const HeadShape &h);
 hipError_t launch_head_sample(const HeadShape &h, float *U, const float *part, int splits, const float *ba,
                               const int32_t *labels, const float *Wf, const float *bf, float *Pq, int32_t *parg,
                               float *dz, float *loss_n, float *dU, const RelayJob &rj, hipStream_t st);
-// Everything after F_n for a large activation map in one launch (head_wide_applicable: a linear
-// layer of at most 16384 weights): gamma_n, loss, dL/dz, dPq recomputed per slice of a sample, dU,
+// Everything after F_n for a large activation map in one launch (where
+// head_wide_applicable): gamma_n, loss, dL/dz, dPq recomputed per slice of a sample, dU,
 // and the RelayJob.  Reads Pq (and the max-pooling selection) left by
 // launch_head_pool; leaves dz and loss_n for the batch-reducing jobs (GammaJob).
 // `ppart` (or null): column sums per 16 pixels from the aux convolution's epilogue
