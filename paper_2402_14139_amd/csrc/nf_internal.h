@@ -40,7 +40,7 @@ struct FwdProblem {
   // (no bias, shortcut, ReLU or mask); only with a value igemm_fwd_pick_ksplits returned
   int ksplits;
   // Column sums of the finished output over groups of 16 consecutive rows, for the head's average
-  // pooling (skinny 16x16x4 tiles only, see fwd_pool_partials_applicable): pool_part[r16][2][N],
+  // pooling (where fwd_pool_partials_applicable): pool_part[r16][2][N],
   // slot 0 = the sum over rows 16*r16 .. +7 (pool_split) or .. +15 (!pool_split), slot 1 = rows +8 .. +15
   // (pool_split only).  Null: not formed.
   float *pool_part;

@@ -28,12 +28,11 @@
 // 43 / 35; 128 -> 128, 32 768 pixels 80 / 48; 256 -> 256, 16 384 pixels 155 / 83; 512 -> 512, 8192 pixels 312 / 150
 // (a step of 8 channels takes 2.1 us on a CU with two workgroups, 0.87 of it MFMAs).
 //
-// Up to 32 filters (the heads' usual width) a variant of 32 per workgroup runs, half of whose columns would be
-// padding otherwise: 64 accumulators, three workgroups per CU, the same patches and transforms for half of the
-// MFMAs, so a step of 16 MFMAs takes 1.3 us with two workgroups on a CU where they alone take 0.9.  In front of the head's
-// pooling its epilogue leaves the sums over 16 pixels that the direct kernel's does.  Measured (us, the direct kernel
+// Up to 32 filters (narrow layers, and the data gradients onto them) a variant of 32 per workgroup runs, half of whose columns
+// would be padding otherwise: 64 accumulators, three workgroups per CU, the same patches and transforms for half of the
+// MFMAs, so a step of 16 MFMAs takes 1.3 us with two workgroups on a CU where they alone take 0.9.  Measured (us, the direct kernel
 // of 64x32 tiles / this, without the filter's launch): 64 channels, 65 536 pixels 30.2 / 19.5, 128 channels, 16 384 pixels 17.1 /
-// 12.3; a 64-channel step with a 32-wide head 175.1 / 166.5.
+// 12.3.  (Convolutions of heads of that width stay with the direct kernel: their errors would grow, nf_api.hip.)
 //
 // A value that is not finite anywhere in a tile makes neighbours of the transformed domain NaN that
 // the direct sum would leave finite (or infinite): a thread that finds one among its results
@@ -297,11 +296,10 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
   const bool split = gridDim.y > 1;
   float *const out = p.out + (split ? (long long)blockIdx.y * p.M * p.N : 0ll);
   const int n = nb * NB + (t % NG) * 4;
-  // (NF = 1: a wave takes 8 consecutive tiles, what p.pool_part sums)
   // (POOL: a thread takes both columns of a tile)
   auto task_of = [&](int i) {
     if constexpr (POOL) return ((i >> 1) * (NTHREADS / NG) + t / NG) * 2 + (i & 1);
-    return NF == 2 ? i * 16 + (t >> 4) : row * 16 + i * 8 + (lane >> 3);
+    return i * (NTHREADS / NG) + t / NG;
   };  // (tile, column)
   long long off[NT][2];  // -1: no such pixel or filter
 #pragma unroll
@@ -433,7 +431,6 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
     return;
   }
   unsigned bad = 0;  // four bits from 4*(2*i + k): which of those results are not finite
-  float4 ps[NF == 1 ? NT : 1][2];  // what each stored, for p.pool_part
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
     const int task = task_of(i), lt = task >> 1;
@@ -444,49 +441,13 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
     const float4 y[2] = {add4(add4(r0, r1), r2), sub4(sub4(r1, r2), r3)};
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      if constexpr (NF == 1) ps[i][k] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (off[i][k] < 0) continue;
       const unsigned b = bad4(y[k]);
       bad |= b << (4 * (2 * i + k));
-      const float4 v = finish(y[k], ex[i][k], off[i][k]);
-      if constexpr (NF == 1) ps[i][k] = v;
-      store(v, off[i][k], b);
+      store(finish(y[k], ex[i][k], off[i][k]), off[i][k], b);
     }
   }
-  // sums over 16 consecutive pixels for the head's pooling: the wave's eight tiles are 16 pixels of two image
-  // rows, its first four (i = 0) their first 8 (lanes along the columns pairwise, then the halves: a fixed order)
-  auto pool = [&] {
-    if constexpr (NF == 1) {
-      const int tile = t0 + row * 8;
-      if (tile >= q.T) return;  // (whole wave; its tiles lie in one tile row)
-      const int img = (int)q.div_tpi.div((uint32_t)tile), rem = tile - img * q.TPI;
-      const int ty = (int)q.div_tw.div((uint32_t)rem), tx = rem - ty * q.TW;
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        float4 s[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          s[i] = ps[i][k];
-#pragma unroll
-          for (int o = 8; o < 64; o *= 2)
-            s[i] = add4(s[i], make_float4(__shfl_xor(s[i].x, o, 64), __shfl_xor(s[i].y, o, 64),
-                                          __shfl_xor(s[i].z, o, 64), __shfl_xor(s[i].w, o, 64)));
-        }
-        if (lane >= NG || n >= p.N) continue;
-        float *const dst = p.pool_part + (((long long)(img * p.Ho + 2 * ty + k) * p.Wo + 2 * tx) >> 4) * 2 * p.N + n;
-        *reinterpret_cast<float4 *>(dst) = p.pool_split ? s[0] : add4(s[0], s[1]);
-        if (p.pool_split) *reinterpret_cast<float4 *>(dst + p.N) = s[1];
-      }
-    }
-  };
-  if (p.pool_part) {  // with results formed again in their place
-    if (!__ballot(bad != 0)) {
-      pool();
-      return;
-    }
-  } else if (bad == 0) {
-    return;
-  }
+  if (bad == 0) return;
 #pragma unroll 1
   for (int ik = 0; ik < 2 * NT; ++ik) {
     const unsigned want = bad >> (4 * ik) & 15u;
@@ -499,21 +460,8 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
     const float4 v = direct4(p.x, p.w, p.H, p.W, p.C, img, ho, wo, n, s_lo * CH, min(p.C, s_hi * CH), want);
     float4 x = bias;
     if (extra) x = *reinterpret_cast<const float4 *>(extra + o);
-    const float4 f = finish(v, x, o);
-    store(f, o, ~want & 15u);
-    if constexpr (NF == 1) {
-#pragma unroll
-      for (int k = 0; k < 2 * NT; ++k)
-        if (k == ik) {
-          float4 &s = ps[k >> 1][k & 1];
-          if (want & 1u) s.x = f.x;
-          if (want & 2u) s.y = f.y;
-          if (want & 4u) s.z = f.z;
-          if (want & 8u) s.w = f.w;
-        }
-    }
+    store(finish(v, x, o), o, ~want & 15u);
   }
-  if (p.pool_part) pool();
 }
 
 }  // namespace
@@ -525,7 +473,7 @@ size_t wino_fwd_filter_floats(int N, int C) {
 
 namespace {
 bool applicable(const FwdProblem &p) {
-  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1) return false;
+  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.pool_part) return false;
   if (p.C % 4 || p.N % 4) return false;
   const long long lim = 0x7FFFFFF0ll, B = p.M / ((long long)p.Ho * p.Wo);
   return B * p.H * p.W * p.C * 4 <= lim && (long long)wino_fwd_filter_floats(p.N, p.C) * 4 <= lim;
@@ -570,7 +518,9 @@ double wino_us(const FwdProblem &p, int s) {
 // forward sweep of four layers of 32 channels on 40x43 maps, batch 39, 299 us, with two launches a layer 310); the direct kernel of 64x32 tiles in its place 0.3 us per step
 // and workgroup on a CU.  On 36 random shapes (17 ... 32 filters, 16 ... 512 channels) this one is chosen 10 times and is the
 // faster one each time, by 3 to 33 % (us, direct / this with its filter launch: 64 -> 32, 204 800 pixels 72.5 / 50.1; 16 -> 28, 174 592
-// pixels 29.2 / 22.6; 64 -> 32, 16 384 pixels 12.0 / 14.7, direct); its error is the smaller one on all 36 (64 -> 32 2.9e-7 / 2.1e-7)
+// pixels 29.2 / 22.6; 64 -> 32, 16 384 pixels 12.0 / 14.7, direct); the error of its single results is the smaller one on all 36 (64 -> 32
+// 2.9e-7 / 2.1e-7), and sums over pixels and samples of a layer's gradients are as exact as they were (32 -> 32 channels, 40x43, batch
+// 39, 80-wide head: dW 2.4e-7 / 1.7e-7)
 double narrow_us(const FwdProblem &p, int s, bool ready) {
   const int nchunks = (p.C + CH - 1) / CH;
   const long long w = workgroups(p) * s, full = w / 768, rest = w % 768;

@@ -1,6 +1,5 @@
-"""F(2x2, 3x3) in its variant of 32 filters (csrc/wino_fwd.hip): heads and layers of 17 ... 32 filters
-against the CPU oracle, its sums for the head's pooling, and values that are not finite."""
-import numpy as np
+"""F(2x2, 3x3) in its variant of 32 filters (csrc/wino_fwd.hip): layers of 17 ... 32 filters and the data gradients onto them
+against the CPU oracle, and the convolutions that do not run through it for the accuracy of averages over their results."""
 import pytest
 import torch
 
@@ -12,16 +11,17 @@ pytestmark = pytest.mark.gpu
 
 # name -> (spec, B, classes, launches of the variant)
 CASES = {
-    # pooling sums from the epilogue: rows of 16 pixels (two slots), of 32, of 64 (a ragged head)
-    "pool_16": (S(16, 16, 16, 64, 32), 256, 10, 1),
-    "pool_32": (S(64, 32, 32, 64, 32), 64, 10, 1),
-    "pool_64_a20": (S(8, 6, 64, 64, 20), 170, 10, 1),
-    # odd maps: pooled by a launch of its own; a ragged last tile block and channels that are no multiple of 8
-    "odd_13x15_a28": (S(20, 13, 15, 68, 28), 260, 10, 1),
-    # a layer and its data gradient of few filters, and the head
+    # a layer and its data gradient of few filters
     "narrow_layer": (S(48, 28, 27, 28, 24), 80, 10, 2),
-    # reduction in parts, which the pooling launch adds
-    "parts": (S(8, 12, 12, 256, 32), 100, 10, 1),
+    # odd maps: a ragged last tile block, channels that are no multiple of 8
+    "odd_13x15_k28": (S(68, 13, 15, 28, 20), 260, 10, 1),
+    # reduction in parts
+    "parts": (S(256, 12, 12, 32, 16), 100, 10, 1),
+    # heads of few filters keep the direct kernel
+    "pool_16": (S(16, 16, 16, 64, 32), 256, 10, 0),
+    "pool_32": (S(64, 32, 32, 64, 32), 64, 10, 0),
+    "odd_13x15_a28": (S(20, 13, 15, 68, 28), 260, 10, 0),
+    "head_parts": (S(8, 12, 12, 256, 32), 100, 10, 0),
 }
 
 
@@ -33,43 +33,43 @@ def test_narrow_steps_match_oracle(name):
     out, final = G.run_step_both(spec, cls, B, seed=330, lr=0.05, mu=0.9, steps=1)
     got = {r["kernel"]: r["launches"] for r in nf.nf_prof_end()}
     G.check_step_results(name, out, final)
-    assert got.get("wino_fwd_32", 0) >= launches, got
+    n = got.get("wino_fwd_32", 0)
+    assert n >= launches and (launches or not n), got
 
 
-@pytest.mark.parametrize("W", [16, 32])
-def test_pooling_sums_hold_results_formed_again(W):
-    """An infinity in one pixel: the loss of that sample alone is not finite, all others keep theirs."""
-    B, H, K, A, cls = 256, 16, 64, 32, 10
-    g = torch.Generator(device="cuda").manual_seed(3)
+def filter_rounding_mean(x, w):
+    """What the fp32 rounding of the transformed filter alone adds to a convolution's results (x [B,H,W,C], even sizes; w
+    [K,3,3,C]), averaged over images and pixels [K]: everything else in 64 bits."""
+    Gm = torch.tensor([[1, 0, 0], [.5, .5, .5], [.5, -.5, .5], [0, 0, 1]], device=w.device, dtype=torch.float64)
+    Bt = torch.tensor([[1, 0, -1, 0], [0, 1, 1, 0], [0, -1, 1, 0], [0, 1, 0, -1]], device=w.device, dtype=torch.float64)
+    At = torch.tensor([[1, 1, 1, 0], [0, 1, -1, -1]], device=w.device, dtype=torch.float64)
+    U = torch.einsum("ar,krsc,bs->kabc", Gm, w.double(), Gm)
+    dU = U.float().double() - U
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    # the mean patch d[i][j] over all tiles: rows i, i + 2, ... of the padded image
+    H, W = x.shape[1:3]
+    d = torch.stack([torch.stack([xp[:, i:i + H:2, j:j + W:2].mean(dim=(0, 1, 2)) for j in range(4)]) for i in range(4)])
+    V = torch.einsum("ai,ijc,bj->abc", Bt, d, Bt)
+    return torch.einsum("pa,kab,qb->kpq", At, torch.einsum("kabc,abc->kab", dU, V), At).mean(dim=(1, 2))
+
+
+@pytest.mark.parametrize("C,H,A,B", [(64, 32, 32, 64), (128, 16, 20, 256), (64, 64, 32, 16)])
+def test_averages_of_head_convolutions(C, H, A, B):
+    """F_n averages a head's activation over pixels and its gradients sum over samples: rounding that is the same for all of them
+    stays.  The direct sum's is not the same (its averages are off by about a third of what a transformed filter's single rounding
+    leaves), so that the line lies at 0.6 of that."""
+    g = torch.Generator(device="cuda").manual_seed(C)
     rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
-    d = nf.LayerDesc(C_in=8, H_in=H, W_in=W, C_out=K, R=3, S=3, stride=1, pad=1)
-    a = nf.AuxDesc(C_in=K, H_in=H, W_in=W, A=A, R=3, S=3, pad=1, relu=1, pool_oh=2, pool_ow=2, n_classes=cls)
-    y = rn(B, H, W, K).relu()
-    labels = torch.randint(0, cls, (B,), generator=g, device="cuda", dtype=torch.int32)
-    p = [rn(A, 3, 3, K) * 0.05, rn(A), rn(cls, 4 * A) * 0.2, rn(cls)]
-    ap = nf.aux_params(*p)
+    d = nf.LayerDesc(C_in=16, H_in=H, W_in=H, C_out=C, R=3, S=3, stride=1, pad=1)
+    a = nf.AuxDesc(C_in=C, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=0, pool_oh=2, pool_ow=2, n_classes=10)
+    y, labels = rn(B, H, H, C).relu(), torch.zeros(B, device="cuda", dtype=torch.int32)
+    Wa = rn(A, 3, 3, C) * (2.0 / (9 * C)) ** 0.5
+    ap = nf.aux_params(Wa, torch.zeros(A, device="cuda"), rn(10, 4 * A) * 0.1, torch.zeros(10, device="cuda"))
     ws = torch.empty(nf.nf_workspace_bytes(d, a, B), dtype=torch.uint8, device="cuda")
+    nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, torch.zeros(1, device="cuda"), ws)
     off, nbytes = nf.nf_workspace_region(d, a, B, nf.NF_WS_AUX_ACT)
-    loss, acts = torch.zeros(1, device="cuda"), []
-    for bad in (False, True):
-        if bad:
-            y[5, 4, 7, 3] = float("inf")
-        nf.nf_prof_begin()
-        nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, loss, ws)
-        names = {r["kernel"] for r in nf.nf_prof_end()}
-        assert "wino_fwd_32" in names and "head_pool" not in names, names
-        u = ws[off:off + nbytes].view(torch.float32).reshape(B, H, W, A).double()
-        # the pooled features, logits and loss in 64 bits from the activation the kernel stored
-        q = u.reshape(B, 2, H // 2, 2, W // 2, A).mean(dim=(2, 4)).reshape(B, -1)
-        z = q @ p[2].double().t() + p[3].double()
-        acts.append((u, torch.nn.functional.cross_entropy(z, labels.long(), reduction="none"), float(loss)))
-    (u0, l0, got0), (u1, l1, got1) = acts
-    assert abs(got0 - float(l0.mean())) <= 1e-5 * abs(float(l0.mean()))
-    inf = torch.isinf(u1)
-    at = torch.zeros_like(inf)
-    at[5, 3:6, 6:9, :] = p[0].permute(1, 2, 0, 3)[..., 3].flip(0, 1) > 0  # positive taps on that pixel, the others' ReLU is 0
-    assert torch.equal(inf, at) and not np.isfinite(got1)
-    # 576-term sums in two orders where a neighbour was not finite: a few 1e-7 of the largest value
-    seen = torch.zeros_like(inf)
-    seen[5, 3:6, 6:9, :] = True
-    assert (u1 - u0)[~seen].abs().max() <= 5e-6 * u0.max()
+    got = ws[off:off + nbytes].view(torch.float32).reshape(-1, A).double().mean(0)
+    yp = torch.nn.functional.pad(y.double(), (0, 0, 1, 1, 1, 1))
+    mean = torch.stack([torch.stack([yp[:, r:r + H, s:s + H].mean(dim=(0, 1, 2)) for s in range(3)]) for r in range(3)])
+    ref = torch.einsum("krsc,rsc->k", Wa.double(), mean)
+    assert (got - ref).norm() <= 0.6 * filter_rounding_mean(y, Wa).norm()
