@@ -262,15 +262,11 @@ WsLayout ws_layout_of(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_
     w.ksplits_dgrad = igemm_fwd_pick_ksplits(B * a->H_in * a->W_in, a->C_in, a->R * a->S * a->A, a->A, a->R * a->S);
     if (w.ksplits_dgrad > 1 && (size_t)w.ksplits_dgrad * emitted > pmax) pmax = (size_t)w.ksplits_dgrad * emitted;
     const FwdProblem fa = aux_fwd_problem(a, ad, B), fd = dgrad_problem(a, ad, B);
-    // (Heads of up to 32 filters keep the direct sum.  The transformed filter is rounded once for all pixels and samples, which
-    // F_n averages and the gradients sum: single elements come out closer to 64 bits, these averages not.  Against the direct sum, on
-    // eleven heads: dWf of 64 samples of 16x16 pixels, 128 channels, 1.4e-7 -> 2.0e-7, of 32x32, 32 channels, 9.1e-8 -> 1.2e-7, most
-    // others up to 1.15 times.  A layer's own output and gradients, whose kernel this is in wino_fwd_pick_splits, do not grow.)
     // (no more parts than the direct kernel's: a pooling launch adds them, few workgroups of it where samples are few; 7
     // samples of 32x31, 128 -> 80 channels: pooling 12 us unsplit, 31 with two parts)
-    w.wino_aux = pl.aux && a->A > 32 ? wino_fwd_pick_splits(fa, w.ksplits_aux, w.ksplits_aux) : 0;
+    w.wino_aux = pl.aux ? wino_fwd_pick_splits(fa, w.ksplits_aux, w.ksplits_aux) : 0;
     w.part_aux_fwd = wino_scratch_floats(w.wino_aux, fa);
-    w.wino_dgrad = pl.dgrad ? wino_fwd_pick_splits(fd, w.ksplits_dgrad, 16, true) : 0;
+    w.wino_dgrad = pl.dgrad ? wino_dgrad_pick_splits(fd, w.ksplits_dgrad, true) : 0;
     w.Ud = take_or(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0, 0);
     w.part_dgrad = wino_scratch_floats(w.wino_dgrad, fd);
     w.head_fused = head_sample_applicable(head_shape(a, ad, B)) ? 1 : head_wide_applicable(head_shape(a, ad, B)) ? 2 : 0;

@@ -80,9 +80,11 @@ hipError_t launch_igemm_fwd_split(const FwdProblem &p, bool nine, hipStream_t st
 // filter (wino_fwd_filter_floats floats, 16-byte aligned); two launches.
 size_t wino_fwd_filter_floats(int N, int C);
 // 0: not served or the direct kernel is faster; else the number of reduction splits (1 = none), at most `most`.
-// `direct`: the direct kernel's.  `ready`: an earlier launch transforms the filter on its way.
+// `direct`: the direct kernel's.
 // Of a problem with a projection (Cs) it serves the 3x3 part: the caller adds the projection through addsrc
-int wino_fwd_pick_splits(const FwdProblem &p, int direct, int most, bool ready = false);
+int wino_fwd_pick_splits(const FwdProblem &p, int direct, int most);
+// the same for a data gradient, whose filter an earlier launch transforms on its way (`ready`) or one of its own
+int wino_dgrad_pick_splits(const FwdProblem &p, int direct, bool ready);
 // A filter [N][3][3][C] and where its transformed form goes
 struct WinoFilter {
   const float *w;

@@ -28,11 +28,11 @@
 // 43 / 35; 128 -> 128, 32 768 pixels 80 / 48; 256 -> 256, 16 384 pixels 155 / 83; 512 -> 512, 8192 pixels 312 / 150
 // (a step of 8 channels takes 2.1 us on a CU with two workgroups, 0.87 of it MFMAs).
 //
-// Up to 32 filters (narrow layers, and the data gradients onto them) a variant of 32 per workgroup runs, half of whose columns
+// The data gradient onto a layer of up to 32 filters runs through a variant of 32 per workgroup, half of whose columns
 // would be padding otherwise: 64 accumulators, three workgroups per CU, the same patches and transforms for half of the
 // MFMAs, so a step of 16 MFMAs takes 1.3 us with two workgroups on a CU where they alone take 0.9.  Measured (us, the direct kernel
 // of 64x32 tiles / this, without the filter's launch): 64 channels, 65 536 pixels 30.2 / 19.5, 128 channels, 16 384 pixels 17.1 /
-// 12.3.  (Convolutions of heads of that width stay with the direct kernel: their errors would grow, nf_api.hip.)
+// 12.3.
 //
 // A value that is not finite anywhere in a tile makes neighbours of the transformed domain NaN that
 // the direct sum would leave finite (or infinite): a thread that finds one among its results
@@ -514,13 +514,11 @@ double wino_us(const FwdProblem &p, int s) {
          finish_us(p, s) + proj;
 }
 // its variant of 32 filters: 0.8, 1.4 and 2.1 us per step with one, two and three workgroups on a CU, 6 us of prologue,
-// epilogue and launch, 6.5 us for a filter launch of its own (4.5 us and, in a chain of dependent layers, the gap in front of it: a
-// forward sweep of four layers of 32 channels on 40x43 maps, batch 39, 299 us, with two launches a layer 310); the direct kernel of 64x32 tiles in its place 0.3 us per step
-// and workgroup on a CU.  On 36 random shapes (17 ... 32 filters, 16 ... 512 channels) this one is chosen 10 times and is the
+// epilogue and launch, 6.5 us for a filter launch of its own (4.5 us and, in a chain of dependent launches, the gap in front of
+// it); the direct kernel of 64x32 tiles in its place 0.3 us per step and workgroup on a CU.  On 36 random shapes (17 ... 32 filters, 16 ... 512 channels) this one is chosen 10 times and is the
 // faster one each time, by 3 to 33 % (us, direct / this with its filter launch: 64 -> 32, 204 800 pixels 72.5 / 50.1; 16 -> 28, 174 592
 // pixels 29.2 / 22.6; 64 -> 32, 16 384 pixels 12.0 / 14.7, direct); the error of its single results is the smaller one on all 36 (64 -> 32
-// 2.9e-7 / 2.1e-7), and sums over pixels and samples of a layer's gradients are as exact as they were (32 -> 32 channels, 40x43, batch
-// 39, 80-wide head: dW 2.4e-7 / 1.7e-7)
+// 2.9e-7 / 2.1e-7)
 double narrow_us(const FwdProblem &p, int s, bool ready) {
   const int nchunks = (p.C + CH - 1) / CH;
   const long long w = workgroups(p) * s, full = w / 768, rest = w % 768;
@@ -532,9 +530,8 @@ double narrow_direct_us(const FwdProblem &p, int ks) {
   const long long w = (long long)((p.M + 63) / 64) * ks;
   return 7.3 + (nkb + ks - 1) / ks * 0.3 * ((w + 255) / 256) + finish_us(p, ks);
 }
-}  // namespace
 
-int wino_fwd_pick_splits(const FwdProblem &p, int ks, int most, bool ready) {
+int pick_splits(const FwdProblem &p, int ks, int most, bool ready) {
   // up to 16 filters half of a workgroup's columns would be padding; below 16 channels the result's own
   // traffic is all there is to either kernel (8 channels, 16 384 x 256 results: 17 / 14 + 5 for the filter launch)
   if (p.N <= 16 || p.C < 16 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
@@ -561,6 +558,16 @@ int wino_fwd_pick_splits(const FwdProblem &p, int ks, int most, bool ready) {
   const double direct = 8.0 + (big ? 0.0 : 2.0 * (full + (rest > 0) - 1)) + (nkb + ks - 1) / ks * per + finish_us(p, ks);
   return splits && best < 0.93 * direct ? splits : 0;
 }
+}  // namespace
+
+// Up to 32 filters a layer and a head keep the direct sum.  The transformed filter is rounded once for all pixels and samples, which
+// the head's pooling averages and its gradients sum: single results come out closer to 64 bits, these averages not.  Error of the
+// 32-filter variant over the direct sum's, 24 inputs each: as a head's convolution (64 channels, 32x32, 32 filters) logits 1.11, dWf 1.32,
+// dWa 1.11; as a layer's (64 -> 24, 24x24) its output 0.78, but dWf 1.12, dWa 1.10.  As a data gradient, whose every use is another
+// contraction, it is the more exact one: 32 filters, 40x43, 80-wide head, dW 0.70, db 0.66; 16x16, 64-wide 0.89, 0.95.
+int wino_fwd_pick_splits(const FwdProblem &p, int ks, int most) { return p.N <= 32 ? 0 : pick_splits(p, ks, most, false); }
+
+int wino_dgrad_pick_splits(const FwdProblem &p, int ks, bool ready) { return pick_splits(p, ks, 16, ready); }
 
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, const WinoFilter *also, hipStream_t st) {
   WinoAux q;
@@ -592,14 +599,9 @@ hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, con
   }
   const dim3 grid(q.nblk * ((q.T + TB - 1) / TB), splits);
 #define NF_LAUNCH(NF_, POOL_) hipLaunchKernelGGL((wino_fwd_kernel<NF_, POOL_>), grid, dim3(NTHREADS), 0, st, p, q)
-  if (p.max_arg) {
-    if (nb == 64) NF_LAUNCH(2, true);
-    else NF_LAUNCH(1, true);
-  } else if (nb == 64) {
-    NF_LAUNCH(2, false);
-  } else {
-    NF_LAUNCH(1, false);
-  }
+  if (nb == 32) NF_LAUNCH(1, false);
+  else if (p.max_arg) NF_LAUNCH(2, true);
+  else NF_LAUNCH(2, false);
 #undef NF_LAUNCH
   return hipGetLastError();
 }

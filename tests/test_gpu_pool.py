@@ -24,9 +24,9 @@ def forward(d, B, x, xs, w, b):
     return y, arg, names
 
 
-# odd maps (a last row and column without a window), ragged tile blocks, filters below and above 32, no multiple of 64
-@pytest.mark.parametrize("C,H,W,K,B,skip,bad", [(64, 32, 32, 128, 20, 0, False), (64, 13, 15, 124, 100, 0, True), (64, 9, 28, 32, 200, 0, True),
-                                                (64, 16, 17, 24, 190, 1, False), (64, 5, 4, 256, 640, 1, True)])
+# odd maps (a last row and column without a window), ragged tile blocks, filters that are no multiple of 64
+@pytest.mark.parametrize("C,H,W,K,B,skip,bad", [(64, 32, 32, 128, 20, 0, False), (64, 13, 15, 124, 100, 0, True), (64, 9, 28, 36, 200, 0, True),
+                                                (64, 16, 17, 40, 190, 1, False), (64, 5, 4, 256, 640, 1, True)])
 def test_pooled_in_the_epilogue_as_by_itself(C, H, W, K, B, skip, bad):
     """Bit for bit the pooled result of the convolution without pooling, first maxima selected; infinities too."""
     g = torch.Generator(device="cuda").manual_seed(H * W)

@@ -1,5 +1,5 @@
-"""F(2x2, 3x3) in its variant of 32 filters (csrc/wino_fwd.hip): layers of 17 ... 32 filters and the data gradients onto them
-against the CPU oracle, and the convolutions that do not run through it for the accuracy of averages over their results."""
+"""F(2x2, 3x3) in its variant of 32 filters (csrc/wino_fwd.hip): data gradients onto layers of 17 ... 32 filters against the CPU
+oracle, and the convolutions of that width, which do not run through it, for the accuracy of averages over their results."""
 import pytest
 import torch
 
@@ -11,13 +11,14 @@ pytestmark = pytest.mark.gpu
 
 # name -> (spec, B, classes, launches of the variant)
 CASES = {
-    # a layer and its data gradient of few filters
-    "narrow_layer": (S(48, 28, 27, 28, 24), 80, 10, 2),
+    # not the layer and the head themselves
+    "narrow_layer": (S(48, 28, 27, 28, 24), 80, 10, 1),
     # odd maps: a ragged last tile block, channels that are no multiple of 8
     "odd_13x15_k28": (S(68, 13, 15, 28, 20), 260, 10, 1),
     # reduction in parts
     "parts": (S(256, 12, 12, 32, 16), 100, 10, 1),
-    # heads of few filters keep the direct kernel
+    "pooled_narrow": (S(64, 32, 32, 32, 32, pool=(2, 2, 0)), 200, 10, 1),
+    # heads and layers of few filters keep the direct kernel
     "pool_16": (S(16, 16, 16, 64, 32), 256, 10, 0),
     "pool_32": (S(64, 32, 32, 64, 32), 64, 10, 0),
     "odd_13x15_a28": (S(20, 13, 15, 68, 28), 260, 10, 0),
@@ -34,7 +35,7 @@ def test_narrow_steps_match_oracle(name):
     got = {r["kernel"]: r["launches"] for r in nf.nf_prof_end()}
     G.check_step_results(name, out, final)
     n = got.get("wino_fwd_32", 0)
-    assert n >= launches and (launches or not n), got
+    assert n == launches, got
 
 
 def filter_rounding_mean(x, w):
@@ -53,23 +54,35 @@ def filter_rounding_mean(x, w):
     return torch.einsum("pa,kab,qb->kpq", At, torch.einsum("kabc,abc->kab", dU, V), At).mean(dim=(1, 2))
 
 
+@pytest.mark.parametrize("what", ["head", "layer"])
 @pytest.mark.parametrize("C,H,A,B", [(64, 32, 32, 64), (128, 16, 20, 256), (64, 64, 32, 16)])
-def test_averages_of_head_convolutions(C, H, A, B):
-    """F_n averages a head's activation over pixels and its gradients sum over samples: rounding that is the same for all of them
-    stays.  The direct sum's is not the same (its averages are off by about a third of what a transformed filter's single rounding
-    leaves), so that the line lies at 0.6 of that."""
+def test_averages_of_narrow_convolutions(C, H, A, B, what):
+    """F_n averages an activation over pixels and the gradients sum over samples: rounding that is the same for all of them
+    stays.  The direct sum's is not the same: its averages are off by a tenth of what a single rounding of a transformed filter
+    leaves; the line lies at 0.6 of that.  (The layer's bias keeps its ReLU from cutting anything.)"""
     g = torch.Generator(device="cuda").manual_seed(C)
     rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
-    d = nf.LayerDesc(C_in=16, H_in=H, W_in=H, C_out=C, R=3, S=3, stride=1, pad=1)
-    a = nf.AuxDesc(C_in=C, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=0, pool_oh=2, pool_ow=2, n_classes=10)
     y, labels = rn(B, H, H, C).relu(), torch.zeros(B, device="cuda", dtype=torch.int32)
-    Wa = rn(A, 3, 3, C) * (2.0 / (9 * C)) ** 0.5
-    ap = nf.aux_params(Wa, torch.zeros(A, device="cuda"), rn(10, 4 * A) * 0.1, torch.zeros(10, device="cuda"))
-    ws = torch.empty(nf.nf_workspace_bytes(d, a, B), dtype=torch.uint8, device="cuda")
-    nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, torch.zeros(1, device="cuda"), ws)
-    off, nbytes = nf.nf_workspace_region(d, a, B, nf.NF_WS_AUX_ACT)
-    got = ws[off:off + nbytes].view(torch.float32).reshape(-1, A).double().mean(0)
+    Wa, bias = rn(A, 3, 3, C) * (2.0 / (9 * C)) ** 0.5, 0.0
+    if what == "layer":
+        bias = 8.0  # of about the standard deviation 1.2
+        d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=A, R=3, S=3, stride=1, pad=1)
+        got = torch.empty(B, H, H, A, device="cuda")
+        ws = torch.empty(max(256, nf.nf_workspace_bytes(d, None, B)), dtype=torch.uint8, device="cuda")
+        nf.nf_layer_fwd(d, B, y, None, nf.layer_params(Wa, torch.full((A,), bias, device="cuda"), None), got, ws)
+        assert (got > 0).all()
+    else:
+        d = nf.LayerDesc(C_in=16, H_in=H, W_in=H, C_out=C, R=3, S=3, stride=1, pad=1)
+        a = nf.AuxDesc(C_in=C, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=0, pool_oh=2, pool_ow=2, n_classes=10)
+        ap = nf.aux_params(Wa, torch.zeros(A, device="cuda"), rn(10, 4 * A) * 0.1, torch.zeros(10, device="cuda"))
+        ws = torch.empty(nf.nf_workspace_bytes(d, a, B), dtype=torch.uint8, device="cuda")
+        nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, torch.zeros(1, device="cuda"), ws)
+        off, nbytes = nf.nf_workspace_region(d, a, B, nf.NF_WS_AUX_ACT)
+        got = ws[off:off + nbytes].view(torch.float32)
+    got = got.reshape(-1, A).double().mean(0) - bias
     yp = torch.nn.functional.pad(y.double(), (0, 0, 1, 1, 1, 1))
     mean = torch.stack([torch.stack([yp[:, r:r + H, s:s + H].mean(dim=(0, 1, 2)) for s in range(3)]) for r in range(3)])
     ref = torch.einsum("krsc,rsc->k", Wa.double(), mean)
-    assert (got - ref).norm() <= 0.6 * filter_rounding_mean(y, Wa).norm()
+    err, line = float((got - ref).norm()), 0.6 * float(filter_rounding_mean(y, Wa).norm())
+    print(f"{what} {C} channels: {err:.3e}, line {line:.3e}", flush=True)
+    assert err <= line
