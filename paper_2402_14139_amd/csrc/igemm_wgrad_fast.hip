@@ -31,15 +31,6 @@ __device__ inline float4 bload(__amdgpu_buffer_rsrc_t r, int voff) {
   return make_float4(v.x, v.y, v.z, v.w);
 }
 
-struct PositionRows {
-  FastDiv div_imgs;
-  int bias_tile;  // the column tile of a tap that every position sees
-};
-
-struct TileGrid {
-  int x, y, z;  // column tiles, row tiles, splits
-};
-
 // LDS of a tile: two steps of both operands' rows and of the row table
 constexpr int lds_floats(int bp, int bq) { return 2 * BKM * ((bp + 4) + (bq + 4) + 4); }
 
@@ -402,13 +393,6 @@ __global__ __launch_bounds__(NTHREADS, 2) void igemm_wgrad_fast_kernel(WgradProb
 // 139.3 / 133; 96 -> 48 channels, 5x5, 32x32, 64 images 448 / 437.
 enum Form { F64, F64_POS, F32, F64_PROJ, F_STEM, F_NONE };  // 64x64, 32x128 (by PROJ, PM), stem_wgrad; a head's are the first three
 
-struct WgradPair {
-  WgradProblem p[2];  // the layer's, the head's
-  PositionRows q[2];
-  TileGrid grid[2];
-  int head_at;  // the head's first workgroup: a multiple of 8, so that both grids' indices lie on the XCDs as in launches of their own
-};
-
 constexpr int form_lds(int form) {
   return form == F_STEM ? STEM_WGRAD_LDS : form == F32 ? lds_floats(32, 128) : lds_floats(64, 64);
 }
@@ -566,16 +550,15 @@ hipError_t launch_igemm_wgrad_fast(const WgradProblem &p0, hipStream_t st, const
   return launch_cfg<32, 128, 1, 4>(p, st);
 }
 
-bool wgrad_pair_applicable(const WgradProblem &layer, const WgradProblem &head) {
-  WgradPair a;
-  return make_pair(layer, head, &a) != nullptr;
+WgradPairPlan plan_wgrad_pair(const WgradProblem &layer, const WgradProblem &head) {
+  WgradPairPlan plan;
+  plan.kernel = make_pair(layer, head, &plan.args);
+  return plan;
 }
 
-hipError_t launch_wgrad_pair(const WgradProblem &layer, const WgradProblem &head, hipStream_t st) {
-  WgradPair a;
-  const PairKernel kernel = make_pair(layer, head, &a);
-  if (!kernel) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(a.head_at + tiles(a.grid[1]))), dim3(NTHREADS), 0, st, a);
+hipError_t launch_wgrad_pair(const WgradPairPlan &plan, hipStream_t st) {
+  const WgradPair &a = plan.args;
+  hipLaunchKernelGGL(plan.kernel, dim3((unsigned)(a.head_at + tiles(a.grid[1]))), dim3(NTHREADS), 0, st, a);
   return hipGetLastError();
 }
 

@@ -653,9 +653,11 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
   g.m_per_split = ((g.M + g.splits - 1) / g.splits + 31) / 32 * 32;  // whole 32-row steps
   const bool wino = run_wino(g, w.wino_wgrad);
   // one launch for both where that serves them, after the data gradient.  (A measurement times each kernel by itself.)
-  const bool pair = !wino && !prof_active() && wgrad_pair_applicable(g, gh);
+  WgradPairPlan pair;
+  pair.kernel = nullptr;
+  if (!wino && !prof_active()) pair = plan_wgrad_pair(g, gh);
   int32_t rc;
-  if (!pair && (rc = enqueue_wgrad(gh, st))) return rc;
+  if (!pair.kernel && (rc = enqueue_wgrad(gh, st))) return rc;
   // beta_n: data gradient w.r.t. the emitted activation, layer ReLU mask fused when un-pooled
   {
     FwdProblem f = dgrad_problem(a, ad, B);
@@ -686,8 +688,8 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
       if ((rc = enqueue_wgrad(pr, st))) return rc;
       red.job[2] = reduce_job(pr, gp->Wp, nullptr, nullptr);
     }
-  } else if (pair) {
-    NF_HIP(launch_wgrad_pair(g, gh, st));
+  } else if (pair.kernel) {
+    NF_HIP(launch_wgrad_pair(pair, st));
   } else if ((rc = enqueue_wgrad(g, st))) {
     return rc;
   }

@@ -121,9 +121,27 @@ hipError_t launch_igemm_wgrad(const WgradProblem &p, hipStream_t st, const char 
 // software-pipelined buffer-load variant (igemm_wgrad_fast.hip); launch_igemm_wgrad picks it when applicable
 bool igemm_wgrad_fast_applicable(const WgradProblem &p);
 hipError_t launch_igemm_wgrad_fast(const WgradProblem &p, hipStream_t st, const char **kernel);
-// a layer's weight gradient and its head's in one launch (igemm_wgrad_fast.hip), the same tiles and sums as in two
-bool wgrad_pair_applicable(const WgradProblem &layer, const WgradProblem &head);
-hipError_t launch_wgrad_pair(const WgradProblem &layer, const WgradProblem &head, hipStream_t st);
+// A layer's weight gradient and its head's in one launch (igemm_wgrad_fast.hip), the same tiles and sums as in two
+struct PositionRows {
+  FastDiv div_imgs;
+  int bias_tile;  // the column tile of a tap that every position sees
+};
+struct TileGrid {
+  int x, y, z;  // column tiles, row tiles, splits
+};
+struct WgradPair {
+  WgradProblem p[2];  // the layer's, the head's
+  PositionRows q[2];
+  TileGrid grid[2];
+  int head_at;  // the head's first workgroup: a multiple of 8, so that both grids' indices lie on the XCDs as in launches of their own
+};
+// What a call launches: settled once (`kernel` null: two launches), since the mode in force may change while a call enqueues
+struct WgradPairPlan {
+  WgradPair args;
+  void (*kernel)(WgradPair);
+};
+WgradPairPlan plan_wgrad_pair(const WgradProblem &layer, const WgradProblem &head);
+hipError_t launch_wgrad_pair(const WgradPairPlan &plan, hipStream_t st);
 // fp32 weight gradient on the bf16 matrix cores through three-way split operands
 // (igemm_wgrad_split.hip); launch_igemm_wgrad_fast hands over to it in the NF_CONTRACT_BF16X* modes
 bool igemm_wgrad_split_applicable(const WgradProblem &p);

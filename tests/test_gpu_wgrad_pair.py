@@ -1,10 +1,13 @@
 """A layer's weight gradient and its head's in one launch (csrc/igemm_wgrad_fast.hip, wgrad_pair_kernel): the variants of either,
 grids that are not whole multiples of eight workgroups.  Against the oracle, and bit for bit against the same step while a
 measurement is on, which launches the two by themselves."""
+import threading
+
 import numpy as np
 import pytest
 
 from paper_2402_14139_amd import binding as nf
+from paper_2402_14139_amd import layout
 from tests import gpu_common as G
 from tests.test_gpu_parity import S
 
@@ -42,3 +45,33 @@ def test_pairs_match_oracle_and_single_launches(name):
     for k, v in out[0][0][1].items():
         if v is not None:
             assert np.array_equal(v, alone[0][0][1][k]), k
+
+
+def test_the_mode_may_change_while_a_step_is_enqueued():
+    """Another thread sets the contraction mode all the while: every step succeeds, in the one or the other."""
+    spec, B, cls = S(64, 2, 2, 128, 80), 17, 10
+    x, xs, labels, p = G.make_inputs(spec, B, cls, 371)
+    L = G.gpu_layer(spec, cls, p, B, 0.0)
+    xd, ld = G.to_dev(layout.act_to_lib(x)), G.to_dev(labels)
+    L.step(xd, None, ld, 0.0, 0.0)
+    ref = {k: v.double().clone() for k, v in L.g.items() if v is not None}
+    prev, stop, turns = nf.nf_contraction(), threading.Event(), [0]
+
+    def toggle():
+        while not stop.is_set():
+            nf.nf_contraction(nf.NF_CONTRACT_BF16X6)
+            nf.nf_contraction(nf.NF_CONTRACT_F32)
+            turns[0] += 1
+
+    t = threading.Thread(target=toggle)
+    t.start()
+    try:
+        for _ in range(3000):
+            L.step(xd, None, ld, 0.0, 0.0)
+    finally:
+        stop.set()
+        t.join()
+        nf.nf_contraction(prev)
+    assert turns[0] > 100
+    for k, v in ref.items():
+        assert (L.g[k].double() - v).norm() <= G.REL * v.norm(), k
