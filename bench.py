@@ -269,7 +269,7 @@ def main():
     roofline, kernels, hbm = None, [], []
     if not args.no_prof:
         psteps = min(args.steps, 5)
-        nf.nf_prof_begin()
+        nf.nf_prof_begin_as_run()
         for s in range(psteps):
             one_step(args.warmup + args.steps + s)
         recs = nf.nf_prof_end()

@@ -344,7 +344,10 @@ int32_t nf_partition(int32_t n_layers, const nf_linear_model *R, double M, int32
  * HIP-event pair on the caller's stream.  nf_prof_end waits for those events (the only call
  * that blocks the host), and returns one record per kernel: launches, summed duration (ms),
  * summed algorithmic FLOPs and bytes.  Records are sorted by duration, at most `cap` are
- * written, *n receives the number of distinct kernels.  Process-wide state (one recording at a time;
+ * written, *n receives the number of distinct kernels.  Kernels that a call puts into one launch (the two
+ * weight gradients of small steps) are launched and recorded one by one after nf_prof_begin;
+ * nf_prof_begin_as_run records the launches that a call makes without a measurement, such a one under
+ * a name of its own.  Process-wide state (one recording at a time;
  * the record list is guarded by a mutex so that launches from several host threads may be recorded),
  * creates HIP events: keep it out of production loops. */
 typedef struct {
@@ -356,6 +359,7 @@ typedef struct {
  * (the fp32 MFMA peak is compute_units x 4 SIMDs x 64 flop/clk x clock). */
 int32_t nf_device_info(int32_t *compute_units, int32_t *clock_khz);
 int32_t nf_prof_begin(void);
+int32_t nf_prof_begin_as_run(void);
 int32_t nf_prof_end(nf_prof_record *out, int32_t cap, int32_t *n);
 
 #ifdef __cplusplus

@@ -22,7 +22,7 @@ NF_CONTRACT_F32, NF_CONTRACT_BF16X6, NF_CONTRACT_BF16X9 = 0, 1, 2
 
 EXPORTS = ("nf_strerror", "nf_layer_out_dims", "nf_workspace_bytes", "nf_layer_fwd", "nf_aux_fwd_loss",
            "nf_local_bwd_wgrad", "nf_sgd_update", "nf_cache_write", "nf_cache_read", "nf_local_step",
-           "nf_prof_begin", "nf_prof_end", "nf_workspace_region", "nf_block_workspace_bytes",
+           "nf_prof_begin", "nf_prof_begin_as_run", "nf_prof_end", "nf_workspace_region", "nf_block_workspace_bytes",
            "nf_block_train_epoch", "nf_block_fill_cache", "nf_layer_step_bytes", "nf_fit_linear",
            "nf_profile_layer", "nf_partition", "nf_aux_predict", "nf_block_evaluate", "nf_select_exit",
            "nf_device_info", "nf_local_step_static", "nf_contraction", "nf_block_graph_create",
@@ -278,6 +278,11 @@ def nf_local_step_static(d, a, lr, momentum, B, x, x_skip, labels, p, ap, gp, ga
 
 def nf_prof_begin():
     _check(lib().nf_prof_begin(), "nf_prof_begin")
+
+
+def nf_prof_begin_as_run():
+    """nf_prof_begin, but kernels that share a launch stay together and are recorded under a name of their own."""
+    _check(lib().nf_prof_begin_as_run(), "nf_prof_begin_as_run")
 
 
 def nf_prof_end(cap: int = 64):

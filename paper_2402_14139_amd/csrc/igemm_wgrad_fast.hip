@@ -473,7 +473,15 @@ PairKernel pair_kernel_of(int head) {
                            : nullptr;
 }
 
-PairKernel make_pair(const WgradProblem &layer, const WgradProblem &head, WgradPair *a) {
+const char *pair_name(int layer, int head) {
+#define NF_NAMES(L) {"igemm_wgrad_pair_" L "_64x64", "igemm_wgrad_pair_" L "_64x64_rows", "igemm_wgrad_pair_" L "_32x128"}
+  static const char *const names[F_NONE][3] = {NF_NAMES("64x64"), NF_NAMES("64x64_rows"), NF_NAMES("32x128"),
+                                               NF_NAMES("64x64_proj"), NF_NAMES("stem")};
+#undef NF_NAMES
+  return names[layer][head];
+}
+
+PairKernel make_pair(const WgradProblem &layer, const WgradProblem &head, WgradPair *a, const char **name) {
   a->p[0] = layer, a->p[1] = head;
   const int fl = pair_form(&a->p[0], &a->q[0], &a->grid[0]), fh = pair_form(&a->p[1], &a->q[1], &a->grid[1]);
   if (fl == F_NONE || fh > F32) return nullptr;
@@ -485,6 +493,7 @@ PairKernel make_pair(const WgradProblem &layer, const WgradProblem &head, WgradP
   const bool three = fl == F32 || fl == F64_PROJ || fh == F32;
   const double flops = 2.0 * ((double)layer.M * layer.P * layer.Q + (double)head.M * head.P * head.Q);
   if (three && tiles(a->grid[0]) + tiles(a->grid[1]) > 3 * 256 && flops > 1e9) return nullptr;
+  *name = pair_name(fl, fh);
   return fl == F64       ? pair_kernel_of<F64>(fh)
          : fl == F64_POS ? pair_kernel_of<F64_POS>(fh)
          : fl == F32     ? pair_kernel_of<F32>(fh)
@@ -552,7 +561,7 @@ hipError_t launch_igemm_wgrad_fast(const WgradProblem &p0, hipStream_t st, const
 
 WgradPairPlan plan_wgrad_pair(const WgradProblem &layer, const WgradProblem &head) {
   WgradPairPlan plan;
-  plan.kernel = make_pair(layer, head, &plan.args);
+  plan.kernel = make_pair(layer, head, &plan.args, &plan.name);
   return plan;
 }
 

@@ -356,6 +356,7 @@ struct ProfEvent {
 };
 struct ProfState {
   bool on = false;
+  bool apart = false;  // kernels that share a launch are launched one by one
   std::vector<ProfEvent> ev;
   std::mutex mu;  // guards ev: launches from several host threads may record while profiling is on
 };
@@ -479,15 +480,19 @@ int32_t enqueue_conv(const FwdProblem &f, float *out, int wino, int ksplits, flo
   return enqueue_fwd_split(f, out, ksplits, part, st);
 }
 
-int32_t enqueue_wgrad(const WgradProblem &g, hipStream_t st) {
+double wgrad_flops(const WgradProblem &g) { return 2.0 * g.M * g.P * g.Q; }
+double wgrad_bytes(const WgradProblem &g) {
   const double B = (double)g.M / ((double)g.Ho * g.Wo);
-  const double flops = 2.0 * g.M * g.P * g.Q;
   double elems = (double)g.M * g.P + B * g.H * g.W * g.C + (double)g.P * g.Q;
   if (g.Cs) elems += B * g.Hs * g.Ws * g.Cs;
+  return 4.0 * elems;
+}
+
+int32_t enqueue_wgrad(const WgradProblem &g, hipStream_t st) {
   ProfScope sc(st);
   const char *kn = "igemm_wgrad";
   NF_HIP(launch_igemm_wgrad(g, st, &kn));
-  sc.done(kn, flops, 4.0 * elems);
+  sc.done(kn, wgrad_flops(g), wgrad_bytes(g));
   return NF_OK;
 }
 
@@ -652,10 +657,10 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
   g.splits = w.splits_layer;
   g.m_per_split = ((g.M + g.splits - 1) / g.splits + 31) / 32 * 32;  // whole 32-row steps
   const bool wino = run_wino(g, w.wino_wgrad);
-  // one launch for both where that serves them, after the data gradient.  (A measurement times each kernel by itself.)
+  // one launch for both where that serves them, after the data gradient
   WgradPairPlan pair;
   pair.kernel = nullptr;
-  if (!wino && !prof_active()) pair = plan_wgrad_pair(g, gh);
+  if (!wino && !(g_prof.on && g_prof.apart)) pair = plan_wgrad_pair(g, gh);
   int32_t rc;
   if (!pair.kernel && (rc = enqueue_wgrad(gh, st))) return rc;
   // beta_n: data gradient w.r.t. the emitted activation, layer ReLU mask fused when un-pooled
@@ -689,7 +694,7 @@ int32_t run_bwd(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_desc *
       red.job[2] = reduce_job(pr, gp->Wp, nullptr, nullptr);
     }
   } else if (pair.kernel) {
-    NF_HIP(launch_wgrad_pair(pair, st));
+    NF_RUN(st, pair.name, wgrad_flops(g) + wgrad_flops(gh), wgrad_bytes(g) + wgrad_bytes(gh), launch_wgrad_pair(pair, st));
   } else if ((rc = enqueue_wgrad(g, st))) {
     return rc;
   }
@@ -1096,16 +1101,18 @@ int32_t nf_device_info(int32_t *compute_units, int32_t *clock_khz) {
   return NF_OK;
 }
 
-int32_t nf_prof_begin(void) {
+static int32_t prof_begin(bool apart) {
   std::lock_guard<std::mutex> lk(g_prof.mu);
   for (auto &e : g_prof.ev) {
     (void)hipEventDestroy(e.a);
     (void)hipEventDestroy(e.b);
   }
   g_prof.ev.clear();
-  g_prof.on = true;
+  g_prof.apart = apart, g_prof.on = true;
   return NF_OK;
 }
+int32_t nf_prof_begin(void) { return prof_begin(true); }
+int32_t nf_prof_begin_as_run(void) { return prof_begin(false); }
 
 int32_t nf_prof_end(nf_prof_record *out, int32_t cap, int32_t *n) {
   g_prof.on = false;

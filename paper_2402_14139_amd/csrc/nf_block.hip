@@ -14,7 +14,7 @@
 #include "../../include/nf.h"
 
 namespace nf {
-bool prof_active();  // nf_api.hip: true between nf_prof_begin and nf_prof_end
+bool prof_active();  // nf_api.hip: true while launches are measured
 // nf_api.hip: least workspace the single-layer calls accept (nf_workspace_bytes: what they want)
 int32_t workspace_least_bytes(const nf_layer_desc *d, const nf_aux_desc *a, int32_t B, size_t *out);
 }

@@ -49,3 +49,29 @@ def test_padding_contributes_nothing():
     inf = torch.zeros_like(y, dtype=torch.bool)
     inf[:, 1, 1, 9] = True
     assert torch.equal(torch.isinf(y), inf) and (y > 0).all()
+
+
+@pytest.mark.parametrize("B,C,H,A", [(17, 64, 2, 80), (9, 128, 3, 40), (33, 64, 4, 64), (64, 128, 2, 200)])
+def test_padding_contributes_nothing_to_weight_gradients(B, C, H, A):
+    """An infinite gradient at the pixels that one pooling window alone sees: the taps that lie over the padding there stay finite."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    d = nf.LayerDesc(C_in=16, H_in=H, W_in=H, C_out=C, R=3, S=3, stride=1, pad=1)
+    a = nf.AuxDesc(C_in=C, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=1, pool_oh=H, pool_ow=H, n_classes=4, loss_kind=1)
+    x = torch.rand(B, H, H, 16, generator=g, device="cuda")
+    y = torch.rand(B, H, H, C, generator=g, device="cuda") + 0.1
+    labels = torch.zeros(B, device="cuda", dtype=torch.int32)
+    Wa, Wf = torch.zeros(A, 3, 3, C, device="cuda"), torch.zeros(4, H * H * A, device="cuda")
+    Wf[2, 5] = 3e38  # of filter 5 at pixel (0, 0): the logit is 3e8, its gradient infinite
+    z = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
+    layer = [z(C, 3, 3, 16), z(C), z(C, 3, 3, 16), z(C)]
+    head = [Wa, z(A) + 1e-30, Wf, z(4), z(A, 3, 3, C), z(A), z(4, H * H * A), z(4)]
+    lp, gp, ap, ga = nf.layer_params(*layer[:2], None), nf.layer_params(*layer[2:], None), nf.aux_params(*head[:4]), nf.aux_params(*head[4:])
+    loss, gWa = z(1), head[4]
+    ws = torch.empty(nf.nf_workspace_bytes(d, a, B), dtype=torch.uint8, device="cuda")
+    nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, loss, ws)
+    nf.nf_local_bwd_wgrad(d, a, B, x, None, y, lp, ap, gp, ga, ws)
+    if nf.nf_contraction() != nf.NF_CONTRACT_F32:
+        pytest.skip("the split modes turn an infinity into NaN")
+    over = torch.zeros(3, 3, dtype=torch.bool, device="cuda")
+    over[0, :] = over[:, 0] = True
+    assert torch.isfinite(gWa[5][over]).all() and not torch.isfinite(gWa[5][~over]).any()

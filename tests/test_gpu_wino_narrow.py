@@ -63,20 +63,21 @@ def test_averages_of_narrow_convolutions(C, H, A, B, what):
     g = torch.Generator(device="cuda").manual_seed(C)
     rn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
     y, labels = rn(B, H, H, C).relu(), torch.zeros(B, device="cuda", dtype=torch.int32)
-    Wa, bias = rn(A, 3, 3, C) * (2.0 / (9 * C)) ** 0.5, 0.0
+    Wa, bias, loss = rn(A, 3, 3, C) * (2.0 / (9 * C)) ** 0.5, 0.0, torch.zeros(1, device="cuda")
     if what == "layer":
-        bias = 8.0  # of about the standard deviation 1.2
+        bias = 8.0  # the results' standard deviation is about 1.2
+        b = torch.full((A,), bias, device="cuda")
         d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=A, R=3, S=3, stride=1, pad=1)
         got = torch.empty(B, H, H, A, device="cuda")
         ws = torch.empty(max(256, nf.nf_workspace_bytes(d, None, B)), dtype=torch.uint8, device="cuda")
-        nf.nf_layer_fwd(d, B, y, None, nf.layer_params(Wa, torch.full((A,), bias, device="cuda"), None), got, ws)
+        nf.nf_layer_fwd(d, B, y, None, nf.layer_params(Wa, b, None), got, ws)
         assert (got > 0).all()
     else:
         d = nf.LayerDesc(C_in=16, H_in=H, W_in=H, C_out=C, R=3, S=3, stride=1, pad=1)
         a = nf.AuxDesc(C_in=C, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=0, pool_oh=2, pool_ow=2, n_classes=10)
-        ap = nf.aux_params(Wa, torch.zeros(A, device="cuda"), rn(10, 4 * A) * 0.1, torch.zeros(10, device="cuda"))
+        p = [Wa, torch.zeros(A, device="cuda"), rn(10, 4 * A) * 0.1, torch.zeros(10, device="cuda")]
         ws = torch.empty(nf.nf_workspace_bytes(d, a, B), dtype=torch.uint8, device="cuda")
-        nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, torch.zeros(1, device="cuda"), ws)
+        nf.nf_aux_fwd_loss(d, a, B, y, labels, nf.aux_params(*p), loss, ws)
         off, nbytes = nf.nf_workspace_region(d, a, B, nf.NF_WS_AUX_ACT)
         got = ws[off:off + nbytes].view(torch.float32)
     got = got.reshape(-1, A).double().mean(0) - bias
