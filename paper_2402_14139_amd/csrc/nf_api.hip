@@ -1021,7 +1021,10 @@ int32_t nf_local_bwd_wgrad(const nf_layer_desc *d, const nf_aux_desc *a, int32_t
   if (!aligned16(y)) return NF_ERR_BAD_DESC;
   WsLayout w = ws_layout(d, ld, a, ad, B, ws_bytes);
   if ((rc = check_ws(ws, ws_bytes, w.total))) return rc;
-  w.wino_dgrad = wino_splits_now(dgrad_problem(a, ad, B), w.wino_dgrad);
+  const FwdProblem fd = dgrad_problem(a, ad, B);
+  // (behind a head in one launch, which belongs to the forward call, the transformed filter takes a launch of its own here)
+  if (w.wino_dgrad && w.head_fused && !wino_dgrad_pick_splits(fd, w.ksplits_dgrad, false)) w.wino_dgrad = 0;
+  w.wino_dgrad = wino_splits_now(fd, w.wino_dgrad);
   return run_bwd(d, ld, a, ad, B, x, x_skip, y, p, ap, gp, ga, nullptr, nullptr, nullptr, nullptr, ws, w,
                  static_cast<hipStream_t>(stream));
 }

@@ -514,8 +514,9 @@ double wino_us(const FwdProblem &p, int s) {
          finish_us(p, s) + proj;
 }
 // its variant of 32 filters: 0.8, 1.4 and 2.1 us per step with one, two and three workgroups on a CU, 6 us of prologue,
-// epilogue and launch, 6.5 us for a filter launch of its own (4.5 us and, in a chain of dependent launches, the gap in front of
-// it); the direct kernel of 64x32 tiles in its place 0.3 us per step and workgroup on a CU.  On 36 random shapes (17 ... 32 filters, 16 ... 512 channels) this one is chosen 10 times and is the
+// epilogue and launch, 3 us for a filter launch of its own in front of it (0.3 ... 5.3 us in backward calls of ten sizes: us a call, with
+// it / direct: 8 -> 32 channels, 16x16, 64-wide head, batch 8 26.3 / 24.0, 64 35.8 / 35.8, 128 45.1 / 46.2; 28x28, 24 channels,
+// 80-wide head, batch 50 72.4 / 77.5); the direct kernel of 64x32 tiles in its place 0.3 us per step and workgroup on a CU.  On 36 random shapes (17 ... 32 filters, 16 ... 512 channels) this one is chosen 10 times and is the
 // faster one each time, by 3 to 33 % (us, direct / this with its filter launch: 64 -> 32, 204 800 pixels 72.5 / 50.1; 16 -> 28, 174 592
 // pixels 29.2 / 22.6; 64 -> 32, 16 384 pixels 12.0 / 14.7, direct); the error of its single results is the smaller one on all 36 (64 -> 32
 // 2.9e-7 / 2.1e-7)
@@ -523,7 +524,7 @@ double narrow_us(const FwdProblem &p, int s, bool ready) {
   const int nchunks = (p.C + CH - 1) / CH;
   const long long w = workgroups(p) * s, full = w / 768, rest = w % 768;
   const double per = 2.1 * full + (rest > 512 ? 2.1 : rest > 256 ? 1.4 : rest > 0 ? 0.8 : 0.0);
-  return (ready ? 6.0 : 12.5) + 3.0 * (full + (rest > 0) - 1) + (nchunks + s - 1) / s * per + finish_us(p, s);
+  return (ready ? 6.0 : 9.0) + 3.0 * (full + (rest > 0) - 1) + (nchunks + s - 1) / s * per + finish_us(p, s);
 }
 double narrow_direct_us(const FwdProblem &p, int ks) {
   const int nkb = (p.Kg + 31) / 32;

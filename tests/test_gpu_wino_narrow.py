@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2402_14139_amd import binding as nf
+from paper_2402_14139_amd import layout
 from tests import gpu_common as G
 from tests.test_gpu_parity import S
 
@@ -87,3 +88,25 @@ def test_averages_of_narrow_convolutions(C, H, A, B, what):
     err, line = float((got - ref).norm()), 0.6 * float(filter_rounding_mean(y, Wa).norm())
     print(f"{what} {C} channels: {err:.3e}, line {line:.3e}", flush=True)
     assert err <= line
+
+
+@pytest.mark.parametrize("B,classes,step,calls", [(192, 10, True, False), (193, 10, True, True), (3, 10, True, False), (3, 1200, True, True)])
+def test_filter_of_the_data_gradient(B, classes, step, calls):
+    """The transformed filter comes with a head launch of the step, or with the backward call's own; behind a forward call with
+    the whole head in it, it takes a launch that pays from a certain size on."""
+    spec = S(8, 16, 16, 28, 32)
+    x, _, labels, p = G.make_inputs(spec, B, classes, 372)
+    L = G.gpu_layer(spec, classes, p, B, 0.0)
+    xd, ld = G.to_dev(layout.act_to_lib(x)), G.to_dev(labels)
+    got = []
+    for separate in (False, True):
+        if separate:
+            y = L.forward(xd, None)
+            L.aux_loss(y, ld)
+        nf.nf_prof_begin()
+        if separate:
+            L.backward(xd, None, y)
+        else:
+            L.step(xd, None, ld, 0.0, 0.0)
+        got.append("wino_fwd_32" in {r["kernel"] for r in nf.nf_prof_end()})
+    assert got == [step, calls]
