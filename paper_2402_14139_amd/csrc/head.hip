@@ -4,6 +4,8 @@
 // three (gradient line of Algorithm 2).
 // These steps are tiny next to the convolutions; they are written as fused wavefront /
 // workgroup reductions with a fixed summation order (deterministic).
+#include <algorithm>
+
 #include "head_gamma.h"
 #include "nf_internal.h"
 #include "wino_filter.h"
@@ -1007,17 +1009,31 @@ hipError_t launch_head_sample(const HeadShape &h, float *U, const float *part, i
   return hipGetLastError();
 }
 
+// slices per sample of head_wide_kernel: about 512 workgroups in all (768: 13.7 us for 64 samples of 32x32 pixels, 32 filters, 512:
+// 13.0, 384: 14.2), at least 1024 values of dU each
+static int wide_slices(const HeadShape &h) {
+  const long long per_sample = (long long)h.Hu * h.Wu * h.A;
+  return (int)std::max(1ll, std::min((511ll + h.B) / h.B, per_sample / 1024));
+}
+
+// One launch after the pooling (head_wide_kernel: the linear layer is recomputed by every slice of a sample, its weights read from
+// L2 by every workgroup) or two (the linear layer, then head_bwd_kernel).
 bool head_wide_applicable(const HeadShape &h) {
-  // the linear layer small enough to be recomputed by every slice of a sample (its weights read
-  // from L2 by every workgroup); wider ones share the weights between samples (head_fc_wide_kernel)
-  // Wide rows are read side by side (logits_sample): from 256 features and 100 classes on, on maps of up to 256 pixels, one launch is
-  // faster than three, too (step, us, three / one: 64 samples of 16x16 pixels, 64 filters, 200 classes 114.2 / 100.7, 100 classes 101.8 /
-  // 95.2; 100 of 14x14, 200 classes 139.2 / 128.1, 37 of 7x7 80.5 / 66.9; 80 filters, 100 classes, 256 of 16x16 260 / 253).
-  // Not so on larger maps (80 filters, 60 classes, 500 of 32x32 1518 / 1525), with 512 features (37 classes, 100 of 14x14 153 / 156) or
-  // fewer classes (80 filters, 60, 256 of 16x16, gradients alone 236.6 / 238.8), and with 128 features, where the launches it saves are
-  // short, only for some (32 filters, 200 classes, 64 of 16x16 from 32 channels 88.9 / 84.0, gradients from 128 102.6 / 107.1).
-  const bool rows = h.A % 4 == 0 && h.F >= 256 && h.F <= 320 && h.Cls >= 100 && h.Cls <= 200 && h.Hu * h.Wu <= 256;
-  return !head_sample_applicable(h) && (rows || (long long)h.F * h.Cls <= 16384) && h.F <= 1024 && h.Cls <= 1024;
+  if (head_sample_applicable(h) || h.F > 1024 || h.Cls > 1024) return false;
+  // the other side is head_fc_kernel: the same sums, without the slices
+  if (h.F < 256 || h.F % 4) return (long long)h.F * h.Cls <= 16384;
+  // The other side is head_fc_wide_kernel, which shares the weights between four samples, so that 1024 samples are a round of the
+  // chip; a chain over the classes bounds it.  Against that, per workgroup on a CU, the weights read twice (the logits in
+  // passes of 16 or 128 classes), and the few workgroups that store dU.  us, fitted to 335 random heads of 256 ... 1024 features, 10
+  // ... 880 classes, 1 ... 5800 samples of up to 48x48 pixels (means of a step and of the separate calls): of the 1924 us that the
+  // better side of each is ahead in one launch, this choice takes 1853, 16384 weights as the line -75.  Two launches / one, a step: 64 filters, 100
+  // classes, 1 of 6x6 60 / 52; 72, 200, 509 of 21x21 364 / 349; 68, 815, 87 of 16x16 297 / 255; 100, 599, 2 of 33x33 198 / 154.
+  // And the other way: 140, 37, 465 of 6x6 167 / 175; 252, 162, 259 of 5x5 116 / 125.  On a fifth of the heads neither is ahead by 1 us.
+  const int pass = h.Cls <= 16 ? 16 : 128, padded = (h.Cls + pass - 1) / pass * pass;
+  const double chain = 0.073 * h.Cls * std::max(1.0, h.B / 1024.0);
+  const double weights = 0.3e-4 * h.F * 0.5 * (padded + h.Cls) * std::max(1.0, (double)h.B * wide_slices(h) / 256);
+  const double stores = 0.19e-6 * h.B * h.Hu * h.Wu * h.A;
+  return chain - weights - stores > 0.3;
 }
 
 bool head_pool_partials_applicable(const HeadShape &h) {
@@ -1030,12 +1046,7 @@ hipError_t launch_head_wide(const HeadShape &h, const float *U, float *Pq, const
                             const float *Wf, const float *bf, float *dz, float *loss_n, const int32_t *parg,
                             float *dU, const RelayJob &rj, hipStream_t st) {
   const int V = h.A % 4 == 0 ? 4 : 1;
-  // slices per sample: about 512 workgroups in all (768: 13.7 us for 64 samples of 32x32 pixels, 32 filters, 512: 13.0, 384:
-  // 14.2), at least 1024 values of dU each
-  const long long per_sample = (long long)h.Hu * h.Wu * h.A;
-  int NS = (512 + h.B - 1) / h.B;
-  if (NS > per_sample / 1024) NS = (int)(per_sample / 1024);
-  if (NS < 1) NS = 1;
+  const int NS = wide_slices(h);
   const unsigned nb_t = (unsigned)(rj.nb_t + rj.nb_u);
   const dim3 grid((unsigned)(h.B * NS) + nb_t);
   const size_t lds = (size_t)(2 * h.F + h.Cls + 8) * sizeof(float);

@@ -16,7 +16,7 @@ CASES = {
     "f128_c128": (S(8, 16, 16, 16, 32), 70, 128),  # a hundred and more classes: every range of a batch
     "f512_c31": (S(8, 9, 8, 16, 128), 3, 31),
     "f1024_c9": (S(16, 2, 2, 32, 256), 33, 9),
-    "f260_c300": (S(8, 10, 10, 16, 65), 4, 300),   # pooling, linear layer and backward as launches of their own
+    "f260_c300": (S(8, 10, 10, 16, 65), 4, 300),
 }
 
 

@@ -1,5 +1,5 @@
-"""Heads of more than 16 384 weights in one launch (csrc/head.hip, head_wide_applicable): both sides of each line of the rule, both
-poolings and losses, against the oracle."""
+"""Heads of 256 and more features in one launch after the pooling or in two (csrc/head.hip, head_wide_applicable): both sides of the
+choice, both poolings and losses, against the oracle."""
 import pytest
 
 from paper_2402_14139_amd import binding as nf
@@ -10,15 +10,21 @@ pytestmark = pytest.mark.gpu
 
 # name -> (spec, B, classes, one launch)
 CASES = {
-    "f256_c100_one_sample": (S(8, 6, 6, 16, 64), 1, 100, True),
     "f240_c100": (S(8, 16, 16, 16, 60), 6, 100, False),
+    "f256_c100_one_sample": (S(8, 6, 6, 16, 64), 1, 100, True),
     "f256_c100_many_samples": (S(8, 12, 12, 16, 64), 128, 100, True),
-    "f256_c99": (S(8, 16, 16, 16, 64), 5, 99, False),
-    "f320_c200": (S(8, 16, 16, 16, 80), 7, 200, True),
-    "f320_c201": (S(8, 16, 16, 16, 80), 7, 201, False),
-    "f336_c100": (S(8, 12, 12, 16, 84), 6, 100, False),
-    "f256_c100_map_17x16": (S(8, 17, 16, 16, 64), 5, 100, False),
+    "f256_c16_two_to_a_unit": (S(8, 16, 16, 16, 64), 32, 16, True),
+    "f256_c17_two_to_a_unit": (S(8, 16, 16, 16, 64), 32, 17, False),
+    "f292_c60_odd_filters": (S(8, 7, 7, 16, 73), 3, 60, True),
+    "f320_c201": (S(8, 16, 16, 16, 80), 7, 201, True),
     "f320_c150_odd_map": (S(8, 13, 11, 16, 80), 9, 150, True),
+    "f512_c37_ten_samples": (S(8, 14, 14, 16, 128), 10, 37, True),
+    "f512_c37_twenty_samples": (S(8, 14, 14, 16, 128), 20, 37, False),
+    "f1008_c24": (S(8, 16, 16, 16, 252), 9, 24, False),
+    "f1008_c200": (S(8, 16, 16, 16, 252), 9, 200, True),
+    "f1024_c1024": (S(8, 2, 2, 16, 256), 2, 1024, True),
+    "f1024_c1025": (S(8, 2, 2, 16, 256), 2, 1025, False),
+    "f1028_c200": (S(8, 2, 2, 16, 257), 2, 200, False),
 }
 
 
