@@ -38,6 +38,11 @@
  *   (they are data on the device); such a label contributes as if no class matched and
  *   such an index is clamped into range.
  *   Calls sharing a workspace must be ordered on one stream.
+ *   Values that are not finite: an infinity in the input or the weights reaches the results whose sum holds
+ *   it.  A window that lies partly over the zero padding, with an infinite or NaN weight there (or, in a
+ *   weight gradient, an infinite gradient beside the padding), is the exception: kernels that leave the padding
+ *   out (the 3x3 minimal filtering, and the direct kernels on small maps, by sizes and batch) do not see it, the
+ *   others form 0 * inf = NaN there, which a ReLU makes 0.
  */
 #ifndef NF_H
 #define NF_H

@@ -72,8 +72,8 @@ struct Mfma<16> {
 // the fabric once per tap (measured: less than half of the fetched bytes).
 // PM (with TI, modes 0 and 2): a tile is BM images at ONE output position, so that a tap lies over the padding for all of its
 // rows or for none, and its steps are left out: 4 of 9 remain on 2x2 maps, 6.25 on average on 4x4 ones.  The others keep
-// their order and their split, so the sums are the same bits.  (Padding contributes nothing: an infinite weight over it, which
-// used to make a NaN of 0 * inf, is not read.)
+// their order and their split, so the sums are the same bits.  (Padding contributes nothing: an infinite weight over it, of
+// which the other tiles make a NaN by 0 * inf, is not read.)
 template <int BM, int BN, int BK, int WM, int WN, int MF, int MODE, bool SCHED, bool TI, bool PM>
 __global__ __launch_bounds__(WM *WN * 64) void igemm_fwd_fast_kernel(FwdProblem p, FastAux q) {
   constexpr bool PROJ = MODE == 1, EPI = MODE == 2;

@@ -62,7 +62,7 @@ struct Frag<4> {
 // PM (no projection, channels a multiple of BQ: a tile is one tap): the reduction runs over the output positions whose window
 // holds a pixel under that tap, all images of a position after the other; rows of padding are left out, 5 of 9 on 2x2 maps.  A
 // split is a range of the rows that remain (a tap at the rim has shorter ones than the one in the centre, which forms the
-// bias gradient).  (Padding contributes nothing: an infinite gradient beside it, which used to make a NaN of inf * 0, is not read.)
+// bias gradient).  (Padding contributes nothing: an infinite gradient beside it, of which the other tiles make a NaN by inf * 0, is not read.)
 template <int BP, int BQ, int WP, int WQ, int PROJ, bool PM>
 __device__ __forceinline__ void wgrad_tile(const WgradProblem &p, const PositionRows &q, const TileGrid &grid, int lin,
                                            float *lds) {

@@ -109,8 +109,9 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(FilterJobs js) {
   wino_filter_store(g, f.U, n, c4, nchunks, wino_nb(f.N));
 }
 
-// Four outputs (filters n .. n+3 of pixel (img, ho, wo)) by the direct sum over channels [c_lo, c_hi);
-// taps outside the image multiply a zero, as in the direct kernel.
+// Four outputs (filters n .. n+3 of pixel (img, ho, wo)) by the direct sum over channels [c_lo, c_hi).
+// Taps outside the image are left out, as in the direct kernel's position tiles: an infinite weight over the padding is not one of
+// the sum's.  (Its other tiles multiply it by the zero they load.)
 __device__ inline float4 direct4(const float *x, const float *w, int H, int W, int C, int img, int ho, int wo, int n,
                                  int c_lo, int c_hi, unsigned want) {
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -118,12 +119,12 @@ __device__ inline float4 direct4(const float *x, const float *w, int H, int W, i
 #pragma unroll 1
   for (int tap = 0; tap < 9; ++tap) {
     const int hi = ho + tap / 3 - 1, wi = wo + tap % 3 - 1;
-    const bool in = ((unsigned)hi < (unsigned)H) & ((unsigned)wi < (unsigned)W);
-    const float *xr = x + ((long long)(img * H + (in ? hi : 0)) * W + (in ? wi : 0)) * C;
+    if (((unsigned)hi >= (unsigned)H) | ((unsigned)wi >= (unsigned)W)) continue;
+    const float *xr = x + ((long long)(img * H + hi) * W + wi) * C;
     const float *wr = w + ((long long)n * 9 + tap) * C;
 #pragma unroll 1
     for (int c = c_lo; c < c_hi; c += 4) {
-      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f), v = in ? *reinterpret_cast<const float4 *>(xr + c) : z;
+      const float4 v = *reinterpret_cast<const float4 *>(xr + c);
       auto dot = [&](int k, float a) {
         const float4 g = *reinterpret_cast<const float4 *>(wr + k * ws + c);
         return __builtin_fmaf(v.w, g.w, __builtin_fmaf(v.z, g.z, __builtin_fmaf(v.y, g.y, __builtin_fmaf(v.x, g.x, a))));

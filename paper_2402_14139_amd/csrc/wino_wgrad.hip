@@ -300,7 +300,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_wgrad_kernel(WgradProblem p,
   }
   if (!__syncthreads_or(bad)) return;
 
-  // ---- the direct sum: wave w forms taps w, w+4, w+8 ----
+  // ---- the direct sum: wave w forms taps w, w+4, w+8; a pixel outside the image takes no part, whatever its gradient ----
 #pragma unroll 1
   for (int tap = row; tap < 9; tap += 4) {
 #pragma unroll
@@ -313,10 +313,9 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_wgrad_kernel(WgradProblem p,
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int ho = 2 * ty + (k >> 1), wo = 2 * tx + (k & 1), hi = ho + tap / 3 - 1, wi = wo + tap % 3 - 1;
-        const bool okd = (tile < t_hi) & (ho < p.Ho) & (wo < p.Wo);
-        const bool okx = okd & ((unsigned)hi < (unsigned)p.H) & ((unsigned)wi < (unsigned)p.W);
-        const floatx4 d = bload4(rsd, poff + (okd ? ((img * p.Ho + ho) * p.Wo + wo) * p.P * 4 : OOB_T));
-        const floatx2 x = bload2(rsx, qoff + (okx ? ((img * p.H + hi) * p.W + wi) * p.C * 4 : OOB_T));
+        const bool ok = (tile < t_hi) & (ho < p.Ho) & (wo < p.Wo) & ((unsigned)hi < (unsigned)p.H) & ((unsigned)wi < (unsigned)p.W);
+        const floatx4 d = bload4(rsd, poff + (ok ? ((img * p.Ho + ho) * p.Wo + wo) * p.P * 4 : OOB_T));
+        const floatx2 x = bload2(rsx, qoff + (ok ? ((img * p.H + hi) * p.W + wi) * p.C * 4 : OOB_T));
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll

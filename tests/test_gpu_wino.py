@@ -151,6 +151,54 @@ def test_wino_results_of_filters_that_are_nan():
     assert (ys[1] - ys[0])[..., ~bad].abs().max() <= 5e-6 * ys[0].abs().max()
 
 
+def test_wino_padding_contributes_nothing():
+    """An infinite weight at the rim of a filter reaches the pixels whose window holds a pixel under it, and no others."""
+    B, C, H, K = 48, 64, 16, 256
+    g = torch.Generator(device="cuda").manual_seed(15)
+    x = torch.rand(B, H, H, C, generator=g, device="cuda") + 0.1
+    w, b = torch.randn(K, 3, 3, C, generator=g, device="cuda") * 0.06, torch.full((K,), 50.0, device="cuda")
+    w[200, 0, 2, 9] = float("inf")  # over the padding in the first row and the last column
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=K, R=3, S=3, stride=1, pad=1)
+    y = torch.empty(B, H, H, K, device="cuda")
+    ws = torch.empty(nf.nf_workspace_bytes(d, None, B), dtype=torch.uint8, device="cuda")
+    nf.nf_prof_begin()
+    nf.nf_layer_fwd(d, B, x, None, nf.layer_params(w, b, None), y, ws)
+    names = {r["kernel"] for r in nf.nf_prof_end()}
+    if nf.nf_contraction() != nf.NF_CONTRACT_F32:
+        pytest.skip("the split modes turn an infinity into NaN")
+    assert "wino_fwd" in names
+    inf = torch.zeros_like(y, dtype=torch.bool)
+    inf[:, 1:, :-1, 200] = True
+    assert torch.equal(torch.isinf(y), inf) and (y > 0).all()
+
+
+def test_wino_wgrad_padding_contributes_nothing():
+    """An infinite gradient at one corner pixel: the taps that lie over the padding there stay zero."""
+    B, C, H, K, A = 64, 64, 16, 128, 8
+    g = torch.Generator(device="cuda").manual_seed(16)
+    z = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
+    d = nf.LayerDesc(C_in=C, H_in=H, W_in=H, C_out=K, R=3, S=3, stride=1, pad=1)
+    a = nf.AuxDesc(C_in=K, H_in=H, W_in=H, A=A, R=3, S=3, pad=1, relu=1, pool_oh=2, pool_ow=2, n_classes=4, loss_kind=1)
+    x, y = torch.rand(B, H, H, C, generator=g, device="cuda") + 0.1, z(B, H, H, K)
+    y[3, 0, 0] = 1e-28  # the one pixel that passes the ReLU
+    p = [z(K, 3, 3, C), z(K), z(A, 3, 3, K), z(A) + 1e-30, z(4, 4 * A), z(4)]
+    p[2][5] = 0.01
+    p[4][2, 5] = 3e38  # filter 5, first quadrant: a finite logit, an infinite gradient
+    gr, labels, loss = [torch.zeros_like(t) for t in p], torch.zeros(B, device="cuda", dtype=torch.int32), z(1)
+    lp, ap, gp, ga = nf.layer_params(*p[:2], None), nf.aux_params(*p[2:]), nf.layer_params(*gr[:2], None), nf.aux_params(*gr[2:])
+    ws = torch.empty(nf.nf_workspace_bytes(d, a, B), dtype=torch.uint8, device="cuda")
+    nf.nf_aux_fwd_loss(d, a, B, y, labels, ap, loss, ws)
+    nf.nf_prof_begin()
+    nf.nf_local_bwd_wgrad(d, a, B, x, None, y, lp, ap, gp, ga, ws)
+    names = {r["kernel"] for r in nf.nf_prof_end()}
+    if nf.nf_contraction() != nf.NF_CONTRACT_F32:
+        pytest.skip("the split modes turn an infinity into NaN")
+    assert "wino_wgrad" in names
+    seen = torch.zeros(K, 3, 3, C, dtype=torch.bool, device="cuda")
+    seen[:, 1:, 1:] = True
+    assert torch.isinf(gr[0][seen]).all() and (gr[0][~seen] == 0).all()
+
+
 # data gradients whose transformed filter comes from a head launch: the per-sample head, the wide one and the
 # backward of a wide linear layer; channels of the head and of the layer that are not multiples of 8 and 64
 DGRAD_CASES = {
