@@ -22,11 +22,12 @@
 //     takes 84, 64 channels on 56x56 maps, batch 64; equal where both fill the chip once).
 // The reduction has C terms per position instead of 9 C: the rounding error against 64 bits is
 // smaller than that of the direct sum (emitted activation, relative: 64 channels 1.7e-7 against 2.2e-7, four
-// layers of 256 channels in a row 5.9e-7 against 7.1e-7).
+// layers of 256 channels in a row 5.9e-7 against 7.1e-7).  That is a single result's: an average over pixels and samples keeps the
+// rounding of the transformed filter (wino_fwd_pick_splits).
 //
 // Measured (us, the direct kernel / this with its filter launch of 5-8 us): 64 -> 64 channels, 65 536 pixels
-// 43 / 35; 128 -> 128, 32 768 pixels 80 / 48; 256 -> 256, 16 384 pixels 155 / 83; 512 -> 512, 8192 pixels 312 / 150
-// (a step of 8 channels takes 2.1 us on a CU with two workgroups, 0.87 of it MFMAs).
+// 50 / 32; 128 -> 128, 32 768 pixels 78 / 46; 256 -> 256, 8x8 pixels, batch 256 132 / 78; 512 -> 512, 4x4, batch 512 228 / 142 (the direct
+// kernel without the padding there); a step of 8 channels takes 1.93 us on a CU with two workgroups, 0.87 of it MFMAs.
 //
 // The data gradient onto a layer of up to 32 filters runs through a variant of 32 per workgroup, half of whose columns
 // would be padding otherwise: 64 accumulators, three workgroups per CU, the same patches and transforms for half of the
@@ -502,9 +503,11 @@ long long workgroups(const FwdProblem &p) {
   const int nb = wino_nb(p.N);
   return tiles * ((p.N + nb - 1) / nb);
 }
-// this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two, in rounds of 512 workgroups; 11 us of
-// prologue, epilogue and launches, 3 us for each further round; the transformed filter written and read at 4 TB/s; a projection shortcut is a launch of
-// its own whose result this kernel adds (enqueue_conv)
+// this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two (before load offsets advanced in scalar registers; 1.03
+// and 1.93 now, so that layers near the line keep the direct kernel), in rounds of 512 workgroups; 11 us of prologue, epilogue
+// and launches, 3 us for each further round; the transformed filter written and read at 4 TB/s; a projection shortcut is a
+// launch of its own whose result this kernel adds (enqueue_conv).  The pooling launch that a layer with 2x2 windows saves
+// here (8 us) is not counted
 double wino_us(const FwdProblem &p, int s) {
   const int nchunks = (p.C + CH - 1) / CH;
   const long long w = workgroups(p) * s;
