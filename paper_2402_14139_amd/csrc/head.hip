@@ -1026,14 +1026,15 @@ bool head_wide_applicable(const HeadShape &h) {
   // chip; a chain over the classes bounds it.  Against that, per workgroup on a CU, the weights read twice (the logits in
   // passes of 16 or 128 classes), and the few workgroups that store dU.  us, fitted to 335 random heads of 256 ... 1024 features, 10
   // ... 880 classes, 1 ... 5800 samples of up to 48x48 pixels (means of a step and of the separate calls): of the 1924 us that the
-  // better side of each is ahead in one launch, this choice takes 1853, 16384 weights as the line -75.  Two launches / one, a step: 64 filters, 100
-  // classes, 1 of 6x6 60 / 52; 72, 200, 509 of 21x21 364 / 349; 68, 815, 87 of 16x16 297 / 255; 100, 599, 2 of 33x33 198 / 154.
-  // And the other way: 140, 37, 465 of 6x6 167 / 175; 252, 162, 259 of 5x5 116 / 125.  On a fifth of the heads neither is ahead by 1 us.
+  // better side of each is ahead in one launch, this choice takes 1840, 16384 weights as the line -75; of 200 more, with 2 ... 37
+  // classes, 59 of 114.  Two launches / one, a step: 64 filters, 100 classes, 1 of 6x6 60 / 52; 72, 200, 509 of 21x21 364 / 349; 68,
+  // 815, 87 of 16x16 297 / 255; 100, 599, 2 of 33x33 198 / 154.  And the other way: 140, 37, 465 of 6x6 167 / 175; 252, 162, 259 of
+  // 5x5 116 / 125.  On a fifth of the heads neither is ahead by 1 us.
   const int pass = h.Cls <= 16 ? 16 : 128, padded = (h.Cls + pass - 1) / pass * pass;
   const double chain = 0.073 * h.Cls * std::max(1.0, h.B / 1024.0);
   const double weights = 0.3e-4 * h.F * 0.5 * (padded + h.Cls) * std::max(1.0, (double)h.B * wide_slices(h) / 256);
   const double stores = 0.19e-6 * h.B * h.Hu * h.Wu * h.A;
-  return chain - weights - stores > 0.3;
+  return chain - weights - stores > 0.1;
 }
 
 bool head_pool_partials_applicable(const HeadShape &h) {

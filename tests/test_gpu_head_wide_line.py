@@ -19,7 +19,7 @@ CASES = {
     "f320_c201": (S(8, 16, 16, 16, 80), 7, 201, True),
     "f320_c150_odd_map": (S(8, 13, 11, 16, 80), 9, 150, True),
     "f512_c37_ten_samples": (S(8, 14, 14, 16, 128), 10, 37, True),
-    "f512_c37_twenty_samples": (S(8, 14, 14, 16, 128), 20, 37, False),
+    "f512_c37_thirty_samples": (S(8, 14, 14, 16, 128), 30, 37, False),
     "f1008_c24": (S(8, 16, 16, 16, 252), 9, 24, False),
     "f1008_c200": (S(8, 16, 16, 16, 252), 9, 200, True),
     "f1024_c1024": (S(8, 2, 2, 16, 256), 2, 1024, True),
