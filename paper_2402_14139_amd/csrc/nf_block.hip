@@ -119,7 +119,13 @@ int32_t plan_block(const nf_block *blk, int32_t B, int32_t B_last, PlanMode mode
 // what it holds of their scratch.
 int32_t plan_block_in(const nf_block *blk, int32_t B, int32_t B_last, PlanMode mode, size_t have, BlockPlan *pl) {
   const int32_t rc = plan_block(blk, B, B_last, mode, pl);
-  if (rc || have >= pl->total || have < pl->layer_ws_off + up(pl->layer_ws_least)) return rc;
+  if (rc || have < pl->layer_ws_off + up(pl->layer_ws_least)) return rc;
+  if (have >= pl->total) {
+    // a workspace made for training holds more than a sweep plans: a partial last batch, whose reductions are cut to fill the
+    // chip, gets it (four layers of 256 channels, 8x8, 600 samples in batches of 256: 830 us without it, 758 with it)
+    pl->layer_ws_bytes = std::max(pl->layer_ws_bytes, (have - pl->layer_ws_off) / ALIGN * ALIGN);
+    return rc;
+  }
   BlockPlan q;
   for (int32_t b = B + 1; plan_block(blk, b, b, mode, &q) == NF_OK && q.layer_ws_off <= have; ++b)
     if (q.total <= have) {
