@@ -35,7 +35,8 @@ def test_layer_forward_against_64_bits(C, H, W, K, B, pool, skip):
     nf.nf_prof_begin()
     y = L.forward(x, xs, y=L.new_output(B))
     names = {r["kernel"] for r in nf.nf_prof_end()}
-    assert "wino_fwd" in names, names
+    if nf.nf_contraction() == nf.NF_CONTRACT_F32:
+        assert "wino_fwd" in names, names
     ref = torch.nn.functional.conv2d(x.cpu().double().permute(0, 3, 1, 2), W_.cpu().double().permute(0, 3, 1, 2), b.cpu().double(), padding=1)
     if skip:
         ref = ref + xs.cpu().double().permute(0, 3, 1, 2)
