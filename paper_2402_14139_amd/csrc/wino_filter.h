@@ -48,11 +48,13 @@ __device__ inline void wino_filter_columns(const float4 (&q)[3], float4 (&v)[4])
   const float4 e = wino_add4(q[0], q[2]);
   v[0] = q[0], v[1] = wino_half4(wino_add4(e, q[1])), v[2] = wino_half4(wino_sub4(e, q[1])), v[3] = q[2];
 }
-// the pieces of four channels at word o of piece 0
-__device__ inline void wino_store_pieces(float *o, const float4 &v) {
+// the pieces of four channels at word o of piece 0, the positions with a + b odd (`odd`) negated: bf16 MFMAs round their running sum
+// down, not to nearest, and with every other position's sum of the other sign that cancels in the output transform (wino_fwd_split.hip)
+__device__ inline void wino_store_pieces(float *o, const float4 &v, bool odd) {
+  const float s = odd ? -1.f : 1.f;
   unsigned w[3][2];
-  wino_split2(v.x, v.y, w[0][0], w[1][0], w[2][0]);
-  wino_split2(v.z, v.w, w[0][1], w[1][1], w[2][1]);
+  wino_split2(s * v.x, s * v.y, w[0][0], w[1][0], w[2][0]);
+  wino_split2(s * v.z, s * v.w, w[0][1], w[1][1], w[2][1]);
 #pragma unroll
   for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2 *>(o + k * 256) = make_uint2(w[k][0], w[k][1]);
 }
@@ -73,7 +75,7 @@ __device__ inline void wino_filter_store(const float4 (&g)[3][3], float *U, int 
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       float *const ob = o + (a * 4 + b) * (words / 16);
-      if (pieces) wino_store_pieces(ob, v[b]);
+      if (pieces) wino_store_pieces(ob, v[b], (a + b) & 1);
       else *reinterpret_cast<float4 *>(ob) = v[b];
     }
   }

@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void wino_filter_split_kernel(FilterJobs js) {
   constexpr int words = wino_step_words(64, true);
   float *const o = f.U + (long long)at * words + a * (words / 4) + nn * 768 + (h * 32 + j) * 4 + i * 2;
 #pragma unroll
-  for (int p = 0; p < 4; ++p) wino_store_pieces(o + p * (words / 16), v[p]);
+  for (int p = 0; p < 4; ++p) wino_store_pieces(o + p * (words / 16), v[p], (a + p) & 1);
 }
 
 // The fp32 form of one filter: 5-8 us, most of it the launch

@@ -4,8 +4,10 @@
 // piece products the six largest are accumulated in fp32.  The pieces are rounded to nearest, so that the three left out (2^-25
 // of the product each, at most) have no common sign.  Per 16 channels of a 32x32 tile that is 192 cycles of the matrix pipe where fp32
 // MFMAs take 512, and six roundings of the running sum where those make eight: the error against 64 bits is the smaller one (emitted
-// activation and logits, relative, fp32 MFMAs / this: 64 channels 1.7e-7 / 1.4e-7, 64 -> 128 1.9e-7 / 1.6e-7, 256 with a projection
-// 3.2e-7 / 2.9e-7, four layers of 128-256 channels 5.2e-7 / 4.9e-7).
+// activation and logits, relative, fp32 MFMAs / this: 64 channels 2.3e-7 / 1.9e-7, 256 4.4e-7 / 3.8e-7, 512 6.5e-7 / 5.7e-7, four layers of
+// 128-256 channels in a row 5.2e-7 / 4.9e-7).  Averages over all pixels: bf16 MFMAs do not round their running sum to nearest but, on
+// average, down; the positions with row + column odd are therefore formed negated, so that in the sum over a tile's outputs as many
+// positions err up as down (512 channels, 8192 pixels 3.9e-8 / 4.0e-8, without it 4.7e-8; 64 to 256 channels equal).
 //
 // Layout of the work:
 //   - a workgroup owns 64 output tiles (256 pixels) x 64 filters x all 16 positions, one per CU; its eight waves take two positions
@@ -307,7 +309,8 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_split_kernel(FwdProblem 
   for (int g = 0; g < G; ++g) {
     const int tg = t0 + 32 * g;
     if (tg >= q.T) break;
-    // output transform: a wave's part of the columns in registers, the rest through LDS
+    // output transform: a wave's part of the columns in registers, the rest through LDS (positions with row + column odd stand
+    // negated: the columns here, the rows below)
     __syncthreads();
     {
       float *const cw = S + wave * WS + 2 * j;
@@ -318,7 +321,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_split_kernel(FwdProblem 
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
           const float m0 = acc[0][g][f][e], m1 = acc[1][g][f][e];
-          y0[f] = cb ? m0 : m0 + m1, y1[f] = cb ? -m0 - m1 : m1;
+          y0[f] = cb ? m0 : m0 - m1, y1[f] = cb ? m1 - m0 : -m1;
         }
         *reinterpret_cast<float2 *>(cw + (r * 2 + 0) * NB) = make_float2(y0[0], y0[1]);
         *reinterpret_cast<float2 *>(cw + (r * 2 + 1) * NB) = make_float2(y1[0], y1[1]);
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_fwd_split_kernel(FwdProblem 
 #pragma unroll
       for (int a = 0; a < 4; ++a)
         r[a] = add4(*reinterpret_cast<const float4 *>(c + 2 * a * WS), *reinterpret_cast<const float4 *>(c + (2 * a + 1) * WS));
-      y[i][0] = add4(add4(r[0], r[1]), r[2]), y[i][1] = sub4(sub4(r[1], r[2]), r[3]);
+      y[i][0] = add4(sub4(r[0], r[1]), r[2]), y[i][1] = sub4(r[3], add4(r[1], r[2]));
 #pragma unroll
       for (int k = 0; k < 2; ++k)
         if (off[g][i][k] >= 0) bad |= bad4(y[i][k]) << (4 * (2 * i + k));
