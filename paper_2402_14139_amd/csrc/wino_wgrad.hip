@@ -14,7 +14,7 @@
 //     wave loads them in fragment order straight from memory (rows of 128 / 256 contiguous bytes, two
 //     steps ahead), transforms them in registers and needs no barrier and no staged operand in its
 //     loop.  A step is 32 MFMAs, 12 loads and 62 vector operations; the latter two are not free beside
-//     MFMAs (about 4 and 9 cycles each), which is what keeps a step at 1650 of its 1024 cycles per wave.
+//     fp32 MFMAs, which is what keeps a step at 1500 of its 1024 cycles per wave (the vector operations in clumps, see step).
 //     (32x32x2 MFMAs, two tiles per step: half the operands per load, 24 loads for the same
 //     MFMAs, 232 us where this takes 216; 512 channels, 8192 pixels);
 //   - the byte offsets of 64 tiles at a time stand in a table in LDS (one thread decodes a tile; what
@@ -126,10 +126,8 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_wgrad_kernel(WgradProblem p,
   floatx4 dr[SETS][2][2];  // [set][row da, db][column], four filters
   int4 ea, eb;             // table entries of the step to load next
   int2 fa, fb;
-  auto tread = [&](int i) {  // i: step within the table
-    const int e = KT * i + h;
-    ea = Tx[ra][e], eb = Tx[rb][e], fa = Td[da][e], fb = Td[db][e];
-  };
+  auto tread_x = [&](int i) { ea = Tx[ra][KT * i + h], eb = Tx[rb][KT * i + h]; };  // i: step within the table
+  auto tread_d = [&](int i) { fa = Td[da][KT * i + h], fb = Td[db][KT * i + h]; };
   auto gload = [&](int set, int part) {  // a third of a step's twelve loads
     if (part == 0) {
       xr[set][0][0] = bload2(rsx, ea.x + qoff), xr[set][0][1] = bload2(rsx, ea.y + qoff);
@@ -158,37 +156,45 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_wgrad_kernel(WgradProblem p,
       for (int a = 0; a < 4; ++a) u[c][a] = __builtin_fmaf(sd, dr[set][1][c][a], dr[set][0][c][a]);
   };
 
-  // Step i, one section per column b of the transformed domain: the column's operands, then its MFMAs.
-  // Under the MFMAs of sections 0-2: the loads of step i+SETS into set `cur`, whose rows step i already
-  // combined (spread out: a burst of all twelve from four waves holds the waves up at the address
-  // unit, 16 cycles a load); of section 3: the row combination of step i+1 and the next table entries.
+  // Step i, two sections of two columns of the transformed domain each: their operands, then their MFMAs, and the loads of step i+SETS
+  // into set `cur`, whose rows step i already combined (one behind an MFMA: a burst of all twelve from four waves holds the waves
+  // up at the address unit, 16 cycles a load); in the second also the row combination of step i+1.  The vector instructions stand
+  // in two clumps a section: an fp32 MFMA and a vector instruction hold each other up, about 14 cycles for each change from the one
+  // to the other and 2 (two waves on a SIMD) for each instruction, so that 62 of them spread singly behind 32 MFMAs cost 550 cycles of
+  // a step's 2048 and in four clumps half of that (512 channels, 8192 pixels 210 / 192 us; in two clumps, with more registers held
+  // and spilled, 199).
   auto step = [&](int i, int cur, bool first) {  // first: the sums start at zero
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const floatx2 v = b == 0 ? xc[0] - xc[2] : b == 1 ? xc[1] + xc[2] : b == 2 ? xc[2] - xc[1] : xc[1] - xc[3];
-      const floatx4 g = b == 0 ? u[0] : b == 1 ? u[0] + u[1] : b == 2 ? u[0] - u[1] : u[1];
-      if (b == 1) bs += g;
-      if (b < 3) {
-        gload(cur, b);
+    for (int half = 0; half < 2; ++half) {
+      floatx2 v[2];
+      floatx4 g[2];
+      if (half == 0) {
+        v[0] = xc[0] - xc[2], v[1] = xc[1] + xc[2], g[0] = u[0], g[1] = u[0] + u[1];
+        bs += g[1];
+        gload(cur, 0), gload(cur, 1);
+        tread_d(i + SETS);
       } else {
+        v[0] = xc[2] - xc[1], v[1] = xc[1] - xc[3], g[0] = u[0] - u[1], g[1] = u[1];
+        gload(cur, 2);
         combine((cur + 1) % SETS);
-        tread(i + 1 + SETS);
+        tread_x(i + 1 + SETS);
       }
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
-          acc[b][a][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[a], v[n], first ? (floatx4)(0.f) : acc[b][a][n], 0, 0, 0);
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int n = 0; n < 2; ++n)
+            acc[2 * half + c][a][n] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(g[c][a], v[c][n], first ? (floatx4)(0.f) : acc[2 * half + c][a][n], 0, 0, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 40, 0);
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (b < 3) {
-          __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);             // + an address
-          if (k & 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // + a load
-        } else {
-          __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);             // + row combination
-          if (k >= 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); // + a table read
-        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                         // one MFMA
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                         // + a load
+        if (k >= 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // + a table read
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -244,12 +250,12 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_wgrad_kernel(WgradProblem p,
   // in this order, or the loop's waits are for the last of the loads
 #pragma unroll
   for (int a = 0; a < SETS; ++a) {
-    tread(a);
+    tread_x(a), tread_d(a);
     for (int k = 0; k < 3; ++k) gload(a, k);
     __builtin_amdgcn_sched_barrier(0);
   }
   combine(0);
-  tread(SETS);
+  tread_x(SETS);
   __builtin_amdgcn_sched_barrier(0);
   for (int base = t_lo; base < t_hi; base += q.period) {
     const int nsteps = (min(q.period, t_hi - base) + KT * SETS - 1) / (KT * SETS) * SETS;
