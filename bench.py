@@ -34,7 +34,6 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 # WRITE_SIZE x 1.0.  Averages over the launches of one step; summary under profiles/.
 TRAFFIC_BYTES_PER_LAUNCH = {
     ("cfg3_resnet18", "wino_wgrad"): 40.5e6 + 42.0e6,
-    ("cfg3_resnet18", "wino_fwd"): 38.1e6 + 16.9e6,
 }
 TRAFFIC_SOURCE = ("offline: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes over this script, scaled by a 1 GiB copy "
                   "(FETCH x 2.0, WRITE x 1.0); summary in profiles/local_step_cfg3_hbm_traffic.md; not re-measured "
@@ -286,12 +285,13 @@ def main():
             # minimal filtering carries out 16 multiply-adds of the dense formula's 36: priced as carried out
             wino = dom["kernel"].startswith("wino")
             ach *= 16.0 / 36.0 if wino else 1.0
-            # a split-operand kernel spends six bf16 matrix-core multiply-adds per algorithmic one
-            split = 6 if "_split_" in dom["kernel"] else 9 if "_split9_" in dom["kernel"] else 0
+            # a split-operand kernel spends six bf16 matrix-core multiply-adds per algorithmic one (wino_fwd: per one carried out)
+            split = 6 if "_split_" in dom["kernel"] or dom["kernel"] == "wino_fwd" else 9 if "_split9_" in dom["kernel"] else 0
             peak = round(MFMA_BF16_PEAK_TFLOPS / split, 1) if split else MFMA_F32_PEAK_TFLOPS
             roofline = {"kernel": dom["kernel"], "bound": "mfma", "achieved": round(ach, 2),
                         "peak": peak, "unit": "TFLOP/s", "frac": round(ach / peak, 4),
                         "peak_note": (f"bf16 dense matrix peak 2500 TFLOP/s / {split} piece products per fp32 multiply-add"
+                                      + ("; achieved = multiply-adds carried out, 16 for 36 of the dense formula" if wino else "")
                                       if split else "fp32 dense matrix peak; achieved = multiply-adds carried out, "
                                       "16 for 36 of the dense formula" if wino else "fp32 dense matrix peak"),
                         "traffic": TRAFFIC_BYTES_PER_LAUNCH.get((cfg.name, dom["kernel"])),
