@@ -976,7 +976,8 @@ RelayJob relay_job(const float *Wa, float *WaT, float *U, int A, int R, int S, i
   j.nchunks = (A + ch - 1) / ch;
   j.nb_t = (int)(((long long)A * R * S * K + HT - 1) / HT);
   const int nb = wino_nb(K);
-  j.nb_u = U ? ((K + nb - 1) / nb * nb * (ch / 4) * j.nchunks + HT - 1) / HT : 0;
+  const int rows = wino_pieces(K, A) ? 4 : 1;  // of the transformed domain, a thread each
+  j.nb_u = U ? ((K + nb - 1) / nb * nb * (ch / 4) * j.nchunks * rows + HT - 1) / HT : 0;
   return j;
 }
 

@@ -58,14 +58,23 @@ __device__ inline void wino_store_pieces(float *o, const float4 &v, bool odd) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2 *>(o + k * 256) = make_uint2(w[k][0], w[k][1]);
 }
-// U = G g G^T for four consecutive channels 4*c4 .. +3 of filter n, g[r][s] holding their taps
-__device__ inline void wino_filter_store(const float4 (&g)[3][3], float *U, int n, int c4, int nchunks, int nb, bool pieces) {
-  const int in = n & (nb - 1), two = nb >> 6, words = wino_step_words(nb, pieces);
-  // of this thread's four channels, position 0 (piece 0)
-  float *const o = pieces ? U + ((long long)(n / 64) * nchunks + (c4 >> 2)) * words + (in & 1) * 768 + ((c4 & 1) * 32 + (in >> 1)) * 4 +
-                                (c4 >> 1 & 1) * 2
-                          : U + ((long long)(n / nb) * nchunks + (c4 >> 1)) * words + (in & two) * 256 +
-                                ((c4 & 1) * 32 + (in >> two)) * 4;
+// where the pieces of row a of the transformed domain, channels 4*c4 .. +3 of filter n begin
+__device__ inline float *wino_pieces_at(float *U, int n, int c4, int nchunks, int a) {
+  constexpr int words = wino_step_words(64, true);
+  return U + ((long long)(n / 64) * nchunks + (c4 >> 2)) * words + a * (words / 4) + (n & 1) * 768 + ((c4 & 1) * 32 + (n & 63) / 2) * 4 +
+         (c4 >> 1 & 1) * 2;
+}
+// the four positions of row a, its three columns of taps in q
+__device__ inline void wino_store_row(float *o, const float4 (&q)[3], int a) {
+  float4 v[4];
+  wino_filter_columns(q, v);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) wino_store_pieces(o + b * (wino_step_words(64, true) / 16), v[b], (a + b) & 1);
+}
+// the fp32 form of U = G g G^T for four consecutive channels 4*c4 .. +3 of filter n, g[r][s] holding their taps
+__device__ inline void wino_filter_store(const float4 (&g)[3][3], float *U, int n, int c4, int nchunks, int nb) {
+  const int in = n & (nb - 1), two = nb >> 6, words = wino_step_words(nb, false);
+  float *const o = U + ((long long)(n / nb) * nchunks + (c4 >> 1)) * words + (in & two) * 256 + ((c4 & 1) * 32 + (in >> two)) * 4;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     float4 q[3], v[4];
@@ -73,17 +82,14 @@ __device__ inline void wino_filter_store(const float4 (&g)[3][3], float *U, int 
     for (int s = 0; s < 3; ++s) q[s] = wino_filter_row(a, g[0][s], g[1][s], g[2][s]);
     wino_filter_columns(q, v);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      float *const ob = o + (a * 4 + b) * (words / 16);
-      if (pieces) wino_store_pieces(ob, v[b], (a + b) & 1);
-      else *reinterpret_cast<float4 *>(ob) = v[b];
-    }
+    for (int b = 0; b < 4; ++b) *reinterpret_cast<float4 *>(o + (a * 4 + b) * (words / 16)) = v[b];
   }
 }
 
 // What block b (256 threads) of a RelayJob does: the first nb_t blocks re-lay, one element per thread,
 // WaT[k][r][s][a] = Wa[a][R-1-r][S-1-s][k]; the other nb_u form the transformed filter of that (R = S = 3), four
-// channels a of one filter k per thread, lanes along k (coalesced reads of Wa).  Independent of the head's
+// channels a of one filter k per thread (as pieces: one row of the transformed domain of them; all four in a thread took a head_bwd launch
+// of 64 samples, 128 filters, 32-wide head from 5.2 to 6.8 us), lanes along k (coalesced reads of Wa).  Independent of the head's
 // samples, so it fills compute units that those leave idle; as a launch of its own in front of wino_fwd it
 // took 4-5 us of a step (64 channels, batch 128: step 178 -> 173.5 us).
 __device__ inline void relay_block(const RelayJob &j, int b) {
@@ -99,23 +105,39 @@ __device__ inline void relay_block(const RelayJob &j, int b) {
     return;
   }
   const int nb = wino_nb(j.K), i = (b - j.nb_t) * 256 + threadIdx.x, nk = (j.K + nb - 1) / nb * nb;
-  const int k = i % nk, c4 = i / nk;
-  if (c4 >= wino_ch(j.K, j.A) / 4 * j.nchunks) return;
+  const int c4s = wino_ch(j.K, j.A) / 4 * j.nchunks, k = i % nk, c4 = i / nk % c4s, row = i / nk / c4s;
+  const bool pieces = wino_pieces(j.K, j.A);
+  if (row >= (pieces ? 4 : 1)) return;
+  auto tap = [&](int r, int s) {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int a = c4 * 4 + e, ac = a < j.A ? a : 0, kc = k < j.K ? k : 0;
+      const float x = j.Wa[((long long)ac * 9 + (2 - r) * 3 + (2 - s)) * j.K + kc];
+      v[e] = ((a < j.A) & (k < j.K)) ? x : 0.f;
+    }
+    return make_float4(v[0], v[1], v[2], v[3]);
+  };
+  if (pieces && (row == 0 || row == 3)) {  // (one row of taps)
+    float4 q[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) q[s] = tap(row == 0 ? 0 : 2, s);
+    wino_store_row(wino_pieces_at(j.U, k, c4, j.nchunks, row), q, row);
+    return;
+  }
   float4 g[3][3];
 #pragma unroll
   for (int r = 0; r < 3; ++r)
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      float v[4];
+    for (int s = 0; s < 3; ++s) g[r][s] = tap(r, s);
+  if (!pieces) {
+    wino_filter_store(g, j.U, k, c4, j.nchunks, nb);
+    return;
+  }
+  float4 q[3];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int a = c4 * 4 + e, ac = a < j.A ? a : 0, kc = k < j.K ? k : 0;
-        const float x = j.Wa[((long long)ac * 9 + (2 - r) * 3 + (2 - s)) * j.K + kc];
-        v[e] = ((a < j.A) & (k < j.K)) ? x : 0.f;
-      }
-      g[r][s] = make_float4(v[0], v[1], v[2], v[3]);
-    }
-  wino_filter_store(g, j.U, k, c4, j.nchunks, nb, wino_pieces(j.K, j.A));
+  for (int s = 0; s < 3; ++s) q[s] = wino_filter_row(row, g[0][s], g[1][s], g[2][s]);
+  wino_store_row(wino_pieces_at(j.U, k, c4, j.nchunks, row), q, row);
 }
 
 }  // namespace nf

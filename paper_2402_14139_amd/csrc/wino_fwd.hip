@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void wino_filter_split_kernel(FilterJobs js) {
   auto tap = [&](int r, int s) {
     return ok ? *reinterpret_cast<const float4 *>(w + (r * 3 + s) * f.C) : make_float4(0.f, 0.f, 0.f, 0.f);
   };
-  float4 q[3], v[4];
+  float4 q[3];
   if (a == 0 || a == 3) {  // (one row of taps)
 #pragma unroll
     for (int s = 0; s < 3; ++s) q[s] = tap(a == 0 ? 0 : 2, s);
@@ -81,11 +81,7 @@ __global__ __launch_bounds__(256) void wino_filter_split_kernel(FilterJobs js) {
 #pragma unroll
     for (int s = 0; s < 3; ++s) q[s] = wino_filter_row(a, g[0][s], g[1][s], g[2][s]);
   }
-  wino_filter_columns(q, v);
-  constexpr int words = wino_step_words(64, true);
-  float *const o = f.U + (long long)at * words + a * (words / 4) + nn * 768 + (h * 32 + j) * 4 + i * 2;
-#pragma unroll
-  for (int p = 0; p < 4; ++p) wino_store_pieces(o + p * (words / 16), v[p], (a + p) & 1);
+  wino_store_row(wino_pieces_at(f.U, n, c / 4, nsteps, a), q, a);
 }
 
 // The fp32 form of one filter: 5-8 us, most of it the launch
@@ -101,7 +97,7 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(WinoFilter f, int nchu
     for (int s = 0; s < 3; ++s)
       g[r][s] = ok ? *reinterpret_cast<const float4 *>(f.w + ((long long)n * 9 + r * 3 + s) * f.C + c4 * 4)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
-  wino_filter_store(g, f.U, n, c4, nchunks, wino_nb(f.N), false);
+  wino_filter_store(g, f.U, n, c4, nchunks, wino_nb(f.N));
 }
 
 // NF: MFMA columns of 32 filters per workgroup (2, or 1 for few filters).  POOL: the 2x2 max pooling of Eq. 1 follows in the
