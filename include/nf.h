@@ -124,8 +124,8 @@ const char *nf_strerror(int32_t status);
  *                       square, i.e. of the size of an fp32 rounding; over the reductions of this
  *                       library (36 ... 4608 terms) the measured error against fp64 equals that of
  *                       the fp32 instructions.  An operand element that is +-inf gives NaN
- *                       instead of +-inf.  Weight gradients and whole 3x3 convolutions that
- *                       NF_CONTRACT_F32 carries out faster run as there.
+ *                       instead of +-inf.  Weight gradients that NF_CONTRACT_F32 carries out faster
+ *                       run as there.
  *   NF_CONTRACT_BF16X9  the same with all nine piece products: every product x*w enters the fp32
  *                       accumulation exactly, as with the fp32 instructions; 1.5x the matrix-core
  *                       work of BF16X6.

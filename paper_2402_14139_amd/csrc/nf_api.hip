@@ -445,13 +445,11 @@ int32_t enqueue_wino(FwdProblem f, float *out, int splits, float *scratch, float
 }
 
 // The reduction splits with which a contraction that the layout plans as wino_fwd runs in the mode in force;
-// 0: the direct kernels.  The split-operand modes keep their kernels where those serve it, but for whole reductions of the
-// six-product mode whose six products wino_fwd_split carries out faster.
+// 0: the direct kernels.  The split-operand modes keep their kernels where those serve it: a ReLU decision that
+// is a tie to within rounding falls as that mode's sums have it.
 int wino_splits_now(const FwdProblem &f, int splits) {
-  const int mode = contraction_mode();
-  const bool wino = mode == NF_CONTRACT_F32 || !igemm_fwd_fast_applicable(f) || !igemm_fwd_split_applicable(f) ||
-                    (mode == NF_CONTRACT_BF16X6 && wino_fwd_beats_split(f, splits));
-  return wino ? splits : 0;
+  return contraction_mode() == NF_CONTRACT_F32 || !igemm_fwd_fast_applicable(f) || !igemm_fwd_split_applicable(f) ? splits
+                                                                                                                  : 0;
 }
 // whether the layer's weight gradient, planned as wino_wgrad, runs that way in the mode in force
 bool run_wino(const WgradProblem &g, int splits) {

@@ -85,8 +85,6 @@ size_t wino_fwd_filter_floats(int N, int C);
 int wino_fwd_pick_splits(const FwdProblem &p, int direct, int most);
 // the same for a data gradient, whose filter an earlier launch transforms on its way (`ready`) or one of its own
 int wino_dgrad_pick_splits(const FwdProblem &p, int direct, bool ready);
-// against the direct split-operand kernel (six products)
-bool wino_fwd_beats_split(const FwdProblem &p, int splits);
 // A filter [N][3][3][C] and where its transformed form goes
 struct WinoFilter {
   const float *w;

@@ -552,14 +552,6 @@ int wino_fwd_pick_splits(const FwdProblem &p, int ks, int most) { return p.N <= 
 
 int wino_dgrad_pick_splits(const FwdProblem &p, int ks, bool ready) { return pick_splits(p, ks, 16, ready); }
 
-// The direct kernel with six piece products reaches 185 TFLOP/s in 128x128 tiles.  512 -> 512 channels, 8192 pixels, with the filter
-// launch: 208 us there, 112 here, and the same six products of fewer terms: error against 64 bits of that layer's step 5.2e-7 / 4.8e-7.
-bool wino_fwd_beats_split(const FwdProblem &p, int splits) {
-  if (splits != 1 || !wino_pieces(p.N, p.C)) return false;
-  const double m = (p.M + 127) / 128 * 128.0, n = (p.N + 127) / 128 * 128.0;
-  return wino_us(p, 1, false) < 0.95 * (8.0 + 2.0 * m * n * p.Kg / 185e6);
-}
-
 hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, const WinoFilter *also, hipStream_t st) {
   WinoAux q;
   const int TH = (p.Ho + 1) / 2, B = p.M / (p.Ho * p.Wo);
