@@ -112,11 +112,8 @@ const char *nf_strerror(int32_t status);
  * in both modes.
  *   NF_CONTRACT_F32     (default) fp32 matrix-core instructions (v_mfma_f32_*).  3x3 convolutions of
  *                       stride 1 and pad 1, and their weight gradients, go through the minimal filtering
- *                       algorithms F(2x2,3x3) / F(3x3,2x2) where that is faster and its error against 64
- *                       bits is below the direct sum's: transforms and sums in fp32; the products of
- *                       convolutions of more than 24 channels onto more than 32 filters by pieces as in
- *                       NF_CONTRACT_BF16X6 (rounded to nearest), whose error there is below that of the
- *                       fp32 instructions.  An infinite operand gives what the direct sum gives.
+ *                       algorithms F(2x2,3x3) / F(3x3,2x2), all in fp32, where that is faster and its
+ *                       error against 64 bits is below the direct sum's.
  *   NF_CONTRACT_BF16X6  each fp32 operand element is cut into three bfloat16 pieces that sum to it
  *                       exactly; six of the nine piece products are accumulated in fp32 by bf16
  *                       matrix-core instructions.  The three left out are together below 2^-21 of

@@ -972,12 +972,10 @@ RelayJob relay_job(const float *Wa, float *WaT, float *U, int A, int R, int S, i
   static_assert(HT == 256, "relay_block");
   RelayJob j;
   j.Wa = Wa, j.WaT = WaT, j.U = U, j.A = A, j.R = R, j.S = S, j.K = K;
-  const int ch = wino_ch(K, A);
-  j.nchunks = (A + ch - 1) / ch;
+  j.nchunks = (A + WINO_CH - 1) / WINO_CH;
   j.nb_t = (int)(((long long)A * R * S * K + HT - 1) / HT);
   const int nb = wino_nb(K);
-  const int rows = wino_pieces(K, A) ? 4 : 1;  // of the transformed domain, a thread each
-  j.nb_u = U ? ((K + nb - 1) / nb * nb * (ch / 4) * j.nchunks * rows + HT - 1) / HT : 0;
+  j.nb_u = U ? ((K + nb - 1) / nb * nb * 2 * j.nchunks + HT - 1) / HT : 0;
   return j;
 }
 

@@ -159,7 +159,7 @@ struct WsLayout {
   // head_fused == 2 only: F_n is formed from column sums left by the aux convolution's epilogue
   // (region ppart), no pooling launch
   int pool_fused;
-  bool aux_filter;  // the layer's launch has left the head's transformed filter in dU (set by nf_local_step)
+  float *aux_filter;  // the head's transformed filter where the layer's launch left it (set by nf_local_step)
   int aux_least;  // how few splits the head's weight gradient makes do with
   size_t least;   // `total` of the layout that gives up all it can (WsPlan)
   // floats of scratch in `part` that the direct kernels, and each contraction as planned, need
@@ -198,7 +198,7 @@ FwdProblem layer_fwd_problem(const nf_layer_desc *d, const LayerDims &ld, int B)
 }
 
 // Whether the region of dU, which no launch before the head's convolution is done writes, holds that convolution's
-// transformed filter: then it stands there, and nf_local_step has the layer's filter launch form it
+// transformed filter: then nf_local_step has the layer's filter launch form it there
 bool filter_in_dU(const FwdProblem &f) { return wino_fwd_filter_floats(f.N, f.C) <= (size_t)f.M * f.N; }
 
 // scratch of a forward-type contraction that runs as wino_fwd
@@ -266,7 +266,6 @@ WsLayout ws_layout_of(const nf_layer_desc *d, const LayerDims &ld, const nf_aux_
     // samples of 32x31, 128 -> 80 channels: pooling 12 us unsplit, 31 with two parts)
     w.wino_aux = pl.aux ? wino_fwd_pick_splits(fa, w.ksplits_aux, w.ksplits_aux) : 0;
     w.part_aux_fwd = wino_scratch_floats(w.wino_aux, fa);
-    if (w.wino_aux && filter_in_dU(fa)) w.part_aux_fwd -= wino_fwd_filter_floats(fa.N, fa.C);
     w.wino_dgrad = pl.dgrad ? wino_dgrad_pick_splits(fd, w.ksplits_dgrad, true) : 0;
     w.Ud = take_or(w.wino_dgrad ? wino_fwd_filter_floats(a->C_in, a->A) * f : 0, 0);
     w.part_dgrad = wino_scratch_floats(w.wino_dgrad, fd);
@@ -543,8 +542,7 @@ int32_t run_aux_conv(const nf_aux_desc *a, const AuxDims &ad, int B, const float
   const int wino = wino_splits_now(f, w.wino_aux);
   const int splits = wino ? wino : igemm_fwd_fast_applicable(f) ? w.ksplits_aux : 1;
   *ks = splits > 1 ? splits : 0;
-  const bool in_dU = wino && filter_in_dU(f);
-  float *const part = wsf(ws, w.part) + (wino && !in_dU ? wino_fwd_filter_floats(f.N, f.C) : 0);
+  float *const part = wsf(ws, w.part) + (wino ? wino_fwd_filter_floats(f.N, f.C) : 0);
   *parts = part;
   f.ksplits = *ks;
   f.out = *ks ? part : wsf(ws, w.U);
@@ -552,7 +550,8 @@ int32_t run_aux_conv(const nf_aux_desc *a, const AuxDims &ad, int B, const float
   if (!wino) return enqueue_fwd(f, st);
   const double mn = (double)f.M * f.N, byts = 4.0 * ((double)B * f.H * f.W * f.C + (double)f.N * f.Kg + mn);
   NF_RUN(st, "wino_fwd", 2.0 * mn * f.Kg, byts,
-         launch_wino_fwd(f, wsf(ws, in_dU ? w.dU : w.part), w.aux_filter, nullptr, st));
+         launch_wino_fwd(f, w.aux_filter ? w.aux_filter : wsf(ws, w.part), w.aux_filter != nullptr,
+                         nullptr, st));
   return NF_OK;
 }
 
@@ -838,7 +837,7 @@ int32_t local_step_impl(const nf_layer_desc *d, const nf_aux_desc *a, const nf_s
   const bool share = wino_splits_now(fa, w.wino_aux) && filter_in_dU(fa);
   bool formed = false;
   if ((rc = run_layer_fwd(d, ld, B, x, x_skip, p, y_out, ws, w, st, share ? &also : nullptr, &formed))) return rc;
-  w.aux_filter = formed;
+  if (formed) w.aux_filter = wsf(ws, w.dU);
   // the batch-mean loss rides on the head's backward launch
   if ((rc = run_aux_fwd(a, ad, B, y_out, labels, ap, nullptr, ws, w, st))) return rc;
   // ... and the update on the launch that finishes the weight gradients

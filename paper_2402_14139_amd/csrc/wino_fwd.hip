@@ -1,46 +1,52 @@
 // 3x3 / stride 1 / pad 1 convolution (Eq. 1, NeuroFlux, arXiv 2402.14139) through the minimal
 // filtering algorithm F(2x2, 3x3) (S. Winograd, "Arithmetic Complexity of Computations", 1980;
-// A. Lavin, S. Gray, arXiv 1509.09308): a 2x2 output tile is
+// A. Lavin, S. Gray, arXiv 1509.09308), entirely in fp32: a 2x2 output tile is
 //     Y = A^T [ (G g G^T) . (B^T d B) ] A
 // with d the 4x4 input patch and g the 3x3 filter: 16 multiplications per channel where the direct
 // sum takes 36.  The 16 positions of the transformed domain are 16 independent contractions over
-// the channels, run on the matrix cores.  This file: the filters' transform, the rule that picks the algorithm, and the kernel whose
-// products are fp32 MFMAs, for up to 32 filters or up to 24 channels; the others go to wino_fwd_split.hip.
+// the channels, run on the fp32 matrix cores.
 //
-// What bounds the kernel here: the fp32 MFMA rate (16/36 of the direct kernel's MFMAs).  Layout of the work:
+// What bounds it: the fp32 MFMA rate (16/36 of the direct kernel's MFMAs).  Layout of the work:
 //   - a workgroup owns 32 output tiles (128 pixels) x 64 filters x all 16 positions, so the patches
 //     are transformed on their way into the MFMA and the results on their way out: nothing of the
 //     transformed domain but the filters (wino_filter_kernel) ever reaches memory;
 //   - 4 waves = the 4 rows of the transformed domain.  A wave's row needs two rows of the patch (B^T
-//     has two non-zeros per row), which it reads from LDS and combines in registers;
-//     its filters come straight from memory in fragment order (no other wave of the
+//     has two non-zeros per row), which it reads from LDS and combines in registers (32 additions
+//     per 32 MFMAs); its filters come straight from memory in fragment order (no other wave of the
 //     workgroup uses them, so LDS would only add a copy);
 //   - 8 channels per step, one barrier per step; patches are loaded three steps ahead, written to
 //     LDS two steps ahead, read and row-combined one step ahead; a filter fragment is re-loaded
 //     for the next step right after its last MFMA;
 //   - 128 accumulators per lane, two workgroups per CU: one's transforms, LDS traffic, loads and
-//     stores fill in under the other's MFMAs.  Up to 24 channels, one or two steps of wino_fwd_split, that overlap is worth more than
-//     that kernel's faster products (us, it / this: 16 -> 256 channels, 46 475 pixels 47 / 42; a step with a data gradient of 20 -> 132
-//     channels, 22 197 pixels 137 / 132; but 32 -> 100, 11 264 pixels 13.4 / 15.8).
+//     stores fill in under the other's MFMAs (one workgroup of 64 tiles per CU: 101 us where this
+//     takes 84, 64 channels on 56x56 maps, batch 64; equal where both fill the chip once).
+// The reduction has C terms per position instead of 9 C: the rounding error against 64 bits is
+// smaller than that of the direct sum (emitted activation, relative: 64 channels 1.7e-7 against 2.2e-7, four
+// layers of 256 channels in a row 5.9e-7 against 7.1e-7).  That is a single result's: an average over pixels and samples keeps the
+// rounding of the transformed filter (wino_fwd_pick_splits).
 //
-// Data gradients onto a layer of up to 32 filters run through a variant of 32 per workgroup, half of whose columns
+// Measured (us, the direct kernel / this with its filter launch of 5-8 us): 64 -> 64 channels, 65 536 pixels
+// 50 / 32; 128 -> 128, 32 768 pixels 78 / 46; 256 -> 256, 8x8 pixels, batch 256 132 / 78; 512 -> 512, 4x4, batch 512 228 / 142 (the direct
+// kernel without the padding there); a step of 8 channels takes 1.93 us on a CU with two workgroups, 0.87 of it MFMAs.
+//
+// The data gradient onto a layer of up to 32 filters runs through a variant of 32 per workgroup, half of whose columns
 // would be padding otherwise: 64 accumulators, three workgroups per CU, the same patches and transforms for half of the
 // MFMAs, so a step of 16 MFMAs takes 1.3 us with two workgroups on a CU where they alone take 0.9.  Measured (us, the direct kernel
 // of 64x32 tiles / this, without the filter's launch): 64 channels, 65 536 pixels 30.2 / 19.5, 128 channels, 16 384 pixels 17.1 /
 // 12.3.
-// The reduction has C terms per position instead of 9 C: the rounding error against 64 bits is
-// smaller than that of the direct sum.  That is a single result's: an average over pixels and samples keeps the
-// rounding of the transformed filter (wino_fwd_pick_splits).
 //
 // A value that is not finite anywhere in a tile makes neighbours of the transformed domain NaN that
 // the direct sum would leave finite (or infinite): a thread that finds one among its results
 // forms those results again by the direct sum.
 #include <algorithm>
 
-#include "wino_common.h"
+#include "wino_filter.h"
 
 namespace nf {
 namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int NTHREADS = 256;
 constexpr int TB = 32;                   // output tiles per workgroup
@@ -48,45 +54,49 @@ constexpr int CH = WINO_CH;              // channels per step
 constexpr int OOB = (int)0x80000000;     // offset no buffer of < 2 GiB contains
 constexpr int RSRC_FLAGS = 0x00020000;   // raw buffer, 32-bit data format
 
-// One or two transformed filters as pieces, zero past the last filter and channel.  HBM-bound where they are large: 36
-// bytes read, 96 written per (filter, channel).  A workgroup forms one row of the transformed domain for 64 filters x 16
-// channels: a wave's 64 lanes write 512 contiguous bytes, and small filters spread over as many CUs as they have steps times four (one
-// thread for all 16 positions: 7.7 us for 64 -> 64 channels, 11.7 for 512 -> 512).  The head's filter rides on its layer's (a launch
-// of 4.5 us less).
-struct FilterJobs {
-  WinoFilter f[2];
-  int nsteps[2], nrow[2], blocks0;  // steps of 16 channels; workgroups per row of the transformed domain; blocks of job 0
+struct WinoAux {
+  int TW, TPI, T;        // tiles per image row, per image, in all
+  int nchunks, per;      // steps of 8 channels; steps per reduction split
+  int nblk;              // filter blocks
+  FastDiv div_tpi, div_tw;
+  uint32_t x_bytes, u_bytes;
+  const float *U;
 };
-__global__ __launch_bounds__(256) void wino_filter_split_kernel(FilterJobs js) {
-  const int k = (int)blockIdx.x >= js.blocks0, b = blockIdx.x - (k ? js.blocks0 : 0);
-  const WinoFilter f = js.f[k];
-  const int nsteps = js.nsteps[k], a = b / js.nrow[k], at = b % js.nrow[k];  // at: (filter block, step)
-  const int t = threadIdx.x, i = t & 1, j = t >> 1 & 31, nn = t >> 6 & 1, h = t >> 7;
-  const int n = at / nsteps * 64 + 2 * j + nn, c = at % nsteps * 16 + 8 * i + 4 * h;
-  const bool ok = (n < f.N) & (c < f.C);
-  const float *const w = f.w + (long long)n * 9 * f.C + c;
-  auto tap = [&](int r, int s) {
-    return ok ? *reinterpret_cast<const float4 *>(w + (r * 3 + s) * f.C) : make_float4(0.f, 0.f, 0.f, 0.f);
-  };
-  float4 q[3];
-  if (a == 0 || a == 3) {  // (one row of taps)
-#pragma unroll
-    for (int s = 0; s < 3; ++s) q[s] = tap(a == 0 ? 0 : 2, s);
-  } else {
-    float4 g[3][3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-      for (int s = 0; s < 3; ++s) g[r][s] = tap(r, s);
-#pragma unroll
-    for (int s = 0; s < 3; ++s) q[s] = wino_filter_row(a, g[0][s], g[1][s], g[2][s]);
-  }
-  wino_store_row(wino_pieces_at(f.U, n, c / 4, nsteps, a), q, a);
+
+__device__ inline float4 bload(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  const floatx4 v = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ inline float el(const float4 &v, int k) { return k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w; }
+__device__ inline float4 add4(const float4 &a, const float4 &b) {
+  return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+__device__ inline float4 sub4(const float4 &a, const float4 &b) {
+  return make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w);
+}
+// a + s*b with s = +-1 (exact product)
+__device__ inline float4 fma4(float s, const float4 &b, const float4 &a) {
+  return make_float4(__builtin_fmaf(s, b.x, a.x), __builtin_fmaf(s, b.y, a.y), __builtin_fmaf(s, b.z, a.z),
+                     __builtin_fmaf(s, b.w, a.w));
+}
+// bit e: component e is not finite
+__device__ inline unsigned bad4(const float4 &v) {
+  return (__builtin_isfinite(v.x) ? 0u : 1u) | (__builtin_isfinite(v.y) ? 0u : 2u) | (__builtin_isfinite(v.z) ? 0u : 4u) |
+         (__builtin_isfinite(v.w) ? 0u : 8u);
 }
 
-// The fp32 form of one filter: 5-8 us, most of it the launch
-__global__ __launch_bounds__(256) void wino_filter_kernel(WinoFilter f, int nchunks, int bx) {
-  const int t = threadIdx.x, b = blockIdx.x;
+// One or two transformed filters, zero past the last filter and channel.  HBM-bound: 36 bytes read, 64 written per
+// (filter, channel); 5-8 us, most of it the launch: the head's filter rides on its layer's (64 -> 64 channels, batch
+// 64, 32-wide head: a launch of 4.5 us less).
+struct FilterJobs {
+  WinoFilter f[2];
+  int nchunks[2], bx[2], blocks0;  // steps of 8 channels; blocks along the channels; blocks of job 0
+};
+__global__ __launch_bounds__(256) void wino_filter_kernel(FilterJobs js) {
+  const int k = (int)blockIdx.x >= js.blocks0, b = blockIdx.x - (k ? js.blocks0 : 0);
+  const WinoFilter f = js.f[k];
+  const int nchunks = js.nchunks[k], bx = js.bx[k];
+  const int t = threadIdx.x;
   const int c4 = b % bx * 8 + (t & 7), n = b / bx * 32 + (t >> 3);  // 8 lanes read 128 contiguous bytes
   if (c4 >= 2 * nchunks) return;
   float4 g[3][3];
@@ -98,6 +108,36 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(WinoFilter f, int nchu
       g[r][s] = ok ? *reinterpret_cast<const float4 *>(f.w + ((long long)n * 9 + r * 3 + s) * f.C + c4 * 4)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
   wino_filter_store(g, f.U, n, c4, nchunks, wino_nb(f.N));
+}
+
+// Four outputs (filters n .. n+3 of pixel (img, ho, wo)) by the direct sum over channels [c_lo, c_hi).
+// Taps outside the image are left out, as in the direct kernel's position tiles: an infinite weight over the padding is not one of
+// the sum's.  (Its other tiles multiply it by the zero they load.)
+__device__ inline float4 direct4(const float *x, const float *w, int H, int W, int C, int img, int ho, int wo, int n,
+                                 int c_lo, int c_hi, unsigned want) {
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  const long long ws = 9ll * C;
+#pragma unroll 1
+  for (int tap = 0; tap < 9; ++tap) {
+    const int hi = ho + tap / 3 - 1, wi = wo + tap % 3 - 1;
+    if (((unsigned)hi >= (unsigned)H) | ((unsigned)wi >= (unsigned)W)) continue;
+    const float *xr = x + ((long long)(img * H + hi) * W + wi) * C;
+    const float *wr = w + ((long long)n * 9 + tap) * C;
+#pragma unroll 1
+    for (int c = c_lo; c < c_hi; c += 4) {
+      const float4 v = *reinterpret_cast<const float4 *>(xr + c);
+      auto dot = [&](int k, float a) {
+        const float4 g = *reinterpret_cast<const float4 *>(wr + k * ws + c);
+        return __builtin_fmaf(v.w, g.w, __builtin_fmaf(v.z, g.z, __builtin_fmaf(v.y, g.y, __builtin_fmaf(v.x, g.x, a))));
+      };
+      s.x = dot(0, s.x), s.y = dot(1, s.y), s.z = dot(2, s.z), s.w = dot(3, s.w);
+      // a NaN stays one: filters that have become NaN, as in a network that has diverged, cost a step of this
+      const unsigned nan = (__builtin_isnan(s.x) ? 1u : 0u) | (__builtin_isnan(s.y) ? 2u : 0u) |
+                           (__builtin_isnan(s.z) ? 4u : 0u) | (__builtin_isnan(s.w) ? 8u : 0u);
+      if ((nan & want) == want) return s;
+    }
+  }
+  return s;
 }
 
 // NF: MFMA columns of 32 filters per workgroup (2, or 1 for few filters).  POOL: the 2x2 max pooling of Eq. 1 follows in the
@@ -429,8 +469,8 @@ __global__ __launch_bounds__(NTHREADS, NF == 2 ? 2 : 3) void wino_fwd_kernel(Fwd
 }  // namespace
 
 size_t wino_fwd_filter_floats(int N, int C) {
-  const int nb = wino_nb(N), ch = wino_ch(N, C);
-  return (size_t)((N + nb - 1) / nb) * ((C + ch - 1) / ch) * wino_step_words(nb, wino_pieces(N, C));
+  const int nb = wino_nb(N);
+  return (size_t)((N + nb - 1) / nb) * ((C + CH - 1) / CH) * (16 * nb * CH);
 }
 
 namespace {
@@ -443,12 +483,14 @@ bool applicable(const FwdProblem &p) {
 }  // namespace
 
 // Which kernel, and how many reduction splits: both times are estimated from the step times below and
-// the smaller one wins.  On 40 random layers of 2e8 ... 4e10 operations the forward calls take 1342 us in all, 1565 with fp32 products, 2206 with
-// the direct kernels alone; whole steps with a 16- to 256-wide head 7202, 7614 and 8764.  Examples (us, direct / wino_fwd_split with its filter launch): 512 -> 512 channels,
-// 8192 pixels 312 / 120; 256 -> 256, 16 384 pixels 132 / 68; 64 -> 64, 65 536 pixels 43 / 32.
+// the smaller one wins.  Of 440 random shapes for which this kernel is chosen (16 ... 512 channels, 36 ... 512 filters) it
+// takes 0.63 of the direct kernels' time in all, and is the slower one for 7, by 14 % at most (reductions split in two or
+// four, whose direct form the estimate has a tenth too slow).  Examples (us, direct / this): 512 -> 512 channels,
+// 8192 pixels 312 / 150; 128 -> 128, 16 384 pixels 45 / 30, 4096 pixels 20 / 22 (direct); 512 -> 512, 1024 pixels
+// 52 / 40 (8 splits); 64 -> 64, 65 536 pixels 43 / 34.
 // Two lines are drawn by accuracy, not by time.  Where the direct kernel splits its reduction its sums
 // are short, and this one needs about as many splits to stay below their error (512 -> 512, 1024 pixels,
-// 8 direct splits 2.7e-7: 4 splits of the fp32 products 3.4e-7, 8 splits 2.5e-7).  On maps narrower than 4 most taps
+// 8 direct splits 2.7e-7: 4 splits here 3.4e-7, 8 splits 2.5e-7).  On maps narrower than 4 most taps
 // multiply padding: the direct sum skips their rounding, the transforms do not (2x2 maps 1.5e-7
 // against 1.9e-7 ... 2.9e-7).
 namespace {
@@ -461,32 +503,15 @@ long long workgroups(const FwdProblem &p) {
   const int nb = wino_nb(p.N);
   return tiles * ((p.N + nb - 1) / nb);
 }
-// wino_fwd_split's workgroups of 64 tiles
-long long workgroups64(const FwdProblem &p) {
-  const long long T = (long long)(p.M / (p.Ho * p.Wo)) * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2);
-  return (T + 63) / 64 * ((p.N + 63) / 64);
-}
-// wino_fwd_split, as an event around the launches sees it: a step of 16 channels takes 1.2 ... 2.0 us with 32 tiles a workgroup (by how
-// many of the 128 pairs of compute units have one), with 64 tiles 2.7 in a full round of 256 and 1.4 ... 2.7 in the last one; 5.5 and 9 us of
-// prologue and epilogue, the traffic of both tensors, which one workgroup per CU does not overlap with its MFMAs, 4 us for each
-// further round, 4 us for a filter launch of its own, 3 us for many parts; a projection shortcut is a
+// this kernel: 1.13 us per step with one workgroup on a CU, 2.12 with two (before load offsets advanced in scalar registers; 1.03
+// and 1.93 now, so that layers near the line keep the direct kernel), in rounds of 512 workgroups; 11 us of prologue, epilogue
+// and launches, 3 us for each further round; the transformed filter written and read at 4 TB/s; a projection shortcut is a
 // launch of its own whose result this kernel adds (enqueue_conv).  The pooling launch that a layer with 2x2 windows saves
 // here (8 us) is not counted
-double wino_us(const FwdProblem &p, int s, bool ready) {
-  const int nchunks = (p.C + WINO_CH64 - 1) / WINO_CH64;
-  const long long w = workgroups64(p) * s, full = w / 256, rest = w % 256;
-  const double mn = (double)p.M * p.N;
-  const double per = wino_fwd_split_small(w) ? 1.2 + 0.8 * w / 128 : 2.7 * full + (rest > 0 ? 1.4 + 1.3 * rest / 256 : 0.0);
-  const double proj = p.Cs ? 8.0 + 2.0 * mn * p.Cs / 90e6 + 4.0 * mn / 4e6 : 0.0;
-  const double base = (wino_fwd_split_small(w) ? 5.5 : 9.0 + 4.0 * (full + (rest > 0) - 1)) +
-                      (s > (wino_fwd_split_small(w) ? 2 : 8) ? 3.0 : 0.0) + (ready ? 0.0 : 4.0);
-  return base + 4.0 * p.M * ((double)p.N + p.C) / 8e6 + (nchunks + s - 1) / s * per + finish_us(p, s) + proj;
-}
-// the kernel here, 64 filters per workgroup, up to 24 channels: 1.13 us per step of 8 with one workgroup on a CU, 2.12 with two, in
-// rounds of 512 workgroups; 11 us of prologue, epilogue and launches, 3 us for each further round
-double wino_f32_us(const FwdProblem &p, int s) {
+double wino_us(const FwdProblem &p, int s) {
   const int nchunks = (p.C + CH - 1) / CH;
-  const long long w = workgroups(p) * s, full = w / 512, rest = w % 512;
+  const long long w = workgroups(p) * s;
+  const long long full = w / 512, rest = w % 512;
   const double per = 2.12 * full + (rest > 256 ? 2.12 : rest > 0 ? 1.13 : 0.0), mn = (double)p.M * p.N;
   const double proj = p.Cs ? 8.0 + 2.0 * mn * p.Cs / 90e6 + 4.0 * mn / 4e6 : 0.0;
   return 11.0 + 3.0 * (full + (rest > 0) - 1) + (double)p.C * p.N * 100.0 / 4e6 + (nchunks + s - 1) / s * per +
@@ -515,18 +540,15 @@ int pick_splits(const FwdProblem &p, int ks, int most, bool ready) {
   // up to 16 filters half of a workgroup's columns would be padding; below 16 channels the result's own
   // traffic is all there is to either kernel (8 channels, 16 384 x 256 results: 17 / 14 + 5 for the filter launch)
   if (p.N <= 16 || p.C < 16 || p.Ho < 4 || p.Wo < 4 || !applicable(p)) return 0;
-  const bool narrow = wino_nb(p.N) == 32, pieces = wino_pieces(p.N, p.C);
-  // small data gradients: the filter's transform, 1-2 us of the head's launch, and its scratch are not worth what is saved
-  if (ready && pieces && p.M < (p.C < 128 ? 7168 : 1024)) return 0;
-  const int ch = wino_ch(p.N, p.C), nchunks = (p.C + ch - 1) / ch;
-  const long long wgs = pieces ? workgroups64(p) : workgroups(p), places = pieces ? 256 : 512;
+  const int nchunks = (p.C + CH - 1) / CH;
+  const bool narrow = wino_nb(p.N) == 32;
   double best = 0.0;
   int splits = 0;
   for (int s = 1; s <= 16; s *= 2) {
     if (4 * s < 3 * ks) continue;
     if (s > most) break;
-    if (s > 1 && (nchunks / s * ch < 16 || wgs * s > places)) break;
-    const double us = narrow ? narrow_us(p, s, ready) : pieces ? wino_us(p, s, ready) : wino_f32_us(p, s);
+    if (s > 1 && (nchunks / s < 2 || workgroups(p) * s > 512)) break;
+    const double us = narrow ? narrow_us(p, s, ready) : wino_us(p, s);
     if (!splits || us < best) best = us, splits = s;
   }
   if (narrow) return splits && best < 0.93 * narrow_direct_us(p, ks) ? splits : 0;
@@ -537,7 +559,7 @@ int pick_splits(const FwdProblem &p, int ks, int most, bool ready) {
   const int bt = big ? 128 : 64;
   const long long w = (long long)((p.M + bt - 1) / bt) * ((p.N + bt - 1) / bt) * ks;
   const long long full = w / 1024, rest = w % 1024;
-  const double per = big ? 2.06 * ((w + 255) / 256) : 2.2 * full + (rest > 0 ? std::max(full ? 0.56 : 0.3, 0.55 * rest / 256.0) : 0.0);
+  const double per = big ? 2.06 * ((w + 255) / 256) : 2.2 * full + (rest > 0 ? std::max(0.56, 0.55 * rest / 256.0) : 0.0);
   const double direct = 8.0 + (big ? 0.0 : 2.0 * (full + (rest > 0) - 1)) + (nkb + ks - 1) / ks * per + finish_us(p, ks);
   return splits && best < 0.93 * direct ? splits : 0;
 }
@@ -556,9 +578,8 @@ hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, con
   WinoAux q;
   const int TH = (p.Ho + 1) / 2, B = p.M / (p.Ho * p.Wo);
   q.TW = (p.Wo + 1) / 2, q.TPI = TH * q.TW, q.T = B * q.TPI;
-  const bool pieces = wino_pieces(p.N, p.C);
-  const int nb = wino_nb(p.N), ch = wino_ch(p.N, p.C);
-  q.nchunks = (p.C + ch - 1) / ch;
+  q.nchunks = (p.C + CH - 1) / CH;
+  const int nb = wino_nb(p.N);
   q.nblk = (p.N + nb - 1) / nb;
   q.div_tpi = FastDiv(q.TPI), q.div_tw = FastDiv(q.TW);
   q.x_bytes = (uint32_t)((long long)B * p.H * p.W * p.C * 4);
@@ -566,28 +587,21 @@ hipError_t launch_wino_fwd(const FwdProblem &p, float *U, bool filter_ready, con
   q.U = U;
   const int splits = p.ksplits > 1 ? p.ksplits : 1;
   q.per = (q.nchunks + splits - 1) / splits;
-  FilterJobs js;
-  int blocks = js.blocks0 = 0, n = 0;
-  for (int k = 0; k < 2; ++k) {
-    if (k == 0 ? filter_ready : !also) continue;
-    const WinoFilter f = k ? *also : WinoFilter{p.w, U, p.N, p.C};
-    if (wino_pieces(f.N, f.C)) {
-      js.f[n] = f, js.nsteps[n] = (f.C + WINO_CH64 - 1) / WINO_CH64, js.nrow[n] = (f.N + 63) / 64 * js.nsteps[n];
-      blocks += 4 * js.nrow[n];
+  if (!filter_ready || also) {
+    FilterJobs js;
+    int blocks = js.blocks0 = 0, n = 0;
+    for (int k = 0; k < 2; ++k) {
+      if (k == 0 ? filter_ready : !also) continue;
+      const WinoFilter f = k ? *also : WinoFilter{p.w, U, p.N, p.C};
+      const int fnb = wino_nb(f.N);
+      js.f[n] = f, js.nchunks[n] = (f.C + CH - 1) / CH, js.bx[n] = (2 * js.nchunks[n] + 7) / 8;
+      blocks += js.bx[n] * ((f.N + fnb - 1) / fnb) * (fnb / 32);
       if (n++ == 0) js.blocks0 = blocks;
-    } else {
-      const int nchunks = (f.C + CH - 1) / CH, bx = (2 * nchunks + 7) / 8, fnb = wino_nb(f.N);
-      hipLaunchKernelGGL(wino_filter_kernel, dim3(bx * ((f.N + fnb - 1) / fnb) * (fnb / 32)), dim3(256), 0, st, f, nchunks, bx);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
     }
-  }
-  if (n) {
-    hipLaunchKernelGGL(wino_filter_split_kernel, dim3(blocks), dim3(256), 0, st, js);
+    hipLaunchKernelGGL(wino_filter_kernel, dim3(blocks), dim3(256), 0, st, js);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (pieces) return launch_wino_fwd_split(p, q, splits, st);
   const dim3 grid(q.nblk * ((q.T + TB - 1) / TB), splits);
 #define NF_LAUNCH(NF_, POOL_) hipLaunchKernelGGL((wino_fwd_kernel<NF_, POOL_>), grid, dim3(NTHREADS), 0, st, p, q)
   if (nb == 32) NF_LAUNCH(1, false);

@@ -1,5 +1,5 @@
-"""F(2x2, 3x3) onto more than 32 filters (csrc/wino_fwd_split.hip): a layer's forward against its 64-bit sum where the kernel's
-blocks end: 32 and 64 tiles, 16 channels a step, 64 filters, both workgroup sizes, split reductions, 2x2 pooling."""
+"""F(2x2, 3x3) onto more than 32 filters (csrc/wino_fwd.hip): a layer's forward against its 64-bit sum where the kernel's blocks
+end: 32 tiles, 8 channels a step, 64 filters, whole and split reductions, 2x2 pooling."""
 import math
 
 import numpy as np
@@ -8,15 +8,18 @@ import pytest
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-CASES = [  # C, H, W, K, batch, pooled, shortcut
-    (20, 29, 27, 68, 165, 0, 0), (24, 20, 21, 132, 64, 0, 1), (28, 33, 31, 132, 16, 0, 0), (36, 32, 32, 64, 64, 1, 0),
-    (60, 23, 26, 100, 60, 1, 1), (64, 32, 32, 64, 65, 0, 1), (68, 27, 25, 124, 64, 1, 0), (100, 16, 16, 256, 33, 0, 0),
-    (128, 17, 17, 256, 21, 0, 0), (256, 8, 8, 256, 256, 0, 1), (512, 8, 8, 512, 16, 0, 0), (512, 4, 4, 512, 107, 0, 0),
+# C, H, W, K, batch, pooled, shortcut, how the reduction runs: whole, in parts, or by the direct kernel (the estimate's choice)
+CASES = [
+    (20, 29, 27, 68, 165, 0, 0, "whole"), (24, 20, 21, 132, 64, 0, 1, "whole"), (28, 33, 31, 132, 16, 0, 0, "whole"),
+    (36, 32, 32, 64, 64, 1, 0, "whole"), (60, 23, 26, 100, 60, 1, 1, "whole"), (64, 32, 32, 64, 65, 0, 1, "whole"),
+    (68, 27, 25, 124, 64, 1, 0, "whole"), (100, 16, 16, 256, 33, 0, 0, "direct"), (100, 16, 16, 256, 63, 0, 0, "whole"),
+    (128, 17, 17, 256, 21, 0, 0, "parts"), (256, 8, 8, 256, 256, 0, 1, "whole"), (512, 8, 8, 512, 16, 0, 0, "parts"),
+    (512, 4, 4, 512, 107, 0, 0, "parts"),
 ]
 
 
-@pytest.mark.parametrize("C,H,W,K,B,pool,skip", CASES)
-def test_layer_forward_against_64_bits(C, H, W, K, B, pool, skip):
+@pytest.mark.parametrize("C,H,W,K,B,pool,skip,how", CASES)
+def test_layer_forward_against_64_bits(C, H, W, K, B, pool, skip, how):
     from paper_2402_14139_amd import binding as nf
     from paper_2402_14139_amd.layer import LocalLayer
 
@@ -36,7 +39,7 @@ def test_layer_forward_against_64_bits(C, H, W, K, B, pool, skip):
     y = L.forward(x, xs, y=L.new_output(B))
     names = {r["kernel"] for r in nf.nf_prof_end()}
     if nf.nf_contraction() == nf.NF_CONTRACT_F32:
-        assert "wino_fwd" in names, names
+        assert ("wino_fwd" in names) == (how != "direct") and (how == "direct" or ("fwd_finish" in names) == (how == "parts")), names
     ref = torch.nn.functional.conv2d(x.cpu().double().permute(0, 3, 1, 2), W_.cpu().double().permute(0, 3, 1, 2), b.cpu().double(), padding=1)
     if skip:
         ref = ref + xs.cpu().double().permute(0, 3, 1, 2)
