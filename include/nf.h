@@ -248,7 +248,10 @@ typedef struct {
 
 /* Workspace of the two block calls at batch size B: two input batches (double buffer), every
  * layer's emitted batch, and the largest single-layer workspace.  It serves smaller batches too, also where
- * those would ask for more (the kernels planned for them want more scratch; they take those that fit). */
+ * those would ask for more (the kernels planned for them want more scratch; they take those that fit, and a call
+ * takes what a larger workspace holds beyond this).  In a block without heads the direct kernels of a small last
+ * batch, whose reductions are split, may need more than this: the call then returns NF_ERR_WORKSPACE before it
+ * enqueues anything. */
 int32_t nf_block_workspace_bytes(const nf_block *blk, int32_t B, size_t *out);
 
 /* One pass of the block over n_items cached samples in batches of B (the last one may be
