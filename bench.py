@@ -33,7 +33,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 # scaled by what the same counter reads for a plain 1 GiB copy (`--traffic-calib`): FETCH_SIZE x 2.0,
 # WRITE_SIZE x 1.0.  Averages over the launches of one step; summary under profiles/.
 TRAFFIC_BYTES_PER_LAUNCH = {
-    ("cfg3_resnet18", "wino_wgrad"): 40.5e6 + 42.0e6,
+    ("cfg3_resnet18", "wino_wgrad"): 40.8e6 + 42.5e6,
+    ("cfg3_resnet18", "wino_fwd"): 39.0e6 + 16.8e6,
 }
 TRAFFIC_SOURCE = ("offline: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes over this script, scaled by a 1 GiB copy "
                   "(FETCH x 2.0, WRITE x 1.0); summary in profiles/local_step_cfg3_hbm_traffic.md; not re-measured "
@@ -44,11 +45,10 @@ TRAFFIC_SOURCE = ("offline: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes over 
 # live below) add about 3 us to every launch, which halves the apparent rate of a 6 us copy.
 HBM_OFFLINE = {
     "cfg3_resnet18": [
-        ("cache_copy_kernel", 1048576, 33.59e6, 6.29), ("cache_copy_kernel", 2097152, 67.15e6, 17.33),
-        ("wgrad_reduce_kernel", 325376, 47.22e6, 11.86), ("wgrad_reduce_kernel", 1283584, 50.12e6, 15.52),
-        ("wgrad_reduce_kernel", 402944, 76.87e6, 17.78), ("wgrad_reduce_kernel", 697856, 113.19e6, 25.99),
-        ("head_wide_kernel<4>", 215552, 22.61e6, 18.34), ("head_wide_kernel<4>", 150016, 6.62e6, 10.53),
-        ("head_sample_kernel<4, false>", 83968, 4.39e6, 10.78),
+        ("cache_copy_kernel", 1048576, 33.59e6, 6.32), ("cache_copy_kernel", 2097152, 67.15e6, 17.81),
+        ("wgrad_reduce_kernel", 325376, 47.22e6, 11.65), ("wgrad_reduce_kernel", 1283584, 50.12e6, 15.45),
+        ("wgrad_reduce_kernel", 402944, 76.87e6, 17.83), ("wgrad_reduce_kernel", 697856, 113.19e6, 26.19),
+        ("head_wide_kernel<4>", 150016, 16.97e6, 12.44), ("head_sample_kernel<4, false>", 83968, 4.39e6, 10.29),
     ],
 }
 HBM_OFFLINE_SOURCE = "profiles/local_step_cfg3_hbm_traffic.md (offline rocprofv3 passes; not re-measured by this run)"
@@ -82,7 +82,7 @@ def main():
     ap.add_argument("--contraction", choices=["f32", "bf16x6", "bf16x9"], default="f32",
                     help="how the wide contractions run: fp32 matrix-core instructions (the default), or "
                          "bf16 matrix-core instructions on three-way split fp32 operands (six or all nine piece "
-                         "products; same accuracy)")
+                         "products; a single result is as exact)")
     ap.add_argument("--trace-loss", action="store_true", help="print every layer's loss after each step (syncs)")
     ap.add_argument("--traffic-calib", action="store_true",
                     help="only run 5 plain copies of 1 GiB (nf_cache_read, contiguous rows): the known-size kernel "
@@ -285,13 +285,12 @@ def main():
             # minimal filtering carries out 16 multiply-adds of the dense formula's 36: priced as carried out
             wino = dom["kernel"].startswith("wino")
             ach *= 16.0 / 36.0 if wino else 1.0
-            # a split-operand kernel spends six bf16 matrix-core multiply-adds per algorithmic one (wino_fwd: per one carried out)
-            split = 6 if "_split_" in dom["kernel"] or dom["kernel"] == "wino_fwd" else 9 if "_split9_" in dom["kernel"] else 0
+            # a split-operand kernel spends six bf16 matrix-core multiply-adds per algorithmic one
+            split = 6 if "_split_" in dom["kernel"] else 9 if "_split9_" in dom["kernel"] else 0
             peak = round(MFMA_BF16_PEAK_TFLOPS / split, 1) if split else MFMA_F32_PEAK_TFLOPS
             roofline = {"kernel": dom["kernel"], "bound": "mfma", "achieved": round(ach, 2),
                         "peak": peak, "unit": "TFLOP/s", "frac": round(ach / peak, 4),
                         "peak_note": (f"bf16 dense matrix peak 2500 TFLOP/s / {split} piece products per fp32 multiply-add"
-                                      + ("; achieved = multiply-adds carried out, 16 for 36 of the dense formula" if wino else "")
                                       if split else "fp32 dense matrix peak; achieved = multiply-adds carried out, "
                                       "16 for 36 of the dense formula" if wino else "fp32 dense matrix peak"),
                         "traffic": TRAFFIC_BYTES_PER_LAUNCH.get((cfg.name, dom["kernel"])),

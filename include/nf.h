@@ -109,7 +109,7 @@ const char *nf_strerror(int32_t status);
 
 /* How the wide contractions (the convolution of Eq. 1 and its weight gradient in Algorithm 2, for
  * layers with at least 128 filters) are carried out.  Operands, results and accumulation are fp32
- * in both modes.
+ * in all modes.
  *   NF_CONTRACT_F32     (default) fp32 matrix-core instructions (v_mfma_f32_*).  3x3 convolutions of
  *                       stride 1 and pad 1, and their weight gradients, go through the minimal filtering
  *                       algorithms F(2x2,3x3) / F(3x3,2x2), all in fp32, where that is faster and its
@@ -119,13 +119,16 @@ const char *nf_strerror(int32_t status);
  *                       matrix-core instructions.  The three left out are together below 2^-21 of
  *                       the product in the worst case and about 2^-24 of it in the root mean
  *                       square, i.e. of the size of an fp32 rounding; over the reductions of this
- *                       library (36 ... 4608 terms) the measured error against fp64 equals that of
- *                       the fp32 instructions.  An operand element that is +-inf gives NaN
- *                       instead of +-inf.  Weight gradients that NF_CONTRACT_F32 carries out faster
- *                       run as there.
+ *                       library (36 ... 4608 terms) a single result's measured error against fp64
+ *                       equals that of the fp32 instructions.  These instructions round their
+ *                       running sums down, not to nearest: errors of different results share a
+ *                       sign, and averages over the pixels of a 512-channel layer are off by 1.4e-7
+ *                       to 1.7e-7, fp32 instructions' by 4e-8; of sums that only grow 2e-6 and 1e-8.
+ *                       An operand element that is +-inf gives NaN instead of +-inf.  Weight
+ *                       gradients that NF_CONTRACT_F32 carries out faster run as there.
  *   NF_CONTRACT_BF16X9  the same with all nine piece products: every product x*w enters the fp32
- *                       accumulation exactly, as with the fp32 instructions; 1.5x the matrix-core
- *                       work of BF16X6.
+ *                       accumulation exactly, as with the fp32 instructions (the running sums are
+ *                       rounded as in BF16X6); 1.5x the matrix-core work of BF16X6.
  * Process-wide (read when a call enqueues its kernels); returns the previous mode, or
  * NF_ERR_BAD_DESC for an unknown mode.  mode = -1 only queries. */
 enum { NF_CONTRACT_F32 = 0, NF_CONTRACT_BF16X6 = 1, NF_CONTRACT_BF16X9 = 2 };

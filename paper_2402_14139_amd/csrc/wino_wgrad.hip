@@ -14,9 +14,10 @@
 //     wave loads them in fragment order straight from memory (rows of 128 / 256 contiguous bytes, two
 //     steps ahead), transforms them in registers and needs no barrier and no staged operand in its
 //     loop.  A step is 32 MFMAs, 12 loads and 62 vector operations; the latter two are not free beside
-//     fp32 MFMAs, which is what keeps a step at 1500 of its 1024 cycles per wave (the vector operations in clumps, see step).
+//     fp32 MFMAs: two waves on a SIMD take about 3000 cycles for a step each, 2048 of them MFMAs (the vector operations in clumps,
+//     see step; pipe busy 63 % of whole launches, 56 % with them spread singly);
 //     (32x32x2 MFMAs, two tiles per step: half the operands per load, 24 loads for the same
-//     MFMAs, 232 us where this takes 216; 512 channels, 8192 pixels);
+//     MFMAs, 232 us where this took 216 before the clumps; 512 channels, 8192 pixels);
 //   - the byte offsets of 64 tiles at a time stand in a table in LDS (one thread decodes a tile; what
 //     is outside the image is an offset the hardware answers with zeros);
 //   - every 64 tiles the accumulators go through A^T . A (columns in registers, in place and once per row, rows in
@@ -160,9 +161,9 @@ __global__ __launch_bounds__(NTHREADS, 2) void wino_wgrad_kernel(WgradProblem p,
   // into set `cur`, whose rows step i already combined (one behind an MFMA: a burst of all twelve from four waves holds the waves
   // up at the address unit, 16 cycles a load); in the second also the row combination of step i+1.  The vector instructions stand
   // in two clumps a section: an fp32 MFMA and a vector instruction hold each other up, about 14 cycles for each change from the one
-  // to the other and 2 (two waves on a SIMD) for each instruction, so that 62 of them spread singly behind 32 MFMAs cost 550 cycles of
-  // a step's 2048 and in four clumps half of that (512 channels, 8192 pixels 210 / 192 us; in two clumps, with more registers held
-  // and spilled, 199).
+  // to the other and 2 (two waves on a SIMD) for each instruction, so that 62 of them spread singly behind 32 MFMAs add 550 cycles to
+  // the 2048 of two waves' MFMAs and in four clumps half of that (512 channels, 8192 pixels 210 / 192 us; in two clumps, with more
+  // registers held and spilled, 199).
   auto step = [&](int i, int cur, bool first) {  // first: the sums start at zero
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
